@@ -31,7 +31,7 @@
  *     ATTN_ETOOLARGE are found before anything is enqueued: no output has been touched.
  *     ATTN_ELAUNCH (the HIP runtime refused a launch or an attribute) can come from any of the
  *     launches of a call that has several (the backward pass: dQ kernel, then dK/dV kernel; the
- *     variable-length and strided calls: a small table kernel first): the launches before the
+ *     variable-length calls: a small table kernel first): the launches before the
  *     failed one stay enqueued and write their outputs (dq, the workspace); the outputs of the
  *     failed and later launches are untouched.
  *   - Re-entrant; no global state.  Calls on different streams may run concurrently
@@ -217,8 +217,8 @@ int attn_varlen_bwd_dtype(int dtype, const void* q, const void* k, const void* v
  * causal != 0: the last query is aligned with the last key, key j is visible to query i iff
  * j <= i + Nk - Nq (the convention of the variable-length calls; the paper is silent on
  * Nq != Nk), and Nk >= Nq is required (ATTN_EINVAL otherwise).
- * Runs the variable-length kernels on the sequence boundaries {0, Nq, 2 Nq, ...} and
- * {0, Nk, 2 Nk, ...} generated on the device; on contiguous [B, N, H, d] tensors with
+ * Runs the variable-length kernels as on the sequence boundaries {0, Nq, 2 Nq, ...} and
+ * {0, Nk, 2 Nk, ...}, whose tiles the kernels number themselves; on contiguous [B, N, H, d] tensors with
  * Nq = Nk = N a multiple of 128 the results are bit-identical to attn_fwd_ex / attn_bwd_ex.
  *   workspace: attn_strided_workspace_bytes(..., backward) bytes, 256-byte aligned, contents
  *   ignored on entry.  Other conventions as in attn_fwd_dtype / attn_bwd_dtype. */

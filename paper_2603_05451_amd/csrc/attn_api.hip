@@ -229,7 +229,7 @@ VarlenLayout varlen_layout(int B, int Tq, int Tk, int H)
 // Strides of packed [T, heads, d] tensors and of lse [H, Tq].
 attn::VarlenStrides packed_strides(int Tq, int H, int Hkv, int d_qk, int d_v)
 {
-    attn::VarlenStrides st;
+    attn::VarlenStrides st = {};
     st.q = st.dq = {0, (long long)H * d_qk, d_qk};
     st.k = st.dk = {0, (long long)Hkv * d_qk, d_qk};
     st.v = st.dv = {0, (long long)Hkv * d_v, d_v};
@@ -249,7 +249,7 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     attn::FwdArgs a{q, k, v, o, lse, B, H, Hkv, 0, d_qk, d_v, scale, causal != 0, stream};
     a.plan = ws + w.plan_q_off;
     a.T = Tq;
-    a.max_tiles = w.max_tiles_q;
+    a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
     const int rc = attn::launch_fwd(a);
@@ -270,9 +270,9 @@ int varlen_bwd_run(int dtype, const void* q, const void* k, const void* v, const
                     stream, ATTN_BWD_ALL};
     a.plan = ws + w.plan_q_off;
     a.T = Tq;
-    a.max_tiles = w.max_tiles_q;
+    a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.plan_k = ws + w.plan_k_off;
-    a.max_tiles_k = w.max_tiles_k;
+    a.max_tiles_k = st.nq > 0 ? B * ((st.nk + 127) / 128) : w.max_tiles_k;
     a.st = st;
     a.rows_per_batch = rows_per_batch;
     a.f16 = dtype == ATTN_F16;
@@ -365,8 +365,10 @@ int attn_varlen_bwd(const void* q, const void* k, const void* v, const void* o, 
 
 // ---------------------------------------------------------------------------------------------
 // strided entry points: equal-length batches (Nq queries and Nk keys per sequence) in any layout
-// whose head dim is contiguous, run by the variable-length kernels on generated boundaries
-// cu_seqlens_q = {0, Nq, 2 Nq, ...}, cu_seqlens_k = {0, Nk, 2 Nk, ...}
+// whose head dim is contiguous, run by the variable-length kernels as if on the boundaries
+// cu_seqlens_q = {0, Nq, 2 Nq, ...}, cu_seqlens_k = {0, Nk, 2 Nk, ...}: the kernels compute the tile-table
+// entries of such a batch themselves (tile_entry in launch.h).  The workspace keeps the room that the
+// boundaries and tables used to take, so that its size is the packed call's.
 
 namespace {
 
@@ -422,18 +424,16 @@ int attn_fwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
         return ATTN_EINVAL;
     if (workspace_bytes < attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, 0)) return ATTN_EINVAL;
     char* ws = static_cast<char*>(workspace);
-    int* cu_q = reinterpret_cast<int*>(ws);
-    int* cu_k = reinterpret_cast<int*>(ws + cu_bytes(B));
-    if (attn::launch_uniform_cu(cu_q, B, Nq, stream) != 0 || attn::launch_uniform_cu(cu_k, B, Nk, stream) != 0)
-        return ATTN_ELAUNCH;
     attn::VarlenStrides st = {};
+    st.nq = Nq;
+    st.nk = Nk;
     st.q = as_packed(sq, Nq);
     st.k = as_packed(sk, Nk);
     st.v = as_packed(sv, Nk);
     st.o = as_packed(so, Nq);
     st.lse_head = Nq;                      // lse [B, H, Nq]
     st.lse_batch = (long long)(H - 1) * Nq;
-    return varlen_fwd_run(dtype, q, k, v, o, lse, cu_q, cu_k, B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, scale, causal,
+    return varlen_fwd_run(dtype, q, k, v, o, lse, nullptr, nullptr, B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, scale, causal,
                           ws + 2 * cu_bytes(B), st, stream);
 }
 
@@ -459,11 +459,9 @@ int attn_bwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
     if (misaligned(lse, 4) || misaligned(workspace, 256)) return ATTN_EINVAL;
     if (workspace_bytes < attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, 1)) return ATTN_EINVAL;
     char* ws = static_cast<char*>(workspace);
-    int* cu_q = reinterpret_cast<int*>(ws);
-    int* cu_k = reinterpret_cast<int*>(ws + cu_bytes(B));
-    if (attn::launch_uniform_cu(cu_q, B, Nq, stream) != 0 || attn::launch_uniform_cu(cu_k, B, Nk, stream) != 0)
-        return ATTN_ELAUNCH;
     attn::VarlenStrides st = {};
+    st.nq = Nq;
+    st.nk = Nk;
     st.q = as_packed(sq, Nq);
     st.k = as_packed(sk, Nk);
     st.v = as_packed(sv, Nk);
@@ -474,7 +472,7 @@ int attn_bwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
     st.dv = as_packed(sdv, Nk);
     st.lse_head = Nq;
     st.lse_batch = (long long)(H - 1) * Nq;
-    return varlen_bwd_run(dtype, q, k, v, o, d_o, lse, dq, dk, dv, cu_q, cu_k, B, B * Nq, B * Nk, H, Hkv, d_qk, d_v,
+    return varlen_bwd_run(dtype, q, k, v, o, d_o, lse, dq, dk, dv, nullptr, nullptr, B, B * Nq, B * Nk, H, Hkv, d_qk, d_v,
                           scale, causal, ws + 2 * cu_bytes(B), st, Nq, stream);
 }
 

@@ -98,17 +98,6 @@ varlen_plan_kernel(const int* __restrict__ cu_q, const int* __restrict__ cu_k, i
     if (plan_k) plan_build(cu_q, cu_k, B, Tq, Tk, false, plan_k, max_tiles_k, hist, start, part);   // backward only
 }
 
-__global__ void uniform_cu_kernel(int* __restrict__ cu, int B, int N)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b <= B) cu[b] = b * N;
-}
-
-int launch_uniform_cu(int* cu, int B, int N, void* stream)
-{
-    return launch_kernel(uniform_cu_kernel, dim3((B + 256) / 256), dim3(256), 0, stream, cu, B, N) == hipSuccess ? 0 : -3;
-}
-
 int launch_varlen_plan(const int* cu_q, const int* cu_k, int B, int Tq, int Tk, void* plan_q, int max_tiles_q,
                        void* plan_k, int max_tiles_k, void* stream)
 {

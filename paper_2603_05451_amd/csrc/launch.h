@@ -17,11 +17,32 @@ struct Stride3 {
 struct VarlenStrides {
     Stride3 q, k, v, o, d_o, dq, dk, dv;
     long long lse_batch, lse_head;      // lse index = t + s * lse_batch + h * lse_head
+    // equal-length batches (the strided calls): every sequence has nq queries and nk keys, and a kernel
+    // computes its tile-table entry (tile_entry) instead of reading one; 0: the tables say
+    int nq, nk;
 };
 
 // Mark of a used entry of the tile tables.  Not 1: a workspace that was never planned, or whose
 // tables were overwritten, then holds no entry that a kernel would act on.
 constexpr int kPlanUsed = 0x5A17AB1E;
+
+// Entry e of a tile table: seq = {first query row, query length, first key row, key length} of the sequence,
+// til = {tile of 128 rows inside it, kPlanUsed, sequence, -}; a sequence's tiles are listed last to first.
+// Equal-length batches need no table: the entry follows from e, which spares the strided calls the two
+// boundary kernels and the plan kernel (three launches in a row, 10 us of a call).
+template <bool QUERY_SIDE>
+__device__ __forceinline__ void tile_entry(const int4* __restrict__ plan, int e, const VarlenStrides& st, int4& seq, int4& til)
+{
+    if (st.nq > 0) {
+        const int nt = ((QUERY_SIDE ? st.nq : st.nk) + 127) / 128;
+        const int b = e / nt;
+        seq = make_int4(b * st.nq, st.nq, b * st.nk, st.nk);
+        til = make_int4(nt - 1 - (e - b * nt), kPlanUsed, b, 0);
+    } else {
+        seq = plan[2 * e];
+        til = plan[2 * e + 1];
+    }
+}
 
 struct FwdArgs {
     const void *q, *k, *v;
@@ -31,7 +52,7 @@ struct FwdArgs {
     float scale;
     int causal;
     void* stream;
-    // variable-length mode (plan != nullptr): B and N unused; plan = table of query tiles,
+    // variable-length mode (max_tiles > 0): B and N unused; plan = table of query tiles (unread if st.nq > 0),
     // max_tiles its size (an upper bound on the number of 128-row query tiles), T = total query rows
     const void* plan = nullptr;
     int T = 0, max_tiles = 0;
@@ -51,7 +72,7 @@ struct BwdArgs {
     float* lse2;
     void* stream;
     int phases;   // bit mask: 1 prepare, 2 dK/dV kernel, 4 dQ kernel
-    const void* plan = nullptr;   // variable-length mode, as in FwdArgs: query-tile table (dQ kernel)
+    const void* plan = nullptr;   // variable-length mode (max_tiles > 0), as in FwdArgs: query-tile table (dQ kernel)
     int T = 0, max_tiles = 0;
     const void* plan_k = nullptr; // key-tile table (dK/dV kernels) and its size
     int max_tiles_k = 0;
@@ -106,8 +127,6 @@ int launch_bwd_dkdv_t32(const BwdArgs& a);
 // The dQ kernel with one wave per SIMD and 32 queries per wave (head dims 128 and (192, 128), fixed length,
 // N % 128 = 0); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_t32(const BwdArgs& a);
-// cu[b] = b * N for b = 0 .. B (device): the equal-length batch as a packed one.
-int launch_uniform_cu(int* cu, int B, int N, void* stream);
 // Fills the two plan tables of the variable-length entry points on the device: 0 or -3.
 int launch_varlen_plan(const int* cu_q, const int* cu_k, int B, int Tq, int Tk, void* plan_q, int max_tiles_q,
                        void* plan_k, int max_tiles_k, void* stream);
