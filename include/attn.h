@@ -147,7 +147,9 @@ size_t attn_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d_qk, int d_v)
  *   tiles per head and total_k/128 + B key tiles per key/value head.
  *   workspace: attn_varlen_workspace_bytes(..., backward) bytes, 256-byte aligned; the forward
  *   call needs the backward = 0 size, the backward call the backward = 1 size.  Contents on entry
- *   are ignored.  All other conventions (device pointers, stream, alignment, head dims, error
+ *   are ignored.  (Where few queries meet many keys the forward size includes room for partial results
+ *   of a pass whose keys are divided over several blocks; with less room, down to the tables alone,
+ *   a call divides them less, and its results differ by the rounding of another summation order.)  All other conventions (device pointers, stream, alignment, head dims, error
  *   codes) are those of attn_fwd_ex / attn_bwd_ex.  The table kernel checks every sequence's
  *   boundaries on the device against total_q and total_k: a sequence whose rows do not lie inside
  *   the tensors (decreasing boundaries, boundaries past the totals) is left out, i.e. none of its

@@ -25,6 +25,7 @@ VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]
 SOURCES = [("attn_api.hip", "attn_api.o", []),
            ("attn_fwd.hip", "attn_fwd.o", VGPR_FORM),
            ("attn_fwd_q64.hip", "attn_fwd_q64.o", []),
+           ("attn_decode.hip", "attn_decode.o", VGPR_FORM),
            ("attn_bwd.hip", "attn_bwd.o", []),
            ("attn_bwd.hip", "attn_bwd_vgpr_form.o", ["-DATTN_BWD_VGPR_FORM_PART=1", *VGPR_FORM]),
            ("attn_bwd_dq_q64.hip", "attn_bwd_dq_q64.o", []),

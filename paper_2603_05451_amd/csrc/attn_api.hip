@@ -205,24 +205,75 @@ int check_varlen(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v)
     return ATTN_OK;
 }
 
-// Workspace of the variable-length calls: table of query tiles | table of key tiles | -D | LSE2
-// (forward: the first table only).  A table entry is 32 bytes.
-struct VarlenLayout {
-    int max_tiles_q, max_tiles_k;
-    size_t plan_q_off, plan_k_off, d_off, lse2_off, total_fwd, total_bwd;
+// How the forward pass of a variable-length call runs.  Functions of the sizes alone (the host never sees
+// the lengths, and the workspace is sized before the mask is known), so calls that share tables agree.
+struct FwdRoute {
+    bool decode;        // the kernel for few queries per sequence (attn_decode_kernel.inc)
+    int nsub;           // its 32-row groups per (sequence, KV head)
+    int nsplit;         // parts of the keys; 1: no partial results
 };
 
-VarlenLayout varlen_layout(int B, int Tq, int Tk, int H)
+FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform)
+{
+    FwdRoute r{false, 1, 1};
+    const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
+    auto clamp = [](int64_t n, int64_t most) { return (int)(n < 1 || most < 1 ? 1 : n < most ? n : most); };
+    // Decode: a (sequence, KV head) is nsub groups of 32 rows there and G tiles of 128 rows in attn_fwd_kernel,
+    // at about the same cost per group as per tile (B = 4, H = 32/8, Nk = 4096, d = 128: Nq = 16 31 us against
+    // 44, Nq = 24 34 against 44, Nq = 32 45 against 45; G = 1: Nq = 64 46 against 41).  In a packed batch only
+    // the totals are known; with no more queries than sequences it is the usual decode step, whereas a batch
+    // that mixes steps with a prompt chunk has to keep the 128-row tiles for the chunk.
+    const int64_t nsub = ((uniform ? Nq : 1) * G + 31) / 32;
+    if (uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B) {
+        r.decode = true;
+        r.nsub = (int)nsub;
+        const int64_t items = (int64_t)B * Hkv * nsub, steps = (Nk + 127) / 128;
+        if (items > 0xffffff) return r;
+        if (!uniform) {
+            // uneven lengths, longest first: four blocks per CU even out (48 sequences of 67 ... 7696 keys, 384
+            // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average
+            r.nsplit = clamp((1023 + items) / items, (steps + 2) / 3);
+        } else if (items < 128) {
+            // 128 blocks reach the memory's rate; parts below four steps cost more than they spread
+            // (B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
+            r.nsplit = clamp((127 + items) / items, steps / 4);
+        } else if (items > 256 && items % 256 != 0 && items < 1024) {
+            // a last round that leaves CUs idle (320 items of 4001 keys: 142 us whole, 126 in 2, 127 in 3)
+            r.nsplit = clamp(3, steps / 4);
+        }
+    }
+    return r;
+}
+
+size_t partial_bytes(int nsplit, int Tq, int H, int d_v)
+{
+    return nsplit > 1 ? align_up((size_t)nsplit * Tq * H * (d_v + 2) * sizeof(float), 256) : 0;
+}
+
+// Workspace of the variable-length calls: table of query tiles | table of key tiles | -D | LSE2
+// (forward: the first table only, and, where the keys are divided, the partial results behind the place of
+// the second table, which a forward call leaves alone).  A table entry is 32 bytes.
+struct VarlenLayout {
+    int max_tiles_q, max_tiles_k;
+    size_t plan_q_off, plan_k_off, part_off, d_off, lse2_off;
+    size_t min_fwd, total_fwd, min_bwd, total_bwd;      // least that a call accepts, what it is best given
+};
+
+VarlenLayout varlen_layout(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v, bool uniform)
 {
     VarlenLayout w;
     w.max_tiles_q = Tq / 128 + B;       // sum over sequences of ceil(len / 128) never exceeds this
     w.max_tiles_k = Tk / 128 + B;
     w.plan_q_off = 0;
-    w.total_fwd = align_up((size_t)w.max_tiles_q * 32, 256);
-    w.plan_k_off = w.total_fwd;
-    w.d_off = w.plan_k_off + align_up((size_t)w.max_tiles_k * 32, 256);
+    w.min_fwd = align_up((size_t)w.max_tiles_q * 32, 256);
+    w.plan_k_off = w.min_fwd;
+    w.part_off = w.d_off = w.plan_k_off + align_up((size_t)w.max_tiles_k * 32, 256);
     w.lse2_off = w.d_off + align_up((size_t)H * Tq * sizeof(float), 256);
-    w.total_bwd = w.lse2_off + align_up((size_t)H * Tq * sizeof(float), 256);
+    w.min_bwd = w.lse2_off + align_up((size_t)H * Tq * sizeof(float), 256);
+    // with less than the partial results need, a call divides the keys as far as its workspace goes
+    const size_t part = partial_bytes(fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform).nsplit, Tq, H, d_v);
+    w.total_fwd = part ? w.part_off + part : w.min_fwd;
+    w.total_bwd = w.min_bwd > w.total_fwd ? w.min_bwd : w.total_fwd;
     return w;
 }
 
@@ -241,18 +292,31 @@ attn::VarlenStrides packed_strides(int Tq, int H, int Hkv, int d_qk, int d_v)
 
 int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void* o, float* lse,
                    const int* cu_q, const int* cu_k, int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v,
-                   float scale, int causal, char* ws, const attn::VarlenStrides& st, void* stream)
+                   float scale, int causal, char* ws, size_t ws_bytes, const attn::VarlenStrides& st, void* stream)
 {
-    const VarlenLayout w = varlen_layout(B, Tq, Tk, H);
+    const bool uniform = st.nq > 0;
+    const VarlenLayout w = varlen_layout(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);
     if (cu_q && attn::launch_varlen_plan(cu_q, cu_k, B, Tq, Tk, ws + w.plan_q_off, w.max_tiles_q, nullptr, 0, stream) != 0)
-        return ATTN_ELAUNCH;
+        return ATTN_ELAUNCH;                               // (equal lengths: no boundaries, no table)
     attn::FwdArgs a{q, k, v, o, lse, B, H, Hkv, 0, d_qk, d_v, scale, causal != 0, stream};
     a.plan = ws + w.plan_q_off;
     a.T = Tq;
     a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
-    const int rc = attn::launch_fwd(a);
+    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform);
+    a.nsub = r.nsub;
+    a.nsplit = r.nsplit;
+    while (a.nsplit > 1 && w.part_off + partial_bytes(a.nsplit, Tq, H, d_v) > ws_bytes) --a.nsplit;
+    if (a.nsplit > 1) {
+        a.part_o = reinterpret_cast<float*>(ws + w.part_off);
+        a.part_ml = a.part_o + (size_t)a.nsplit * Tq * H * d_v;
+        // rows of a tile, in turns of 1024 / d_v per block of the merge kernel; packed tiles mostly hold one query
+        const int rows = (uniform ? (st.nq < 128 ? st.nq : 128) : 1) * (H / Hkv), per = 1024 / d_v;
+        a.nshare = (rows + per - 1) / per;
+    }
+    int rc = r.decode ? attn::launch_decode(a) : attn::launch_fwd(a);
+    if (rc == 0 && a.nsplit > 1) rc = attn::launch_combine(a);
     return rc == 0 ? ATTN_OK : (rc == -2 ? ATTN_EUNSUPPORTED : ATTN_ELAUNCH);
 }
 
@@ -261,7 +325,7 @@ int varlen_bwd_run(int dtype, const void* q, const void* k, const void* v, const
                    const int* cu_q, const int* cu_k, int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v,
                    float scale, int causal, char* ws, const attn::VarlenStrides& st, int rows_per_batch, void* stream)
 {
-    const VarlenLayout w = varlen_layout(B, Tq, Tk, H);
+    const VarlenLayout w = varlen_layout(B, Tq, Tk, H, Hkv, d_qk, d_v, st.nq > 0);
     if (cu_q && attn::launch_varlen_plan(cu_q, cu_k, B, Tq, Tk, ws + w.plan_q_off, w.max_tiles_q,
                                          ws + w.plan_k_off, w.max_tiles_k, stream) != 0)
         return ATTN_ELAUNCH;
@@ -285,7 +349,7 @@ int varlen_bwd_run(int dtype, const void* q, const void* k, const void* v, const
 size_t attn_varlen_workspace_bytes(int B, int total_q, int total_k, int H, int Hkv, int d_qk, int d_v, int backward)
 {
     if (check_varlen(B, total_q, total_k, H, Hkv, d_qk, d_v) != ATTN_OK) return 0;
-    const VarlenLayout w = varlen_layout(B, total_q, total_k, H);
+    const VarlenLayout w = varlen_layout(B, total_q, total_k, H, Hkv, d_qk, d_v, false);
     return backward ? w.total_bwd : w.total_fwd;
 }
 
@@ -295,8 +359,8 @@ int attn_varlen_plan(const int* cu_seqlens_q, const int* cu_seqlens_k, int B, in
     if (!cu_seqlens_q || !cu_seqlens_k || !workspace) return ATTN_EINVAL;
     if (int rc = check_varlen(B, total_q, total_k, H, Hkv, d_qk, d_v)) return rc;
     if (misaligned(cu_seqlens_q, 4) || misaligned(cu_seqlens_k, 4) || misaligned(workspace, 256)) return ATTN_EINVAL;
-    const VarlenLayout w = varlen_layout(B, total_q, total_k, H);
-    if (workspace_bytes < w.total_bwd) return ATTN_EINVAL;
+    const VarlenLayout w = varlen_layout(B, total_q, total_k, H, Hkv, d_qk, d_v, false);
+    if (workspace_bytes < w.min_bwd) return ATTN_EINVAL;
     char* ws = static_cast<char*>(workspace);
     return attn::launch_varlen_plan(cu_seqlens_q, cu_seqlens_k, B, total_q, total_k, ws + w.plan_q_off, w.max_tiles_q,
                                     ws + w.plan_k_off, w.max_tiles_k, stream) == 0 ? ATTN_OK : ATTN_ELAUNCH;
@@ -315,10 +379,10 @@ int attn_varlen_fwd_dtype(int dtype, const void* q, const void* k, const void* v
     if (misaligned(q, 16) || misaligned(k, 16) || misaligned(v, 16) || misaligned(o, 16) ||
         misaligned(lse, 4) || misaligned(cu_seqlens_q, 4) || misaligned(cu_seqlens_k, 4) || misaligned(workspace, 256))
         return ATTN_EINVAL;
-    if (workspace_bytes < varlen_layout(B, total_q, total_k, H).total_fwd) return ATTN_EINVAL;
+    if (workspace_bytes < varlen_layout(B, total_q, total_k, H, Hkv, d_qk, d_v, false).min_fwd) return ATTN_EINVAL;
     return varlen_fwd_run(dtype, q, k, v, o, lse, cu_seqlens_q, cu_seqlens_k, B, total_q, total_k, H, Hkv, d_qk, d_v,
-                          scale, causal, static_cast<char*>(workspace), packed_strides(total_q, H, Hkv, d_qk, d_v),
-                          stream);
+                          scale, causal, static_cast<char*>(workspace), workspace_bytes,
+                          packed_strides(total_q, H, Hkv, d_qk, d_v), stream);
 }
 
 int attn_varlen_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -346,7 +410,7 @@ int attn_varlen_bwd_dtype(int dtype, const void* q, const void* k, const void* v
         if (misaligned(p, 16)) return ATTN_EINVAL;
     if (misaligned(lse, 4) || misaligned(cu_seqlens_q, 4) || misaligned(cu_seqlens_k, 4) || misaligned(workspace, 256))
         return ATTN_EINVAL;
-    if (workspace_bytes < varlen_layout(B, total_q, total_k, H).total_bwd) return ATTN_EINVAL;
+    if (workspace_bytes < varlen_layout(B, total_q, total_k, H, Hkv, d_qk, d_v, false).min_bwd) return ATTN_EINVAL;
     return varlen_bwd_run(dtype, q, k, v, o, d_o, lse, dq, dk, dv, cu_seqlens_q, cu_seqlens_k, B, total_q, total_k,
                           H, Hkv, d_qk, d_v, scale, causal, static_cast<char*>(workspace),
                           packed_strides(total_q, H, Hkv, d_qk, d_v), 0, stream);
@@ -403,7 +467,7 @@ attn::Stride3 as_packed(const attn_strides_t* s, int N)
 size_t attn_strided_workspace_bytes(int B, int H, int Hkv, int Nq, int Nk, int d_qk, int d_v, int backward)
 {
     if (check_strided(B, H, Hkv, Nq, Nk, d_qk, d_v) != ATTN_OK) return 0;
-    const VarlenLayout w = varlen_layout(B, B * Nq, B * Nk, H);
+    const VarlenLayout w = varlen_layout(B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, true);
     return 2 * cu_bytes(B) + (backward ? w.total_bwd : w.total_fwd);
 }
 
@@ -422,7 +486,7 @@ int attn_fwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
     if (misaligned(q, 16) || misaligned(k, 16) || misaligned(v, 16) || misaligned(o, 16) ||
         misaligned(lse, 4) || misaligned(workspace, 256))
         return ATTN_EINVAL;
-    if (workspace_bytes < attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, 0)) return ATTN_EINVAL;
+    if (workspace_bytes < 2 * cu_bytes(B) + varlen_layout(B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, true).min_fwd) return ATTN_EINVAL;
     char* ws = static_cast<char*>(workspace);
     attn::VarlenStrides st = {};
     st.nq = Nq;
@@ -434,7 +498,7 @@ int attn_fwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
     st.lse_head = Nq;                      // lse [B, H, Nq]
     st.lse_batch = (long long)(H - 1) * Nq;
     return varlen_fwd_run(dtype, q, k, v, o, lse, nullptr, nullptr, B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, scale, causal,
-                          ws + 2 * cu_bytes(B), st, stream);
+                          ws + 2 * cu_bytes(B), workspace_bytes - 2 * cu_bytes(B), st, stream);
 }
 
 int attn_bwd_strided(int dtype, const void* q, const attn_strides_t* sq, const void* k, const attn_strides_t* sk,
@@ -457,7 +521,7 @@ int attn_bwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
     for (const void* p : ptrs)
         if (misaligned(p, 16)) return ATTN_EINVAL;
     if (misaligned(lse, 4) || misaligned(workspace, 256)) return ATTN_EINVAL;
-    if (workspace_bytes < attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, 1)) return ATTN_EINVAL;
+    if (workspace_bytes < 2 * cu_bytes(B) + varlen_layout(B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, true).min_bwd) return ATTN_EINVAL;
     char* ws = static_cast<char*>(workspace);
     attn::VarlenStrides st = {};
     st.nq = Nq;

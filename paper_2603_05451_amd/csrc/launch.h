@@ -58,6 +58,12 @@ struct FwdArgs {
     int T = 0, max_tiles = 0;
     VarlenStrides st = {};   // variable-length mode: q, k, v, o and lse strides
     bool f16 = false;   // 16-bit storage type of q, k, v, o: bf16 (default) or IEEE fp16
+    // variable-length mode: keys of a sequence divided over nsplit blocks whose unnormalised results go to
+    // part_o [nsplit][T][H][d_v] and part_ml [nsplit][T][H] {reference maximum, row sum} (nsplit > 1)
+    int nsplit = 1;
+    float *part_o = nullptr, *part_ml = nullptr;
+    int nsub = 1;       // decode kernel: blocks that share the 32-row groups of one tile
+    int nshare = 1;     // merge kernel: blocks that share the rows of one tile
 };
 
 struct BwdArgs {
@@ -118,6 +124,10 @@ int launch_fwd(const FwdArgs& a);
 int launch_bwd(const BwdArgs& a);
 // The 64-queries-per-wave forward kernel (head dims 128, 64 or (192, 128); fixed length, N % 256 = 0).
 int launch_fwd_q64(const FwdArgs& a);
+// The decode kernel (variable-length mode, every head dim): few queries per sequence; and the merge of the
+// partial results of a pass with nsplit > 1.
+int launch_decode(const FwdArgs& a);
+int launch_combine(const FwdArgs& a);
 // The dQ kernel with 64 queries per wave (d_qk = d_v = 128 or 64, fixed length, N % 256 = 0); it also
 // leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_q64(const BwdArgs& a);

@@ -1,0 +1,101 @@
+"""GPU tests of the forward pass with few queries per sequence against many keys: the decode kernel (the
+query heads of a KV head as rows of one tile, keys divided over waves and over blocks), and the 128-row
+kernel with its key loop divided over blocks (a chunk of queries against a long cache).  Everything against
+the fp64 oracle; sizes sit at the edges of the 32-key tiles, of the rounds of four waves and of the splits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_05451_amd import inputs as I
+from parity import LSE_ABS, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(B, H, Hkv, Nq, Nk, dqk, dv, causal, seed, f16=False):
+    x = I.make_inputs(I.Workload("decode", B, H, Hkv, max(Nq, Nk), dqk, dv, causal, seed), with_do=False)
+    x = {n: t[:, :(Nq if n == "q" else Nk)].contiguous() for n, t in x.items()}
+    return {n: t.float().to(torch.float16) for n, t in x.items()} if f16 else x
+
+
+def _check(oracle, x, o, lse, scale, causal, name):
+    Nq, Nk = x["q"].shape[1], x["k"].shape[1]
+    ro, rlse = oracle.attn_fwd(*(I.to_f64(x[n]) for n in ("q", "k", "v")), scale, causal, q_pos=np.arange(Nq) + (Nk - Nq))
+    assert np.abs(lse.cpu().numpy() - rlse).max() <= LSE_ABS, name
+    assert_close(o.float().cpu().numpy(), ro, name)
+
+
+# (B, H, Hkv, Nq, Nk, d_qk, d_v, causal): one key; around one tile and one round of the four waves; every head
+# dim; two queries whose last keys lie in different tiles; two 32-row groups; 64 heads on one KV head; few
+# sequences with long caches (many splits, the last of them empty or ragged); chunks with a divided key loop
+SHAPES = [(1, 2, 2, 1, 1, 64, 64, True), (3, 4, 1, 1, 31, 128, 128, True), (2, 8, 2, 1, 33, 96, 96, False),
+          (2, 4, 4, 1, 127, 192, 128, True), (1, 8, 2, 1, 129, 256, 256, True), (2, 4, 2, 2, 65, 128, 128, True),
+          (2, 8, 1, 3, 130, 64, 64, True), (1, 64, 1, 1, 515, 128, 128, True), (2, 16, 4, 10, 300, 128, 128, True),
+          (1, 2, 2, 1, 8200, 128, 128, True), (1, 4, 2, 1, 5121, 64, 64, False), (1, 2, 1, 5, 4100, 192, 128, True),
+          (1, 2, 1, 2, 3077, 256, 256, True), (1, 3, 3, 1, 2600, 96, 96, True),
+          (1, 2, 2, 200, 4161, 128, 128, True), (1, 2, 1, 130, 3300, 64, 64, False), (1, 2, 1, 129, 2500, 256, 256, True),
+          (1, 2, 1, 300, 2900, 192, 128, True), (2, 1, 1, 140, 2300, 96, 96, True)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=["B%d_H%d_%d_q%d_k%d_d%d_%d_%s" % s for s in SHAPES])
+def test_few_queries_against_many_keys(oracle, shape):
+    import paper_2603_05451_amd as A
+    B, H, Hkv, Nq, Nk, dqk, dv, causal = shape
+    x = _case(*shape, seed=700 + Nk, f16=Nk % 2 == 0)
+    cache = lambda t: torch.cat([t, torch.full_like(t[:, :32], float("nan"))], 1).cuda()[:, :t.shape[1]]    # room behind it
+    q, k, v = x["q"].cuda(), cache(x["k"]), cache(x["v"])
+    o, lse = A.attn_fwd_strided(q, k, v, dqk ** -0.5, causal)
+    # the least workspace a call accepts: fewer parts of the keys, the same result
+    nt = lambda n: -(-(B * n // 128 + B) * 32 // 256) * 256
+    ws = torch.empty(2 * 256 + nt(Nq), dtype=torch.uint8, device="cuda")
+    o1, lse1 = A.attn_fwd_strided(q, k, v, dqk ** -0.5, causal, workspace=ws)
+    torch.cuda.synchronize()
+    _check(oracle, x, o, lse, dqk ** -0.5, causal, "divided")
+    _check(oracle, x, o1, lse1, dqk ** -0.5, causal, "whole")
+
+
+@pytest.mark.parametrize("H,Hkv,d,lens", [(8, 2, 128, (700, 1, 64, 0, 33, 5000)), (4, 4, 64, (31, 32, 2000)),
+                                          (64, 1, 256, (129, 400)), (6, 3, 96, (1500, 96, 5))])
+def test_packed_decode_step(oracle, H, Hkv, d, lens):
+    """One query per sequence against packed caches of mixed lengths; the sequence without keys has no query."""
+    import paper_2603_05451_amd as A
+    cuk = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cuq = np.concatenate([[0], np.cumsum([n > 0 for n in lens])]).astype(np.int32)
+    x = _case(1, H, Hkv, int(cuq[-1]), int(cuk[-1]), d, d, False, seed=720 + d)
+    q, k, v = (x[n][0].cuda() for n in ("q", "k", "v"))
+    o, lse = A.attn_varlen_fwd(q, k, v, torch.from_numpy(cuq).cuda(), d ** -0.5, True, cu_seqlens_k=torch.from_numpy(cuk).cuda())
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        if n:
+            s = slice(int(cuq[b]), int(cuq[b + 1]))
+            part = {"q": x["q"][:, s], "k": x["k"][:, cuk[b]:cuk[b + 1]], "v": x["v"][:, cuk[b]:cuk[b + 1]]}
+            _check(oracle, part, o[None, s], lse[None, :, s], d ** -0.5, True, f"sequence {b}")
+
+
+def test_decode_replays_in_a_graph_and_skips_what_is_not_planned():
+    """A captured decode step on new queries gives the eager call's bits; on a workspace without tables a call
+    that relies on them leaves its outputs alone, the merge kernel included."""
+    import paper_2603_05451_amd as A
+    B, H, Hkv, Nk, d = 2, 8, 2, 3000, 128
+    x = _case(B, H, Hkv, 1, Nk, d, d, True, seed=740)
+    q, k, v = (x[n].cuda() for n in ("q", "k", "v"))
+    ws = torch.zeros(A.attn_strided_workspace_bytes(B, H, Hkv, 1, Nk, d, d, False), dtype=torch.uint8, device="cuda")
+    o, lse = torch.empty_like(q), torch.empty(B, H, 1, device="cuda")
+    A.attn_fwd_strided(q, k, v, 0.1, True, o=o, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        A.attn_fwd_strided(q, k, v, 0.1, True, o=o, lse=lse, workspace=ws, stream=torch.cuda.current_stream())
+    for i in range(3):
+        q.copy_(torch.randn(q.shape, generator=torch.Generator().manual_seed(i)).bfloat16())
+        graph.replay()
+        torch.cuda.synchronize()
+        ro, rl = A.attn_fwd_strided(q, k, v, 0.1, True)
+        assert torch.equal(o, ro) and torch.equal(lse, rl)
+    n = A.attn_varlen_workspace_bytes(B, B, B * Nk, H, Hkv, d, d, False)
+    o.fill_(7.0)
+    lse2 = torch.full((H, B), 7.0, device="cuda")
+    A.attn_varlen_fwd(q[:, 0], k.flatten(0, 1), v.flatten(0, 1), None, 0.1, True, o=o[:, 0], lse=lse2, B=B,
+                      workspace=torch.zeros(n, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert (o == 7.0).all() and (lse2 == 7.0).all()
