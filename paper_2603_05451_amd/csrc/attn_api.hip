@@ -241,6 +241,14 @@ FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform
             // a last round that leaves CUs idle (320 items of 4001 keys: 142 us whole, 126 in 2, 127 in 3)
             r.nsplit = clamp(3, steps / 4);
         }
+    } else if (Tk > Tq) {
+        // (self-attention is never divided: its results are those of the fixed-length calls, bit for bit)
+        // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
+        // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
+        // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose
+        // loops are half as long: 42 whole, 49 in 2)
+        const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
+        r.nsplit = clamp((d_qk > 192 ? 256 : 512) / blocks, (Nk - Nq / 2) / (16 * 64));
     }
     return r;
 }
