@@ -29,6 +29,7 @@ SOURCES = [("attn_api.hip", "attn_api.o", []),
            ("attn_bwd.hip", "attn_bwd.o", []),
            ("attn_bwd.hip", "attn_bwd_vgpr_form.o", ["-DATTN_BWD_VGPR_FORM_PART=1", *VGPR_FORM]),
            ("attn_bwd_dq_q64.hip", "attn_bwd_dq_q64.o", []),
+           ("attn_bwd_dq_q64.hip", "attn_bwd_dq_q64_f16.o", ["-DATTN_F16_PART=1"]),
            ("attn_varlen.hip", "attn_varlen.o", []),
            ("exp2_emulated.hip", "exp2_emulated.o", [])]
 PROBE_SOURCES = [("probes.hip", "probes.o", [])]

@@ -19,6 +19,7 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 #define ATTN_LDS __attribute__((address_space(3)))
 
@@ -190,6 +191,31 @@ struct TileCopy {
         }
     }
 };
+
+// Tile copies of ragged sequences without per-lane work: the tile is addressed through a buffer descriptor whose
+// range ends behind its last existing row, and lanes out of range write zeros to LDS (verified on the device
+// with a probe: 16- and 4-byte copies, ranges that end anywhere and empty ones).  nbytes = (existing rows) x
+// (row stride in bytes), which needs a row stride of at least the row; base, nbytes and m0 wave-uniform.
+__device__ __forceinline__ i32x4 tile_rsrc(const void* base, uint32_t nbytes)
+{
+    const uint64_t b = (uint64_t)base;
+    i32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) & 0xffff;
+    r[2] = __builtin_amdgcn_readfirstlane((int)nbytes);
+    r[3] = 0x00020000;                      // raw buffer, 32-bit data format
+    return r;
+}
+__device__ __forceinline__ void dma16_ranged(uint32_t m0, uint32_t voff, const void* base, uint32_t nbytes)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(m0), "v"(voff), "s"(tile_rsrc(base, nbytes)) : "memory");
+}
+__device__ __forceinline__ void dma4_ranged(uint32_t m0, uint32_t voff, const void* base, uint32_t nbytes)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :: "s"(m0), "v"(voff), "s"(tile_rsrc(base, nbytes)) : "memory");
+}
 
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0 .. N-1.
 template <int I, int N, typename F>

@@ -88,6 +88,15 @@ struct BwdArgs {
     bool f16 = false;             // as in FwdArgs
 };
 
+// Order of the table entries for kernels whose blocks take two 128-row tiles and have nothing to do for every
+// second tile of a sequence: entries 0, 2, 4, ... first, then 1, 3, 5, ...  Dispatched alternately, the empty
+// blocks would all fall to the same shader engines and leave the others twice the work.
+__device__ __forceinline__ int pair_order(int p, int n)
+{
+    const int half = (n + 1) >> 1;
+    return p < half ? 2 * p : 2 * (p - half) + 1;
+}
+
 // Launch through hipLaunchKernel so that the status returned belongs to THIS launch (the
 // sticky hipGetLastError slot may hold an unrelated earlier error of the host program).
 template <typename... KArgs, typename... Args>
@@ -128,14 +137,14 @@ int launch_fwd_q64(const FwdArgs& a);
 // partial results of a pass with nsplit > 1.
 int launch_decode(const FwdArgs& a);
 int launch_combine(const FwdArgs& a);
-// The dQ kernel with 64 queries per wave (d_qk = d_v = 128 or 64, fixed length, N % 256 = 0); it also
-// leaves -D and the base-2 LSE of every row in the workspace.
+// The dQ kernel with 64 queries per wave (d_qk = d_v = 128 or 64; fixed length N % 256 = 0, or variable-length
+// mode with row strides of at least a row); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_q64(const BwdArgs& a);
 // The dK/dV kernel with one wave per SIMD and 32-query tiles (head dims 128, (192, 128): N % 128 = 0; 64:
-// N % 256 = 0; fixed length, with or without the causal mask); -D and the base-2 LSE must be in the workspace.
+// N % 256 = 0; or variable-length mode as above; with or without the causal mask); -D and the base-2 LSE must be in the workspace.
 int launch_bwd_dkdv_t32(const BwdArgs& a);
-// The dQ kernel with one wave per SIMD and 32 queries per wave (head dims 128 and (192, 128), fixed length,
-// N % 128 = 0); it also leaves -D and the base-2 LSE of every row in the workspace.
+// The dQ kernel with one wave per SIMD and 32 queries per wave (head dims (192, 128); fixed length N % 128 = 0,
+// or variable-length mode as above); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_t32(const BwdArgs& a);
 // Fills the two plan tables of the variable-length entry points on the device: 0 or -3.
 int launch_varlen_plan(const int* cu_q, const int* cu_k, int B, int Tq, int Tk, void* plan_q, int max_tiles_q,
