@@ -87,12 +87,9 @@ int launch_bwd(const BwdArgs& a)
         return a.f16 ? f16k::launch_bwd_dims(part) : launch_bwd_dims(part);
     };
     const bool d128 = a.d_qk == 128 && a.d_v == 128, d64 = a.d_qk == 64 && a.d_v == 64, d192 = a.d_qk == 192 && a.d_v == 128;
-    // The kernels with one wave per SIMD at a fixed length of N tokens.  Below these lengths the 4-wave dQ kernel
-    // wins (its blocks are half the size and fill the chip better); at d = 64 the 256-key blocks of the dK/dV
-    // kernel are too few on short sequences (measured against the 4-wave kernel: +10 % at N = 512, +1 % at
-    // N = 1024, -4 % at N = 2048; under the mask +4 % at N = 4096, -6 % at N = 8192).  (192, 128): the 64-query dQ
-    // kernel's fragments and accumulators do not fit; 32 queries per wave.
-    auto dq_q64_at = [&](int N) { return N % 256 == 0 && ((d128 && N >= (a.causal ? 4096 : 1024)) || (d64 && N >= (a.causal ? 8192 : 2048))); };
+    // The dQ kernels with one wave per SIMD at a fixed length of N tokens.  (192, 128): the 64-query kernel's
+    // fragments and accumulators do not fit; 32 queries per wave.
+    auto dq_q64_at = [&](int N) { return (d128 || d64) && attn::dq_one_wave(a.d_qk, a.causal, N, (long long)a.B * a.H * N / 256); };
     auto dq_t32_at = [&](int N) { return d192 && N % 128 == 0 && N >= (a.causal ? 1024 : 512); };
     bool dq_q64, dq_t32, dkdv_t32;
     if (a.max_tiles > 0) {
@@ -122,7 +119,7 @@ int launch_bwd(const BwdArgs& a)
     } else {
         dq_q64 = dq_q64_at(a.N);
         dq_t32 = dq_t32_at(a.N);
-        dkdv_t32 = ((d128 || d192) && a.N % 128 == 0) || (d64 && a.N % 256 == 0 && a.N >= (a.causal ? 8192 : 2048));
+        dkdv_t32 = ((d128 || d192) && a.N % 128 == 0) || (d64 && dkdv64_one_wave(a.causal, a.N, (long long)a.B * a.Hkv * a.N / 256));
     }
     dq_q64 = dq_q64 && (a.phases & 4);
     dq_t32 = dq_t32 && (a.phases & 4);

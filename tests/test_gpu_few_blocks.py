@@ -1,0 +1,56 @@
+"""GPU tests of the fixed-length kernels with one wave per SIMD where the number of blocks, not the length, sends a
+call to them (more than 128 blocks of 256 rows): short sequences of many heads.  Two heads are generated and
+repeated, so that the oracle computes two and every repetition has to reproduce their bits; the scores of the
+forward cases grow or climb along the keys, which sends those kernels through the second pass and through the
+step of the reference inside the loop."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_05451_amd import inputs as I
+from parity import LSE_ABS, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _repeat(t, H):
+    return t.repeat(1, 1, H // 2, 1).cuda()
+
+
+# 144, 208, 136, 320, 136, 224 blocks of 256 queries
+@pytest.mark.parametrize("causal,N,H,d,dv", [(False, 2048, 18, 128, 128), (True, 2048, 26, 128, 128), (False, 1024, 34, 64, 64),
+                                             (True, 8192, 10, 64, 64), (False, 1024, 34, 192, 128), (True, 4096, 14, 192, 128)])
+@pytest.mark.parametrize("kind", ["normal", "growing", "climbing"])
+def test_forward(oracle, causal, N, H, d, dv, kind):
+    import paper_2603_05451_amd as A
+    g = torch.Generator("cpu").manual_seed(300 + d + N)
+    q, k, v = (torch.randn(1, N, 2, e, generator=g) for e in (d, d, dv))
+    if kind == "growing":        # by hundreds of binary orders: relative to the first tile the exponentials overflow
+        q, k = q.abs(), k.abs() * torch.linspace(0.2, 30.0, N).view(1, N, 1, 1)
+    if kind == "climbing":       # by 300 binary orders in small steps
+        q, k = 1.0 + 0.1 * q, torch.linspace(0.0, 300.0 / (1.4427 * d ** 0.5), N).view(1, N, 1, 1) + 0.1 * k
+    q, k, v = (t.bfloat16() for t in (q, k, v))
+    o, lse = A.attn_fwd(_repeat(q, H), _repeat(k, H), _repeat(v, H), d ** -0.5, causal)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o[:, :, h], o[:, :, h % 2]) and torch.equal(lse[:, h], lse[:, h % 2]) for h in range(H))
+    rows = np.unique(np.concatenate([[0, 1, 63, 64, 255, 256, N - 257, N - 1], np.arange(5, N, 61)]))
+    ro, rlse = oracle.attn_fwd(I.to_f64(q[:, rows]), I.to_f64(k), I.to_f64(v), d ** -0.5, causal, q_pos=rows)
+    assert_close(o[:, rows, :2].float().cpu().numpy(), ro, f"O {kind}")
+    # (LSE is an fp32 number: half an ulp of one above 1024 is 6e-5, of one above 8192 5e-4)
+    assert np.abs(lse[:, :2].cpu().numpy()[:, :, rows] - rlse).max() <= LSE_ABS * max(1.0, np.abs(rlse).max() / 64)
+
+
+# 136, 136, 136, 200, 320 blocks of 256 queries or keys
+@pytest.mark.parametrize("causal,N,H,d", [(True, 1024, 34, 128), (False, 1024, 34, 128), (False, 1024, 34, 64), (True, 1024, 50, 64),
+                                          (True, 8192, 10, 64)])
+def test_backward(oracle, causal, N, H, d):
+    import paper_2603_05451_amd as A
+    x = I.make_inputs(I.Workload("few", 1, 2, 2, N, d, d, causal, 320 + d + H))
+    q, k, v, do = (_repeat(x[n], H) for n in ("q", "k", "v", "do"))
+    o, lse = A.attn_fwd(q, k, v, d ** -0.5, causal)
+    got = A.attn_bwd(q, k, v, o, do, lse, d ** -0.5, causal)
+    torch.cuda.synchronize()
+    ref = oracle.attn_bwd(*(I.to_f64(x[n]) for n in ("q", "k", "v", "do")), d ** -0.5, causal)
+    for what, a, r in zip(("dQ", "dK", "dV"), got, ref):
+        assert all(torch.equal(a[:, :, h], a[:, :, h % 2]) for h in range(H)), what
+        assert_close(a[:, :, :2].float().cpu().numpy(), r, what)
