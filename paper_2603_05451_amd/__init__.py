@@ -6,8 +6,10 @@ or eager fallback: if the library is missing or a call fails, an exception is ra
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
+from functools import lru_cache
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn.so")
@@ -59,7 +61,7 @@ def lib():
         L.attn_varlen_bwd_dtype.restype = i
         L.attn_varlen_workspace_bytes.argtypes = [i] * 8
         L.attn_varlen_workspace_bytes.restype = sz
-        sp = ctypes.POINTER(AttnStrides)
+        sp = vp              # attn_strides_t*: an address (see _strides) or byref(AttnStrides(...))
         L.attn_strided_workspace_bytes.argtypes = [i] * 8
         L.attn_strided_workspace_bytes.restype = sz
         L.attn_fwd_strided.argtypes = [i] + [vp, sp] * 4 + [vp] + [i] * 7 + [f, i, vp, sz, vp]
@@ -94,10 +96,15 @@ def _check(rc: int):
         raise AttnError(rc, attn_strerror(rc))
 
 
+# The marshalling below is most of a small call's time (three kernels of 5 us each against 37 us for forward and
+# backward of 2 heads x 128 tokens when every argument was wrapped in a ctypes object of its own and the stream
+# came from torch.cuda.current_stream()): plain integers, which ctypes converts by argtypes, and the raw stream.
 def _stream(stream):
+    """Raw hipStream_t of `stream`, or of the current device's current stream."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 ATTN_BF16, ATTN_F16 = 0, 1
@@ -113,17 +120,23 @@ def _dtype_code(t):
     raise ValueError(f"unsupported element type {t.dtype}: bf16 or fp16")
 
 
-def _dev_bf16(t, name, shape=None, like=None):
-    """Device pointer of a contiguous 16-bit CUDA tensor (bf16, or the element type of `like`)."""
-    import torch
-    want = torch.bfloat16 if like is None else like.dtype
-    if not (t.is_cuda and t.dtype == want and t.is_contiguous()):
-        raise ValueError(f"{name} must be a contiguous {want} CUDA tensor")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+def _dev(t, name, shape, dtype):
+    """Device address of a contiguous CUDA tensor of that element type and shape."""
+    if not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
+        raise ValueError(f"{name} must be a contiguous {dtype} CUDA tensor")
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
+def _dev_lse(lse, shape, axes):
+    import torch
+    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and lse.shape == shape):
+        raise ValueError(f"lse must be a contiguous fp32 CUDA tensor [{axes}]")
+    return lse.data_ptr()
+
+
+@lru_cache(maxsize=256)
 def attn_bwd_workspace_bytes(B, H, Hkv, N, d_qk, d_v) -> int:
     return int(lib().attn_bwd_workspace_bytes(B, H, Hkv, N, d_qk, d_v))
 
@@ -140,18 +153,14 @@ def attn_fwd(q, k, v, scale, causal, o=None, lse=None, stream=None):
         o = torch.empty((B, N, H, dv), dtype=q.dtype, device=q.device)
     if lse is None:
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and
-            tuple(lse.shape) == (B, H, N)):
-        raise ValueError("lse must be a contiguous fp32 CUDA tensor [B,H,N]")
-    args = (_dev_bf16(q, "q", like=q), _dev_bf16(k, "k", (B, N, Hkv, dqk), q),
-            _dev_bf16(v, "v", (B, N, Hkv, dv), q), _dev_bf16(o, "o", (B, N, H, dv), q),
-            ctypes.c_void_p(lse.data_ptr()), B, H, Hkv, N, dqk, dv,
-            float(scale), int(bool(causal)), _stream(stream))
-    rc = lib().attn_fwd_ex(*args) if code == ATTN_BF16 else lib().attn_fwd_dtype(code, *args)
-    _check(rc)
+    lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,N"), q.dtype
+    _check(lib().attn_fwd_dtype(code, _dev(q, "q", q.shape, dt), _dev(k, "k", (B, N, Hkv, dqk), dt),
+                                _dev(v, "v", (B, N, Hkv, dv), dt), _dev(o, "o", (B, N, H, dv), dt), lse_p,
+                                B, H, Hkv, N, dqk, dv, float(scale), int(bool(causal)), _stream(stream)))
     return o, lse
 
 
+@lru_cache(maxsize=256)
 def attn_varlen_workspace_bytes(B, total_q, total_k, H, Hkv, d_qk, d_v, backward) -> int:
     return int(lib().attn_varlen_workspace_bytes(B, total_q, total_k, H, Hkv, d_qk, d_v, int(bool(backward))))
 
@@ -163,17 +172,16 @@ def attn_varlen_plan(cu_seqlens, total_q, total_k, H, Hkv, d_qk, d_v, workspace,
     if cu_seqlens_k is None:
         cu_seqlens_k = cu_seqlens
     _check(lib().attn_varlen_plan(_dev_cu(cu_seqlens, B), _dev_cu(cu_seqlens_k, B, "cu_seqlens_k"), B, total_q, total_k,
-                                  H, Hkv, d_qk, d_v, ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                  _stream(stream)))
+                                  H, Hkv, d_qk, d_v, workspace.data_ptr(), workspace.numel(), _stream(stream)))
 
 
 def _dev_cu(cu, B, name="cu_seqlens"):
     import torch
     if cu is None:
         return None
-    if not (cu.is_cuda and cu.dtype == torch.int32 and cu.is_contiguous() and tuple(cu.shape) == (B + 1,)):
+    if not (cu.is_cuda and cu.dtype == torch.int32 and cu.is_contiguous() and cu.shape == (B + 1,)):
         raise ValueError(f"{name} must be a contiguous int32 CUDA tensor [B+1]")
-    return ctypes.c_void_p(cu.data_ptr())
+    return cu.data_ptr()
 
 
 def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, workspace=None, stream=None,
@@ -195,18 +203,15 @@ def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, worksp
         o = torch.empty((T, H, dv), dtype=q.dtype, device=q.device)
     if lse is None:
         lse = torch.empty((H, T), dtype=torch.float32, device=q.device)
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and tuple(lse.shape) == (H, T)):
-        raise ValueError("lse must be a contiguous fp32 CUDA tensor [H,Tq]")
-    need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv, False)
+    lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
     if workspace is None:
+        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv, False)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    code = _dtype_code(q)
-    args = (_dev_bf16(q, "q", like=q), _dev_bf16(k, "k", (Tk, Hkv, dqk), q), _dev_bf16(v, "v", (Tk, Hkv, dv), q),
-            _dev_bf16(o, "o", (T, H, dv), q), ctypes.c_void_p(lse.data_ptr()), _dev_cu(cu_seqlens, B),
-            _dev_cu(cu_seqlens_k, B, "cu_seqlens_k"), B, T, Tk, H, Hkv, dqk, dv, float(scale), int(bool(causal)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream(stream))
-    rc = lib().attn_varlen_fwd(*args) if code == ATTN_BF16 else lib().attn_varlen_fwd_dtype(code, *args)
-    _check(rc)
+    _check(lib().attn_varlen_fwd_dtype(
+        _dtype_code(q), _dev(q, "q", q.shape, dt), _dev(k, "k", (Tk, Hkv, dqk), dt), _dev(v, "v", (Tk, Hkv, dv), dt),
+        _dev(o, "o", (T, H, dv), dt), lse_p, _dev_cu(cu_seqlens, B), _dev_cu(cu_seqlens_k, B, "cu_seqlens_k"),
+        B, T, Tk, H, Hkv, dqk, dv, float(scale), int(bool(causal)), workspace.data_ptr(), workspace.numel(),
+        _stream(stream)))
     return o, lse
 
 
@@ -226,21 +231,16 @@ def attn_varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, scale, causal, dq=None, dk
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
-    need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv_, True)
     if workspace is None:
+        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv_, True)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and tuple(lse.shape) == (H, T)):
-        raise ValueError("lse must be a contiguous fp32 CUDA tensor [H,Tq]")
-    code = _dtype_code(q)
-    args = (_dev_bf16(q, "q", like=q), _dev_bf16(k, "k", (Tk, Hkv, dqk), q), _dev_bf16(v, "v", (Tk, Hkv, dv_), q),
-            _dev_bf16(o, "o", (T, H, dv_), q), _dev_bf16(d_o, "d_o", (T, H, dv_), q),
-            ctypes.c_void_p(lse.data_ptr()), _dev_bf16(dq, "dq", (T, H, dqk), q),
-            _dev_bf16(dk, "dk", (Tk, Hkv, dqk), q), _dev_bf16(dv, "dv", (Tk, Hkv, dv_), q),
-            _dev_cu(cu_seqlens, B), _dev_cu(cu_seqlens_k, B, "cu_seqlens_k"), B, T, Tk, H, Hkv, dqk, dv_,
-            float(scale), int(bool(causal)),
-            ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream(stream))
-    rc = lib().attn_varlen_bwd(*args) if code == ATTN_BF16 else lib().attn_varlen_bwd_dtype(code, *args)
-    _check(rc)
+    lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
+    _check(lib().attn_varlen_bwd_dtype(
+        _dtype_code(q), _dev(q, "q", q.shape, dt), _dev(k, "k", (Tk, Hkv, dqk), dt), _dev(v, "v", (Tk, Hkv, dv_), dt),
+        _dev(o, "o", (T, H, dv_), dt), _dev(d_o, "d_o", (T, H, dv_), dt), lse_p, _dev(dq, "dq", (T, H, dqk), dt),
+        _dev(dk, "dk", (Tk, Hkv, dqk), dt), _dev(dv, "dv", (Tk, Hkv, dv_), dt), _dev_cu(cu_seqlens, B),
+        _dev_cu(cu_seqlens_k, B, "cu_seqlens_k"), B, T, Tk, H, Hkv, dqk, dv_, float(scale), int(bool(causal)),
+        workspace.data_ptr(), workspace.numel(), _stream(stream)))
     return dq, dk, dv
 
 
@@ -249,15 +249,24 @@ class AttnStrides(ctypes.Structure):
     _fields_ = [("batch", ctypes.c_longlong), ("row", ctypes.c_longlong), ("head", ctypes.c_longlong)]
 
 
-def _view(t, name, shape, like):
-    """(pointer, strides) of a [B, N, heads, d] view with a contiguous head dim."""
-    if not (t.is_cuda and t.dtype == like.dtype and t.dim() == 4 and (t.stride(3) == 1 or t.shape[3] == 1)):
-        raise ValueError(f"{name} must be a 4-d {like.dtype} CUDA tensor with a contiguous last axis")
-    if tuple(t.shape) != tuple(shape):
+def _view(t, name, shape, dtype, strides):
+    """Address of a [B, N, heads, d] view with a contiguous head dim; appends its strides to `strides`."""
+    if not (t.is_cuda and t.dtype == dtype and t.dim() == 4 and (t.stride(3) == 1 or t.shape[3] == 1)):
+        raise ValueError(f"{name} must be a 4-d {dtype} CUDA tensor with a contiguous last axis")
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr()), ctypes.byref(AttnStrides(t.stride(0), t.stride(1), t.stride(2)))
+    strides.extend(t.stride()[:3])
+    return t.data_ptr()
 
 
+def _with_strides(pointers, strides):
+    """pointer, attn_strides_t*, pointer, ... for the C ABI.  `strides` (three numbers per pointer, the layout of
+    AttnStrides) has to outlive the call."""
+    at = strides.buffer_info()[0]
+    return [x for i, p in enumerate(pointers) for x in (p, at + 24 * i)]
+
+
+@lru_cache(maxsize=256)
 def attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, backward) -> int:
     return int(lib().attn_strided_workspace_bytes(B, H, Hkv, Nq, Nk, d_qk, d_v, int(bool(backward))))
 
@@ -274,17 +283,15 @@ def attn_fwd_strided(q, k, v, scale, causal, o=None, lse=None, workspace=None, s
         o = torch.empty((B, N, H, dv), dtype=q.dtype, device=q.device)
     if lse is None:
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and tuple(lse.shape) == (B, H, N)):
-        raise ValueError("lse must be a contiguous fp32 CUDA tensor [B,H,Nq]")
-    need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv, False)
+    lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
+        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv, False)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    rc = lib().attn_fwd_strided(_dtype_code(q), *_view(q, "q", (B, N, H, dqk), q), *_view(k, "k", (B, Nk, Hkv, dqk), q),
-                                *_view(v, "v", (B, Nk, Hkv, dv), q), *_view(o, "o", (B, N, H, dv), q),
-                                ctypes.c_void_p(lse.data_ptr()), B, H, Hkv, N, Nk, dqk, dv, float(scale),
-                                int(bool(causal)), ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                _stream(stream))
-    _check(rc)
+    st = array.array("q")
+    ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
+            _view(v, "v", (B, Nk, Hkv, dv), dt, st), _view(o, "o", (B, N, H, dv), dt, st))
+    _check(lib().attn_fwd_strided(_dtype_code(q), *_with_strides(ptrs, st), lse_p, B, H, Hkv, N, Nk, dqk, dv, float(scale),
+                                  int(bool(causal)), workspace.data_ptr(), workspace.numel(), _stream(stream)))
     return o, lse
 
 
@@ -297,19 +304,18 @@ def attn_bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq=None, dk=None, dv=N
     dq = torch.empty((B, N, H, dqk), dtype=q.dtype, device=q.device) if dq is None else dq
     dk = torch.empty((B, Nk, Hkv, dqk), dtype=q.dtype, device=q.device) if dk is None else dk
     dv = torch.empty((B, Nk, Hkv, dv_), dtype=q.dtype, device=q.device) if dv is None else dv
-    if not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous() and tuple(lse.shape) == (B, H, N)):
-        raise ValueError("lse must be a contiguous fp32 CUDA tensor [B,H,Nq]")
-    need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv_, True)
+    lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
+        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv_, True)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    rc = lib().attn_bwd_strided(_dtype_code(q), *_view(q, "q", (B, N, H, dqk), q), *_view(k, "k", (B, Nk, Hkv, dqk), q),
-                                *_view(v, "v", (B, Nk, Hkv, dv_), q), *_view(o, "o", (B, N, H, dv_), q),
-                                *_view(d_o, "d_o", (B, N, H, dv_), q), ctypes.c_void_p(lse.data_ptr()),
-                                *_view(dq, "dq", (B, N, H, dqk), q), *_view(dk, "dk", (B, Nk, Hkv, dqk), q),
-                                *_view(dv, "dv", (B, Nk, Hkv, dv_), q), B, H, Hkv, N, Nk, dqk, dv_, float(scale),
-                                int(bool(causal)), ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
-                                _stream(stream))
-    _check(rc)
+    st = array.array("q")
+    ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
+            _view(v, "v", (B, Nk, Hkv, dv_), dt, st), _view(o, "o", (B, N, H, dv_), dt, st),
+            _view(d_o, "d_o", (B, N, H, dv_), dt, st), _view(dq, "dq", (B, N, H, dqk), dt, st),
+            _view(dk, "dk", (B, Nk, Hkv, dqk), dt, st), _view(dv, "dv", (B, Nk, Hkv, dv_), dt, st))
+    a = _with_strides(ptrs, st)
+    _check(lib().attn_bwd_strided(_dtype_code(q), *a[:10], lse_p, *a[10:], B, H, Hkv, N, Nk, dqk, dv_, float(scale),
+                                  int(bool(causal)), workspace.data_ptr(), workspace.numel(), _stream(stream)))
     return dq, dk, dv
 
 
@@ -319,8 +325,7 @@ def attn_exp2_emulated(x, degree, y=None, stream=None):
     if not (x.is_cuda and x.dtype == torch.float32 and x.is_contiguous()):
         raise ValueError("x must be a contiguous fp32 CUDA tensor")
     y = torch.empty_like(x) if y is None else y
-    _check(lib().attn_exp2_emulated(ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
-                                    x.numel(), int(degree), _stream(stream)))
+    _check(lib().attn_exp2_emulated(x.data_ptr(), y.data_ptr(), x.numel(), int(degree), _stream(stream)))
     return y
 
 
@@ -343,13 +348,11 @@ def attn_bwd(q, k, v, o, do, lse, scale, causal, dq=None, dk=None, dv=None, work
                or ATTN_EINVAL)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    code = _dtype_code(q)
-    args = (_dev_bf16(q, "q", like=q), _dev_bf16(k, "k", (B, N, Hkv, dqk), q),
-            _dev_bf16(v, "v", (B, N, Hkv, dvd), q), _dev_bf16(o, "o", (B, N, H, dvd), q),
-            _dev_bf16(do, "do", (B, N, H, dvd), q), ctypes.c_void_p(lse.data_ptr()),
-            _dev_bf16(dq, "dq", q.shape, q), _dev_bf16(dk, "dk", k.shape, q),
-            _dev_bf16(dv, "dv", v.shape, q), B, H, Hkv, N, dqk, dvd, float(scale),
-            int(bool(causal)), ctypes.c_void_p(workspace.data_ptr()),
+    code, dt = _dtype_code(q), q.dtype
+    args = (_dev(q, "q", q.shape, dt), _dev(k, "k", (B, N, Hkv, dqk), dt), _dev(v, "v", (B, N, Hkv, dvd), dt),
+            _dev(o, "o", (B, N, H, dvd), dt), _dev(do, "do", (B, N, H, dvd), dt), lse.data_ptr(),
+            _dev(dq, "dq", q.shape, dt), _dev(dk, "dk", k.shape, dt), _dev(dv, "dv", v.shape, dt),
+            B, H, Hkv, N, dqk, dvd, float(scale), int(bool(causal)), workspace.data_ptr(),
             workspace.numel() * workspace.element_size(), _stream(stream))
     if code == ATTN_BF16:
         rc = lib().attn_bwd_phases(*args, int(phases))
@@ -371,10 +374,10 @@ def attn_bwd_noalloc(q, k, v, o, do, lse, scale, causal, dq, dk, dv, stream=None
     Hkv, dvd = k.shape[2], v.shape[3]
     if _dtype_code(q) != ATTN_BF16:
         raise ValueError("attn_bwd_noalloc takes bf16 tensors")
-    _check(lib().attn_bwd_noalloc(_dev_bf16(q, "q", like=q), _dev_bf16(k, "k", (B, N, Hkv, dqk), q),
-                                  _dev_bf16(v, "v", (B, N, Hkv, dvd), q), _dev_bf16(o, "o", (B, N, H, dvd), q),
-                                  _dev_bf16(do, "do", (B, N, H, dvd), q), ctypes.c_void_p(lse.data_ptr()),
-                                  _dev_bf16(dq, "dq", q.shape, q), _dev_bf16(dk, "dk", k.shape, q),
-                                  _dev_bf16(dv, "dv", v.shape, q), B, H, Hkv, N, dqk, dvd, float(scale),
-                                  int(bool(causal)), _stream(stream)))
+    dt = q.dtype
+    _check(lib().attn_bwd_noalloc(_dev(q, "q", q.shape, dt), _dev(k, "k", (B, N, Hkv, dqk), dt),
+                                  _dev(v, "v", (B, N, Hkv, dvd), dt), _dev(o, "o", (B, N, H, dvd), dt),
+                                  _dev(do, "do", (B, N, H, dvd), dt), lse.data_ptr(), _dev(dq, "dq", q.shape, dt),
+                                  _dev(dk, "dk", k.shape, dt), _dev(dv, "dv", v.shape, dt), B, H, Hkv, N, dqk, dvd,
+                                  float(scale), int(bool(causal)), _stream(stream)))
     return dq, dk, dv
