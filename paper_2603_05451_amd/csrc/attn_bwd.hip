@@ -86,11 +86,16 @@ int launch_bwd(const BwdArgs& a)
         part.phases = phases;
         return a.f16 ? f16k::launch_bwd_dims(part) : launch_bwd_dims(part);
     };
-    const bool d128 = a.d_qk == 128 && a.d_v == 128, d64 = a.d_qk == 64 && a.d_v == 64, d192 = a.d_qk == 192 && a.d_v == 128;
-    // The dQ kernels with one wave per SIMD at a fixed length of N tokens.  (192, 128): the 64-query kernel's
-    // fragments and accumulators do not fit; 32 queries per wave.
+    const bool d128 = a.d_qk == 128 && a.d_v == 128, d64 = a.d_qk == 64 && a.d_v == 64, d192 = a.d_qk == 192 && a.d_v == 128, d256 = a.d_qk == 256;
+    // The dQ kernels with one wave per SIMD at a fixed length of N tokens.  (192, 128) and 256: the 64-query
+    // kernel's fragments and accumulators do not fit; 32 queries per wave.
     auto dq_q64_at = [&](int N) { return (d128 || d64) && attn::dq_one_wave(a.d_qk, a.causal, N, (long long)a.B * a.H * N / 256); };
     auto dq_t32_at = [&](int N) { return d192 && N % 128 == 0 && N >= (a.causal ? 1024 : 512); };
+    // d = 256, dQ and dK/dV: the pipelined kernels win but on the shortest causal sequences of many blocks (B H = 512
+    // at N = 128: dQ 46.3 -> 47.7 us, dK/dV 70.2 -> 72.7, N = 256: 53.6 -> 51.5, 82.3 -> 84.2, N = 512: 71.8 -> 62.0,
+    // 121 -> 108, N = 2048: 159 -> 125, 295 -> 234; one sequence of 128: 16.5 -> 15.5, 35.7 -> 29.2)
+    auto short_causal = [&](int N, int most, int heads) { return a.causal && N <= most && (long long)a.B * heads * N > 256 * 128; };
+    auto dq256_at = [&](int N) { return d256 && !short_causal(N, 128, a.H); };
     bool dq_q64, dq_t32, dkdv_t32;
     if (a.max_tiles > 0) {
         // Variable-length mode, by the mean number of queries n.  Their copies are bounded by whole rows, so a row has
@@ -109,17 +114,18 @@ int launch_bwd(const BwdArgs& a)
         const int64_t half = ((int64_t)a.T + 255) / 256 * a.H, r = (half + 255) / 256, s = (2 * half + 255) / 256;
         dq_q64 = rows && (as_fixed ? dq_q64_at(a.st.nq)
                                    : (d128 && n >= 512 && 9 * r <= 5 * s) || (d64 && n >= (a.causal ? 4096 : 2048) && half >= 512));
-        dq_t32 = rows && (as_fixed ? dq_t32_at(a.st.nq) : d192 && n >= (a.causal ? 1024 : 512));
-        // dK/dV (the same bits as the general kernels): d = 128 n = 256 297 -> 269 and 284 -> 260, n = 1000 454 -> 425
+        dq_t32 = rows && (as_fixed ? dq_t32_at(a.st.nq) || dq256_at(a.st.nq) : (d192 && n >= (a.causal ? 1024 : 512)) || d256);
+        // d = 256: packed 24 sequences of 251 ... 2025 tokens, H = 16/8, dQ 1435 -> 1306 and 3682 -> 3535, dK/dV
+        // 1435 -> 1182 and 3682 -> 1757.  dK/dV (the same bits as the general kernels): d = 128 n = 256 297 -> 269 and 284 -> 260, n = 1000 454 -> 425
         // and 580 -> 545, n = 8000 1816 -> 1768 and 3401 -> 3275; (192, 128) n = 500 546 -> 433 and 895 -> 474,
         // n = 8000 2970 -> 2322 and 9065 -> 4226; d = 64 (256 keys per block, one per CU, against 128 and two)
         // n = 1000 214 -> 231 and 268 -> 261, n = 2000 337 -> 344 and 486 -> 464, n = 4000 581 -> 571 and 912 -> 871.
         const int64_t blocks64 = (int64_t)a.max_tiles_k / 2 * a.Hkv;
-        dkdv_t32 = rows && (d128 || d192 || (d64 && n >= (a.causal ? 4096 : 2048) && blocks64 >= 512));
+        dkdv_t32 = rows && (d128 || d192 || d256 || (d64 && n >= (a.causal ? 4096 : 2048) && blocks64 >= 512));
     } else {
         dq_q64 = dq_q64_at(a.N);
-        dq_t32 = dq_t32_at(a.N);
-        dkdv_t32 = ((d128 || d192) && a.N % 128 == 0) || (d64 && dkdv64_one_wave(a.causal, a.N, (long long)a.B * a.Hkv * a.N / 256));
+        dq_t32 = dq_t32_at(a.N) || dq256_at(a.N);
+        dkdv_t32 = d128 || d192 || (d256 && !short_causal(a.N, 256, a.Hkv)) || (d64 && dkdv64_one_wave(a.causal, a.N, (long long)a.B * a.Hkv * a.N / 256));
     }
     dq_q64 = dq_q64 && (a.phases & 4);
     dq_t32 = dq_t32 && (a.phases & 4);

@@ -17,7 +17,9 @@ CASES = [(128, 128, True, [(513, 513), (1055, 1055), (300, 300), (896, 896)]),
          (128, 128, False, [(257, 1000), (1025, 95), (640, 640)]),
          (128, 128, True, [(1, 700), (545, 673), (1100, 1133), (700, 1499), (383, 384)]),
          (192, 128, True, [(1153, 1153), (1023, 1200), (1000, 1065)]),
-         (192, 128, False, [(545, 300), (500, 1057)])]
+         (192, 128, False, [(545, 300), (500, 1057)]),
+         (256, 256, True, [(513, 513), (1, 300), (300, 333), (257, 384)]),
+         (256, 256, False, [(129, 700), (385, 95)])]
 
 
 @pytest.mark.parametrize("dqk,dv,causal,lens", CASES, ids=["d%d_%s_%d" % (c[0], "c" if c[2] else "nc", len(c[3])) for c in CASES])
