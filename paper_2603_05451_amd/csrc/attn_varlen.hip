@@ -24,29 +24,41 @@ namespace attn {
 constexpr int PLAN_NT = 1024;
 constexpr int PLAN_BUCKETS = 4096;      // loop lengths 0 .. 4095 tiles; longer ones share the top bucket
 
-// One table.  own/other: the side whose tiles are listed and the side they loop over.
+// What the kernel costs is its chain of dependent steps -- every packed call waits for it, and a small one takes
+// 15-20 us in all.  So: a block per table, boundaries read once into registers (sequences beyond one per thread
+// are read again), a scan by wave shuffles with two barriers, and zeros only behind the last entry.
+// own/other: the side whose tiles are listed and the side they loop over.
 __device__ void plan_build(const int* __restrict__ cu_q, const int* __restrict__ cu_k, int B, int Tq, int Tk, bool own_is_q,
-                           int4* __restrict__ plan, int max_tiles, int* hist, int* start, int* part)
+                           int4* __restrict__ plan, int max_tiles)
 {
+    __shared__ int hist[PLAN_BUCKETS];       // tiles per bucket, then next free entry per bucket
+    __shared__ int wave_sum[PLAN_NT / 64];
     static_assert(PLAN_BUCKETS == 4 * PLAN_NT, "four buckets per thread in the scan below");
-    const int tid = threadIdx.x;
-    for (int i = tid; i < PLAN_BUCKETS; i += PLAN_NT) hist[i] = 0;
-    for (int i = tid; i < 2 * max_tiles; i += PLAN_NT) plan[i] = make_int4(0, 0, 0, 0);
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto tiles = [](int len) { return (len + 127) / 128; };
-    auto bucket_of = [](int nt) { return nt < PLAN_BUCKETS ? nt : PLAN_BUCKETS - 1; };
-    // a sequence contributes its own tiles; query tiles of a sequence without keys are not listed
-    auto own_tiles = [&](int ql, int kl) { return own_is_q ? (kl > 0 ? tiles(ql) : 0) : tiles(kl); };
-    auto key_of = [&](int ql, int kl) { return bucket_of(tiles(own_is_q ? kl : ql)); };
-    // A sequence whose rows do not lie inside the tensors (boundaries that decrease, or that run past
-    // the totals the caller stated) gets no tiles at all: nothing of it is read or written.
-    auto inside = [&](int qs, int ql, int ks, int kl) {
-        return qs >= 0 && ql >= 0 && qs <= Tq - ql && ks >= 0 && kl >= 0 && ks <= Tk - kl;
+    struct Sequence { int qs, ql, ks, kl, nt, key; };
+    auto load = [&](int b) {
+        Sequence s;
+        s.qs = cu_q[b]; s.ql = cu_q[b + 1] - s.qs;
+        s.ks = cu_k[b]; s.kl = cu_k[b + 1] - s.ks;
+        // A sequence whose rows do not lie inside the tensors (boundaries that decrease, or that run past
+        // the totals the caller stated) gets no tiles at all: nothing of it is read or written.  Query tiles
+        // of a sequence without keys are not listed.
+        const bool inside = s.qs >= 0 && s.ql >= 0 && s.qs <= Tq - s.ql && s.ks >= 0 && s.kl >= 0 && s.ks <= Tk - s.kl;
+        s.nt = !inside ? 0 : own_is_q ? (s.kl > 0 ? tiles(s.ql) : 0) : tiles(s.kl);
+        const int loop = tiles(own_is_q ? s.kl : s.ql);
+        s.key = loop < PLAN_BUCKETS ? loop : PLAN_BUCKETS - 1;
+        return s;
     };
-    for (int b = tid; b < B; b += PLAN_NT) {
-        const int qs = cu_q[b], ql = cu_q[b + 1] - qs, ks = cu_k[b], kl = cu_k[b + 1] - ks;
-        const int nt = inside(qs, ql, ks, kl) ? own_tiles(ql, kl) : 0;
-        if (nt > 0) atomicAdd(&hist[key_of(ql, kl)], nt);
+    Sequence own = {};
+    if (tid < B) own = load(tid);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) hist[4 * tid + e] = 0;
+    __syncthreads();
+    if (own.nt > 0) atomicAdd(&hist[own.key], own.nt);
+    for (int b = tid + PLAN_NT; b < B; b += PLAN_NT) {
+        const Sequence s = load(b);
+        if (s.nt > 0) atomicAdd(&hist[s.key], s.nt);
     }
     __syncthreads();
     // Exclusive prefix sum of the tile counts over the buckets from the longest loop down.
@@ -55,53 +67,64 @@ __device__ void plan_build(const int* __restrict__ cu_q, const int* __restrict__
     int w[4], local = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) { w[e] = hist[PLAN_BUCKETS - 1 - (4 * tid + e)]; local += w[e]; }
-    part[tid] = local;
-    __syncthreads();
-    for (int off = 1; off < PLAN_NT; off <<= 1) {          // inclusive Hillis-Steele scan of the partials
-        const int add = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += add;
-        __syncthreads();
+    int scan = local;                        // inclusive, within the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int below = __shfl_up(scan, off);
+        if (lane >= off) scan += below;
     }
-    int run = part[tid] - local;
+    if (lane == 63) wave_sum[wave] = scan;
+    __syncthreads();
+    int run = scan - local, total = 0;
+#pragma unroll
+    for (int v = 0; v < PLAN_NT / 64; ++v) {
+        const int sum = wave_sum[v];
+        if (v < wave) run += sum;
+        total += sum;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        start[PLAN_BUCKETS - 1 - (4 * tid + e)] = run;
+        hist[PLAN_BUCKETS - 1 - (4 * tid + e)] = run;
         run += w[e];
     }
     __syncthreads();
-    for (int i = tid; i < PLAN_BUCKETS; i += PLAN_NT) hist[i] = 0;     // becomes the per-bucket tile cursor
-    __syncthreads();
-    for (int b = tid; b < B; b += PLAN_NT) {
-        const int qs = cu_q[b], ql = cu_q[b + 1] - qs, ks = cu_k[b], kl = cu_k[b + 1] - ks;
-        const int nt = inside(qs, ql, ks, kl) ? own_tiles(ql, kl) : 0;
-        if (nt <= 0) continue;
-        const int key = key_of(ql, kl);
-        const int first = start[key] + atomicAdd(&hist[key], nt);
-        for (int t = 0; t < nt; ++t)
-            if (first + t < max_tiles) {
-                plan[2 * (first + t)] = make_int4(qs, ql, ks, kl);
-                plan[2 * (first + t) + 1] = make_int4(nt - 1 - t, kPlanUsed, b, 0);
-            }
-    }
-    __syncthreads();
+    // the entries: one or two by the sequence's own lane; of longer sequences the wave writes 64 at a time
+    auto entry = [&](int at, int4 rows, int tile, int b) {
+        plan[2 * at] = rows;
+        plan[2 * at + 1] = make_int4(tile, kPlanUsed, b, 0);
+    };
+    auto put = [&](const Sequence& s, int b) {
+        int first = 0;
+        if (s.nt > 0) first = atomicAdd(&hist[s.key], s.nt);
+        if (s.nt > 0 && s.nt <= 2)
+            for (int t = 0; t < s.nt; ++t)
+                if (first + t < max_tiles) entry(first + t, make_int4(s.qs, s.ql, s.ks, s.kl), s.nt - 1 - t, b);
+        for (uint64_t left = __ballot(s.nt > 2); left; left &= left - 1) {
+            const int l = __builtin_ctzll(left);
+            auto of = [&](int x) { return __builtin_amdgcn_readlane(x, l); };
+            const int nt = of(s.nt), at = of(first), sb = of(b);
+            const int4 rows = make_int4(of(s.qs), of(s.ql), of(s.ks), of(s.kl));
+            for (int t = lane; t < nt && at + t < max_tiles; t += 64) entry(at + t, rows, nt - 1 - t, sb);
+        }
+    };
+    put(own, tid);
+    for (int b0 = PLAN_NT; b0 < B; b0 += PLAN_NT) put(b0 + tid < B ? load(b0 + tid) : Sequence{}, b0 + tid);
+    for (int i = 2 * total + tid; i < 2 * max_tiles; i += PLAN_NT) plan[i] = make_int4(0, 0, 0, 0);
 }
 
+// Block 0: the table of query tiles; block 1 (backward only): the table of key tiles.
 __global__ void __launch_bounds__(PLAN_NT)
 varlen_plan_kernel(const int* __restrict__ cu_q, const int* __restrict__ cu_k, int B, int Tq, int Tk,
                    int4* __restrict__ plan_q, int max_tiles_q, int4* __restrict__ plan_k, int max_tiles_k)
 {
-    __shared__ int hist[PLAN_BUCKETS];       // tiles per bucket, then next free tile per bucket
-    __shared__ int start[PLAN_BUCKETS];      // first table entry of each bucket
-    __shared__ int part[PLAN_NT];
-    plan_build(cu_q, cu_k, B, Tq, Tk, true, plan_q, max_tiles_q, hist, start, part);
-    if (plan_k) plan_build(cu_q, cu_k, B, Tq, Tk, false, plan_k, max_tiles_k, hist, start, part);   // backward only
+    const bool queries = blockIdx.x == 0;
+    plan_build(cu_q, cu_k, B, Tq, Tk, queries, queries ? plan_q : plan_k, queries ? max_tiles_q : max_tiles_k);
 }
 
 int launch_varlen_plan(const int* cu_q, const int* cu_k, int B, int Tq, int Tk, void* plan_q, int max_tiles_q,
                        void* plan_k, int max_tiles_k, void* stream)
 {
-    return launch_kernel(varlen_plan_kernel, dim3(1), dim3(PLAN_NT), 0, stream, cu_q, cu_k, B, Tq, Tk,
+    return launch_kernel(varlen_plan_kernel, dim3(plan_k ? 2 : 1), dim3(PLAN_NT), 0, stream, cu_q, cu_k, B, Tq, Tk,
                          (int4*)plan_q, max_tiles_q, (int4*)plan_k, max_tiles_k) == hipSuccess ? 0 : -3;
 }
 
