@@ -240,18 +240,20 @@ def main():
     f_dkdv = 2.0 * pairs * (2 * w.dqk + 2 * w.dv)     # S, dK contract/emit d_qk; dP, dV d_v
     f_dq = 2.0 * pairs * (2 * w.dqk + w.dv)           # S, dQ over d_qk; dP over d_v
     tf = lambda flops, ms: flops / ms / 1e9
-    t32 = ((w.dqk, w.dv) in ((128, 128), (192, 128)) and w.N % 128 == 0) or \
+    # (d = 256: a dV and a dK launch of that kernel)
+    t32 = ((w.dqk, w.dv) in ((128, 128), (192, 128)) and w.N % 128 == 0) or (w.dqk == 256 and w.N >= 512) or \
           ((w.dqk, w.dv) == (64, 64) and w.N % 256 == 0 and w.N >= (8192 if w.causal else 2048))
     dkdv_name = ("attn_bwd_dkdv_t32_kernel" if t32 else
                  "attn_bwd_dkdv_ws_kernel" if w.dqk in (96, 128) else "attn_bwd_dkdv_kernel")
     # on long sequences with N % 256 == 0 the library runs 256-query blocks with 64 queries per wave:
-    # the forward and dQ kernels at d = 128 and d = 64 (same rules as the launchers)
+    # the forward and dQ kernels at d = 128 and d = 64 (the launchers' rules at these workloads' 512 blocks and more)
     wide = w.dqk == 128 and w.dv == 128 and w.N % 256 == 0
     fwd_name = ("attn_fwd_q64_kernel" if ((wide or (w.dqk == 192 and w.dv == 128 and w.N % 256 == 0)) and w.N >= (8192 if w.causal else 2048)) or
                 (w.dqk == 64 and w.dv == 64 and w.N % 256 == 0 and w.N >= (16384 if w.causal else 8192)) else "attn_fwd_kernel")
     dq_name = ("attn_bwd_dq_q64_kernel" if (wide and w.N >= (4096 if w.causal else 1024)) or
                (w.dqk == 64 and w.dv == 64 and w.N % 256 == 0 and w.N >= (8192 if w.causal else 2048)) else
-               "attn_bwd_dq_t32_kernel" if (w.dqk, w.dv) == (192, 128) and w.N % 128 == 0 and w.N >= (1024 if w.causal else 512) else
+               "attn_bwd_dq_t32_kernel" if ((w.dqk, w.dv) == (192, 128) and w.N % 128 == 0 and w.N >= (1024 if w.causal else 512)) or
+               w.dqk == 256 else
                "attn_bwd_dq_kernel")
     # the dQ kernel computes D and the base-2 LSE itself: the full backward launches no prepare kernel
     # (ATTN_BWD_PREPARE alone still does, which is what ms_prep timed above)
