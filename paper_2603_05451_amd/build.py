@@ -22,14 +22,14 @@ PROBES_LIB = os.path.join(HERE, "libattn_probes.so")
 # which no vector instruction touches inside the loop, in AGPRs: they want the default.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]
 # (source, object, additional flags)
-SOURCES = [("attn_api.hip", "attn_api.o", []),
+SOURCES = [*[("attn_bwd_dq_q64.hip", f"attn_bwd_dq_q64_{f16}{varlen}.o", [f"-DATTN_F16={f16}", f"-DATTN_VARLEN={varlen}"])
+             for varlen in (1, 0) for f16 in (0, 1)],        # (the longest compilations, first)
+           ("attn_api.hip", "attn_api.o", []),
            ("attn_fwd.hip", "attn_fwd.o", VGPR_FORM),
            ("attn_fwd_q64.hip", "attn_fwd_q64.o", []),
            ("attn_decode.hip", "attn_decode.o", VGPR_FORM),
            ("attn_bwd.hip", "attn_bwd.o", []),
            ("attn_bwd.hip", "attn_bwd_vgpr_form.o", ["-DATTN_BWD_VGPR_FORM_PART=1", *VGPR_FORM]),
-           ("attn_bwd_dq_q64.hip", "attn_bwd_dq_q64.o", []),
-           ("attn_bwd_dq_q64.hip", "attn_bwd_dq_q64_f16.o", ["-DATTN_F16_PART=1"]),
            ("attn_varlen.hip", "attn_varlen.o", []),
            ("exp2_emulated.hip", "exp2_emulated.o", [])]
 PROBE_SOURCES = [("probes.hip", "probes.o", [])]

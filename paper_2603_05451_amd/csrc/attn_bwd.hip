@@ -75,6 +75,22 @@ namespace f16k {
 }  // namespace f16k
 
 #if !ATTN_BWD_VGPR_FORM_PART
+int launch_bwd_dq_q64(const BwdArgs& a)
+{
+    if (a.max_tiles > 0) return a.f16 ? f16k::run_bwd_dq_q64_varlen(a) : run_bwd_dq_q64_varlen(a);
+    return a.f16 ? f16k::run_bwd_dq_q64(a) : run_bwd_dq_q64(a);
+}
+int launch_bwd_dq_t32(const BwdArgs& a)
+{
+    if (a.max_tiles > 0) return a.f16 ? f16k::run_bwd_dq_t32_varlen(a) : run_bwd_dq_t32_varlen(a);
+    return a.f16 ? f16k::run_bwd_dq_t32(a) : run_bwd_dq_t32(a);
+}
+int launch_bwd_dkdv_t32(const BwdArgs& a)
+{
+    if (a.max_tiles > 0) return a.f16 ? f16k::run_bwd_dkdv_t32_varlen(a) : run_bwd_dkdv_t32_varlen(a);
+    return a.f16 ? f16k::run_bwd_dkdv_t32(a) : run_bwd_dkdv_t32(a);
+}
+
 int launch_bwd(const BwdArgs& a)
 {
     // Fixed-length batches at head dims 128, 64 and (192, 128): kernels with one wave per SIMD

@@ -5,73 +5,45 @@
 //                             head dims 128, (192, 128) with 32 keys per wave and 64 with 64 keys per wave
 //                             (attn_bwd_dkdv_t32_kernel.inc).
 // What is computed is described in attn_bwd.hip; how, at the top of the two kernel files.  A translation
-// unit of its own, like attn_fwd_q64.hip, whose techniques it shares; compiled twice, for bf16 and (with
-// ATTN_F16_PART) for fp16, because the compiler takes minutes over these schedules.
+// unit of its own, like attn_fwd_q64.hip, whose techniques it shares; compiled four times
+// (ATTN_F16: 0 bf16, 1 fp16; ATTN_VARLEN: 0 fixed, 1 variable length), because the compiler takes minutes over
+// these schedules.
 #include "common.h"
 #include "launch.h"
 
 namespace attn {
 
-#if ATTN_F16_PART
+#if ATTN_F16
 namespace f16k {
 #define ATTN_ELEM f16
 #define ATTN_ELEM8 f16x8
 #define ATTN_ELEM4 f16x4
-#include "elem.inc"
-#undef ATTN_ELEM
-#undef ATTN_ELEM8
-#undef ATTN_ELEM4
 #define ATTN_MFMA "v_mfma_f32_32x32x16_f16"
 typedef __attribute__((ext_vector_type(2))) _Float16 elem2;
-#define ATTN_VARLEN 0
-#include "attn_bwd_dq_q64_kernel.inc"
-#include "attn_bwd_dkdv_t32_kernel.inc"
-#include "attn_bwd_dq_t32_kernel.inc"
-#undef ATTN_VARLEN
-#define ATTN_VARLEN 1
-#include "attn_bwd_dq_q64_kernel.inc"
-#include "attn_bwd_dkdv_t32_kernel.inc"
-#include "attn_bwd_dq_t32_kernel.inc"
-#undef ATTN_VARLEN
-#undef ATTN_MFMA
-#include "attn_bwd_dq_q64_launch.inc"
-
-int run_bwd_dq_q64(const BwdArgs& a) { return launch_bwd_dq_q64_t(a); }
-int run_bwd_dq_t32(const BwdArgs& a) { return launch_bwd_dq_t32_t(a); }
-int run_bwd_dkdv_t32(const BwdArgs& a) { return launch_bwd_dkdv_t32_t(a); }
-}  // namespace f16k
 #else
 #define ATTN_ELEM bf16
 #define ATTN_ELEM8 bf16x8
 #define ATTN_ELEM4 bf16x4
-#include "elem.inc"
-#undef ATTN_ELEM
-#undef ATTN_ELEM8
-#undef ATTN_ELEM4
 #define ATTN_MFMA "v_mfma_f32_32x32x16_bf16"
 typedef bf16x2 elem2;
-#define ATTN_VARLEN 0
+#endif
+#include "elem.inc"
 #include "attn_bwd_dq_q64_kernel.inc"
 #include "attn_bwd_dkdv_t32_kernel.inc"
 #include "attn_bwd_dq_t32_kernel.inc"
-#undef ATTN_VARLEN
-#define ATTN_VARLEN 1
-#include "attn_bwd_dq_q64_kernel.inc"
-#include "attn_bwd_dkdv_t32_kernel.inc"
-#include "attn_bwd_dq_t32_kernel.inc"
-#undef ATTN_VARLEN
-#undef ATTN_MFMA
 #include "attn_bwd_dq_q64_launch.inc"
 
-namespace f16k {
-int run_bwd_dq_q64(const BwdArgs& a);
-int run_bwd_dq_t32(const BwdArgs& a);
-int run_bwd_dkdv_t32(const BwdArgs& a);
+#if ATTN_VARLEN
+int run_bwd_dq_q64_varlen(const BwdArgs& a) { return launch_bwd_dq_q64_t(a); }
+int run_bwd_dq_t32_varlen(const BwdArgs& a) { return launch_bwd_dq_t32_t(a); }
+int run_bwd_dkdv_t32_varlen(const BwdArgs& a) { return launch_bwd_dkdv_t32_t(a); }
+#else
+int run_bwd_dq_q64(const BwdArgs& a) { return launch_bwd_dq_q64_t(a); }
+int run_bwd_dq_t32(const BwdArgs& a) { return launch_bwd_dq_t32_t(a); }
+int run_bwd_dkdv_t32(const BwdArgs& a) { return launch_bwd_dkdv_t32_t(a); }
+#endif
+#if ATTN_F16
 }  // namespace f16k
-
-int launch_bwd_dq_q64(const BwdArgs& a) { return a.f16 ? f16k::run_bwd_dq_q64(a) : launch_bwd_dq_q64_t(a); }
-int launch_bwd_dq_t32(const BwdArgs& a) { return a.f16 ? f16k::run_bwd_dq_t32(a) : launch_bwd_dq_t32_t(a); }
-int launch_bwd_dkdv_t32(const BwdArgs& a) { return a.f16 ? f16k::run_bwd_dkdv_t32(a) : launch_bwd_dkdv_t32_t(a); }
 #endif
 
 }  // namespace attn

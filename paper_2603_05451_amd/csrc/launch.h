@@ -182,6 +182,21 @@ int launch_bwd_dkdv_t32(const BwdArgs& a);
 // The dQ kernel with one wave per SIMD and 32 queries per wave (head dims (192, 128); fixed length N % 128 = 0,
 // or variable-length mode as above); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_t32(const BwdArgs& a);
+// The same by element type (bf16 in attn::, fp16 in attn::f16k::) and mode: one translation unit each.
+int run_bwd_dq_q64(const BwdArgs& a);
+int run_bwd_dq_t32(const BwdArgs& a);
+int run_bwd_dkdv_t32(const BwdArgs& a);
+int run_bwd_dq_q64_varlen(const BwdArgs& a);
+int run_bwd_dq_t32_varlen(const BwdArgs& a);
+int run_bwd_dkdv_t32_varlen(const BwdArgs& a);
+namespace f16k {
+int run_bwd_dq_q64(const BwdArgs& a);
+int run_bwd_dq_t32(const BwdArgs& a);
+int run_bwd_dkdv_t32(const BwdArgs& a);
+int run_bwd_dq_q64_varlen(const BwdArgs& a);
+int run_bwd_dq_t32_varlen(const BwdArgs& a);
+int run_bwd_dkdv_t32_varlen(const BwdArgs& a);
+}  // namespace f16k
 // Fills the two plan tables of the variable-length entry points on the device: 0 or -3.
 int launch_varlen_plan(const int* cu_q, const int* cu_k, int B, int Tq, int Tk, void* plan_q, int max_tiles_q,
                        void* plan_k, int max_tiles_k, void* stream);
