@@ -242,7 +242,7 @@ FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform
             r.nsplit = clamp(3, steps / 4);
         }
     } else if (Tk > Tq) {
-        // (self-attention is never divided: its results are those of the fixed-length calls, bit for bit)
+        // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call's 128-row kernel)
         // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
         // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
         // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose
@@ -465,6 +465,13 @@ bool bad_stride(const attn_strides_t* s, int B, int N, int heads)
     return false;
 }
 
+// rows and batches back to back: the layout of the fixed-length calls (the stride of an axis with one entry is not used)
+bool contiguous(const attn_strides_t* s, int B, int N, int heads, int d)
+{
+    return (heads == 1 || s->head == d) && (N == 1 || s->row == (long long)heads * d) &&
+           (B == 1 || s->batch == (long long)N * heads * d);
+}
+
 attn::Stride3 as_packed(const attn_strides_t* s, int N)
 {
     return {s->batch - (long long)N * s->row, s->row, s->head};
@@ -495,6 +502,11 @@ int attn_fwd_strided(int dtype, const void* q, const attn_strides_t* sq, const v
         misaligned(lse, 4) || misaligned(workspace, 256))
         return ATTN_EINVAL;
     if (workspace_bytes < 2 * cu_bytes(B) + varlen_layout(B, B * Nq, B * Nk, H, Hkv, d_qk, d_v, true).min_fwd) return ATTN_EINVAL;
+    // The fixed-length call promises its bits to a contiguous one, and which kernel it runs (whose summation orders differ)
+    // depends on the sizes: so this is that call.  (The backward pass reaches the same bits in its variable-length kernels.)
+    if (Nq == Nk && Nq % 128 == 0 && contiguous(sq, B, Nq, H, d_qk) && contiguous(sk, B, Nk, Hkv, d_qk) &&
+        contiguous(sv, B, Nk, Hkv, d_v) && contiguous(so, B, Nq, H, d_v))
+        return attn_fwd_dtype(dtype, q, k, v, o, lse, B, H, Hkv, Nq, d_qk, d_v, scale, causal, stream);
     char* ws = static_cast<char*>(workspace);
     attn::VarlenStrides st = {};
     st.nq = Nq;

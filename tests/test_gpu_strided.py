@@ -37,6 +37,28 @@ def test_bhsd_views_match_contiguous_calls_bitwise(dqk, dv, H, Hkv, causal, seed
         assert torch.equal(view(got), ref)
 
 
+# N, H at which attn_fwd and attn_bwd leave their 128-row kernels: one round of 256-row blocks (136 ... 208 of them), more
+# than 512 of them at a length that pays, and d = 256; three sequences in one case, GQA in another
+@pytest.mark.parametrize("dqk,dv,B,N,H,Hkv,causal", [(64, 64, 1, 1280, 30, 30, False), (128, 128, 1, 1024, 34, 34, False),
+                                                     (128, 128, 1, 2048, 26, 13, True), (192, 128, 3, 2048, 8, 4, True),
+                                                     (64, 64, 1, 2048, 64, 32, False), (256, 256, 1, 512, 4, 2, True)])
+def test_contiguous_calls_give_the_fixed_length_bits(dqk, dv, B, N, H, Hkv, causal):
+    """Contiguous [B, N, H, d] tensors with N a multiple of 128, handed to the strided entry points: the bits of attn_fwd
+    and attn_bwd at every size, whichever kernels those take there."""
+    import paper_2603_05451_amd as A
+    gen = torch.Generator(device="cuda").manual_seed(dqk + N + H)
+    q, k, v, do = (torch.randn(B, N, h, e, generator=gen, device="cuda").bfloat16()
+                   for h, e in ((H, dqk), (Hkv, dqk), (Hkv, dv), (H, dv)))
+    o_ref, lse_ref = A.attn_fwd(q, k, v, dqk ** -0.5, causal)
+    ref = A.attn_bwd(q, k, v, o_ref, do, lse_ref, dqk ** -0.5, causal)
+    o, lse = A.attn_fwd_strided(q, k, v, dqk ** -0.5, causal)
+    got = A.attn_bwd_strided(q, k, v, o_ref, do, lse_ref, dqk ** -0.5, causal)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o_ref) and torch.equal(lse, lse_ref)
+    for what, a, r in zip(("dQ", "dK", "dV"), got, ref):
+        assert torch.equal(a, r), what
+
+
 @pytest.mark.parametrize("d,N,causal,seed", [(64, 200, True, 84), (128, 333, False, 85), (128, 1, True, 86),
                                              (96, 130, True, 88), (256, 190, True, 89)])
 def test_fused_qkv_buffer_any_length(oracle, d, N, causal, seed):
