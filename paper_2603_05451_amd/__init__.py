@@ -61,13 +61,20 @@ def lib():
         L.attn_varlen_bwd_dtype.restype = i
         L.attn_varlen_workspace_bytes.argtypes = [i] * 8
         L.attn_varlen_workspace_bytes.restype = sz
-        sp = vp              # attn_strides_t*: an address (see _strides) or byref(AttnStrides(...))
+        sp = ctypes.POINTER(AttnStrides)
         L.attn_strided_workspace_bytes.argtypes = [i] * 8
         L.attn_strided_workspace_bytes.restype = sz
         L.attn_fwd_strided.argtypes = [i] + [vp, sp] * 4 + [vp] + [i] * 7 + [f, i, vp, sz, vp]
         L.attn_fwd_strided.restype = i
         L.attn_bwd_strided.argtypes = [i] + [vp, sp] * 5 + [vp] + [vp, sp] * 3 + [i] * 7 + [f, i, vp, sz, vp]
         L.attn_bwd_strided.restype = i
+        # the same two for this module's own calls, with the addresses that _with_strides makes
+        L.strides_by_address = []
+        for fn in ("attn_fwd_strided", "attn_bwd_strided"):
+            own = L[fn]                     # (indexing gives a function object of its own)
+            own.argtypes = [vp if t is sp else t for t in getattr(L, fn).argtypes]
+            own.restype = i
+            L.strides_by_address.append(own)
         L.attn_varlen_plan.argtypes = [vp, vp] + [i] * 7 + [vp, sz, vp]
         L.attn_varlen_plan.restype = i
         L.attn_varlen_fwd.argtypes = [vp] * 7 + [i] * 7 + [f, i, vp, sz, vp]
@@ -205,7 +212,7 @@ def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, worksp
         lse = torch.empty((H, T), dtype=torch.float32, device=q.device)
     lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
     if workspace is None:
-        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv, False)
+        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv, 0)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     _check(lib().attn_varlen_fwd_dtype(
         _dtype_code(q), _dev(q, "q", q.shape, dt), _dev(k, "k", (Tk, Hkv, dqk), dt), _dev(v, "v", (Tk, Hkv, dv), dt),
@@ -232,7 +239,7 @@ def attn_varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, scale, causal, dq=None, dk
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     if workspace is None:
-        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv_, True)
+        need = attn_varlen_workspace_bytes(B, T, Tk, H, Hkv, dqk, dv_, 1)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
     _check(lib().attn_varlen_bwd_dtype(
@@ -285,12 +292,12 @@ def attn_fwd_strided(q, k, v, scale, causal, o=None, lse=None, workspace=None, s
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
-        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv, False)
+        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv, 0)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     st = array.array("q")
     ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
             _view(v, "v", (B, Nk, Hkv, dv), dt, st), _view(o, "o", (B, N, H, dv), dt, st))
-    _check(lib().attn_fwd_strided(_dtype_code(q), *_with_strides(ptrs, st), lse_p, B, H, Hkv, N, Nk, dqk, dv, float(scale),
+    _check(lib().strides_by_address[0](_dtype_code(q), *_with_strides(ptrs, st), lse_p, B, H, Hkv, N, Nk, dqk, dv, float(scale),
                                   int(bool(causal)), workspace.data_ptr(), workspace.numel(), _stream(stream)))
     return o, lse
 
@@ -306,7 +313,7 @@ def attn_bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq=None, dk=None, dv=N
     dv = torch.empty((B, Nk, Hkv, dv_), dtype=q.dtype, device=q.device) if dv is None else dv
     lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
-        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv_, True)
+        need = attn_strided_workspace_bytes(B, H, Hkv, N, Nk, dqk, dv_, 1)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     st = array.array("q")
     ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
@@ -314,7 +321,7 @@ def attn_bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq=None, dk=None, dv=N
             _view(d_o, "d_o", (B, N, H, dv_), dt, st), _view(dq, "dq", (B, N, H, dqk), dt, st),
             _view(dk, "dk", (B, Nk, Hkv, dqk), dt, st), _view(dv, "dv", (B, Nk, Hkv, dv_), dt, st))
     a = _with_strides(ptrs, st)
-    _check(lib().attn_bwd_strided(_dtype_code(q), *a[:10], lse_p, *a[10:], B, H, Hkv, N, Nk, dqk, dv_, float(scale),
+    _check(lib().strides_by_address[1](_dtype_code(q), *a[:10], lse_p, *a[10:], B, H, Hkv, N, Nk, dqk, dv_, float(scale),
                                   int(bool(causal)), workspace.data_ptr(), workspace.numel(), _stream(stream)))
     return dq, dk, dv
 

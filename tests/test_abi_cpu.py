@@ -186,3 +186,20 @@ def test_varlen_workload_recipe_is_deterministic():
     cu = x["cu_seqlens"].tolist()
     assert cu[0] == 0 and cu[-1] == T and [cu[i + 1] - cu[i] for i in range(w.B)] == a
     assert w.fwd_flops() == sum(2.0 * n * n * (w.dqk + w.dv) * w.H for n in a) / 2      # causal
+
+
+def test_strided_prototypes_take_structures_and_refuse_integers(L):
+    """The strided entry points of lib(): an AttnStrides as it is, by reference or as a pointer, None (which the
+    library refuses), and nothing else: an integer is not a structure."""
+    import paper_2603_05451_amd as A
+    p = ctypes.c_void_p(0x1000)
+    s = A.AttnStrides(100 * 4 * 64, 4 * 64, 64)
+    tail = (2, 4, 4, 100, 100, 64, 64, 0.125, 0, p, 256, None)               # (the workspace is too small: nothing runs)
+    fwd = lambda x: L.attn_fwd_strided(A.ATTN_BF16, p, x, p, x, p, x, p, x, p, *tail)
+    bwd = lambda x: L.attn_bwd_strided(A.ATTN_BF16, p, x, p, x, p, x, p, x, p, x, p, p, x, p, x, p, x, *tail)
+    for call in (fwd, bwd):
+        for x in (s, ctypes.byref(s), ctypes.pointer(s), None):
+            assert call(x) == A.ATTN_EINVAL
+        for x in (ctypes.addressof(s), ctypes.c_void_p(ctypes.addressof(s))):
+            with pytest.raises(ctypes.ArgumentError):
+                call(x)
