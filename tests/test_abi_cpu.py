@@ -203,3 +203,25 @@ def test_strided_prototypes_take_structures_and_refuse_integers(L):
         for x in (ctypes.addressof(s), ctypes.c_void_p(ctypes.addressof(s))):
             with pytest.raises(ctypes.ArgumentError):
                 call(x)
+
+
+def test_workspace_sizes_are_asked_anew(L):
+    """What a size function refuses, it refuses after any earlier call too, and an argument is read at each call."""
+    import paper_2603_05451_amd as A
+
+    class Size:                             # an index, as an integer tensor is one: its value may change
+        def __init__(self, n):
+            self.n = n
+
+        def __index__(self):
+            return self.n
+    for f, at, args in ((A.attn_bwd_workspace_bytes, 3, (1, 2, 2, 128, 64, 64)),
+                        (A.attn_varlen_workspace_bytes, 1, (3, 1000, 5000, 4, 2, 128, 128, True)),
+                        (A.attn_strided_workspace_bytes, 3, (3, 4, 2, 1000, 5000, 128, 128, True))):
+        assert f(*args) > 0
+        with pytest.raises(ctypes.ArgumentError):
+            f(*args[:at], float(args[at]), *args[at + 1:])
+        n = Size(args[at])
+        assert f(*args[:at], n, *args[at + 1:]) == f(*args)
+        n.n *= 2
+        assert f(*args[:at], n, *args[at + 1:]) == f(*args[:at], 2 * args[at], *args[at + 1:]) > f(*args)
