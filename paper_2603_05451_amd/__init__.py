@@ -147,7 +147,7 @@ def _dev_lse(lse, shape, axes):
 def _bytes(size_function, *sizes):
     """What a size function of the library says, asked once per set of plain integers (of tensor shapes: not what a
     caller of the public functions passes, which may compare equal and be refused, or change its value)."""
-    return size_function(*sizes)
+    return getattr(lib(), size_function)(*sizes)
 
 
 def attn_bwd_workspace_bytes(B, H, Hkv, N, d_qk, d_v) -> int:
@@ -217,7 +217,7 @@ def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, worksp
         lse = torch.empty((H, T), dtype=torch.float32, device=q.device)
     lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
     if workspace is None:
-        need = _bytes(lib().attn_varlen_workspace_bytes, B, T, Tk, H, Hkv, dqk, dv, 0)
+        need = _bytes("attn_varlen_workspace_bytes", B, T, Tk, H, Hkv, dqk, dv, 0)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     _check(lib().attn_varlen_fwd_dtype(
         _dtype_code(q), _dev(q, "q", q.shape, dt), _dev(k, "k", (Tk, Hkv, dqk), dt), _dev(v, "v", (Tk, Hkv, dv), dt),
@@ -244,7 +244,7 @@ def attn_varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, scale, causal, dq=None, dk
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     if workspace is None:
-        need = _bytes(lib().attn_varlen_workspace_bytes, B, T, Tk, H, Hkv, dqk, dv_, 1)
+        need = _bytes("attn_varlen_workspace_bytes", B, T, Tk, H, Hkv, dqk, dv_, 1)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     lse_p, dt = _dev_lse(lse, (H, T), "H,Tq"), q.dtype
     _check(lib().attn_varlen_bwd_dtype(
@@ -296,7 +296,7 @@ def attn_fwd_strided(q, k, v, scale, causal, o=None, lse=None, workspace=None, s
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
-        need = _bytes(lib().attn_strided_workspace_bytes, B, H, Hkv, N, Nk, dqk, dv, 0)
+        need = _bytes("attn_strided_workspace_bytes", B, H, Hkv, N, Nk, dqk, dv, 0)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     st = array.array("q")
     ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
@@ -317,7 +317,7 @@ def attn_bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq=None, dk=None, dv=N
     dv = torch.empty((B, Nk, Hkv, dv_), dtype=q.dtype, device=q.device) if dv is None else dv
     lse_p, dt = _dev_lse(lse, (B, H, N), "B,H,Nq"), q.dtype
     if workspace is None:
-        need = _bytes(lib().attn_strided_workspace_bytes, B, H, Hkv, N, Nk, dqk, dv_, 1)
+        need = _bytes("attn_strided_workspace_bytes", B, H, Hkv, N, Nk, dqk, dv_, 1)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     st = array.array("q")
     ptrs = (_view(q, "q", (B, N, H, dqk), dt, st), _view(k, "k", (B, Nk, Hkv, dqk), dt, st),
@@ -353,7 +353,7 @@ def attn_bwd(q, k, v, o, do, lse, scale, causal, dq=None, dk=None, dv=None, work
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
-    need = _bytes(lib().attn_bwd_workspace_bytes, B, H, Hkv, N, dqk, dvd)
+    need = _bytes("attn_bwd_workspace_bytes", B, H, Hkv, N, dqk, dvd)
     if need == 0:
         _check(lib().attn_bwd_ex(*([None] * 9), B, H, Hkv, N, dqk, dvd, float(scale), 0, None, 0, None)
                or ATTN_EINVAL)

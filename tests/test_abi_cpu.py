@@ -218,7 +218,7 @@ def test_workspace_sizes_are_asked_anew(L):
     for f, at, args in ((A.attn_bwd_workspace_bytes, 3, (1, 2, 2, 128, 64, 64)),
                         (A.attn_varlen_workspace_bytes, 1, (3, 1000, 5000, 4, 2, 128, 128, True)),
                         (A.attn_strided_workspace_bytes, 3, (3, 4, 2, 1000, 5000, 128, 128, True))):
-        assert f(*args) > 0
+        assert f(*args) > 0 and A._bytes(f.__name__, *args) == f(*args)        # (the binding's own calls)
         with pytest.raises(ctypes.ArgumentError):
             f(*args[:at], float(args[at]), *args[at + 1:])
         n = Size(args[at])
