@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdlib.h>
 #include <tuple>
+#include "dispatch.h"
 
 namespace attn {
 
@@ -87,15 +88,6 @@ struct BwdArgs {
                                   // tensors have a batch stride (equal lengths), 0 for packed tensors
     bool f16 = false;             // as in FwdArgs
 };
-
-// Order of the table entries for kernels whose blocks take two 128-row tiles and have nothing to do for every
-// second tile of a sequence: entries 0, 2, 4, ... first, then 1, 3, 5, ...  Dispatched alternately, the empty
-// blocks would all fall to the same shader engines and leave the others twice the work.
-__device__ __forceinline__ int pair_order(int p, int n)
-{
-    const int half = (n + 1) >> 1;
-    return p < half ? 2 * p : 2 * (p - half) + 1;
-}
 
 // Launch through hipLaunchKernel so that the status returned belongs to THIS launch (the
 // sticky hipGetLastError slot may hold an unrelated earlier error of the host program).
