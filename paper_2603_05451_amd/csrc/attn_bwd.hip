@@ -93,8 +93,8 @@ int launch_bwd_dkdv_t32(const BwdArgs& a)
 
 int launch_bwd(const BwdArgs& a)
 {
-    // Fixed-length batches at head dims 128, 64 and (192, 128): kernels with one wave per SIMD
-    // (attn_bwd_dq_q64.hip), faster than the kernels of this file.  The dK/dV kernel gives the same bits
+    // Head dims 128, 64, (192, 128) and 256: kernels with one wave per SIMD (attn_bwd_dq_q64.hip), where dispatch.h
+    // says that they are faster than the kernels of this file.  The dK/dV kernel gives the same bits
     // as they do; the dQ kernel differs by the fp32 rounding of dP - D.  The dQ kernel, and with it -D and
     // the base-2 LSE, comes first as in every backward call.
     auto generic = [&](int phases) {
@@ -105,13 +105,9 @@ int launch_bwd(const BwdArgs& a)
     const bool d128 = a.d_qk == 128 && a.d_v == 128, d64 = a.d_qk == 64 && a.d_v == 64, d192 = a.d_qk == 192 && a.d_v == 128, d256 = a.d_qk == 256;
     // The dQ kernels with one wave per SIMD at a fixed length of N tokens.  (192, 128) and 256: the 64-query
     // kernel's fragments and accumulators do not fit; 32 queries per wave.
-    auto dq_q64_at = [&](int N) { return (d128 || d64) && attn::dq_one_wave(a.d_qk, a.causal, N, (long long)a.B * a.H * N / 256); };
+    auto dq_q64_at = [&](int N) { return (d128 || d64) && dq_one_wave(a.d_qk, a.causal, N, (long long)a.B * a.H * N / 256); };
     auto dq_t32_at = [&](int N) { return d192 && N % 128 == 0 && N >= (a.causal ? 1024 : 512); };
-    // d = 256, dQ and dK/dV: the pipelined kernels win but on the shortest causal sequences of many blocks (B H = 512
-    // at N = 128: dQ 46.3 -> 47.7 us, dK/dV 70.2 -> 72.7, N = 256: 53.6 -> 51.5, 82.3 -> 84.2, N = 512: 71.8 -> 62.0,
-    // 121 -> 108, N = 2048: 159 -> 125, 295 -> 234; one sequence of 128: 16.5 -> 15.5, 35.7 -> 29.2)
-    auto short_causal = [&](int N, int most, int heads) { return a.causal && N <= most && (long long)a.B * heads * N > 256 * 128; };
-    auto dq256_at = [&](int N) { return d256 && !short_causal(N, 128, a.H); };
+    auto dq256_at = [&](int N) { return d256 && dq256_one_wave(a.causal, N, (long long)a.B * a.H); };
     bool dq_q64, dq_t32, dkdv_t32;
     if (a.max_tiles > 0) {
         // Variable-length mode, by the mean number of queries n.  Their copies are bounded by whole rows, so a row has
@@ -141,7 +137,8 @@ int launch_bwd(const BwdArgs& a)
     } else {
         dq_q64 = dq_q64_at(a.N);
         dq_t32 = dq_t32_at(a.N) || dq256_at(a.N);
-        dkdv_t32 = d128 || d192 || (d256 && !short_causal(a.N, 256, a.Hkv)) || (d64 && dkdv64_one_wave(a.causal, a.N, (long long)a.B * a.Hkv * a.N / 256));
+        dkdv_t32 = d128 || d192 || (d256 && dkdv256_one_wave(a.N, (long long)a.B * a.Hkv)) ||
+                   (d64 && dkdv64_one_wave(a.causal, a.N, (long long)a.B * a.Hkv * a.N / 256));
     }
     dq_q64 = dq_q64 && (a.phases & 4);
     dq_t32 = dq_t32 && (a.phases & 4);

@@ -120,42 +120,6 @@ struct LdsOptIn {
     }
 };
 
-// Fixed-length calls: where the kernels with one wave per SIMD (blocks of 256 rows, one per CU) take less time than
-// the 4-wave ones (128 rows, two per CU).  b = number of 256-row blocks of the launch.  Measured at d = 128, H and N
-// varied, us, 4-wave -> one wave per SIMD.  Up to 128 blocks half the chip would idle (forward N = 8192, b = 128:
-// 133 -> 159 causal, 146 -> 163).  From there to 256 one round of large blocks beats two small ones per CU
-// (b = 256, N = 4096: forward 132 -> 113, 102 -> 92 causal, dQ 181 -> 155, 142 -> 118 causal).  Between 256 and 512 a
-// second round is partly empty, which the mask's uneven loops fill (b = 384, N = 8192: forward 382 -> 366, 236 -> 209
-// causal).  From 512 on the length decides: it has to outweigh a lone block's prologue.
-inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
-{
-    if (N % 256 != 0 || N < 1024 || b <= 128) return false;
-    if (d_qk == 64) {       // the vector port binds there and the gain is smaller (b = 384, N = 8192: 224 -> 270, 167 -> 152 causal)
-        if (causal) return b > 256 && N >= (b < 512 ? 8192 : 16384);
-        return b <= 256 || (b >= 512 && N >= 8192);
-    }
-    if (!causal) return b <= 256 || N >= 2048;
-    if (b <= 256) return b > 192 && N >= 2048 && N <= 4096;     // (b = 256, N = 8192: 161 -> 168)
-    return N >= (b < 512 ? 4096 : 8192);
-}
-// dQ with 64 queries per wave (d_qk = d_v = 128 or 64).  512 blocks: d = 128, N = 2048 185 -> 164, 132 -> 127 causal.
-inline bool dq_one_wave(int d_qk, bool causal, int N, long long b)
-{
-    if (N % 256 != 0 || N < 1024 || b <= 128) return false;
-    if (d_qk == 128) return b <= 512 || N >= (causal ? 4096 : 1024);
-    if (!causal) return b <= 256 || N >= 2048;
-    if (b <= 256) return b > 192 && N <= 4096;                  // (b = 256: N = 4096 82 -> 73, N = 8192 123 -> 134)
-    return b < 512 || N >= 8192;                                // (b = 384: 192 -> 164; b = 512, N = 4096: 123 -> 129)
-}
-// dK/dV with 64 keys per wave (d = 64); b counts 256-key blocks.
-inline bool dkdv64_one_wave(bool causal, int N, long long b)
-{
-    if (N % 256 != 0 || N < 1024 || b <= 128) return false;
-    if (!causal) return b <= 256 || (b >= 512 && N >= 2048);    // (N = 8192: b = 192 225 -> 188, b = 384 379 -> 395)
-    if (b <= 256) return b > 192 && N <= 4096;                  // (b = 256: N = 4096 109 -> 98, N = 8192 159 -> 186)
-    return b < 512 || N >= 8192;                                // (b = 384: 253 -> 224; b = 512, N = 4096: 156 -> 175)
-}
-
 // 0 on success, -2 unsupported head dims, -3 launch failure.
 int launch_fwd(const FwdArgs& a);
 int launch_bwd(const BwdArgs& a);

@@ -14,6 +14,11 @@ SHIM = r"""
 using namespace attn;
 extern "C" {
 int t_section_order(int block, int total) { return section_order(block, total); }
+int t_fwd(int d, int causal, int N, long long b) { return fwd_one_wave(d, causal, N, b); }
+int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, N, b); }
+int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
+int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
+int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
 }
 """
 
@@ -24,7 +29,11 @@ def D(tmp_path_factory):
     (d / "shim.cpp").write_text(SHIM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(d / "shim.cpp"),
                     "-o", str(d / "shim.so")], check=True)
-    return ctypes.CDLL(str(d / "shim.so"))
+    L = ctypes.CDLL(str(d / "shim.so"))
+    q = ctypes.c_longlong
+    for f in (L.t_fwd, L.t_dq, L.t_dkdv64):
+        f.argtypes = [ctypes.c_int] * 3 + [q]
+    return L
 
 
 @pytest.mark.parametrize("heads", [1, 2, 3, 4, 6, 8, 16, 32])
@@ -48,3 +57,32 @@ def test_places_of_blocks_that_take_two_tiles(D, heads, lens):
         assert took[xcd::8].sum() == want
         used = (mine % max_tiles < len(tiles)).sum()            # half of a section's used entries, and one per sequence
         assert used / 2 - 1 <= want <= used / 2 + len(lens) * (1 + heads // 8)
+
+
+# measured times of the kernels with one wave per SIMD over those of the 4-wave kernels: (pass, d, causal, N, 256-row blocks,
+# ratio), both sides of every line of the rules
+MEASURED = [
+    ("fwd", 128, 0, 8192, 128, 1.08), ("fwd", 128, 0, 2048, 136, 0.78), ("fwd", 128, 0, 1024, 256, 0.95), ("fwd", 128, 0, 1024, 264, 1.16),
+    ("fwd", 128, 0, 2048, 416, 0.85), ("fwd", 64, 0, 1024, 160, 1.04), ("fwd", 64, 0, 2048, 256, 0.94), ("fwd", 64, 0, 8192, 320, 1.24),
+    ("fwd", 64, 0, 8192, 448, 0.92), ("fwd", 64, 0, 4096, 576, 1.19), ("fwd", 128, 1, 1024, 136, 1.04), ("fwd", 128, 1, 2048, 160, 0.94),
+    ("fwd", 128, 1, 3072, 192, 1.13), ("fwd", 128, 1, 4096, 256, 0.90), ("fwd", 128, 1, 8192, 256, 1.06), ("fwd", 128, 1, 4096, 448, 1.12),
+    ("fwd", 128, 1, 8192, 512, 0.88), ("fwd", 192, 1, 8192, 192, 0.91), ("fwd", 192, 1, 4096, 288, 1.04), ("fwd", 192, 1, 6144, 288, 0.87),
+    ("fwd", 64, 1, 4096, 448, 1.15), ("fwd", 64, 1, 8192, 320, 0.92), ("fwd", 64, 1, 8192, 448, 1.14), ("fwd", 64, 1, 12288, 336, 1.10),
+    ("fwd", 64, 1, 16384, 512, 0.96),
+    ("dq", 128, 0, 1024, 128, 1.12), ("dq", 128, 0, 1024, 136, 0.78), ("dq", 128, 1, 1024, 192, 0.84), ("dq", 128, 1, 1024, 288, 1.33),
+    ("dq", 128, 1, 2048, 288, 1.23), ("dq", 128, 1, 1280, 450, 0.92), ("dq", 128, 1, 3072, 288, 0.94), ("dq", 64, 0, 1024, 256, 0.91),
+    ("dq", 64, 0, 1024, 288, 1.20), ("dq", 64, 1, 2048, 160, 0.91), ("dq", 64, 1, 1024, 288, 1.61), ("dq", 64, 1, 4096, 448, 1.07),
+    ("dq", 64, 1, 8192, 256, 1.10), ("dq", 64, 1, 8192, 384, 0.85),
+    ("dkdv64", 64, 0, 1024, 136, 0.85), ("dkdv64", 64, 0, 8192, 320, 1.12), ("dkdv64", 64, 0, 8192, 448, 0.89), ("dkdv64", 64, 0, 1024, 576, 1.08),
+    ("dkdv64", 64, 1, 2048, 192, 0.92), ("dkdv64", 64, 1, 1024, 288, 1.55), ("dkdv64", 64, 1, 3072, 192, 1.12), ("dkdv64", 64, 1, 8192, 256, 1.18),
+    ("dkdv64", 64, 1, 8192, 512, 0.89)]
+
+
+@pytest.mark.parametrize("what,d,causal,N,b,ratio", MEASURED)
+def test_fixed_length_rules_take_the_faster_kernel(D, what, d, causal, N, b, ratio):
+    assert bool(getattr(D, "t_" + what)(d, causal, N, b)) == (ratio < 1)
+
+
+def test_d256_rules(D):
+    assert D.t_dq256(1, 128, 64) and not D.t_dq256(1, 128, 512) and D.t_dq256(0, 128, 512) and D.t_dq256(1, 256, 512)
+    assert D.t_dkdv256(128, 64) and not D.t_dkdv256(128, 256) and D.t_dkdv256(512, 256)
