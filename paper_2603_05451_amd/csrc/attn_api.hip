@@ -345,6 +345,7 @@ int varlen_bwd_run(int dtype, const void* q, const void* k, const void* v, const
     a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.plan_k = ws + w.plan_k_off;
     a.max_tiles_k = st.nq > 0 ? B * ((st.nk + 127) / 128) : w.max_tiles_k;
+    a.Tk = Tk;
     a.st = st;
     a.rows_per_batch = rows_per_batch;
     a.f16 = dtype == ATTN_F16;

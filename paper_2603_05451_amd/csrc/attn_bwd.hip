@@ -110,30 +110,19 @@ int launch_bwd(const BwdArgs& a)
     auto dq256_at = [&](int N) { return d256 && dq256_one_wave(a.causal, N, (long long)a.B * a.H); };
     bool dq_q64, dq_t32, dkdv_t32;
     if (a.max_tiles > 0) {
-        // Variable-length mode, by the mean number of queries n.  Their copies are bounded by whole rows, so a row has
+        // Variable-length mode, by the mean numbers of queries and keys.  Their copies are bounded by whole rows, so a row has
         // to be as long as its stride at most: overlapping rows (sliding windows) stay with the general kernels.
         const bool rows = a.st.q.row >= a.d_qk && a.st.k.row >= a.d_qk && a.st.v.row >= a.d_v && a.st.d_o.row >= a.d_v;
-        const int n = a.T / a.B;
+        const int n = a.T / a.B, k = a.Tk / a.B;
         // Equal lengths in whole tiles promise the bits of the fixed-length call, whose dQ kernels differ by the
         // rounding of dP - D: the same choice there.
         const bool as_fixed = a.st.nq > 0 && a.st.nq == a.st.nk && a.st.nq % 128 == 0;
-        // Backward of 16 384 tokens, H = 16, us, dQ kernel 4-wave -> 64 queries per wave: d = 128 n = 500 369 -> 352
-        // (causal) and 379 -> 348, n = 2000 649 -> 621 and 983 -> 894, n = 8000 1816 -> 1695 and 3401 -> 3088;
-        // d = 64 n = 500 155 -> 176 and 160 -> 168, n = 2000 337 -> 353 and 486 -> 468, n = 4000 581 -> 568 and
-        // 912 -> 881.  (192, 128), 32 queries per wave: n = 500 546 -> 536 and 895 -> 886, n = 4000 1675 -> 1571.
-        // The 64-query kernel has half as many blocks, each with a CU to itself like the 4-wave one's at d = 128: with
-        // r rounds of 256 against s it takes 1.8 r to s.  At d = 64 the 4-wave kernel has two blocks per CU.
-        const int64_t half = ((int64_t)a.T + 255) / 256 * a.H, r = (half + 255) / 256, s = (2 * half + 255) / 256;
-        dq_q64 = rows && (as_fixed ? dq_q64_at(a.st.nq)
-                                   : (d128 && n >= 512 && 9 * r <= 5 * s) || (d64 && n >= (a.causal ? 4096 : 2048) && half >= 512));
-        dq_t32 = rows && (as_fixed ? dq_t32_at(a.st.nq) || dq256_at(a.st.nq) : (d192 && n >= (a.causal ? 1024 : 512)) || d256);
-        // d = 256: packed 24 sequences of 251 ... 2025 tokens, H = 16/8, dQ 1435 -> 1306 and 3682 -> 3535, dK/dV
-        // 1435 -> 1182 and 3682 -> 1757.  dK/dV (the same bits as the general kernels): d = 128 n = 256 297 -> 269 and 284 -> 260, n = 1000 454 -> 425
-        // and 580 -> 545, n = 8000 1816 -> 1768 and 3401 -> 3275; (192, 128) n = 500 546 -> 433 and 895 -> 474,
-        // n = 8000 2970 -> 2322 and 9065 -> 4226; d = 64 (256 keys per block, one per CU, against 128 and two)
-        // n = 1000 214 -> 231 and 268 -> 261, n = 2000 337 -> 344 and 486 -> 464, n = 4000 581 -> 571 and 912 -> 871.
-        const int64_t blocks64 = (int64_t)a.max_tiles_k / 2 * a.Hkv;
-        dkdv_t32 = rows && (d128 || d192 || d256 || (d64 && n >= (a.causal ? 4096 : 2048) && blocks64 >= 512));
+        const int64_t half = ((int64_t)a.T + 255) / 256 * a.H, blocks64 = (int64_t)a.max_tiles_k / 2 * a.Hkv;
+        const bool dq = rows && (as_fixed ? dq_q64_at(a.st.nq) || dq_t32_at(a.st.nq) || dq256_at(a.st.nq)
+                                          : dq_one_wave_varlen(a.d_qk, a.causal, n, k, half));
+        dq_q64 = dq && (d128 || d64);
+        dq_t32 = dq && (d192 || d256);
+        dkdv_t32 = rows && dkdv_one_wave_varlen(a.d_qk, a.causal, n, k, a.H / a.Hkv, blocks64);
     } else {
         dq_q64 = dq_q64_at(a.N);
         dq_t32 = dq_t32_at(a.N) || dq256_at(a.N);

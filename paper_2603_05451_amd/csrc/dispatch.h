@@ -78,4 +78,42 @@ inline bool dkdv64_one_wave(bool causal, int N, long long b)
 inline bool dq256_one_wave(bool causal, int N, long long heads) { return !(causal && N == 128 && heads >= 128); }
 inline bool dkdv256_one_wave(int N, long long heads) { return !(N == 128 && heads >= 128); }
 
+// ---- Variable-length calls, by the mean numbers of queries n and keys k per sequence (the host never sees the lengths).
+// Shares are of the whole backward pass, kernel of the rule against the general one, over equal lengths of 8 ... 8192 and
+// mixed ones, 4096 ... 65 536 tokens, H = 4/4 ... 16/16.
+
+// dQ with one wave per SIMD; half = 256-row blocks of queries x heads.
+//   d = 128  64 queries per wave: half as many blocks as the 4-wave kernel, each with a CU to itself as there; with r rounds
+//            of 256 blocks against s it takes 1.8 r to s.  n = 100 +11 ... +23 %, n = 512 -4 ... -11 %, n = 8192 -9 ... -20 %.
+//            Under the mask a single round of short ragged sequences ends with its longest tile (5 x 800 +13 %).
+//   d = 64   the 4-wave kernel has two blocks per CU: n = 1024 +11 ... +26 % (mask), n = 2048 +5, n = 4096 -1, n = 8192 -5 %;
+//            without the mask n = 800 +7, n = 2048 -3, n = 8192 -6 %.
+//   (192, 128) and 256, 32 queries per wave, 128-row blocks as in the general kernel: n = 64 and less +5 ... +15 % (a tile
+//            mostly empty costs the longer prologue), (192, 128) n = 512 without and 1024 with the mask -2 %, 256 from n = 100
+//            or k = 1000 -2 ... -17 %.
+inline bool dq_one_wave_varlen(int d_qk, bool causal, int64_t n, int64_t k, int64_t half)
+{
+    const int64_t r = (half + 255) / 256, s = (2 * half + 255) / 256;
+    if (d_qk == 128) return n >= 512 && 9 * r <= 5 * s && (!causal || half > 256 || n >= 1500);
+    if (d_qk == 64) return n >= (causal ? 4096 : 2048) && half >= 512;
+    if (d_qk == 192) return n >= (causal ? 1024 : 512);
+    return d_qk == 256 && (n > 64 || k > 64);
+}
+
+// dK/dV with one wave per SIMD (the same bits as the general kernels).
+//   d = 128  n = k <= 32 +14 ... +17 %, 64 +3 ... +12, 100 -6 ... -12, 1000 -6 %; 16 queries against 1000 keys -2 %
+//   (192, 128)  under the mask the same (n = k <= 64 +8 ... +13 %), without it -3 % at n = 8 and -50 % at n = 256
+//   d = 256  two launches: under the mask n = k <= 64 +20 ... +32 %, 128 -8 ... +10, 64 against 4096 keys +20, 256 -1 ... -15;
+//            without it n = 8 +6 ... 0, 32 -2 ... -19, 256 -33 ... -51 %
+//   d = 64   256 keys per block and one block per CU against 128 and two: needs 512 blocks and long loops (n = 2048 +1 % with
+//            and -5 % without the mask, n = 8192 -9 and -6 %); with four query heads per KV head +5 and +1 %
+inline bool dkdv_one_wave_varlen(int d_qk, bool causal, int64_t n, int64_t k, int group, int64_t blocks_of_256_keys)
+{
+    const bool tiny = n <= 64 && k <= 64;
+    if (d_qk == 128) return !tiny;
+    if (d_qk == 192) return !tiny || !causal;
+    if (d_qk == 256) return causal ? n > 128 : n > 16 || k > 16;
+    return d_qk == 64 && n >= (causal ? 8192 : 2048) && group <= 2 && blocks_of_256_keys >= 512;
+}
+
 }  // namespace attn

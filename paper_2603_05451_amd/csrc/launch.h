@@ -81,8 +81,8 @@ struct BwdArgs {
     int phases;   // bit mask: 1 prepare, 2 dK/dV kernel, 4 dQ kernel
     const void* plan = nullptr;   // variable-length mode (max_tiles > 0), as in FwdArgs: query-tile table (dQ kernel)
     int T = 0, max_tiles = 0;
-    const void* plan_k = nullptr; // key-tile table (dK/dV kernels) and its size
-    int max_tiles_k = 0;
+    const void* plan_k = nullptr; // key-tile table (dK/dV kernels), its size, and the total of key rows
+    int max_tiles_k = 0, Tk = 0;
     VarlenStrides st = {};        // variable-length mode: strides of every tensor and of lse
     int rows_per_batch = 0;       // variable-length mode, prepare kernel: tokens per sequence when the
                                   // tensors have a batch stride (equal lengths), 0 for packed tensors

@@ -19,6 +19,9 @@ int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, 
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
+int t_dq_varlen(int d, int causal, long long n, long long k, long long half) { return dq_one_wave_varlen(d, causal, n, k, half); }
+int t_dkdv_varlen(int d, int causal, long long n, long long k, int group, long long blocks64)
+{ return dkdv_one_wave_varlen(d, causal, n, k, group, blocks64); }
 }
 """
 
@@ -33,6 +36,8 @@ def D(tmp_path_factory):
     q = ctypes.c_longlong
     for f in (L.t_fwd, L.t_dq, L.t_dkdv64):
         f.argtypes = [ctypes.c_int] * 3 + [q]
+    L.t_dq_varlen.argtypes = [ctypes.c_int] * 2 + [q] * 3
+    L.t_dkdv_varlen.argtypes = [ctypes.c_int] * 2 + [q] * 2 + [ctypes.c_int, q]
     return L
 
 
@@ -86,3 +91,25 @@ def test_fixed_length_rules_take_the_faster_kernel(D, what, d, causal, N, b, rat
 def test_d256_rules(D):
     assert D.t_dq256(1, 128, 64) and not D.t_dq256(1, 128, 512) and D.t_dq256(0, 128, 512) and D.t_dq256(1, 256, 512)
     assert D.t_dkdv256(128, 64) and not D.t_dkdv256(128, 256) and D.t_dkdv256(512, 256)
+
+
+# the same for variable lengths: (d, causal, mean queries, mean keys, H, Hkv, tokens, share of the backward pass that dQ and dK/dV
+# with one wave per SIMD add)
+MEASURED_VARLEN = [
+    (128, 1, 16, 16, 16, 8, 16384, 0.52, 0.155), (128, 1, 64, 64, 16, 8, 16384, 0.46, 0.072), (128, 1, 100, 100, 16, 8, 16300, 0.174, -0.096),
+    (128, 0, 16, 1000, 16, 8, 512, None, -0.027), (128, 1, 800, 800, 16, 8, 4000, 0.127, -0.03), (128, 1, 1500, 1500, 16, 8, 15000, -0.071, -0.08),
+    (128, 0, 512, 512, 16, 8, 4096, -0.127, -0.07), (192, 1, 32, 32, 16, 8, 16384, 0.133, 0.090), (192, 0, 32, 32, 16, 8, 16384, 0.106, -0.225),
+    (192, 0, 800, 800, 16, 8, 16000, -0.02, -0.40), (256, 1, 64, 64, 16, 16, 16384, 0.071, 0.320), (256, 1, 64, 4096, 16, 8, 1024, -0.049, 0.197),
+    (256, 1, 200, 200, 16, 8, 16200, -0.097, -0.108), (256, 0, 8, 8, 16, 16, 16384, 0.112, 0.056), (256, 0, 64, 64, 16, 8, 16384, 0.077, -0.146),
+    (64, 1, 1024, 1024, 16, 8, 16384, 0.110, None), (64, 1, 8192, 8192, 16, 8, 16384, -0.051, -0.092), (64, 1, 8192, 8192, 8, 2, 65536, -0.029, 0.050),
+    (64, 0, 2048, 2048, 16, 8, 16384, -0.035, -0.057), (64, 0, 2048, 2048, 4, 4, 16384, 0.043, 0.050)]
+
+
+@pytest.mark.parametrize("d,causal,n,k,H,Hkv,tokens,dq,dkdv", MEASURED_VARLEN)
+def test_varlen_rules_take_the_faster_kernel(D, d, causal, n, k, H, Hkv, tokens, dq, dkdv):
+    B = tokens // n
+    half, blocks64 = (tokens + 255) // 256 * H, (B * k // 128 + B) // 2 * Hkv
+    if dq is not None:
+        assert bool(D.t_dq_varlen(d, causal, n, k, half)) == (dq < 0)
+    if dkdv is not None:
+        assert bool(D.t_dkdv_varlen(d, causal, n, k, H // Hkv, blocks64)) == (dkdv < 0)
