@@ -295,6 +295,23 @@ def test_plan_tables_list_every_tile_once_longest_first():
     check_table(tk, {(*e, t) for e in seqs for t in range(tiles(e[3]))}, lambda e: tiles(int(e[1])), index_of)
 
 
+@pytest.mark.parametrize("lens", [[257] * 40, [1000] * 64 + [3] * 5, [9000] * 70, [200] * 61 + [20000, 70, 16385], [130] * 1100 + [7000] * 3])
+def test_plan_tables_of_alike_and_unlike_lengths(lens):
+    """Batches at which the plan kernel's lanes write sequences of up to 4, 8, 64, 2 and (second thousand) 2 tiles themselves
+    and leave the longer ones to the wave."""
+    import paper_2603_05451_amd as A
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, B = int(cu[-1]), len(lens)
+    ws = torch.full((A.attn_varlen_workspace_bytes(B, T, T, 1, 1, 64, 64, True),), 0xAB, dtype=torch.uint8, device="cuda")
+    A.attn_varlen_plan(torch.from_numpy(cu).cuda(), T, T, 1, 1, 64, 64, ws)
+    torch.cuda.synchronize()
+    tiles = lambda n: (n + 127) // 128
+    seqs = [(int(cu[b]), lens[b], int(cu[b]), lens[b]) for b in range(B)]
+    index_of = {e: b for b, e in enumerate(seqs)}
+    for table in read_tables(ws, B, T, T):
+        check_table(table, {(*e, t) for e in seqs for t in range(tiles(e[1]))}, lambda e: tiles(int(e[1])), index_of)
+
+
 def cross_inputs(qlens, klens, H, Hkv, dqk, dv, seed):
     """Packed tensors with separate query and key row counts, from the N(0,1) recipe."""
     Tq, Tk = int(sum(qlens)), int(sum(klens))
