@@ -205,54 +205,6 @@ int check_varlen(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v)
     return ATTN_OK;
 }
 
-// How the forward pass of a variable-length call runs.  Functions of the sizes alone (the host never sees
-// the lengths, and the workspace is sized before the mask is known), so calls that share tables agree.
-struct FwdRoute {
-    bool decode;        // the kernel for few queries per sequence (attn_decode_kernel.inc)
-    int nsub;           // its 32-row groups per (sequence, KV head)
-    int nsplit;         // parts of the keys; 1: no partial results
-};
-
-FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform)
-{
-    FwdRoute r{false, 1, 1};
-    const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
-    auto clamp = [](int64_t n, int64_t most) { return (int)(n < 1 || most < 1 ? 1 : n < most ? n : most); };
-    // Decode: a (sequence, KV head) is nsub groups of 32 rows there and G tiles of 128 rows in attn_fwd_kernel,
-    // at about the same cost per group as per tile (B = 4, H = 32/8, Nk = 4096, d = 128: Nq = 16 31 us against
-    // 44, Nq = 24 34 against 44, Nq = 32 45 against 45; G = 1: Nq = 64 46 against 41).  In a packed batch only
-    // the totals are known; with no more queries than sequences it is the usual decode step, whereas a batch
-    // that mixes steps with a prompt chunk has to keep the 128-row tiles for the chunk.
-    const int64_t nsub = ((uniform ? Nq : 1) * G + 31) / 32;
-    if (uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B) {
-        r.decode = true;
-        r.nsub = (int)nsub;
-        const int64_t items = (int64_t)B * Hkv * nsub, steps = (Nk + 127) / 128;
-        if (items > 0xffffff) return r;
-        if (!uniform) {
-            // uneven lengths, longest first: four blocks per CU even out (48 sequences of 67 ... 7696 keys, 384
-            // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average
-            r.nsplit = clamp((1023 + items) / items, (steps + 2) / 3);
-        } else if (items < 128) {
-            // 128 blocks reach the memory's rate; parts below four steps cost more than they spread
-            // (B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
-            r.nsplit = clamp((127 + items) / items, steps / 4);
-        } else if (items > 256 && items % 256 != 0 && items < 1024) {
-            // a last round that leaves CUs idle (320 items of 4001 keys: 142 us whole, 126 in 2, 127 in 3)
-            r.nsplit = clamp(3, steps / 4);
-        }
-    } else if (Tk > Tq) {
-        // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call's 128-row kernel)
-        // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
-        // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
-        // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose
-        // loops are half as long: 42 whole, 49 in 2)
-        const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
-        r.nsplit = clamp((d_qk > 192 ? 256 : 512) / blocks, (Nk - Nq / 2) / (16 * 64));
-    }
-    return r;
-}
-
 size_t partial_bytes(int nsplit, int Tq, int H, int d_v)
 {
     return nsplit > 1 ? align_up((size_t)nsplit * Tq * H * (d_v + 2) * sizeof(float), 256) : 0;
@@ -279,7 +231,7 @@ VarlenLayout varlen_layout(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int 
     w.lse2_off = w.d_off + align_up((size_t)H * Tq * sizeof(float), 256);
     w.min_bwd = w.lse2_off + align_up((size_t)H * Tq * sizeof(float), 256);
     // with less than the partial results need, a call divides the keys as far as its workspace goes
-    const size_t part = partial_bytes(fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform).nsplit, Tq, H, d_v);
+    const size_t part = partial_bytes(attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform).nsplit, Tq, H, d_v);
     w.total_fwd = part ? w.part_off + part : w.min_fwd;
     w.total_bwd = w.min_bwd > w.total_fwd ? w.min_bwd : w.total_fwd;
     return w;
@@ -312,16 +264,14 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
-    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform);
+    const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform);
     a.nsub = r.nsub;
     a.nsplit = r.nsplit;
     while (a.nsplit > 1 && w.part_off + partial_bytes(a.nsplit, Tq, H, d_v) > ws_bytes) --a.nsplit;
     if (a.nsplit > 1) {
         a.part_o = reinterpret_cast<float*>(ws + w.part_off);
         a.part_ml = a.part_o + (size_t)a.nsplit * Tq * H * d_v;
-        // rows of a tile, in turns of 1024 / d_v per block of the merge kernel; packed tiles mostly hold one query
-        const int rows = (uniform ? (st.nq < 128 ? st.nq : 128) : 1) * (H / Hkv), per = 1024 / d_v;
-        a.nshare = (rows + per - 1) / per;
+        a.nshare = attn::merge_shares(r, uniform, st.nq, H / Hkv, d_v);
     }
     int rc = r.decode ? attn::launch_decode(a) : attn::launch_fwd(a);
     if (rc == 0 && a.nsplit > 1) rc = attn::launch_combine(a);

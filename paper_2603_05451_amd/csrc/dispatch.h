@@ -116,4 +116,62 @@ inline bool dkdv_one_wave_varlen(int d_qk, bool causal, int64_t n, int64_t k, in
     return d_qk == 64 && n >= (causal ? 8192 : 2048) && group <= 2 && blocks_of_256_keys >= 512;
 }
 
+// ---- How the forward pass of a variable-length call runs.  Functions of the sizes alone (the host never sees
+// the lengths, and the workspace is sized before the mask is known), so calls that share tables agree.
+struct FwdRoute {
+    bool decode;        // the kernel for few queries per sequence (attn_decode_kernel.inc)
+    int nsub;           // its 32-row groups per (sequence, KV head)
+    int nsplit;         // parts of the keys; 1: no partial results
+};
+
+inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform)
+{
+    FwdRoute r{false, 1, 1};
+    const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
+    auto clamp = [](int64_t n, int64_t most) { return (int)(n < 1 || most < 1 ? 1 : n < most ? n : most); };
+    // Decode: a (sequence, KV head) is nsub groups of 32 rows there and G tiles of 128 rows in attn_fwd_kernel,
+    // at about the same cost per group as per tile (B = 4, H = 32/8, Nk = 4096, d = 128: Nq = 16 31 us against
+    // 44, Nq = 24 34 against 44, Nq = 32 45 against 45; G = 1: Nq = 64 46 against 41).  In a packed batch only
+    // the totals are known; with no more queries than sequences it is the usual decode step, whereas a batch
+    // that mixes steps with a prompt chunk has to keep the 128-row tiles for the chunk.
+    const int64_t nsub = ((uniform ? Nq : 1) * G + 31) / 32;
+    if (uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B) {
+        r.decode = true;
+        r.nsub = (int)nsub;
+        const int64_t items = (int64_t)B * Hkv * nsub, steps = (Nk + 127) / 128;
+        if (items > 0xffffff) return r;
+        if (!uniform) {
+            // uneven lengths, longest first: four blocks per CU even out (48 sequences of 67 ... 7696 keys, 384
+            // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average
+            r.nsplit = clamp((1023 + items) / items, (steps + 2) / 3);
+        } else if (items < 128) {
+            // 128 blocks reach the memory's rate; parts below four steps cost more than they spread
+            // (B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
+            r.nsplit = clamp((127 + items) / items, steps / 4);
+        } else if (items > 256 && items % 256 != 0 && items < 1024) {
+            // a last round that leaves CUs idle (320 items of 4001 keys: 142 us whole, 126 in 2, 127 in 3)
+            r.nsplit = clamp(3, steps / 4);
+        }
+    } else if (Tk > Tq) {
+        // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call's 128-row kernel)
+        // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
+        // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
+        // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose
+        // loops are half as long: 42 whole, 49 in 2)
+        const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
+        r.nsplit = clamp((d_qk > 192 ? 256 : 512) / blocks, (Nk - Nq / 2) / (16 * 64));
+    }
+    return r;
+}
+
+// Blocks of the merge kernel that share the rows of a tile, in turns of 1024 / d_v rows per block.  On the decode route a
+// packed tile holds one query as a rule; the 128-row kernel's tiles hold up to 128 (shares past a short one's rows end at
+// once: at most 4096 blocks, for only calls of few tiles are divided).  512 packed queries, H = 32/8, 8192 keys, three
+// parts: 91 us, 141 undivided, and 133 with the 40 blocks of 64 turns each that one query per tile would ask for.
+inline int merge_shares(const FwdRoute& r, bool uniform, int nq, int group, int d_v)
+{
+    const int rows = (uniform ? (nq < 128 ? nq : 128) : r.decode ? 1 : 128) * group, per = 1024 / d_v;
+    return (rows + per - 1) / per;
+}
+
 }  // namespace attn

@@ -19,6 +19,12 @@ int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, 
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
+int t_shares(int B, int Tq, int Tk, int H, int Hkv, int d, int uniform, int* nsplit)
+{
+    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d, uniform);
+    *nsplit = r.nsplit;
+    return merge_shares(r, uniform, Tq / B, H / Hkv, d);
+}
 int t_dq_varlen(int d, int causal, long long n, long long k, long long half) { return dq_one_wave_varlen(d, causal, n, k, half); }
 int t_dkdv_varlen(int d, int causal, long long n, long long k, int group, long long blocks64)
 { return dkdv_one_wave_varlen(d, causal, n, k, group, blocks64); }
@@ -113,3 +119,21 @@ def test_varlen_rules_take_the_faster_kernel(D, d, causal, n, k, H, Hkv, tokens,
         assert bool(D.t_dq_varlen(d, causal, n, k, half)) == (dq < 0)
     if dkdv is not None:
         assert bool(D.t_dkdv_varlen(d, causal, n, k, H // Hkv, blocks64)) == (dkdv < 0)
+
+
+@pytest.mark.parametrize("B,Tq,Tk,H,Hkv,d", [(1, 512, 8192, 32, 8, 128), (4, 256, 16384, 32, 8, 128), (8, 1600, 24000, 8, 2, 64),
+                                             (2, 400, 13000, 16, 4, 64), (1, 128, 16384, 32, 8, 256)])
+def test_merge_of_a_packed_chunk_has_blocks_for_its_rows(D, B, Tq, Tk, H, Hkv, d):
+    """Packed sequences of several queries whose keys are divided: every row of a full tile within one turn of a merge block,
+    as for the strided call of the same sizes."""
+    nsplit = ctypes.c_int()
+    shares = D.t_shares(B, Tq, Tk, H, Hkv, d, 0, ctypes.byref(nsplit))
+    assert nsplit.value > 1 and shares * (1024 // d) >= 128 * (H // Hkv)
+
+
+def test_packed_chunks_of_the_gpu_tests_are_divided(D):
+    from test_gpu_decode import CHUNKS
+    for H, Hkv, dqk, dv, pairs, _ in CHUNKS:
+        nsplit = ctypes.c_int()
+        D.t_shares(len(pairs), sum(p[0] for p in pairs), sum(p[1] for p in pairs), H, Hkv, dqk, 0, ctypes.byref(nsplit))
+        assert nsplit.value > 1, pairs

@@ -72,6 +72,34 @@ def test_packed_decode_step(oracle, H, Hkv, d, lens):
             _check(oracle, part, o[None, s], lse[None, :, s], d ** -0.5, True, f"sequence {b}")
 
 
+def _packed_check(oracle, H, Hkv, dqk, dv, pairs, causal, seed, f16=False, **buffers):
+    """attn_varlen_fwd of sequences of (queries, keys), every row against the oracle."""
+    import paper_2603_05451_amd as A
+    cuq, cuk = (np.concatenate([[0], np.cumsum([p[i] for p in pairs])]).astype(np.int32) for i in (0, 1))
+    x = _case(1, H, Hkv, int(cuq[-1]), int(cuk[-1]), dqk, dv, False, seed, f16)
+    q, k, v = (x[n][0].cuda() for n in ("q", "k", "v"))
+    o = torch.full((int(cuq[-1]), H, dv), float("nan"), dtype=q.dtype, device="cuda")
+    o, lse = A.attn_varlen_fwd(q, k, v, torch.from_numpy(cuq).cuda(), dqk ** -0.5, causal, o=o,
+                               cu_seqlens_k=torch.from_numpy(cuk).cuda(), **buffers)
+    torch.cuda.synchronize()
+    for b, (nq, nk) in enumerate(pairs):
+        if nq:
+            sq, sk = slice(int(cuq[b]), int(cuq[b + 1])), slice(int(cuk[b]), int(cuk[b + 1]))
+            part = {"q": x["q"][:, sq], "k": x["k"][:, sk], "v": x["v"][:, sk]}
+            _check(oracle, part, o[None, sq], lse[None, :, sq], dqk ** -0.5, causal, f"sequence {b}")
+
+
+# chunks of several queries against a few thousand keys each: the 128-row kernel with its key loop divided.  Whole and ragged tiles,
+# a chunk of one query, a sequence without queries, one whose first parts hold all its keys
+CHUNKS = [(8, 2, 128, 128, [(200, 5000), (64, 3333), (1, 2500)], True), (4, 4, 64, 64, [(129, 4161), (0, 30), (300, 4500)], False),
+          (2, 1, 256, 256, [(130, 2700), (5, 2600)], True), (4, 1, 192, 128, [(128, 4100), (300, 2900), (17, 40)], True)]
+
+
+@pytest.mark.parametrize("H,Hkv,dqk,dv,pairs,causal", CHUNKS, ids=["d%d_%d" % (c[2], len(c[4])) for c in CHUNKS])
+def test_packed_chunks_with_divided_keys(oracle, H, Hkv, dqk, dv, pairs, causal):
+    _packed_check(oracle, H, Hkv, dqk, dv, pairs, causal, 750 + dqk, f16=dqk == 64)
+
+
 def test_decode_replays_in_a_graph_and_skips_what_is_not_planned():
     """A captured decode step on new queries gives the eager call's bits; on a workspace without tables a call
     that relies on them leaves its outputs alone, the merge kernel included."""
