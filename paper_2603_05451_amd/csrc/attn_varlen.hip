@@ -12,7 +12,9 @@
 // matter because no result depends on which block computes which tile), and inside a sequence
 // from the last tile to the first (under a causal mask the last query tile has the longest key
 // loop; the dK/dV kernels read the index backwards for the same reason).  Unused entries up to
-// the table size are zero.  The kernels size their grids by the table sizes, host-side upper
+// the table size are zero, except in a table of query tiles with no more queries than sequences: there
+// every query of a tile but its first has an entry {the tile's entry, query within the tile, 0, 0}, {0, kPlanHelp,
+// 0, 0} behind the used ones, for the decode and merge kernels, and the tile's own entry ends with 1.  The kernels size their grids by the table sizes, host-side upper
 // bounds, because the host never reads the lengths; for the same reason the boundaries are checked
 // here, on the device, against the row counts the caller stated: a sequence that does not lie
 // inside the tensors is left out of both tables.
@@ -33,6 +35,8 @@ __device__ void plan_build(const int* __restrict__ cu_q, const int* __restrict__
 {
     __shared__ int hist[PLAN_BUCKETS];       // tiles per bucket, then next free entry per bucket
     __shared__ int wave_sum[PLAN_NT / 64];
+    __shared__ int next_free;                // first entry that no tile and no helper has taken
+    const bool spread = own_is_q && Tq <= B;
     static_assert(PLAN_BUCKETS == 4 * PLAN_NT, "four buckets per thread in the scan below");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto tiles = [](int len) { return (len + 127) / 128; };
@@ -87,33 +91,52 @@ __device__ void plan_build(const int* __restrict__ cu_q, const int* __restrict__
         hist[PLAN_BUCKETS - 1 - (4 * tid + e)] = run;
         run += w[e];
     }
+    // (boundaries that overlap can list more tiles than the table holds, or than an int counts)
+    total = min(max(total, 0), max_tiles);
+    if (tid == 0) next_free = total;
+    if (spread)                              // before the helpers' entries
+        for (int i = 2 * total + tid; i < 2 * max_tiles; i += PLAN_NT) plan[i] = make_int4(0, 0, 0, 0);
     __syncthreads();
     // the entries: a sequence's own lane writes them one by one, or the wave 64 at a time, then one sequence after the
     // other.  The lanes take sequences of up to `few` tiles, at least as many as there are longer ones then (both tables, us,
     // all by lanes, all longer than two tiles by the wave, this: 40 x 257 tokens 7.3, 9.4, 3.2; 1500 x 300 20, 32, 8.9;
     // 16 of 64 ... 8192 15, 5.0, 4.4; 3 x 30 000 37, 4.2, 4.3).
-    auto entry = [&](int at, int4 rows, int tile, int b) {
+    auto entry = [&](int at, int4 rows, int4 tile) {
+        if (at < 0 || at >= max_tiles) return;
         plan[2 * at] = rows;
-        plan[2 * at + 1] = make_int4(tile, kPlanUsed, b, 0);
+        plan[2 * at + 1] = tile;
     };
     auto put = [&](const Sequence& s, int b) {
-        int first = 0, few = 2;
+        int first = 0, few = 2, helper = 0, helped = 0;
         if (s.nt > 0) first = atomicAdd(&hist[s.key], s.nt);
+        if (spread && s.nt > 0 && s.ql > s.nt) {
+            helper = atomicAdd(&next_free, s.ql - s.nt);
+            helped = helper >= total && helper <= max_tiles - (s.ql - s.nt);
+        }
         while (few < 64 && __popcll(__ballot(s.nt > few)) > few) few *= 2;
         if (s.nt > 0 && s.nt <= few)
             for (int t = 0; t < s.nt; ++t)
-                if (first + t < max_tiles) entry(first + t, make_int4(s.qs, s.ql, s.ks, s.kl), s.nt - 1 - t, b);
-        for (uint64_t left = __ballot(s.nt > few); left; left &= left - 1) {
-            const int l = __builtin_ctzll(left);
-            auto of = [&](int x) { return __builtin_amdgcn_readlane(x, l); };
-            const int nt = of(s.nt), at = of(first), sb = of(b);
-            const int4 rows = make_int4(of(s.qs), of(s.ql), of(s.ks), of(s.kl));
-            for (int t = lane; t < nt && at + t < max_tiles; t += 64) entry(at + t, rows, nt - 1 - t, sb);
-        }
+                entry(first + t, make_int4(s.qs, s.ql, s.ks, s.kl), make_int4(s.nt - 1 - t, kPlanUsed, b, helped));
+        auto each = [&](bool mine, auto f) {     // f(l) by the whole wave, for every lane l with `mine`
+            for (uint64_t left = __ballot(mine); left; left &= left - 1) f(__builtin_ctzll(left));
+        };
+        auto of = [&](int x, int l) { return __builtin_amdgcn_readlane(x, l); };
+        each(s.nt > few, [&](int l) {
+            const int nt = of(s.nt, l), at = of(first, l), sb = of(b, l), h = of(helped, l);
+            const int4 rows = make_int4(of(s.qs, l), of(s.ql, l), of(s.ks, l), of(s.kl, l));
+            for (int t = lane; t < nt; t += 64) entry(at + t, rows, make_int4(nt - 1 - t, kPlanUsed, sb, h));
+        });
+        if (spread)
+            each(helped != 0, [&](int l) {
+                const int ql = of(s.ql, l), last = of(first, l) + of(s.nt, l) - 1, at = of(helper, l) - 1;
+                for (int i = lane; i < ql; i += 64)
+                    if (i % 128) entry(at + i - i / 128, make_int4(last - i / 128, i % 128, 0, 0), make_int4(0, kPlanHelp, 0, 0));
+            });
     };
     put(own, tid);
     for (int b0 = PLAN_NT; b0 < B; b0 += PLAN_NT) put(b0 + tid < B ? load(b0 + tid) : Sequence{}, b0 + tid);
-    for (int i = 2 * total + tid; i < 2 * max_tiles; i += PLAN_NT) plan[i] = make_int4(0, 0, 0, 0);
+    if (!spread)
+        for (int i = 2 * total + tid; i < 2 * max_tiles; i += PLAN_NT) plan[i] = make_int4(0, 0, 0, 0);
 }
 
 // Block 0: the table of query tiles; block 1 (backward only): the table of key tiles.

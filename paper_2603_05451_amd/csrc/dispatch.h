@@ -132,8 +132,10 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool 
     // Decode: a (sequence, KV head) is nsub groups of 32 rows there and G tiles of 128 rows in attn_fwd_kernel,
     // at about the same cost per group as per tile (B = 4, H = 32/8, Nk = 4096, d = 128: Nq = 16 31 us against
     // 44, Nq = 24 34 against 44, Nq = 32 45 against 45; G = 1: Nq = 64 46 against 41).  In a packed batch only
-    // the totals are known; with no more queries than sequences it is the usual decode step, whereas a batch
-    // that mixes steps with a prompt chunk has to keep the 128-row tiles for the chunk.
+    // the totals are known; with no more queries than sequences it is the usual decode step, and a chunk among empty
+    // slots has table entries for its queries (row_share in launch.h; 128 slots, one with 128 queries against 8192
+    // keys, H = 32/8, d = 128: 65 us, 134 in 128-row tiles, 838 in the blocks of its own entry alone).  More queries
+    // than sequences: the 128-row tiles.
     const int64_t nsub = ((uniform ? Nq : 1) * G + 31) / 32;
     if (uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B) {
         r.decode = true;

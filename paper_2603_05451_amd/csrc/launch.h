@@ -26,9 +26,12 @@ struct VarlenStrides {
 // Mark of a used entry of the tile tables.  Not 1: a workspace that was never planned, or whose
 // tables were overwritten, then holds no entry that a kernel would act on.
 constexpr int kPlanUsed = 0x5A17AB1E;
+// Mark of an entry behind the used ones that takes a share of another tile's rows in the decode and merge kernels (see
+// row_share); the other kernels pass over it like over an unused one.
+constexpr int kPlanHelp = 0x5A17AB1F;
 
 // Entry e of a tile table: seq = {first query row, query length, first key row, key length} of the sequence,
-// til = {tile of 128 rows inside it, kPlanUsed, sequence, -}; a sequence's tiles are listed last to first.
+// til = {tile of 128 rows inside it, kPlanUsed, sequence, helpers}; a sequence's tiles are listed last to first.
 // Equal-length batches need no table: the entry follows from e, which spares the strided calls the two
 // boundary kernels and the plan kernel (three launches in a row, 10 us of a call).
 template <bool QUERY_SIDE>
@@ -43,6 +46,30 @@ __device__ __forceinline__ void tile_entry(const int4* __restrict__ plan, int e,
         seq = plan[2 * e];
         til = plan[2 * e + 1];
     }
+}
+
+// The rows of a tile in units, for the decode and merge kernels: n blocks per entry, block i of entry e takes units `unit`,
+// `unit` + `step`, ...  n units hold the rows of one query.  In a packed batch with no more queries than sequences a tile
+// usually is one query; where one holds more (a prompt chunk among empty slots), each further query has an entry of its
+// own behind the used ones (kPlanHelp: {tile's entry, query within it}; there is room, since queries <= sequences), so
+// that every block takes one unit and the chunk is spread over the chip.  til.w != 0: the tile has such helpers; 0 (and
+// equal lengths, whose n covers the whole tile): the entry's blocks take all units.
+__device__ __forceinline__ bool row_share(const int4* __restrict__ plan, int e, int max_tiles, const VarlenStrides& st, int T,
+                                          int i, int n, int4& seq, int4& til, int& unit, int& step)
+{
+    constexpr int one_turn = 1 << 24;
+    tile_entry<true>(plan, e, st, seq, til);
+    unit = i;
+    step = til.w != 0 ? one_turn : n;
+    if (til.y == kPlanHelp) {
+        const int of = seq.x, query = seq.y;
+        if (of < 0 || of >= max_tiles || query < 1 || query > 127) return false;
+        seq = plan[2 * of];
+        til = plan[2 * of + 1];
+        unit += query * n;
+        step = one_turn;
+    }
+    return til.y == kPlanUsed && seq.x >= 0 && seq.y >= 0 && seq.x + seq.y <= T;
 }
 
 struct FwdArgs {
@@ -63,8 +90,8 @@ struct FwdArgs {
     // part_o [nsplit][T][H][d_v] and part_ml [nsplit][T][H] {reference maximum, row sum} (nsplit > 1)
     int nsplit = 1;
     float *part_o = nullptr, *part_ml = nullptr;
-    int nsub = 1;       // decode kernel: blocks that share the 32-row groups of one tile
-    int nshare = 1;     // merge kernel: blocks that share the rows of one tile
+    int nsub = 1;       // decode kernel: blocks per table entry that share the 32-row groups of a tile (row_share)
+    int nshare = 1;     // merge kernel: blocks per table entry that share the rows of a tile
 };
 
 struct BwdArgs {

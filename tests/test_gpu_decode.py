@@ -100,6 +100,61 @@ def test_packed_chunks_with_divided_keys(oracle, H, Hkv, dqk, dv, pairs, causal)
     _packed_check(oracle, H, Hkv, dqk, dv, pairs, causal, 750 + dqk, f16=dqk == 64)
 
 
+def _slots(n, chunks):
+    """n slots, most of them empty (with and without keys); chunks: {slot: (queries, keys)}."""
+    return [chunks.get(i, (0, 40 if i % 3 == 0 else 0)) for i in range(n)]
+
+
+# no more queries than sequences, yet sequences of many: a chunk of more than a tile among empty slots, two queries, one; 64 heads on
+# one KV head (two 32-row groups per query); three heads (10 rows per turn of the merge kernel at d = 96); keys divided (few slots' worth
+# of items) and whole
+SLOTS = [(8, 2, 128, 128, _slots(160, {7: (130, 700), 8: (2, 33), 20: (1, 5), 159: (1, 900)}), True),
+         (4, 4, 64, 64, _slots(300, {0: (257, 300), 299: (3, 1)}), False), (64, 1, 256, 256, _slots(40, {3: (33, 515), 30: (2, 64)}), True),
+         (6, 2, 96, 96, _slots(20, {1: (11, 3000), 2: (5, 700)}), True), (8, 1, 192, 128, _slots(24, {23: (24, 2100)}), True)]
+
+
+@pytest.mark.parametrize("H,Hkv,dqk,dv,pairs,causal", SLOTS, ids=["d%d_%d" % (c[2], len(c[4])) for c in SLOTS])
+def test_chunks_among_empty_slots(oracle, H, Hkv, dqk, dv, pairs, causal):
+    _packed_check(oracle, H, Hkv, dqk, dv, pairs, causal, 780 + dqk, f16=dqk in (64, 192))
+
+
+def test_every_query_of_a_slot_is_listed_once():
+    """The table of query tiles with no more queries than sequences: behind the tiles one entry for every query of a tile but its
+    first, zeros behind those.  Boundaries that overlap list more queries than there is room for: such a sequence is not listed, its
+    tiles' own blocks take all rows, and the results are those of sound boundaries."""
+    import paper_2603_05451_amd as A
+    from test_gpu_varlen import read_tables
+    USED, HELP = 0x5A17AB1E, 0x5A17AB1F
+    lens = [0] * 200 + [130, 0, 1, 2, 0, 7] + [0] * 40 + [1] * 3 + [0] * 20          # the longest in another wave than the short ones
+    B, cuq = len(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cuk = np.arange(B + 1, dtype=np.int32) * 50
+    Tq, Tk = int(cuq[-1]), int(cuk[-1])
+    ws = torch.full((A.attn_varlen_workspace_bytes(B, Tq, Tk, 1, 1, 64, 64, True),), 0xAB, dtype=torch.uint8, device="cuda")
+    A.attn_varlen_plan(torch.from_numpy(cuq).cuda(), Tq, Tk, 1, 1, 64, 64, ws, cu_seqlens_k=torch.from_numpy(cuk).cuda())
+    torch.cuda.synchronize()
+    table, _ = read_tables(ws, B, Tq, Tk)
+    used = int((table[:, 5] == USED).sum())
+    assert (table[:used, 5] == USED).all() and used == sum((n + 127) // 128 for n in lens)
+    listed = []
+    for e in table[used:Tq]:
+        assert e[5] == HELP and 0 <= e[0] < used and table[e[0], 7] == 1 and (e[2:5] == 0).all() and (e[6:] == 0).all()
+        listed.append((int(table[e[0], 0]), 128 * int(table[e[0], 4]) + int(e[1])))
+    want = [(int(cuq[b]), i) for b, n in enumerate(lens) for i in range(n) if i % 128]
+    assert sorted(listed) == sorted(want) and (table[Tq:] == 0).all()
+    assert all(t[7] == (min(t[1] - 128 * t[4], 128) > 1 or t[1] > 128) for t in table[:used])
+
+    H, Hkv, d, n = 8, 1, 128, 16
+    x = _case(1, H, Hkv, n, 700, d, d, False, 790)
+    q, k, v = (x[m][0].cuda() for m in ("q", "k", "v"))
+    cu = lambda *c: torch.tensor(c, dtype=torch.int32, device="cuda")
+    sound = A.attn_varlen_fwd(q, k, v, cu(0, n, *[n] * (n - 1)), 0.1, True, cu_seqlens_k=cu(0, 700, *[700] * (n - 1)))
+    twice = [torch.full_like(t, float("nan")) for t in sound]
+    A.attn_varlen_fwd(q, k, v, cu(0, n, 0, n, *[n] * (n - 3)), 0.1, True, o=twice[0], lse=twice[1],
+                      cu_seqlens_k=cu(0, 700, 0, 700, *[700] * (n - 3)))
+    torch.cuda.synchronize()
+    assert torch.equal(sound[0], twice[0]) and torch.equal(sound[1], twice[1])
+
+
 def test_decode_replays_in_a_graph_and_skips_what_is_not_planned():
     """A captured decode step on new queries gives the eager call's bits; on a workspace without tables a call
     that relies on them leaves its outputs alone, the merge kernel included."""
