@@ -231,7 +231,7 @@ VarlenLayout varlen_layout(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int 
     w.lse2_off = w.d_off + align_up((size_t)H * Tq * sizeof(float), 256);
     w.min_bwd = w.lse2_off + align_up((size_t)H * Tq * sizeof(float), 256);
     // with less than the partial results need, a call divides the keys as far as its workspace goes
-    const size_t part = partial_bytes(attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform).nsplit, Tq, H, d_v);
+    const size_t part = partial_bytes(attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform).nsplit, Tq, H, d_v);
     w.total_fwd = part ? w.part_off + part : w.min_fwd;
     w.total_bwd = w.min_bwd > w.total_fwd ? w.min_bwd : w.total_fwd;
     return w;
@@ -264,7 +264,7 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
-    const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, uniform);
+    const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);
     a.nsub = r.nsub;
     a.nsplit = r.nsplit;
     while (a.nsplit > 1 && w.part_off + partial_bytes(a.nsplit, Tq, H, d_v) > ws_bytes) --a.nsplit;

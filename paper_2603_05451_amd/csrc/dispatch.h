@@ -124,7 +124,7 @@ struct FwdRoute {
     int nsplit;         // parts of the keys; 1: no partial results
 };
 
-inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool uniform)
+inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int, bool uniform)
 {
     FwdRoute r{false, 1, 1};
     const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
@@ -137,7 +137,17 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, bool 
     // keys, H = 32/8, d = 128: 65 us, 134 in 128-row tiles, 838 in the blocks of its own entry alone).  More queries
     // than sequences: the 128-row tiles.
     const int64_t nsub = ((uniform ? Nq : 1) * G + 31) / 32;
-    if (uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B) {
+    const bool few_queries = uniform ? nsub == 1 || 4 * nsub <= 3 * G : Tq <= B;
+    // ... but not against a few keys, for whose one to four tiles the merge of four waves costs as much as the work.  With
+    // one head per KV head the 128-row kernel has no more blocks (B H = 4096, us, 128-row -> decode: d = 64 Nk = 64 22 -> 34,
+    // 256 47 -> 56, 512 105 -> 109; d = 128 Nk = 64 36 -> 41, 320 126 -> 122; d = 256 Nk = 128 159 -> 164; (192, 128) Nk = 64
+    // 52 -> 50); with more, where they all fit (B H <= 256, Nk <= 128: 4.1 -> 5.2, 5.0 -> 5.7, 7.1 -> 8.1 at 64, 128, 256).
+    // (Packed lengths are uneven: 128 sequences of 16 ... 1024 keys, 235 on average, d = 64: 36 -> 35; empty slots have
+    // no queries.)
+    const int64_t keys = uniform ? Nk : Tk / Tq;
+    const bool few_keys = (G == 1 && d_qk != 192 && keys <= (uniform && d_qk == 64 ? 256 : 128)) ||
+                          (uniform && (int64_t)B * H <= 256 && Nk <= (d_qk == 192 ? 64 : 128));
+    if (few_queries && !few_keys) {
         r.decode = true;
         r.nsub = (int)nsub;
         const int64_t items = (int64_t)B * Hkv * nsub, steps = (Nk + 127) / 128;

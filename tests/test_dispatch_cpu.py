@@ -19,11 +19,15 @@ int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, 
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
-int t_shares(int B, int Tq, int Tk, int H, int Hkv, int d, int uniform, int* nsplit)
+int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
 {
-    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d, uniform);
+    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform);
     *nsplit = r.nsplit;
-    return merge_shares(r, uniform, Tq / B, H / Hkv, d);
+    return r.decode;
+}
+int t_shares(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform)
+{
+    return merge_shares(fwd_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform), uniform, Tq / B, H / Hkv, dv);
 }
 int t_dq_varlen(int d, int causal, long long n, long long k, long long half) { return dq_one_wave_varlen(d, causal, n, k, half); }
 int t_dkdv_varlen(int d, int causal, long long n, long long k, int group, long long blocks64)
@@ -121,19 +125,45 @@ def test_varlen_rules_take_the_faster_kernel(D, d, causal, n, k, H, Hkv, tokens,
         assert bool(D.t_dkdv_varlen(d, causal, n, k, H // Hkv, blocks64)) == (dkdv < 0)
 
 
+def route(D, B, Tq, Tk, H, Hkv, dqk, dv, uniform):
+    """(decode kernel, parts of the keys) of a forward call."""
+    nsplit = ctypes.c_int()
+    return bool(D.t_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform, ctypes.byref(nsplit))), nsplit.value
+
+
 @pytest.mark.parametrize("B,Tq,Tk,H,Hkv,d", [(1, 512, 8192, 32, 8, 128), (4, 256, 16384, 32, 8, 128), (8, 1600, 24000, 8, 2, 64),
                                              (2, 400, 13000, 16, 4, 64), (1, 128, 16384, 32, 8, 256)])
 def test_merge_of_a_packed_chunk_has_blocks_for_its_rows(D, B, Tq, Tk, H, Hkv, d):
     """Packed sequences of several queries whose keys are divided: every row of a full tile within one turn of a merge block,
     as for the strided call of the same sizes."""
-    nsplit = ctypes.c_int()
-    shares = D.t_shares(B, Tq, Tk, H, Hkv, d, 0, ctypes.byref(nsplit))
-    assert nsplit.value > 1 and shares * (1024 // d) >= 128 * (H // Hkv)
+    assert route(D, B, Tq, Tk, H, Hkv, d, d, 0)[1] > 1 and D.t_shares(B, Tq, Tk, H, Hkv, d, d, 0) * (1024 // d) >= 128 * (H // Hkv)
 
 
-def test_packed_chunks_of_the_gpu_tests_are_divided(D):
-    from test_gpu_decode import CHUNKS
-    for H, Hkv, dqk, dv, pairs, _ in CHUNKS:
-        nsplit = ctypes.c_int()
-        D.t_shares(len(pairs), sum(p[0] for p in pairs), sum(p[1] for p in pairs), H, Hkv, dqk, 0, ctypes.byref(nsplit))
-        assert nsplit.value > 1, pairs
+# (B, H, Hkv, Nq, Nk, d, decode kernel over 128-row kernel): both sides of the lines, equal lengths
+MEASURED_DECODE = [(256, 16, 16, 1, 64, 64, 1.52), (256, 16, 16, 1, 256, 64, 1.19), (64, 16, 16, 1, 1024, 64, 0.91), (256, 16, 16, 1, 64, 128, 1.13),
+                   (256, 16, 16, 1, 320, 128, 0.97), (256, 16, 16, 16, 16, 256, 1.29), (256, 16, 16, 1, 64, 192, 0.95), (4, 16, 8, 1, 64, 64, 1.27),
+                   (16, 16, 8, 16, 128, 128, 1.18), (32, 32, 8, 1, 64, 128, 0.59), (512, 16, 4, 16, 16, 192, 0.67), (1, 8, 8, 16, 64, 192, 1.29),
+                   (2, 32, 8, 24, 4096, 128, 0.45)]
+
+
+@pytest.mark.parametrize("B,H,Hkv,Nq,Nk,d,ratio", MEASURED_DECODE)
+def test_decode_rule_takes_the_faster_kernel(D, B, H, Hkv, Nq, Nk, d, ratio):
+    assert route(D, B, B * Nq, B * Nk, H, Hkv, d, 128 if d == 192 else d, 1)[0] == (ratio < 1)
+
+
+def test_packed_steps_against_few_keys(D):
+    assert route(D, 512, 512, 512 * 64, 16, 16, 64, 64, 0)[0] is False          # tiny caches of many heads
+    assert route(D, 512, 32, 32 * 1000, 16, 16, 64, 64, 0)[0] is True           # (slots without a query do not count)
+
+
+def test_gpu_tests_reach_what_they_are_written_for(D):
+    from test_gpu_decode import CHUNKS, FEW_KEYS, SHAPES, SLOTS
+    for B, H, Hkv, Nq, Nk, dqk, dv, _ in SHAPES:
+        decode, nsplit = route(D, B, B * Nq, B * Nk, H, Hkv, dqk, dv, 1)
+        assert decode == (Nq < 100) and (decode or nsplit > 1), (B, H, Hkv, Nq, Nk)
+    for B, H, Hkv, Nq, Nk, dqk, dv, _ in FEW_KEYS:
+        assert route(D, B, B * Nq, B * Nk, H, Hkv, dqk, dv, 1) == (False, 1)
+    for cases, want in ((CHUNKS, False), (SLOTS, True)):
+        for H, Hkv, dqk, dv, pairs, _ in cases:
+            decode, nsplit = route(D, len(pairs), *(sum(p[i] for p in pairs) for i in (0, 1)), H, Hkv, dqk, dv, 0)
+            assert decode == want and (want or nsplit > 1), pairs

@@ -28,16 +28,20 @@ def _check(oracle, x, o, lse, scale, causal, name):
 # (B, H, Hkv, Nq, Nk, d_qk, d_v, causal): one key; around one tile and one round of the four waves; every head
 # dim; two queries whose last keys lie in different tiles; two 32-row groups; 64 heads on one KV head; few
 # sequences with long caches (many splits, the last of them empty or ragged); chunks with a divided key loop
-SHAPES = [(1, 2, 2, 1, 1, 64, 64, True), (3, 4, 1, 1, 31, 128, 128, True), (2, 8, 2, 1, 33, 96, 96, False),
-          (2, 4, 4, 1, 127, 192, 128, True), (1, 8, 2, 1, 129, 256, 256, True), (2, 4, 2, 2, 65, 128, 128, True),
+SHAPES = [(40, 8, 2, 1, 1, 64, 64, True), (40, 8, 1, 1, 31, 128, 128, True), (33, 8, 2, 1, 33, 96, 96, False),
+          (2, 4, 4, 1, 127, 192, 128, True), (1, 8, 2, 1, 129, 256, 256, True), (33, 8, 4, 2, 65, 128, 128, True),
           (2, 8, 1, 3, 130, 64, 64, True), (1, 64, 1, 1, 515, 128, 128, True), (2, 16, 4, 10, 300, 128, 128, True),
           (1, 2, 2, 1, 8200, 128, 128, True), (1, 4, 2, 1, 5121, 64, 64, False), (1, 2, 1, 5, 4100, 192, 128, True),
           (1, 2, 1, 2, 3077, 256, 256, True), (1, 3, 3, 1, 2600, 96, 96, True),
           (1, 2, 2, 200, 4161, 128, 128, True), (1, 2, 1, 130, 3300, 64, 64, False), (1, 2, 1, 129, 2500, 256, 256, True),
           (1, 2, 1, 300, 2900, 192, 128, True), (2, 1, 1, 140, 2300, 96, 96, True)]
 
+# as few queries against so few keys that the 128-row kernel keeps them
+FEW_KEYS = [(1, 2, 2, 1, 1, 64, 64, True), (3, 4, 1, 1, 31, 128, 128, True), (2, 8, 2, 1, 33, 96, 96, False), (2, 4, 2, 2, 65, 128, 128, True),
+            (20, 16, 16, 20, 130, 64, 64, True)]
 
-@pytest.mark.parametrize("shape", SHAPES, ids=["B%d_H%d_%d_q%d_k%d_d%d_%d_%s" % s for s in SHAPES])
+
+@pytest.mark.parametrize("shape", SHAPES + FEW_KEYS, ids=["B%d_H%d_%d_q%d_k%d_d%d_%d_%s" % s for s in SHAPES + FEW_KEYS])
 def test_few_queries_against_many_keys(oracle, shape):
     import paper_2603_05451_amd as A
     B, H, Hkv, Nq, Nk, dqk, dv, causal = shape
@@ -109,7 +113,7 @@ def _slots(n, chunks):
 # one KV head (two 32-row groups per query); three heads (10 rows per turn of the merge kernel at d = 96); keys divided (few slots' worth
 # of items) and whole
 SLOTS = [(8, 2, 128, 128, _slots(160, {7: (130, 700), 8: (2, 33), 20: (1, 5), 159: (1, 900)}), True),
-         (4, 4, 64, 64, _slots(300, {0: (257, 300), 299: (3, 1)}), False), (64, 1, 256, 256, _slots(40, {3: (33, 515), 30: (2, 64)}), True),
+         (4, 2, 64, 64, _slots(300, {0: (257, 300), 299: (3, 1)}), False), (64, 1, 256, 256, _slots(40, {3: (33, 515), 30: (2, 64)}), True),
          (6, 2, 96, 96, _slots(20, {1: (11, 3000), 2: (5, 700)}), True), (8, 1, 192, 128, _slots(24, {23: (24, 2100)}), True)]
 
 
