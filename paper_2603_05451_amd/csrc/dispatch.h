@@ -124,7 +124,7 @@ struct FwdRoute {
     int nsplit;         // parts of the keys; 1: no partial results
 };
 
-inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int, bool uniform)
+inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d_v, bool uniform)
 {
     FwdRoute r{false, 1, 1};
     const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
@@ -154,15 +154,23 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int, 
         if (items > 0xffffff) return r;
         if (!uniform) {
             // uneven lengths, longest first: four blocks per CU even out (48 sequences of 67 ... 7696 keys, 384
-            // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average
-            r.nsplit = clamp((1023 + items) / items, (steps + 2) / 3);
+            // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average; no more
+            // than bring a sequence to 128 blocks by itself (one of 32 k keys, Hkv = 8: 41 us in 16 parts and in 86)
+            const int64_t even = (1023 + items) / items, alone = (127 + Hkv * nsub) / (Hkv * nsub);
+            r.nsplit = clamp(even < alone ? even : alone, (steps + 2) / 3);
         } else if (items < 128) {
             // 128 blocks reach the memory's rate; parts below four steps cost more than they spread
             // (B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
             r.nsplit = clamp((127 + items) / items, steps / 4);
-        } else if (items > 256 && items % 256 != 0 && items < 1024) {
-            // a last round that leaves CUs idle (320 items of 4001 keys: 142 us whole, 126 in 2, 127 in 3)
-            r.nsplit = clamp(3, steps / 4);
+        } else if (items > 256 && items < 1024) {
+            // A last round of 256 that leaves CUs idle, in three parts per sequence, where the keys are long enough and
+            // the round empty enough to pay for the partial results (three parts against one, 264 ... 320 / 352, 384 /
+            // 448 ... 512 items: d = 128, Nk = 1000 0.97 ... 1.06 / 1.10 / 1.09, 2000 0.84 ... 0.91 / 0.98 / 1.07, 4000
+            // 0.78 ... 0.88 / 0.95 / 1.04; d = 256, Nk = 1000 0.91 ... 0.97 / 1.05 / 1.12; d = 64, Nk = 2000 0.87 ... 0.97 /
+            // 1.04 / 1.02, 4000 0.73 ... 0.84 / 0.87 / 0.98)
+            const int64_t last = items % 256, elems = Nk * (d_qk + d_v);
+            const bool pays = d_qk == 64 ? elems >= 250000 : elems >= 500000 && last <= (elems >= 1000000 ? 128 : 64);
+            if (last != 0 && pays) r.nsplit = 3;
         }
     } else if (Tk > Tq) {
         // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call's 128-row kernel)

@@ -151,7 +151,21 @@ def test_decode_rule_takes_the_faster_kernel(D, B, H, Hkv, Nq, Nk, d, ratio):
     assert route(D, B, B * Nq, B * Nk, H, Hkv, d, 128 if d == 192 else d, 1)[0] == (ratio < 1)
 
 
-def test_packed_steps_against_few_keys(D):
+# (items, Nk, d, three parts over one)
+@pytest.mark.parametrize("items,Nk,d,ratio", [(264, 1000, 128, 0.97), (320, 2000, 128, 0.91), (384, 2000, 128, 0.99), (480, 2000, 128, 1.07),
+                                              (320, 4000, 128, 0.88), (480, 4000, 128, 1.04), (800, 4000, 128, 0.93), (320, 300, 256, 1.32),
+                                              (264, 1000, 256, 0.91), (352, 1000, 256, 1.04), (264, 2000, 64, 0.87), (320, 1000, 64, 1.18),
+                                              (448, 4000, 64, 0.97)])
+def test_partly_filled_rounds_are_divided_where_it_pays(D, items, Nk, d, ratio):
+    """(Within 3 % either choice will do.)"""
+    B = items // 8
+    decode, nsplit = route(D, B, B, B * Nk, 32, 8, d, d, 1)
+    assert decode and (abs(ratio - 1) < 0.035 or nsplit == (3 if ratio < 1 else 1))
+
+
+def test_parts_of_a_packed_step(D):
+    assert route(D, 1, 1, 32768, 32, 8, 128, 128, 0) == (True, 16)              # a sequence alone: 128 blocks, not 1024
+    assert route(D, 48, 48, 48 * 1700, 32, 8, 128, 128, 0) == (True, 3)
     assert route(D, 512, 512, 512 * 64, 16, 16, 64, 64, 0)[0] is False          # tiny caches of many heads
     assert route(D, 512, 32, 32 * 1000, 16, 16, 64, 64, 0)[0] is True           # (slots without a query do not count)
 
