@@ -155,7 +155,7 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
         if (!uniform) {
             // uneven lengths, longest first: four blocks per CU even out (48 sequences of 67 ... 7696 keys, 384
             // items: 91, 72, 63, 65 us for 1 ... 4 parts), of at least three steps of 128 keys on average; no more
-            // than bring a sequence to 128 blocks by itself (one of 32 k keys, Hkv = 8: 41 us in 16 parts and in 86)
+            // than bring a sequence to 128 blocks by itself (one of 32 k keys, Hkv = 8: 33 us in 16 parts, 42 in 86)
             const int64_t even = (1023 + items) / items, alone = (127 + Hkv * nsub) / (Hkv * nsub);
             r.nsplit = clamp(even < alone ? even : alone, (steps + 2) / 3);
         } else if (items < 128) {
