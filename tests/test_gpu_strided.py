@@ -38,16 +38,22 @@ def test_bhsd_views_match_contiguous_calls_bitwise(dqk, dv, H, Hkv, causal, seed
 
 
 # N, H at which attn_fwd and attn_bwd leave their 128-row kernels: one round of 256-row blocks (136 ... 208 of them), more
-# than 512 of them at a length that pays, and d = 256; three sequences in one case, GQA in another
-@pytest.mark.parametrize("dqk,dv,B,N,H,Hkv,causal", [(64, 64, 1, 1280, 30, 30, False), (128, 128, 1, 1024, 34, 34, False),
-                                                     (128, 128, 1, 2048, 26, 13, True), (192, 128, 3, 2048, 8, 4, True),
-                                                     (64, 64, 1, 2048, 64, 32, False), (256, 256, 1, 512, 4, 2, True)])
-def test_contiguous_calls_give_the_fixed_length_bits(dqk, dv, B, N, H, Hkv, causal):
+# than 512 of them at a length that pays, and d = 256; three sequences in one case, GQA in another.  fp16: sizes at which the two
+# calls run different dK/dV kernels as well
+BITS = [(64, 64, 1, 1280, 30, 30, False, torch.bfloat16), (128, 128, 1, 1024, 34, 34, False, torch.bfloat16),
+        (128, 128, 1, 2048, 26, 13, True, torch.bfloat16), (192, 128, 3, 2048, 8, 4, True, torch.bfloat16),
+        (64, 64, 1, 2048, 64, 32, False, torch.bfloat16), (256, 256, 1, 512, 4, 2, True, torch.bfloat16),
+        (64, 64, 2, 384, 4, 2, True, torch.float16), (96, 96, 1, 640, 4, 2, False, torch.float16), (64, 64, 1, 1024, 36, 36, False, torch.float16),
+        (256, 256, 2, 128, 8, 8, True, torch.float16), (128, 128, 1, 1024, 34, 17, True, torch.float16), (192, 128, 1, 256, 4, 2, True, torch.float16)]
+
+
+@pytest.mark.parametrize("dqk,dv,B,N,H,Hkv,causal,dtype", BITS, ids=["d%d_N%d_H%d_%s_%s" % (c[0], c[3], c[4], "c" if c[6] else "nc", c[7]) for c in BITS])
+def test_contiguous_calls_give_the_fixed_length_bits(dqk, dv, B, N, H, Hkv, causal, dtype):
     """Contiguous [B, N, H, d] tensors with N a multiple of 128, handed to the strided entry points: the bits of attn_fwd
     and attn_bwd at every size, whichever kernels those take there."""
     import paper_2603_05451_amd as A
     gen = torch.Generator(device="cuda").manual_seed(dqk + N + H)
-    q, k, v, do = (torch.randn(B, N, h, e, generator=gen, device="cuda").bfloat16()
+    q, k, v, do = (torch.randn(B, N, h, e, generator=gen, device="cuda").to(dtype)
                    for h, e in ((H, dqk), (Hkv, dqk), (Hkv, dv), (H, dv)))
     o_ref, lse_ref = A.attn_fwd(q, k, v, dqk ** -0.5, causal)
     ref = A.attn_bwd(q, k, v, o_ref, do, lse_ref, dqk ** -0.5, causal)
