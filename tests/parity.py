@@ -33,6 +33,7 @@ a tolerance and produce no expected value.
 import os
 
 import numpy as np
+import torch
 
 MAX_ABS = 2e-2
 REL_FRO = 1e-2
@@ -178,3 +179,33 @@ def dump_report(path):
             f.write("\nheavy-tailed workload, audit of the term-scaled gate\n")
             for line in AUDIT:
                 f.write(line + "\n")
+
+
+def repeated(t, times):
+    """The heads of [B, N, heads, d] over and over, on the GPU (query heads and their KV heads repeat alike)."""
+    return t.repeat(1, 1, times, 1).cuda()
+
+
+def same_in_every_repetition(t, heads, axis):
+    """Whether every repetition of `heads` heads along `axis` has the bits of the first."""
+    first, *rest = t.split(heads, dim=axis)
+    return all(torch.equal(first, r) for r in rest)
+
+
+def half_ulp(dtype):
+    """Largest relative rounding error of the element type: 8 and 11 significant bits."""
+    return 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -11
+
+
+def dq_bound_of_one_ds_ulp(q, k, v, o, do, lse, scale, first_key=0, causal=False):
+    """Bound on the difference of one head's dQ [n, d] between kernels that round dP - D differently: what one rounding of
+    the row's largest dS moves, computed in fp32 from the same inputs (causal: key j <= query i + first_key).  + 1e-5: dP and D
+    are fp32 sums of d products up to about 20, rounded by up to 2^-23 * 20 d / 2 = 1.5e-4 at the very worst and 1e-5 as seen; it
+    shows alone in a row with one key, where dP - D = 0."""
+    rounding = half_ulp(q.dtype)
+    q, k, v, o, do = (t.float() for t in (q, k, v, o, do))
+    p = (q @ k.T * scale - lse[:, None]).exp()
+    if causal:
+        p = p.tril(first_key)
+    ds = p * (do @ v.T - (do * o).sum(1, keepdim=True))
+    return (rounding * ds.abs().amax(1, keepdim=True) + 1e-5) * k.abs().max() * scale

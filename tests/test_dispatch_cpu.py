@@ -171,13 +171,52 @@ def test_parts_of_a_packed_step(D):
 
 
 def test_gpu_tests_reach_what_they_are_written_for(D):
+    """The case lists of the GPU tests, through the rules: a kernel's tests stop being its tests when a line moves."""
+    import test_gpu_edge as E
+    import test_gpu_few_blocks as S
+    import test_gpu_fp16 as H
+    import test_gpu_fwd as F
+    import test_gpu_varlen as V
+    import test_gpu_varlen_one_wave as W
     from test_gpu_decode import CHUNKS, FEW_KEYS, SHAPES, SLOTS
-    for B, H, Hkv, Nq, Nk, dqk, dv, _ in SHAPES:
-        decode, nsplit = route(D, B, B * Nq, B * Nk, H, Hkv, dqk, dv, 1)
-        assert decode == (Nq < 100) and (decode or nsplit > 1), (B, H, Hkv, Nq, Nk)
-    for B, H, Hkv, Nq, Nk, dqk, dv, _ in FEW_KEYS:
-        assert route(D, B, B * Nq, B * Nk, H, Hkv, dqk, dv, 1) == (False, 1)
+    for w, times in F.Q64 + H.ONE_WAVE:
+        assert D.t_fwd(w.dqk, w.causal, w.N, w.B * w.H * times * w.N // 256), w.name
+    for causal, N, d, _, times, *_ in F.GROWING + F.STEPS:
+        assert D.t_fwd(d, causal, N, 2 * times * N // 256), (causal, N, d)
+    for causal, N, heads, d, _ in S.FORWARD:
+        assert D.t_fwd(d, causal, N, heads * N // 256), (causal, N, heads, d)
+    for causal, N, heads, d in S.BACKWARD:
+        assert bool(D.t_dq(d, causal, N, heads * N // 256)) == ((d, causal, N) != (64, True, 1024))
+        assert d != 64 or D.t_dkdv64(d, causal, N, heads * N // 256)
+    for causal, d, N, times in E.DQ_TILES:
+        assert D.t_dq(d, causal, N, 4 * times * N // 256), (causal, N, d)
+    for w, times in H.ONE_WAVE:
+        assert w.dqk == 192 or D.t_dq(w.dqk, w.causal, w.N, w.H * times * w.N // 256), w.name
+        assert w.dqk != 64 or w.H != w.Hkv or D.t_dkdv64(64, w.causal, w.N, w.Hkv * times * w.N // 256), w.name
+    for cases, want in ((V.SAME_KERNEL, False), (V.OTHER_KERNEL, True)):
+        for B, N, causal in cases:
+            assert bool(D.t_fwd(128, causal, N, B * 4 * N // 256)) == want, (B, N, causal)
+    for cases, want in ((V.BWD_SAME, False), (V.BWD_OTHER, True)):
+        for dqk, _, _, N, causal, B, heads, Hkv in cases:
+            b = B * heads * N // 256
+            assert (dqk != 192 and bool(D.t_dq(dqk, causal, N, b))) == want
+            assert not D.t_dq_varlen(dqk, causal, N, N, b)                          # (the packed call: the general kernel)
+    for d, causal, lens, _ in W.LARGE:
+        n, k = (sum(x[i] for x in lens) for i in (0, 1))
+        B = len(lens)
+        assert D.t_dq_varlen(d, causal, n // B, k // B, (n + 255) // 256 * 16), lens
+        assert D.t_dkdv_varlen(d, causal, n // B, k // B, 2, (k // 128 + B) // 2 * 8), lens
+        for nq, nk in lens:
+            assert not D.t_dq_varlen(d, causal, nq, nk, (nq + 255) // 256 * 2)      # (two heads of one sequence)
+    for dqk, _, causal, lens in W.CASES:
+        n, k = (sum(x[i] for x in lens) // len(lens) for i in (0, 1))
+        assert D.t_dkdv_varlen(dqk, causal, n, k, 2, 1) and (dqk == 128 or D.t_dq_varlen(dqk, causal, n, k, 1)), lens
+    for B, H_, Hkv, Nq, Nk, dqk, dv, _ in SHAPES:
+        decode, nsplit = route(D, B, B * Nq, B * Nk, H_, Hkv, dqk, dv, 1)
+        assert decode == (Nq < 100) and (decode or nsplit > 1), (B, H_, Hkv, Nq, Nk)
+    for B, H_, Hkv, Nq, Nk, dqk, dv, _ in FEW_KEYS:
+        assert route(D, B, B * Nq, B * Nk, H_, Hkv, dqk, dv, 1) == (False, 1)
     for cases, want in ((CHUNKS, False), (SLOTS, True)):
-        for H, Hkv, dqk, dv, pairs, _ in cases:
-            decode, nsplit = route(D, len(pairs), *(sum(p[i] for p in pairs) for i in (0, 1)), H, Hkv, dqk, dv, 0)
+        for H_, Hkv, dqk, dv, pairs, _ in cases:
+            decode, nsplit = route(D, len(pairs), *(sum(p[i] for p in pairs) for i in (0, 1)), H_, Hkv, dqk, dv, 0)
             assert decode == want and (want or nsplit > 1), pairs

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2603_05451_amd import inputs as I
-from parity import LSE_ABS, assert_close
+from parity import LSE_ABS, assert_close, repeated, same_in_every_repetition
 
 pytestmark = pytest.mark.gpu
 
@@ -158,20 +158,24 @@ def test_literal_north_star_entry_points_on_live_tensors():
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("causal,d,N", [(True, 128, 4096), (False, 128, 4096), (True, 64, 8192), (False, 64, 2048)])
-def test_dq_of_every_row_of_the_first_and_last_query_tiles(oracle, causal, d, N):
-    """The dQ kernel with 64 queries per wave at its shortest sequences (d = 128: N = 4096; d = 64: N = 8192
-    with the causal mask, 2048 without).  Every row of the first two and of the
-    last two 256-query tiles of one (batch, head) against the oracle: under the causal mask the first
+# (causal, d, N, times four heads)
+DQ_TILES = [(True, 128, 4096, 3), (False, 128, 4096, 3), (True, 64, 8192, 3), (False, 64, 2048, 5)]
+
+
+@pytest.mark.parametrize("causal,d,N,times", DQ_TILES)
+def test_dq_of_every_row_of_the_first_and_last_query_tiles(oracle, causal, d, N, times):
+    """The dQ kernel with 64 queries per wave (four heads repeated until there are enough blocks for it).  Every row of the
+    first two and of the last two 256-query tiles of one (batch, head) against the oracle: under the causal mask the first
     tiles have the shortest rows and the largest P, so one wrong (query, key) pair of the last key block
     of a tile shows there and nowhere else (sampled rows of long sequences do not see it)."""
     import paper_2603_05451_amd as A
     w = I.Workload("dq_tiles", 1, 4, 2, N, d, d, causal, 73)
     x = I.make_inputs(w)
-    q, k, v, do = (x[n].cuda() for n in ("q", "k", "v", "do"))
+    q, k, v, do = (repeated(x[n], times) for n in ("q", "k", "v", "do"))
     o, lse = A.attn_fwd(q, k, v, w.scale, causal)
     dq, _, _ = A.attn_bwd(q, k, v, o, do, lse, w.scale, causal)
     torch.cuda.synchronize()
+    assert same_in_every_repetition(dq, w.H, 2)
     rows = np.concatenate([np.arange(0, 512), np.arange(w.N - 512, w.N)])
     f = lambda name, r=slice(None), h=3: I.to_f64(x[name][0, r, h])[None, :, None, :]
     rdq, _, _ = oracle.attn_bwd(f("q", rows), f("k", h=1), f("v", h=1), f("do", rows), w.scale, causal, q_pos=rows)

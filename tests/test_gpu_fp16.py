@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2603_05451_amd import inputs as I
-from parity import LSE_ABS, assert_close, errors
+from parity import LSE_ABS, assert_close, repeated, same_in_every_repetition
 
 pytestmark = pytest.mark.gpu
 
@@ -19,11 +19,15 @@ CASES = [
     I.Workload("h_d128_c_gqa", 2, 4, 1, 384, 128, 128, True, 63),
     I.Workload("h_d192_c", 1, 2, 2, 384, 192, 128, True, 64),
     I.Workload("h_d256_c", 1, 2, 1, 256, 256, 256, True, 67),
-    # shapes that run the one-wave-per-SIMD kernels (64 queries per wave forward and dQ, one-wave dK/dV)
-    I.Workload("h_d128_nc_2048_gqa", 1, 2, 1, 2048, 128, 128, False, 68),
-    I.Workload("h_d128_c_4096", 1, 1, 1, 4096, 128, 128, True, 69),
-    I.Workload("h_d64_nc_2048", 1, 2, 1, 2048, 64, 64, False, 71),
-    I.Workload("h_d192_nc_2048_gqa", 1, 2, 1, 2048, 192, 128, False, 72),
+]
+# (workload, times): heads repeated until the kernels with one wave per SIMD take the call -- forward and dQ with 64 queries per
+# wave (32 at (192, 128)), dK/dV with 64 keys per wave at d = 64 (the case without groups) and 32 elsewhere
+ONE_WAVE = [
+    (I.Workload("h_d128_nc_2048_gqa", 1, 2, 1, 2048, 128, 128, False, 68), 9),
+    (I.Workload("h_d128_c_4096", 1, 1, 1, 4096, 128, 128, True, 69), 9),
+    (I.Workload("h_d64_nc_2048", 1, 2, 2, 2048, 64, 64, False, 71), 9),
+    (I.Workload("h_d64_nc_2048_gqa", 1, 2, 1, 2048, 64, 64, False, 73), 9),
+    (I.Workload("h_d192_nc_2048_gqa", 1, 2, 1, 2048, 192, 128, False, 72), 9),
 ]
 
 
@@ -32,14 +36,16 @@ def half_inputs(w):
     return {n: t.float().to(torch.float16) for n, t in x.items()}
 
 
-@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
-def test_fp16_fwd_bwd_parity(oracle, w):
+@pytest.mark.parametrize("w,times", [(w, 1) for w in CASES] + ONE_WAVE, ids=lambda x: x.name if isinstance(x, I.Workload) else str(x))
+def test_fp16_fwd_bwd_parity(oracle, w, times):
     import paper_2603_05451_amd as A
     x = half_inputs(w)
-    q, k, v, do = (x[n].cuda() for n in ("q", "k", "v", "do"))
+    q, k, v, do = (repeated(x[n], times) for n in ("q", "k", "v", "do"))
     o, lse = A.attn_fwd(q, k, v, w.scale, w.causal)
     dq, dk, dv = A.attn_bwd(q, k, v, o, do, lse, w.scale, w.causal)
     torch.cuda.synchronize()
+    assert all(same_in_every_repetition(t, h, 2) for t, h in ((o, w.H), (dq, w.H), (dk, w.Hkv), (dv, w.Hkv)))
+    o, dq, dk, dv, lse = o[:, :, :w.H], dq[:, :, :w.H], dk[:, :, :w.Hkv], dv[:, :, :w.Hkv], lse[:, :w.H]
     assert o.dtype == torch.float16 and dq.dtype == torch.float16
     f = [I.to_f64(x[n]) for n in ("q", "k", "v", "do")]
     ro, rlse = oracle.attn_fwd(f[0], f[1], f[2], w.scale, w.causal)
@@ -54,12 +60,14 @@ def test_fp16_fwd_bwd_parity(oracle, w):
 
 
 def test_fp16_fwd_d64_64_queries_per_wave(oracle):
-    """d = 64, N = 8192 without a mask: the forward kernel with 64 queries per wave in its fp16 form."""
+    """d = 64, N = 8192 without a mask, three times two heads: the forward kernel with 64 queries per wave in its fp16 form."""
     import paper_2603_05451_amd as A
     w = I.Workload("h_d64_nc_8192", 1, 2, 1, 8192, 64, 64, False, 70)
     x = half_inputs(w)
-    o, lse = A.attn_fwd(x["q"].cuda(), x["k"].cuda(), x["v"].cuda(), w.scale, w.causal)
+    o, lse = A.attn_fwd(repeated(x["q"], 3), repeated(x["k"], 3), repeated(x["v"], 3), w.scale, w.causal)
     torch.cuda.synchronize()
+    assert same_in_every_repetition(o, w.H, 2)
+    o, lse = o[:, :, :w.H], lse[:, :w.H]
     ro, rlse = oracle.attn_fwd(I.to_f64(x["q"]), I.to_f64(x["k"]), I.to_f64(x["v"]), w.scale, w.causal)
     _, rf_o = assert_close(o.float().cpu().numpy(), ro, f"fp16 O {w.name}")
     assert np.abs(lse.cpu().numpy() - rlse).max() <= LSE_ABS

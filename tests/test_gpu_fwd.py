@@ -4,7 +4,8 @@ import pytest
 import torch
 
 from paper_2603_05451_amd import inputs as I
-from parity import LSE_ABS, assert_close, assert_close_terms, rounded_reference, term_magnitudes
+from parity import (LSE_ABS, assert_close, assert_close_terms, repeated, rounded_reference, same_in_every_repetition,
+                    term_magnitudes)
 
 pytestmark = pytest.mark.gpu
 
@@ -82,44 +83,57 @@ def test_fwd_full_size_sampled_rows(oracle, w):
         assert err <= LSE_ABS, f"LSE {w.name}: {err:.3e}"
 
 
-Q64 = [I.Workload("q64_nc_2048", 1, 3, 1, 2048, 128, 128, False, 31),
-       I.Workload("q64_nc_2304", 2, 2, 2, 2304, 128, 128, False, 32),
-       I.Workload("q64_d64_nc_8192", 1, 2, 1, 8192, 64, 64, False, 33),
-       I.Workload("q64_d64_c_16384", 1, 1, 1, 16384, 64, 64, True, 34),
-       I.Workload("q64_d192_nc_2304", 1, 3, 1, 2304, 192, 128, False, 35),
-       I.Workload("q64_d192_c_8192", 1, 2, 2, 8192, 192, 128, True, 36)]
+# (workload, times): the oracle computes the workload's heads, the call runs them `times` over, so that there are enough
+# blocks for the kernel with 64 queries per wave (test_dispatch_cpu.py checks that there are)
+Q64 = [(I.Workload("q64_nc_2048", 1, 3, 1, 2048, 128, 128, False, 31), 6),
+       (I.Workload("q64_nc_2304", 2, 2, 2, 2304, 128, 128, False, 32), 4),
+       (I.Workload("q64_c_4096", 1, 4, 2, 4096, 128, 128, True, 37), 3),
+       (I.Workload("q64_d64_nc_8192", 1, 2, 1, 8192, 64, 64, False, 33), 3),
+       (I.Workload("q64_d64_c_16384", 1, 1, 1, 16384, 64, 64, True, 34), 5),
+       (I.Workload("q64_d192_nc_2304", 1, 3, 1, 2304, 192, 128, False, 35), 5),
+       (I.Workload("q64_d192_c_8192", 1, 2, 2, 8192, 192, 128, True, 36), 3)]
 
 
-@pytest.mark.parametrize("w", Q64, ids=lambda w: w.name)
-def test_fwd_64_queries_per_wave_full_parity(oracle, w):
-    """Shapes that run the kernel with 64 queries per wave (N % 256 = 0; d = 128 and (192, 128) from
-    N = 2048 without a mask and N = 8192 with it, d = 64 from N = 8192 without and N = 16384 with the mask),
-    small enough for the oracle to compute every row: 8 to 64 query blocks of 256, GQA and MHA, key loops
-    of 32 to 256 tiles."""
+def repeated_fwd(q, k, v, scale, causal, times):
+    """attn_fwd of the heads `times` over; O and LSE of the first repetition, whose bits the others have to have."""
+    import paper_2603_05451_amd as A
+    o, lse = A.attn_fwd(repeated(q, times), repeated(k, times), repeated(v, times), scale, causal)
+    torch.cuda.synchronize()
+    H = q.shape[2]
+    assert same_in_every_repetition(o, H, 2) and same_in_every_repetition(lse, H, 1)
+    return o[:, :, :H].float().cpu().numpy(), lse[:, :H].cpu().numpy()
+
+
+@pytest.mark.parametrize("w,times", Q64, ids=[w.name for w, _ in Q64])
+def test_fwd_64_queries_per_wave_full_parity(oracle, w, times):
+    """Shapes that run the kernel with 64 queries per wave (one round of more than 128 blocks, more rounds at longer
+    sequences), every row against the oracle: GQA and MHA, key loops of 32 to 256 tiles."""
     x = I.make_inputs(w, with_do=False)
-    o, lse = gpu_fwd(w, x)
+    o, lse = repeated_fwd(x["q"], x["k"], x["v"], w.scale, w.causal, times)
     ro, rlse = oracle.attn_fwd(I.to_f64(x["q"]), I.to_f64(x["k"]), I.to_f64(x["v"]), w.scale, w.causal)
     assert_close(o, ro, f"O {w.name}")
     assert np.abs(lse - rlse).max() <= LSE_ABS, f"LSE {w.name}: {np.abs(lse - rlse).max():.3e}"
 
 
-@pytest.mark.parametrize("causal,N,d,dv", [(False, 2048, 128, 128), (True, 8192, 128, 128), (False, 8192, 64, 64), (True, 16384, 64, 64),
-                                           (False, 2048, 192, 128), (True, 8192, 192, 128)])
-def test_fwd_growing_scores_restart_with_exact_maxima(oracle, causal, N, d, dv):
+# (causal, N, d_qk, d_v, times two heads, element type)
+GROWING = [(False, 2048, 128, 128, 9, torch.bfloat16), (True, 8192, 128, 128, 5, torch.bfloat16), (False, 8192, 64, 64, 3, torch.bfloat16),
+           (True, 16384, 64, 64, 3, torch.bfloat16), (False, 2048, 192, 128, 9, torch.bfloat16), (True, 8192, 192, 128, 3, torch.bfloat16),
+           (False, 2048, 128, 128, 9, torch.float16), (True, 4096, 192, 128, 5, torch.float16)]
+
+
+@pytest.mark.parametrize("causal,N,d,dv,times,dtype", GROWING, ids=["%s_N%d_d%d_%s" % ("c" if c[0] else "nc", c[1], c[2], c[5]) for c in GROWING])
+def test_fwd_growing_scores_restart_with_exact_maxima(oracle, causal, N, d, dv, times, dtype):
     """Scores that grow along the key axis by hundreds of binary orders: relative to the first
     tile's maximum the exponentials overflow, so the pipelined loop of the 64-queries-per-wave
     kernel cannot produce these results; they come from its restart with a row maximum per tile
     and the thresholded rescale (paper Sec. 3.1.4).  Compared on sampled rows."""
-    import paper_2603_05451_amd as A
     g = torch.Generator("cpu").manual_seed(77)
     H = 2
-    q = torch.randn(1, N, H, d, generator=g).abs().to(torch.bfloat16)
-    k = (torch.randn(1, N, 1, d, generator=g).abs() * torch.linspace(0.2, 30.0, N).view(1, N, 1, 1)).to(torch.bfloat16)
-    v = torch.randn(1, N, 1, dv, generator=g).to(torch.bfloat16)
+    q = torch.randn(1, N, H, d, generator=g).abs().to(dtype)
+    k = (torch.randn(1, N, 1, d, generator=g).abs() * torch.linspace(0.2, 30.0, N).view(1, N, 1, 1)).to(dtype)
+    v = torch.randn(1, N, 1, dv, generator=g).to(dtype)
     scale = d ** -0.5
-    o, lse = A.attn_fwd(q.cuda(), k.cuda(), v.cuda(), scale, causal)
-    torch.cuda.synchronize()
-    o, lse = o.float().cpu().numpy(), lse.cpu().numpy()
+    o, lse = repeated_fwd(q, k, v, scale, causal, times)
     assert np.isfinite(o).all() and np.isfinite(lse).all()
     rng = np.random.default_rng(5)
     rows = np.unique(np.concatenate([[0, 1, 63, 64, 255, 256, N - 257, N - 1], rng.integers(0, N, 40)]))
@@ -129,13 +143,15 @@ def test_fwd_growing_scores_restart_with_exact_maxima(oracle, causal, N, d, dv):
     assert err <= LSE_ABS, f"LSE growing scores: {err:.3e} (values up to {np.abs(rlse).max():.0f})"
 
 
-@pytest.mark.parametrize("causal,N,d,dv", [(False, 4096, 128, 128), (True, 8192, 192, 128), (False, 8192, 64, 64)])
-def test_fwd_reference_steps_inside_the_pipelined_loop(oracle, causal, N, d, dv):
+STEPS = [(False, 4096, 128, 128, 5), (True, 8192, 192, 128, 3), (False, 8192, 64, 64, 3)]
+
+
+@pytest.mark.parametrize("causal,N,d,dv,times", STEPS)
+def test_fwd_reference_steps_inside_the_pipelined_loop(oracle, causal, N, d, dv, times):
     """Scores that climb along the key axis by about 300 binary orders in small steps: relative to the first
     tile's maximum the tile sums pass 2^90 several times without ever becoming infinite, so the kernel
     with 64 queries per wave must raise its reference inside the pipelined loop (the rescale of paper
     Sec. 3.1.4 with a power-of-two step); no second pass is involved.  Every 37th row against the oracle."""
-    import paper_2603_05451_amd as A
     g = torch.Generator("cpu").manual_seed(78)
     H = 2
     climb = torch.linspace(0.0, 300.0 / (1.4427 * d ** 0.5), N).view(1, N, 1, 1)         # score = sqrt(d) * climb
@@ -143,9 +159,7 @@ def test_fwd_reference_steps_inside_the_pipelined_loop(oracle, causal, N, d, dv)
     k = (climb + 0.1 * torch.randn(1, N, 1, d, generator=g)).to(torch.bfloat16)
     v = torch.randn(1, N, 1, dv, generator=g).to(torch.bfloat16)
     scale = d ** -0.5
-    o, lse = A.attn_fwd(q.cuda(), k.cuda(), v.cuda(), scale, causal)
-    torch.cuda.synchronize()
-    o, lse = o.float().cpu().numpy(), lse.cpu().numpy()
+    o, lse = repeated_fwd(q, k, v, scale, causal, times)
     assert np.isfinite(o).all() and np.isfinite(lse).all()
     rows = np.unique(np.concatenate([[0, 1, 255, 256, N - 257, N - 1], np.arange(5, N, 37)]))
     ro, rlse = oracle.attn_fwd(I.to_f64(q[:, rows]), I.to_f64(k), I.to_f64(v), scale, causal, q_pos=rows)

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2603_05451_amd import inputs as I
-from parity import assert_close
+from parity import assert_close, dq_bound_of_one_ds_ulp, half_ulp
 
 pytestmark = pytest.mark.gpu
 
@@ -47,20 +47,26 @@ def test_packed_backward_of_every_row(oracle, dqk, dv, causal, lens, f16):
             assert_close(got[None], ref, f"{what} sequence {b}")
 
 
-@pytest.mark.parametrize("d,causal,lens", [(128, True, [(513, 513), (1, 300), (1055, 1088), (1100, 1727)]),
-                                           (128, False, [(257, 1000), (1025, 95), (1300, 640)]),
-                                           (64, False, [(2561, 2561), (3013, 2900), (2699, 255)]),
-                                           (64, True, [(4097, 4127), (4300, 4300)])])
-def test_large_batch_matches_its_sequences_one_by_one(d, causal, lens):
+# (d, causal, (queries, keys) of the sequences, element type) at H = 16/8
+LARGE = [(128, True, [(513, 513), (1, 300), (1055, 1088), (1100, 1727), (1500, 1500), (2000, 2100)], torch.bfloat16),
+         (128, False, [(257, 1000), (1025, 95), (1300, 640)], torch.bfloat16),
+         (128, False, [(1025, 95), (257, 1000), (1300, 640)], torch.float16),
+         (64, False, [(2561, 8561), (3013, 7900), (2699, 255)], torch.bfloat16),
+         (64, False, [(2699, 255), (2561, 7900), (3013, 8561)], torch.float16),
+         (64, True, [(8193, 8193), (8400, 8465)], torch.bfloat16)]
+
+
+@pytest.mark.parametrize("d,causal,lens,dtype", LARGE, ids=["d%d_%s_%s" % (c[0], "c" if c[1] else "nc", c[3]) for c in LARGE])
+def test_large_batch_matches_its_sequences_one_by_one(d, causal, lens, dtype):
     """The 64-query dQ kernel and the 256-key dK/dV kernel of d = 64 need many blocks to be chosen: 16 heads of all
     sequences in one call, against one call per sequence, whose few blocks go to the general kernels (themselves
     compared with the oracle elsewhere).  dK and dV are the same bits; dQ differs by the rounding of dP - D, at most
-    one ulp of the result plus what one ulp (2^-8) of the row's largest dS moves: that dS is computed here, since a
+    one ulp of the result plus what one ulp of the row's largest dS moves: that dS is computed here, since a
     sequence of 95 keys has elements of several units and one of a thousand keys none above 0.5."""
     import paper_2603_05451_amd as A
     H, Hkv = 16, 8
     gen = torch.Generator(device="cuda").manual_seed(790 + d)
-    mk = lambda n, h: torch.randn(n, h, d, generator=gen, device="cuda").bfloat16()
+    mk = lambda n, h: torch.randn(n, h, d, generator=gen, device="cuda").to(dtype)
     tq, tk = (sum(x[i] for x in lens) for i in (0, 1))
     q, k, v, do = mk(tq, H), mk(tk, Hkv), mk(tk, Hkv), mk(tq, H)
     cu = [torch.tensor([0] + list(np.cumsum([x[i] for x in lens])), dtype=torch.int32, device="cuda") for i in (0, 1)]
@@ -79,15 +85,8 @@ def test_large_batch_matches_its_sequences_one_by_one(d, causal, lens):
         assert torch.equal(grads[1][b], ref[1]) and torch.equal(grads[2][b], ref[2]), (nq, nk)
         x, y = grads[0][a].float(), ref[0].float()
         for h in range(H):
-            kh = k[b, h // 2].float()
-            p = (q[a, h].float() @ kh.T * d ** -0.5 - lse[h, a, None]).exp()
-            if causal:
-                p = p.tril(nk - nq)
-            ds = p * (do[a, h].float() @ v[b, h // 2].float().T - (do[a, h].float() * o[a, h].float()).sum(1, keepdim=True))
-            # (+ 1e-5: dP and D are fp32 sums of d products up to about 20, rounded by up to 2^-23 * 20 d / 2 = 1.5e-4
-            # at the very worst and 1e-5 as seen; it shows alone in a row with one key, where dP - D = 0)
-            move = (2.0 ** -8 * ds.abs().amax(1, keepdim=True) + 1e-5) * kh.abs().max() * d ** -0.5
-            assert ((x[:, h] - y[:, h]).abs() <= 2.0 ** -7 * torch.maximum(x[:, h].abs(), y[:, h].abs()) + move).all(), (nq, nk, h)
+            move = dq_bound_of_one_ds_ulp(q[a, h], k[b, h // 2], v[b, h // 2], o[a, h], do[a, h], lse[h, a], d ** -0.5, nk - nq, causal)
+            assert ((x[:, h] - y[:, h]).abs() <= 2 * half_ulp(dtype) * torch.maximum(x[:, h].abs(), y[:, h].abs()) + move).all(), (nq, nk, h)
         assert ((x - y).norm() / y.norm()).item() < 1e-3
         sq, sk = sq + nq, sk + nk
 
