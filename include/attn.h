@@ -30,10 +30,15 @@
  *   - Return value: ATTN_OK, or a negative code.  ATTN_EINVAL, ATTN_EUNSUPPORTED and
  *     ATTN_ETOOLARGE are found before anything is enqueued: no output has been touched.
  *     ATTN_ELAUNCH (the HIP runtime refused a launch or an attribute) can come from any of the
- *     launches of a call that has several (the backward pass: dQ kernel, then dK/dV kernel; the
- *     variable-length calls: a small table kernel first): the launches before the
- *     failed one stay enqueued and write their outputs (dq, the workspace); the outputs of the
- *     failed and later launches are untouched.
+ *     launches of a call that has several (the backward pass: dQ kernel, then dK/dV, at d = 256 as a
+ *     dV and a dK kernel; the variable-length calls: a small table kernel first; a variable-length
+ *     or strided forward pass whose keys are divided: a merge kernel last, without which o and lse
+ *     are untouched): the launches before the failed one stay enqueued and write their outputs (dq,
+ *     dv, the workspace); the outputs of the failed and later launches are untouched.
+ *   - A call's results depend on its arguments alone, bit for bit from run to run.  Kernels are
+ *     chosen by all sizes, B and H among them, and differ in the order of fp32 sums (forward, dQ):
+ *     the rows of one sequence agree to rounding, not to the bit, between calls with another number
+ *     of sequences or heads beside it.
  *   - Re-entrant; no global state.  Calls on different streams may run concurrently
  *     as long as their outputs and workspaces do not overlap.
  */
@@ -76,10 +81,9 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
  * accumulated on chip over all KV tiles; it also forms D = rowsum(dO o O) and the base-2 LSE of
  * its rows and leaves them in the workspace), then the dK/dV kernel (one workgroup per KV tile,
  * dK and dV accumulated on chip over all query tiles and all query heads of the group: the loop
- * structure of paper Sec. 3.2.2).  The paper
- * accumulates dQ with global atomics inside the dK/dV loop (Sec. 3.2.2-3.2.3); on MI355X
- * those atomics are memory-side and cost more than recomputing S and dP, so dQ has its
- * own pass.  No atomics are used: results are bit-reproducible from run to run (the
+ * structure of paper Sec. 3.2.2; at d = 256 a dV and a dK kernel).  The paper accumulates dQ with
+ * global atomics inside the dK/dV loop (Sec. 3.2.2-3.2.3); on MI355X those atomics are memory-side
+ * and cost more than recomputing S and dP, so dQ has its own pass.  No atomics are used: results are bit-reproducible from run to run (the
  * property paper Sec. 3.2.4 obtains with semaphores). */
 int attn_bwd(const void* q, const void* k, const void* v, const void* o, const void* d_o,
              const float* lse, void* dq, void* dk, void* dv,
@@ -98,7 +102,8 @@ int attn_bwd_ex(const void* q, const void* k, const void* v, const void* o, cons
  * itself (the same values bit for bit as the prepare kernel) and writes them to the workspace,
  * so a call whose mask includes ATTN_BWD_DQ launches no prepare kernel: the dQ kernel runs first
  * and ATTN_BWD_DKDV, of the same or of a later call, reads what it left.  attn_bwd_ex is
- * therefore two kernels; ATTN_BWD_PREPARE has an effect only in a mask without ATTN_BWD_DQ. */
+ * therefore two kernels (three at d = 256, where ATTN_BWD_DKDV is two); ATTN_BWD_PREPARE has an
+ * effect only in a mask without ATTN_BWD_DQ. */
 enum { ATTN_BWD_PREPARE = 1, ATTN_BWD_DKDV = 2, ATTN_BWD_DQ = 4, ATTN_BWD_ALL = 7 };
 int attn_bwd_phases(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                     const float* lse, void* dq, void* dk, void* dv,
@@ -148,14 +153,16 @@ size_t attn_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d_qk, int d_v)
  *   workspace: attn_varlen_workspace_bytes(..., backward) bytes, 256-byte aligned; the forward
  *   call needs the backward = 0 size, the backward call the backward = 1 size.  Contents on entry
  *   are ignored.  (Where few queries meet many keys the forward size includes room for partial results
- *   of a pass whose keys are divided over several blocks; with less room, down to the tables alone,
- *   a call divides them less, and its results differ by the rounding of another summation order.)  All other conventions (device pointers, stream, alignment, head dims, error
- *   codes) are those of attn_fwd_ex / attn_bwd_ex.  The table kernel checks every sequence's
- *   boundaries on the device against total_q and total_k: a sequence whose rows do not lie inside
- *   the tensors (decreasing boundaries, boundaries past the totals) is left out, i.e. none of its
- *   rows is read or written, and the other sequences are served.  The remaining conditions (a key
- *   for every sequence with queries; keys >= queries under a causal mask) are not checked: rows
- *   that violate them hold unspecified values, nothing outside the tensors is touched. */
+ *   of a pass whose keys are divided over several blocks; with less room, down to the query-tile table
+ *   alone, a call divides them less, and its results differ by the rounding of another summation
+ *   order.)  All other conventions (device pointers, stream, alignment, head dims, error codes) are
+ *   those of attn_fwd_ex / attn_bwd_ex.
+ *   The table kernel checks every sequence's boundaries on the device against total_q and total_k:
+ *   a sequence whose rows do not lie inside the tensors (decreasing boundaries, boundaries past the
+ *   totals) is left out, i.e. none of its rows is read or written, and the other sequences are
+ *   served.  The remaining conditions (a key for every sequence with queries; keys >= queries under
+ *   a causal mask) are not checked: rows that violate them hold unspecified values, nothing outside
+ *   the tensors is touched. */
 size_t attn_varlen_workspace_bytes(int B, int total_q, int total_k, int H, int Hkv, int d_qk, int d_v, int backward);
 int attn_varlen_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
                     const int* cu_seqlens_q, const int* cu_seqlens_k, int B, int total_q, int total_k,
@@ -167,10 +174,12 @@ int attn_varlen_fwd(const void* q, const void* k, const void* v, void* o, float*
  * then pass cu_seqlens_q = cu_seqlens_k = NULL: it skips the plan kernel and uses the tables as
  * they are (a backward call needs tables written by this function or by an earlier backward call;
  * a forward call with non-NULL cu_seqlens writes the query table only).  Calls never modify the
- * tables otherwise; results are bit-identical to those of calls that rebuild them.  Table entries
- * carry a mark and are checked against total_q: on a workspace that was never planned the kernels
- * find nothing to act on and leave the outputs untouched (tables planned for OTHER lengths with
- * the same totals cannot be told apart: that remains the caller's responsibility). */
+ * tables otherwise (what lies behind them is scratch: calls that share a planned workspace may not
+ * overlap in time); results are bit-identical to those of calls that rebuild them in a workspace of
+ * that size.  Table entries carry a mark and are checked against total_q: on a workspace that was
+ * never planned the kernels find nothing to act on and leave the outputs untouched (tables planned
+ * for OTHER lengths with the same totals cannot be told apart: that remains the caller's
+ * responsibility). */
 int attn_varlen_plan(const int* cu_seqlens_q, const int* cu_seqlens_k, int B, int total_q, int total_k,
                      int H, int Hkv, int d_qk, int d_v, void* workspace, size_t workspace_bytes, void* stream);
 /* Backward of attn_varlen_fwd (paper Sec. 2.1 second display, per sequence): o and lse must be that
@@ -221,7 +230,8 @@ int attn_varlen_bwd_dtype(int dtype, const void* q, const void* k, const void* v
  * Nq != Nk), and Nk >= Nq is required (ATTN_EINVAL otherwise).
  * Runs the variable-length kernels as on the sequence boundaries {0, Nq, 2 Nq, ...} and
  * {0, Nk, 2 Nk, ...}, whose tiles the kernels number themselves; on contiguous [B, N, H, d] tensors with
- * Nq = Nk = N a multiple of 128 the results are bit-identical to attn_fwd_ex / attn_bwd_ex.
+ * Nq = Nk = N a multiple of 128 the results are bit-identical to attn_fwd_dtype / attn_bwd_dtype (the
+ * forward call then is that call).
  *   workspace: attn_strided_workspace_bytes(..., backward) bytes, 256-byte aligned, contents
  *   ignored on entry.  Other conventions as in attn_fwd_dtype / attn_bwd_dtype. */
 typedef struct attn_strides {

@@ -158,12 +158,14 @@ int launch_decode(const FwdArgs& a);
 int launch_combine(const FwdArgs& a);
 // The dQ kernel with 64 queries per wave (d_qk = d_v = 128 or 64; fixed length N % 256 = 0, or variable-length
 // mode with row strides of at least a row); it also leaves -D and the base-2 LSE of every row in the workspace.
+// Which calls these launchers get: dispatch.h.
 int launch_bwd_dq_q64(const BwdArgs& a);
-// The dK/dV kernel with one wave per SIMD and 32-query tiles (head dims 128, (192, 128): N % 128 = 0; 64:
-// N % 256 = 0; or variable-length mode as above; with or without the causal mask); -D and the base-2 LSE must be in the workspace.
+// The dK/dV kernel with one wave per SIMD and 32-query tiles (head dims 128, (192, 128) and 256, there as a dV and a
+// dK launch: N % 128 = 0; 64: N % 256 = 0; or variable-length mode as above; with or without the causal mask); -D and
+// the base-2 LSE must be in the workspace.
 int launch_bwd_dkdv_t32(const BwdArgs& a);
-// The dQ kernel with one wave per SIMD and 32 queries per wave (head dims (192, 128); fixed length N % 128 = 0,
-// or variable-length mode as above); it also leaves -D and the base-2 LSE of every row in the workspace.
+// The dQ kernel with one wave per SIMD and 32 queries per wave (head dims (192, 128) and 256; fixed length
+// N % 128 = 0, or variable-length mode as above); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_t32(const BwdArgs& a);
 // The same by element type (bf16 in attn::, fp16 in attn::f16k::) and mode: one translation unit each.
 int run_bwd_dq_q64(const BwdArgs& a);
