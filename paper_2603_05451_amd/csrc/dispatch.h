@@ -11,18 +11,93 @@
 
 namespace attn {
 
-// Place of a block in the work list (head by head, and within a head table entry by table entry) for kernels whose
-// blocks take two 128-row tiles and have nothing to do for every second entry of a sequence.  Blocks are dealt to the
-// 8 XCDs round robin; an XCD takes one section of the list, so that tiles of one head share its L2, and in it places
-// 0, 2, 4, ... first, then 1, 3, 5, ...: dispatched alternately, the empty blocks would all fall to the same shader
-// engines and leave the others twice the work.  The order is one of the section, not of the head: with a head's even
-// places before its odd ones, 2 or 4 heads left half of the XCDs with empty blocks alone (d = 64, 16 sequences of
-// 4096 tokens, H = 8/2, no mask, dK/dV: 731 us of a 2791 us backward pass).
+// Place of a block in the work list for kernels whose blocks take two 128-row tiles and have nothing to do for every second
+// entry of a sequence.  An XCD takes one section of the list, and in it places 0, 2, 4, ... first, then 1, 3, 5, ...:
+// dispatched alternately, the empty blocks would all fall to the same shader engines and leave the others twice the work.
+// The order is one of the section, not of the head: with a head's even places before its odd ones, 2 or 4 heads left half of
+// the XCDs with empty blocks alone (d = 64, 16 sequences of 4096 tokens, H = 8/2, no mask, dK/dV: 731 us of a 2791 us backward
+// pass).
 ATTN_ANYWHERE int section_order(int block, int total)
 {
     const bool dealt = (total & 7) == 0;
     const int n = dealt ? total >> 3 : total, p = dealt ? block >> 3 : block, half = (n + 1) >> 1;
     return (dealt ? (block & 7) * n : 0) + (p < half ? 2 * p : 2 * (p - half) + 1);
+}
+
+// ---- Order of the blocks of a launch over heads x tiles (a head's tiles listed longest first, or as a table lists them).
+// Blocks are dealt to the 8 XCDs round robin.  An XCD works on heads of its own, one after the other, so that the tiles of a
+// head share its L2.  Where the heads do not divide, 2, 4 or 8 XCDs work on a unit of heads together and take its places in
+// turn: in contiguous shares (the longer tiles of a head here, the shorter there) the first XCD ends last (packed
+// batch of 16 sequences of 64 ... 8192 tokens under the mask, H = 16/4, d = 128, four KV heads on eight XCDs: backward pass
+// 2237 us, 1917 in turn).  Every second turn is taken in reverse: the first XCD does not get the longer tile each time, nor one
+// of them all places of the parity that is empty in kernels which take two entries per block.
+// Under the causal mask the tiles of a group of heads are taken together, longest first: one head's tiles after
+// the other's end with the longest tiles of the last head beside idle CUs, and pair long with short ones on a
+// CU at random.  (Forward / dQ / dK/dV, us, head by head -> groups of 8: B = 16, H = 16, N = 1024, d = 128: 106 -> 92, 170 -> 158,
+// 211 -> 188; B = 4, H = 8, N = 2048, d = 256, a unit of 4 heads: 132 -> 97, 133 -> 110, 233 -> 183; N = 8192, d = 128, H = 16,
+// B = 2: 476 -> 457, 650 -> 632, 943 -> 927; without the mask all tiles are equal and the order stays.)
+struct TileOrder {
+    int dealt;          // whether every XCD gets an eighth of the places; otherwise they go by the block's number
+    int unit, log_m;    // `unit` heads are worked on by 2^log_m XCDs
+    int group;          // heads whose tiles are taken together
+};
+struct Place {
+    int xcd, at;        // at: in the XCD's list
+};
+struct HeadTile {
+    int head, tile;
+};
+
+inline TileOrder tile_order(int heads, int tiles)
+{
+    const int64_t total = (int64_t)heads * tiles;
+    const bool dealt = (total & 7) == 0;
+    int log_m = 0;
+    if (dealt) while (((int64_t)heads << log_m & 7) != 0) ++log_m;
+    return {dealt, dealt ? (int)(((int64_t)heads << log_m) >> 3) : heads, log_m, 1};
+}
+
+// The same under the causal mask.  `share` heads read the same rows, `bytes` of them.  Groups of about 8 heads (4 ... 16 are
+// within 3 % of each other) whose rows are no more than 16 MB: all the blocks of a group walk along them at once, and where
+// they drift apart the L2 no longer holds what they share (N = 16384, d = 128, 8 MB per head, B = 4, H = 16: dK/dV 7586, 7508,
+// 7632, 7958 us in groups of 1, 2, 4, 8).  Equal groups: a small last one ends like a single head (12 heads, N = 1024,
+// d = 256, forward: 102 us one by one, 88 as 8 + 4, 80 as 12).
+inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
+{
+    TileOrder o = tile_order(heads, tiles);
+    const int64_t fit = (16 << 20) / (bytes < 1 ? 1 : bytes), most = (fit < 1 ? 1 : fit) * share;
+    const int want = (int)(most < 8 ? most : 8), n = o.unit / want < 1 ? 1 : o.unit / want;
+    o.group = (o.unit + n - 1) / n;
+    return o;
+}
+
+// Place of a block; for kernels with nothing to do at every second place, in the order of section_order.
+ATTN_ANYWHERE Place block_place(const TileOrder& o, int block)
+{
+    return o.dealt ? Place{block & 7, block >> 3} : Place{0, block};
+}
+ATTN_ANYWHERE Place block_place_alternate(const TileOrder& o, int block, int total)
+{
+    return o.dealt ? Place{block & 7, section_order(block, total) - (block & 7) * (total >> 3)} : Place{0, section_order(block, total)};
+}
+
+// (head, tile) of a place.  Branches instead of divisions by 1: an integer division is 0.1 us of a block's start.
+ATTN_ANYWHERE HeadTile head_tile(const TileOrder& o, Place place, int tiles)
+{
+    const int m = 1 << o.log_m, turn = place.xcd & (m - 1), p = place.at * m + ((place.at & 1) ? m - 1 - turn : turn);
+    const int base = (place.xcd >> o.log_m) * o.unit;
+    if (o.group == 1) {
+        const int head = p / tiles;
+        return {base + head, p - head * tiles};
+    }
+    int first = 0, r = p;
+    if (o.group < o.unit) {
+        const int whole = o.group * tiles, g = p / whole;
+        first = g * o.group;
+        r = p - g * whole;
+    }
+    const int width = o.unit - first < o.group ? o.unit - first : o.group, tile = r / width;
+    return {base + first + (r - tile * width), tile};
 }
 
 // ---- Fixed-length calls: the kernels with one wave per SIMD (blocks of 256 rows, one per CU) or the 4-wave ones (128

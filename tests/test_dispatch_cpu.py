@@ -14,6 +14,13 @@ SHIM = r"""
 using namespace attn;
 extern "C" {
 int t_section_order(int block, int total) { return section_order(block, total); }
+int t_order(int block, int heads, int tiles, int share, long long bytes, int causal, int half_empty)
+{
+    const TileOrder o = causal ? causal_order(heads, tiles, share, bytes) : tile_order(heads, tiles);
+    const int total = heads * tiles;
+    const HeadTile t = head_tile(o, half_empty ? block_place_alternate(o, block, total) : block_place(o, block), tiles);
+    return t.head * tiles + t.tile;
+}
 int t_fwd(int d, int causal, int N, long long b) { return fwd_one_wave(d, causal, N, b); }
 int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, N, b); }
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
@@ -44,6 +51,7 @@ def D(tmp_path_factory):
                     "-o", str(d / "shim.so")], check=True)
     L = ctypes.CDLL(str(d / "shim.so"))
     q = ctypes.c_longlong
+    L.t_order.argtypes = [ctypes.c_int] * 4 + [q] + [ctypes.c_int] * 2
     for f in (L.t_fwd, L.t_dq, L.t_dkdv64):
         f.argtypes = [ctypes.c_int] * 3 + [q]
     L.t_dq_varlen.argtypes = [ctypes.c_int] * 2 + [q] * 3
@@ -72,6 +80,33 @@ def test_places_of_blocks_that_take_two_tiles(D, heads, lens):
         assert took[xcd::8].sum() == want
         used = (mine % max_tiles < len(tiles)).sum()            # half of a section's used entries, and one per sequence
         assert used / 2 - 1 <= want <= used / 2 + len(lens) * (1 + heads // 8)
+
+
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 5, 8, 12, 16, 20, 96, 136, 248])
+@pytest.mark.parametrize("tiles", [1, 2, 3, 8, 16, 31, 64])
+@pytest.mark.parametrize("half_empty", [0, 1])
+def test_order_of_blocks(D, heads, tiles, half_empty):
+    """Every (head, tile) once, whatever the heads, tiles and group; without the mask an XCD with heads of its own takes them one
+    after the other; under it no XCD gets much more work than another, and its blocks go from long to short within a group."""
+    total = heads * tiles
+    for causal, share, nbytes in ((0, 1, 1), (1, 1, 1), (1, 1, 5 << 20), (1, 4, 5 << 20), (1, 1, 1 << 40)):
+        at = np.array([D.t_order(b, heads, tiles, share, nbytes, causal, half_empty) for b in range(total)])
+        assert sorted(at) == list(range(total)), (causal, share, nbytes)
+        if total % 8 or half_empty:
+            continue
+        for xcd in range(8):
+            mine = at[xcd::8]
+            if not causal and heads % 8 == 0:
+                assert (mine == np.arange(xcd * total // 8, (xcd + 1) * total // 8)).all()
+            if causal:
+                work = tiles - mine % tiles                         # tile 0 has the longest loop
+                assert abs(work.sum() - heads * tiles * (tiles + 1) / 16) <= tiles * max(1, heads // 8) / 2
+                falls = (np.diff(mine % tiles) < 0).sum() + 1       # a new group starts
+                unit = max(1, heads // 8) if heads % 8 == 0 else 0
+                if unit and nbytes == 1:
+                    assert falls == max(1, unit // 8) or tiles == 1
+                if unit and nbytes == 1 << 40:
+                    assert falls == unit or tiles == 1
 
 
 # measured times of the kernels with one wave per SIMD over those of the 4-wave kernels: (pass, d, causal, N, 256-row blocks,

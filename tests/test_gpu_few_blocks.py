@@ -60,3 +60,31 @@ def test_backward(oracle, causal, N, H, d):
     for what, a, r in zip(("dQ", "dK", "dV"), got, ref):
         assert all(torch.equal(a[:, :, h], a[:, :, h % 2]) for h in range(H)), what
         assert_close(a[:, :, :2].float().cpu().numpy(), r, what)
+
+
+# heads that do not divide among the 8 XCDs (units of 2, 4 and 8 XCDs, and totals that are not dealt at all), groups of
+# unequal width, one tile per head: the order of the blocks decides which work is done, not what it gives
+@pytest.mark.parametrize("B,H,Hkv,N,d,dv", [(1, 12, 4, 512, 128, 128), (1, 2, 1, 1024, 64, 64), (1, 1, 1, 384, 128, 128), (3, 5, 5, 384, 96, 96),
+                                            (9, 16, 8, 256, 64, 64), (1, 20, 20, 128, 256, 256), (1, 6, 3, 1024, 192, 128)])
+@pytest.mark.parametrize("layout", ["fixed", "views", "packed"])
+def test_orders_of_blocks_under_the_mask(oracle, B, H, Hkv, N, d, dv, layout):
+    import paper_2603_05451_amd as A
+    x = I.make_inputs(I.Workload("order", B, H, Hkv, N, d, dv, True, 340 + B + H))
+    q, k, v, do = (x[n].cuda() for n in ("q", "k", "v", "do"))
+    if layout == "fixed":
+        o, lse = A.attn_fwd(q, k, v, d ** -0.5, True)
+        got = (o,) + tuple(A.attn_bwd(q, k, v, o, do, lse, d ** -0.5, True))
+    elif layout == "views":
+        q, k, v, do = (t.transpose(1, 2).contiguous().transpose(1, 2) for t in (q, k, v, do))
+        o, lse = A.attn_fwd_strided(q, k, v, d ** -0.5, True)
+        got = (o,) + tuple(A.attn_bwd_strided(q, k, v, o, do, lse, d ** -0.5, True))
+    else:
+        cu = torch.arange(B + 1, dtype=torch.int32, device="cuda") * N
+        flat = [t.flatten(0, 1) for t in (q, k, v, do)]
+        o, lse = A.attn_varlen_fwd(*flat[:3], cu, d ** -0.5, True)
+        got = (o,) + tuple(A.attn_varlen_bwd(*flat[:3], o, flat[3], lse, cu, d ** -0.5, True))
+    torch.cuda.synchronize()
+    f64 = [I.to_f64(x[n]) for n in ("q", "k", "v", "do")]
+    ref = (oracle.attn_fwd(*f64[:3], d ** -0.5, True)[0],) + tuple(oracle.attn_bwd(*f64, d ** -0.5, True))
+    for what, a, r in zip(("O", "dQ", "dK", "dV"), got, ref):
+        assert_close(a.float().cpu().numpy().reshape(r.shape), r, what)
