@@ -111,6 +111,7 @@ ATTN_ANYWHERE HeadTile head_tile(const TileOrder& o, Place place, int tiles)
 // Under the mask a round's length is that of its unluckiest CU.  A CU's two small blocks are 32 places apart in an XCD's
 // list: where 32 is a multiple of a head's tiles (N = 1024, 2048, 4096) those are two tiles of the same length, and the
 // CU with the two longest ends last (b = 160, d = 128, forward, N = 2048 ... 8192: 0.94, 1.10 at 3072, 0.89, 0.97, 1.01).
+// (Ratios under the mask beyond one round are of launches that take groups of heads together, longest tiles first.)
 inline bool equal_pairs(int N) { return 32 % (N / 128) == 0; }
 
 inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
@@ -123,8 +124,9 @@ inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
     }
     if (d_qk == 64)         // (N = 8192, b = 288 ... 384: 0.88, 0.92, 1.03, 0.89; N = 12288 there 1.05 ... 1.10)
         return !one_round && (N >= 16384 || (b <= 384 && N >= 8192 && N < 12288));
-    if (one_round) return (equal_pairs(N) && N >= 2048) || (d_qk == 192 && N >= 8192);     // (d = 192, N = 8192: 0.91)
-    return N >= (d_qk == 192 ? 6144 : 8192);        // (N = 4096, b = 288 ... 512: 1.02 ... 1.13, at 192 0.98 ... 1.08)
+    // (d = 192: N = 2048, b = 128 ... 256 1.23 ... 1.15, N = 4096 1.06 ... 0.97, N = 8192 1.00 ... 0.91)
+    if (one_round) return d_qk == 192 ? N == 4096 || N >= 8192 : equal_pairs(N) && N >= 2048;
+    return N >= 6144;           // (b = 384 ... 1152: N = 4096 0.91 ... 1.02, N = 6144 0.96 ... 0.99, at 192 0.97; N = 3072 0.95 ... 1.07)
 }
 
 // dQ with 64 queries per wave (d_qk = d_v = 128 or 64).
@@ -132,8 +134,9 @@ inline bool dq_one_wave(int d_qk, bool causal, int N, long long b)
 {
     if (N % 256 != 0 || N < 1024 || b <= 128) return false;
     const bool one_round = b <= 256;
-    // (causal, b = 264 ... 512: N = 1024 1.33 ... 0.96, N = 2048 1.24 ... 0.96, N = 1280 and 1536 1.03 ... 0.91)
-    if (d_qk == 128) return one_round || !causal || N >= 3072 || !equal_pairs(N);
+    // (causal, N = 1024 and 2048: b = 288 1.33, 1.23; b = 384 0.96, 0.92; b = 512 ... 2048 0.90 ... 0.98; N = 1280 and 1536
+    // 1.03 ... 0.91)
+    if (d_qk == 128) return one_round || !causal || N >= 3072 || !equal_pairs(N) || b > 320;
     if (!causal) return one_round || N >= 2048;
     return one_round ? equal_pairs(N) && N >= 2048 : N >= 8192;            // (N = 1024, b = 264 ... 480: 1.12 ... 1.62)
 }
