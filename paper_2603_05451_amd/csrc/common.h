@@ -227,6 +227,9 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
+// All but the newest N vector memory operations of the wave have ended (they end in the order of their issue).
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 __device__ __forceinline__ void wait_async_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Make the compiler treat a register value as produced here: any wait for the load that fed

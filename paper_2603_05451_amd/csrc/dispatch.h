@@ -71,6 +71,17 @@ inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
     return o;
 }
 
+// Whether the dK/dV kernel of one block per CU gets 256 blocks that take an XCD's places in turns (32 apart, every second
+// turn in reverse) instead of one block per place.  A block then brings in its next tile under the end of the one before
+// (N = 128 ... 1024, 65 536 x 16 rows, d = 128, no mask: 4 ... 10 % of the backward pass, N = 8192 0.5 %), but nobody evens
+// out what the turns leave uneven: under the mask only where they are whole pairs of rounds of short sequences (N = 512
+// -8 %, 1024 and 2048 -2 %, 4096 -1, 8192 0; 12 heads of N = 2176 +16 %, 7 x 12 of 1152 +2).
+inline bool takes_turns(const TileOrder& o, int tiles, int64_t items, bool causal)
+{
+    if (items <= 256) return false;
+    return !causal || (o.dealt && o.log_m == 0 && items % 512 == 0 && tiles <= 16);
+}
+
 // Place of a block; for kernels with nothing to do at every second place, in the order of section_order.
 ATTN_ANYWHERE Place block_place(const TileOrder& o, int block)
 {

@@ -21,6 +21,10 @@ int t_order(int block, int heads, int tiles, int share, long long bytes, int cau
     const HeadTile t = head_tile(o, half_empty ? block_place_alternate(o, block, total) : block_place(o, block), tiles);
     return t.head * tiles + t.tile;
 }
+int t_turns(int heads, int tiles, int causal)
+{
+    return takes_turns(causal ? causal_order(heads, tiles, 1, 1) : tile_order(heads, tiles), tiles, (long long)heads * tiles, causal);
+}
 int t_fwd(int d, int causal, int N, long long b) { return fwd_one_wave(d, causal, N, b); }
 int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, N, b); }
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
@@ -107,6 +111,15 @@ def test_order_of_blocks(D, heads, tiles, half_empty):
                     assert falls == max(1, unit // 8) or tiles == 1
                 if unit and nbytes == 1 << 40:
                     assert falls == unit or tiles == 1
+
+
+def test_turns(D):
+    """Two turns and more; under the mask whole pairs of them, of heads that an XCD has to itself."""
+    import test_gpu_few_blocks as S
+    for causal, N, Hkv, _ in S.TURNS:
+        assert D.t_turns(Hkv, N // 128, causal), (causal, N, Hkv)
+    assert not D.t_turns(256, 1, 0) and not D.t_turns(4, 64, 1) and not D.t_turns(36, 17, 1) and not D.t_turns(84, 9, 1)
+    assert not D.t_turns(32, 64, 1) and D.t_turns(32, 64, 0)
 
 
 # measured times of the kernels with one wave per SIMD over those of the 4-wave kernels: (pass, d, causal, N, 256-row blocks,

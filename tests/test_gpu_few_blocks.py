@@ -88,3 +88,26 @@ def test_orders_of_blocks_under_the_mask(oracle, B, H, Hkv, N, d, dv, layout):
     ref = (oracle.attn_fwd(*f64[:3], d ** -0.5, True)[0],) + tuple(oracle.attn_bwd(*f64, d ** -0.5, True))
     for what, a, r in zip(("O", "dQ", "dK", "dV"), got, ref):
         assert_close(a.float().cpu().numpy().reshape(r.shape), r, what)
+
+
+# blocks that take several key tiles in turns: 257 ... 1536 tiles, totals that are not dealt to the XCDs, a last turn with one
+# tile, one query tile group per key tile, pairs of turns under the mask; two query heads per KV head
+TURNS = [(False, 128, 258, 1), (False, 128, 264, 2), (False, 384, 86, 1), (False, 256, 260, 1), (True, 128, 512, 1), (True, 256, 256, 2),
+         (True, 384, 512, 1)]
+
+
+@pytest.mark.parametrize("causal,N,Hkv,G", TURNS)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_key_tiles_in_turns(oracle, causal, N, Hkv, G, dtype):
+    import paper_2603_05451_amd as A
+    x = I.make_inputs(I.Workload("turns", 1, 2 * G, 2, N, 128, 128, causal, 360 + N + Hkv))
+    q, do = (x[n].to(dtype).repeat(1, 1, Hkv // 2, 1).cuda() for n in ("q", "do"))
+    k, v = (x[n].to(dtype).repeat(1, 1, Hkv // 2, 1).cuda() for n in ("k", "v"))
+    o, lse = A.attn_fwd(q, k, v, 128 ** -0.5, causal)
+    got = A.attn_bwd(q, k, v, o, do, lse, 128 ** -0.5, causal)
+    torch.cuda.synchronize()
+    ref = oracle.attn_bwd(*(I.to_f64(x[n].to(dtype)) for n in ("q", "k", "v", "do")), 128 ** -0.5, causal)
+    for what, a, r, n in zip(("dQ", "dK", "dV"), got, ref, (2 * G, 2, 2)):
+        first = a[:, :, :n]
+        assert torch.equal(a, first.repeat(1, 1, Hkv // 2, 1)), what
+        assert_close(first.float().cpu().numpy(), r, what)
