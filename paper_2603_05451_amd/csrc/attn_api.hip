@@ -262,6 +262,7 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     a.plan = ws + w.plan_q_off;
     a.T = Tq;
     a.max_tiles = st.nq > 0 ? B * ((st.nq + 127) / 128) : w.max_tiles_q;
+    a.Tk = Tk;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
     const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);

@@ -17,11 +17,16 @@ namespace attn {
 // The order is one of the section, not of the head: with a head's even places before its odd ones, 2 or 4 heads left half of
 // the XCDs with empty blocks alone (d = 64, 16 sequences of 4096 tokens, H = 8/2, no mask, dK/dV: 731 us of a 2791 us backward
 // pass).
+ATTN_ANYWHERE int even_before_odd(int p, int n)
+{
+    const int half = (n + 1) >> 1;
+    return p < half ? 2 * p : 2 * (p - half) + 1;
+}
 ATTN_ANYWHERE int section_order(int block, int total)
 {
     const bool dealt = (total & 7) == 0;
-    const int n = dealt ? total >> 3 : total, p = dealt ? block >> 3 : block, half = (n + 1) >> 1;
-    return (dealt ? (block & 7) * n : 0) + (p < half ? 2 * p : 2 * (p - half) + 1);
+    const int n = dealt ? total >> 3 : total;
+    return (dealt ? (block & 7) * n : 0) + even_before_odd(dealt ? block >> 3 : block, n);
 }
 
 // ---- Order of the blocks of a launch over heads x tiles (a head's tiles listed longest first, or as a table lists them).
@@ -170,6 +175,25 @@ inline bool dkdv256_one_wave(int N, long long heads) { return !(N == 128 && head
 // ---- Variable-length calls, by the mean numbers of queries n and keys k per sequence (the host never sees the lengths).
 // Shares are of the whole backward pass, kernel of the rule against the general one, over equal lengths of 8 ... 8192 and
 // mixed ones, 4096 ... 65 536 tokens, H = 4/4 ... 16/16.
+
+// Forward with 64 queries per wave (256-row blocks, one per CU) against the 128-row kernel (two per CU), for calls that do not
+// take the decode kernel; nsplit = parts of the keys.  What decides is the length of a query's loop in a part, `loop`, beside
+// the longer prologue and first two masked tiles of a lone block (us, 128-row -> this):
+//   no mask  1000 keys 229 -> 229 ... 235, 1500 308 -> 293, 2000 397 -> 367, 6000 1081 -> 937 (d = 128; (192, 128) the same)
+//   mask     self-attention of n: 1500 186 -> 212, 3000 316 -> 326, 4000 267 -> 260, 6000 557 -> 534; mixed 64 ... 8192 (1160 on
+//            average) 612 -> 655; in one round of blocks the longest ends last (n = 4096, 256 blocks 83 -> 92)
+//   chunk    512 queries x 32 heads against 8192 in 4 parts 79 -> 74, 16 384 140 -> 125, 32 768 270 -> 231; x 16 heads against 8192 in
+//            8 parts of 1000 52 -> 53; 2 x 1024 x 16 against 3000 in 2 parts 58 -> 61
+// and how the rows fill the blocks: 384 queries x 32 heads are 480 blocks of 128 rows, one round, but 320 of 256 in two: 112 -> 162.
+inline bool fwd_one_wave_varlen(int d_qk, bool causal, int64_t B, int64_t Tq, int64_t Tk, int64_t H, int nsplit, bool uniform)
+{
+    if (d_qk != 128 && d_qk != 192) return false;
+    const int64_t n = Tq / B, k = Tk / B, loop = (causal ? k - n / 2 : k) / nsplit;
+    const int64_t large = (uniform ? B * ((n + 255) / 256) : (Tq + 255) / 256) * H * nsplit;
+    const int64_t small = (uniform ? B * ((n + 127) / 128) : (Tq + 127) / 128) * H * nsplit;
+    if (loop < (causal ? 1750 : 1200) || large <= (causal && k < 2 * n ? 256 : 128)) return false;
+    return (large + 255) / 256 <= (small + 511) / 512;
+}
 
 // dQ with one wave per SIMD; half = 256-row blocks of queries x heads.
 //   d = 128  64 queries per wave: half as many blocks as the 4-wave kernel, each with a CU to itself as there; with r rounds

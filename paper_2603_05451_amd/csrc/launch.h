@@ -108,10 +108,10 @@ struct FwdArgs {
     float scale;
     int causal;
     void* stream;
-    // variable-length mode (max_tiles > 0): B and N unused; plan = table of query tiles (unread if st.nq > 0),
-    // max_tiles its size (an upper bound on the number of 128-row query tiles), T = total query rows
+    // variable-length mode (max_tiles > 0): N unused; plan = table of query tiles (unread if st.nq > 0), max_tiles its size
+    // (an upper bound on the number of 128-row query tiles), T and Tk = total query and key rows
     const void* plan = nullptr;
-    int T = 0, max_tiles = 0;
+    int T = 0, max_tiles = 0, Tk = 0;
     VarlenStrides st = {};   // variable-length mode: q, k, v, o and lse strides
     bool f16 = false;   // 16-bit storage type of q, k, v, o: bf16 (default) or IEEE fp16
     // variable-length mode: keys of a sequence divided over nsplit blocks whose unnormalised results go to
@@ -198,7 +198,8 @@ inline TileOrder key_order(const BwdArgs& a, int rows)
 // 0 on success, -2 unsupported head dims, -3 launch failure.
 int launch_fwd(const FwdArgs& a);
 int launch_bwd(const BwdArgs& a);
-// The 64-queries-per-wave forward kernel (head dims 128, 64 or (192, 128); fixed length, N % 256 = 0).
+// The 64-queries-per-wave forward kernel (head dims 128, 64 or (192, 128), fixed length, N % 256 = 0; or 128 or (192, 128) in
+// variable-length mode with row strides of at least a row).
 int launch_fwd_q64(const FwdArgs& a);
 // The decode kernel (variable-length mode, every head dim): few queries per sequence; and the merge of the
 // partial results of a pass with nsplit > 1.

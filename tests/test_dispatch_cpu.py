@@ -21,6 +21,11 @@ int t_order(int block, int heads, int tiles, int share, long long bytes, int cau
     const HeadTile t = head_tile(o, half_empty ? block_place_alternate(o, block, total) : block_place(o, block), tiles);
     return t.head * tiles + t.tile;
 }
+int t_fwd_varlen(int d, int causal, int B, int Tq, int Tk, int H, int Hkv, int uniform)
+{
+    const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d, 128, uniform);
+    return !r.decode && fwd_one_wave_varlen(d, causal, B, Tq, Tk, H, r.nsplit, uniform);
+}
 int t_turns(int heads, int tiles, int causal)
 {
     return takes_turns(causal ? causal_order(heads, tiles, 1, 1) : tile_order(heads, tiles), tiles, (long long)heads * tiles, causal);
@@ -171,6 +176,36 @@ def test_varlen_rules_take_the_faster_kernel(D, d, causal, n, k, H, Hkv, tokens,
         assert bool(D.t_dq_varlen(d, causal, n, k, half)) == (dq < 0)
     if dkdv is not None:
         assert bool(D.t_dkdv_varlen(d, causal, n, k, H // Hkv, blocks64)) == (dkdv < 0)
+
+
+# forward, variable lengths: (d, causal, B, queries, keys, H, Hkv, equal lengths, 64-queries-per-wave kernel over 128-row kernel)
+MEASURED_FWD_VARLEN = [
+    (128, 0, 24, 1000, 1000, 16, 16, 1, 1.0), (128, 0, 16, 1500, 1500, 16, 16, 1, 0.95), (192, 0, 16, 1500, 1500, 16, 16, 0, 0.98),
+    (192, 0, 24, 1000, 1000, 16, 16, 0, 1.05), (128, 0, 64, 692, 692, 16, 16, 0, 1.10), (128, 1, 8, 3000, 3000, 16, 16, 1, 1.03),
+    (128, 1, 4, 4000, 4000, 16, 16, 1, 0.97), (192, 1, 4, 6000, 6000, 16, 16, 1, 0.93), (192, 1, 8, 3000, 3000, 16, 16, 0, 1.03),
+    (128, 1, 32, 1160, 1160, 16, 16, 0, 1.07), (128, 1, 1, 4096, 4096, 16, 16, 1, 1.10), (128, 1, 1, 512, 8192, 32, 8, 1, 0.93),
+    (128, 1, 1, 512, 32768, 32, 8, 1, 0.86), (192, 1, 2, 512, 8192, 32, 8, 1, 0.87), (128, 1, 1, 512, 8192, 16, 16, 1, 1.02),
+    (128, 1, 2, 1024, 3000, 16, 16, 1, 1.05), (128, 0, 2, 1024, 3000, 16, 16, 1, 0.96), (128, 1, 1, 384, 16384, 32, 8, 1, 1.44),
+    (192, 1, 1, 640, 16384, 32, 8, 1, 1.40), (192, 1, 2, 300, 6000, 16, 8, 1, 1.52), (192, 1, 4, 300, 8192, 32, 8, 1, 0.90),
+    (128, 1, 1, 500, 2000, 64, 64, 1, 1.25), (128, 1, 2, 500, 2000, 64, 64, 1, 0.94), (128, 1, 1, 512, 8192, 32, 8, 0, 0.93)]
+
+
+@pytest.mark.parametrize("d,causal,B,nq,nk,H,Hkv,equal,ratio", MEASURED_FWD_VARLEN)
+def test_varlen_forward_rule_takes_the_faster_kernel(D, d, causal, B, nq, nk, H, Hkv, equal, ratio):
+    assert abs(ratio - 1) < 0.01 or bool(D.t_fwd_varlen(d, causal, B, B * nq, B * nk, H, Hkv, equal)) == (ratio < 1)
+
+
+def test_gpu_tests_of_the_varlen_forward_kernel_reach_it(D):
+    import test_gpu_fwd_varlen_one_wave as W
+    parts = set()
+    for d, causal, B, nq, nk, H in W.EQUAL:
+        assert D.t_fwd_varlen(d, causal, B, B * nq, B * nk, H, H, 1), (d, nq, nk)
+        parts.add(route(D, B, B * nq, B * nk, H, H, d, 128, 1)[1])
+    for d, causal, lens, H in W.PACKED:
+        Tq, Tk = (sum(x[i] for x in lens) for i in (0, 1))
+        assert D.t_fwd_varlen(d, causal, len(lens), Tq, Tk, H, H, 0), lens
+        parts.add(route(D, len(lens), Tq, Tk, H, H, d, 128, 0)[1])
+    assert 1 in parts and len(parts) > 1
 
 
 def route(D, B, Tq, Tk, H, Hkv, dqk, dv, uniform):
