@@ -256,7 +256,9 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
 {
     const bool uniform = st.nq > 0;
     const VarlenLayout w = varlen_layout(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);
-    if (cu_q && attn::launch_varlen_plan(cu_q, cu_k, B, Tq, Tk, ws + w.plan_q_off, w.max_tiles_q, nullptr, 0, stream) != 0)
+    const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);
+    const bool few = cu_q && r.decode && B <= 64;          // the decode kernel makes the table itself
+    if (cu_q && !few && attn::launch_varlen_plan(cu_q, cu_k, B, Tq, Tk, ws + w.plan_q_off, w.max_tiles_q, nullptr, 0, stream) != 0)
         return ATTN_ELAUNCH;                               // (equal lengths: no boundaries, no table)
     attn::FwdArgs a{q, k, v, o, lse, B, H, Hkv, 0, d_qk, d_v, scale, causal != 0, stream};
     a.plan = ws + w.plan_q_off;
@@ -265,7 +267,7 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     a.Tk = Tk;
     a.st = st;
     a.f16 = dtype == ATTN_F16;
-    const attn::FwdRoute r = attn::fwd_route(B, Tq, Tk, H, Hkv, d_qk, d_v, uniform);
+    if (few) { a.cu_q = cu_q; a.cu_k = cu_k; }
     a.nsub = r.nsub;
     a.nsplit = r.nsplit;
     while (a.nsplit > 1 && w.part_off + partial_bytes(a.nsplit, Tq, H, d_v) > ws_bytes) --a.nsplit;

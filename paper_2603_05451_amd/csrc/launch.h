@@ -100,6 +100,62 @@ __device__ __forceinline__ bool row_share(const int4* __restrict__ plan, int e, 
     return til.y == kPlanUsed && seq.x >= 0 && seq.y >= 0 && seq.x + seq.y <= T;
 }
 
+// The same for a packed batch of at most 64 sequences with no more queries than sequences, without a table: every wave finds
+// entry e from the boundaries, a sequence per lane.  All tiles are first ones (a sequence has at most 64 queries).  The entries
+// are those that varlen_plan_kernel makes of such a batch, sequences with the most keys first (ties by index), and are
+// returned as the table holds them (rows, tile).  A table kernel before a decode step of 48 sequences is 5 us and a launch.
+__device__ __forceinline__ bool row_share_of_few(const int* __restrict__ cu_q, const int* __restrict__ cu_k, int B, int Tq, int Tk,
+                                                 int e, int max_tiles, int i, int n, int4& seq, int4& til, int& unit, int& step,
+                                                 int4& rows, int4& tile)
+{
+    constexpr int one_turn = 1 << 24;
+    const int l = threadIdx.x & 63, b = min(l, B - 1);
+    const int qs = cu_q[b], ql = cu_q[b + 1] - qs, ks = cu_k[b], kl = cu_k[b + 1] - ks;
+    const bool inside = l < B && qs >= 0 && ql > 0 && qs <= Tq - ql && ks >= 0 && kl > 0 && ks <= Tk - kl;
+    const int key = inside ? kl : 0, more = inside ? ql - 1 : 0;        // keys; queries beside the first
+    const uint64_t used = __ballot(inside), chunks = __ballot(more > 0);
+    // (boundaries that overlap may list more queries than there is room for)
+    auto helps = [&](int before) { return more > 0 && __popcll(used) + before + more <= max_tiles; };
+    const int total = __popcll(used), h = e - total;
+    uint64_t mine = 0;
+    int before = 0;
+    auto below = [&](uint64_t lanes) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0)); };
+    if (h < 0) {
+        // the (e + 1)-th most keys, bit by bit (ranks of all lanes, one lane after the other: 3 us more per step of 48)
+        int t = 0;
+        for (int bit = 31 - __builtin_clz(Tk); bit >= 0; --bit)
+            if (__popcll(__ballot(key >= (t | 1 << bit))) > e) t |= 1 << bit;
+        const uint64_t equal = __ballot(key == t);
+        const int place = e - __popcll(__ballot(key > t));              // among those of as many keys
+        mine = __ballot(key == t && below(equal) == place);
+    } else if (chunks) {
+        for (uint64_t left = chunks; left; left &= left - 1) {
+            const int m = __builtin_ctzll(left), mm = __builtin_amdgcn_readlane(more, m);
+            before += m < l ? mm : 0;
+        }
+        mine = __ballot(helps(before) && before <= h && h < before + more);
+    }
+    rows = tile = make_int4(0, 0, 0, 0);
+    if (!mine) return false;
+    const int s = __builtin_ctzll(mine);
+    auto of = [&](int x) { return __builtin_amdgcn_readlane(x, s); };
+    seq = make_int4(of(qs), of(ql), of(ks), of(kl));
+    if (h < 0 && of(more) > 0)
+        for (uint64_t left = chunks & ((1ull << s) - 1); left; left &= left - 1) before += __builtin_amdgcn_readlane(more, __builtin_ctzll(left));
+    til = make_int4(0, kPlanUsed, s, of(helps(before)));
+    unit = i;
+    step = til.w != 0 ? one_turn : n;
+    rows = seq;
+    tile = til;
+    if (h >= 0) {
+        const int query = h - of(before) + 1;
+        rows = make_int4(__popcll(__ballot(key > seq.w)) + __popcll(__ballot(key == seq.w) & ((1ull << s) - 1)), query, 0, 0);
+        tile = make_int4(0, kPlanHelp, 0, 0);
+        unit += query * n;
+    }
+    return true;
+}
+
 struct FwdArgs {
     const void *q, *k, *v;
     void* o;
@@ -120,6 +176,7 @@ struct FwdArgs {
     float *part_o = nullptr, *part_ml = nullptr;
     int nsub = 1;       // decode kernel: blocks per table entry that share the 32-row groups of a tile (row_share)
     int nshare = 1;     // merge kernel: blocks per table entry that share the rows of a tile
+    const int *cu_q = nullptr, *cu_k = nullptr;     // decode kernel: boundaries to make the table of (row_share_of_few)
 };
 
 struct BwdArgs {

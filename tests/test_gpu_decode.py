@@ -186,3 +186,41 @@ def test_decode_replays_in_a_graph_and_skips_what_is_not_planned():
                       workspace=torch.zeros(n, dtype=torch.uint8, device="cuda"))
     torch.cuda.synchronize()
     assert (o == 7.0).all() and (lse2 == 7.0).all()
+
+
+# (queries, keys) of at most 64 slots, no more queries than slots: a batch of one, a full wave with equal and unequal keys, empty slots and
+# slots without keys, chunks among them, one chunk of all queries, every slot empty but one
+FEW = [[(1, 700)], [(1, 100 + 37 * (i % 9)) for i in range(64)], [(1, 1 + 61 * i) for i in range(33)],
+       [(0, 40), (3, 500), (1, 0), (0, 0), (2, 129), (1, 4000), (0, 7), (1, 1), (0, 0)], [(0, 5)] * 31 + [(33, 900)] + [(0, 0)] * 3, [(0, 0)] * 20 + [(1, 77)]]
+
+
+@pytest.mark.parametrize("lens", FEW, ids=[str(len(x)) + "_" + str(sum(n[0] for n in x)) for x in FEW])
+@pytest.mark.parametrize("H,Hkv,d", [(8, 2, 128), (4, 4, 64)])
+def test_table_of_a_few_sequences(lens, H, Hkv, d):
+    """A step of at most 64 sequences finds its table entries in the decode kernel: the bits of a call on the table kernel's
+    tables, the same entries left in the workspace (in another order among sequences of one loop length), and those good for a
+    call without boundaries."""
+    import paper_2603_05451_amd as A
+    from test_gpu_varlen import read_tables
+    B = len(lens)
+    cu = [torch.tensor(np.concatenate([[0], np.cumsum([n[i] for n in lens])]), dtype=torch.int32, device="cuda") for i in (0, 1)]
+    Tq, Tk = int(cu[0][-1]), int(cu[1][-1])
+    g = torch.Generator(device="cuda").manual_seed(800 + B)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for n, h in ((Tq, H), (Tk, Hkv), (Tk, Hkv)))
+    size = A.attn_varlen_workspace_bytes(B, Tq, Tk, H, Hkv, d, d, True)
+    planned, ws = torch.zeros(size, dtype=torch.uint8, device="cuda"), torch.full((size,), 0xCD, dtype=torch.uint8, device="cuda")
+    A.attn_varlen_plan(cu[0], Tq, Tk, H, Hkv, d, d, planned, cu_seqlens_k=cu[1])
+    out = []
+    for c, w in ((None, planned), (cu[0], ws), (None, ws)):
+        o, lse = torch.full_like(q, 7.0), torch.full((H, Tq), 7.0, device="cuda")
+        A.attn_varlen_fwd(q, k, v, c, 0.1, False, o=o, lse=lse, workspace=w, cu_seqlens_k=None if c is None else cu[1], B=B)
+        torch.cuda.synchronize()
+        out.append((o, lse))
+    assert all(torch.equal(a, b) for other in out[1:] for a, b in zip(out[0], other))
+    want, got = (read_tables(w, B, Tq, Tk)[0] for w in (planned, ws))
+
+    def entries(t):         # helpers by their query, whatever the place of its tile
+        return sorted(tuple(t[e[0], :4]) + (int(e[1]), 1) if e[5] == 0x5A17AB1F else tuple(e[:4]) + tuple(e[4:]) for e in t)
+    assert entries(got) == entries(want)
+    keys = [e[3] for e in got if e[5] == 0x5A17AB1E]
+    assert keys == sorted(keys, reverse=True)
