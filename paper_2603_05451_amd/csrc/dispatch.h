@@ -78,9 +78,9 @@ inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
 
 // Whether the dK/dV kernel of one block per CU gets 256 blocks that take an XCD's places in turns (32 apart, every second
 // turn in reverse) instead of one block per place.  A block then brings in its next tile under the end of the one before
-// (N = 128 ... 1024, 65 536 x 16 rows, d = 128, no mask: 4 ... 10 % of the backward pass, N = 8192 0.5 %), but nobody evens
-// out what the turns leave uneven: under the mask only where they are whole pairs of rounds of short sequences (N = 512
-// -8 %, 1024 and 2048 -2 %, 4096 -1, 8192 0; 12 heads of N = 2176 +16 %, 7 x 12 of 1152 +2).
+// (N = 128 ... 1024, 65 536 x 16 rows, d = 128, no mask: 4 ... 10 % of the backward pass, N = 8192 0.5 %; d = 64: dkdv64_one_wave),
+// but nobody evens out what the turns leave uneven: under the mask only where they are whole pairs of rounds of short
+// sequences (N = 512 -8 %, 1024 and 2048 -2 %, 4096 -1, 8192 0; 12 heads of N = 2176 +16 %, 7 x 12 of 1152 +2).
 inline bool takes_turns(const TileOrder& o, int tiles, int64_t items, bool causal)
 {
     if (items <= 256) return false;
@@ -160,7 +160,12 @@ inline bool dq_one_wave(int d_qk, bool causal, int N, long long b)
 // dK/dV with 64 keys per wave (d = 64); b counts 256-key blocks.
 inline bool dkdv64_one_wave(bool causal, int N, long long b)
 {
-    if (N % 256 != 0 || N < 1024 || b <= 128) return false;
+    if (N % 256 != 0 || b <= 128) return false;
+    // In turns the next tile's first rows come under the end of the one before: no mask, turns at least 7/8 full (share of the
+    // whole backward pass: N = 256 ... 1024, b = 448 0.88 ... 0.95, 480 0.94 ... 0.96, 896 ... 960 0.94 ... 0.97, 1024 0.94 ... 0.96,
+    // 1856 0.99, 4096 0.94 ... 0.96; b = 264 and 272 1.08 and 1.06, 540 1.04, 576 1.02; N = 2048 and more 0.98 ... 1.00)
+    if (!causal && b > 256 && b >= (b + 255) / 256 * 224) return true;
+    if (N < 1024) return false;
     const bool one_round = b <= 256;
     if (!causal) return one_round || (b > 384 && N >= 2048);               // (N = 8192, b = 288 ... 384: 1.13 ... 1.04, 416: 0.86)
     return one_round ? equal_pairs(N) : N >= 8192;                         // (N = 1024, b = 264 ... 480: 1.06 ... 1.57)
@@ -286,7 +291,8 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
             if (last != 0 && pays) r.nsplit = 3;
         }
     } else if (Tk > Tq) {
-        // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call's 128-row kernel)
+        // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call where both run the
+        // 128-row kernel)
         // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
         // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
         // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose

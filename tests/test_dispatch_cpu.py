@@ -125,6 +125,8 @@ def test_turns(D):
         assert D.t_turns(Hkv, N // 128, causal), (causal, N, Hkv)
     assert not D.t_turns(256, 1, 0) and not D.t_turns(4, 64, 1) and not D.t_turns(36, 17, 1) and not D.t_turns(84, 9, 1)
     assert not D.t_turns(32, 64, 1) and D.t_turns(32, 64, 0)
+    for N, Hkv, _ in S.TURNS64:
+        assert D.t_dkdv64(64, 0, N, Hkv * N // 256) and D.t_turns(Hkv, N // 256, 0), (N, Hkv)
 
 
 # measured times of the kernels with one wave per SIMD over those of the 4-wave kernels: (pass, d, causal, N, 256-row blocks,
@@ -142,6 +144,8 @@ MEASURED = [
     ("dq", 64, 0, 1024, 288, 1.20), ("dq", 64, 1, 2048, 160, 0.91), ("dq", 64, 1, 1024, 288, 1.61), ("dq", 64, 1, 4096, 448, 1.07),
     ("dq", 64, 1, 8192, 256, 1.10), ("dq", 64, 1, 8192, 384, 0.85),
     ("dkdv64", 64, 0, 1024, 136, 0.85), ("dkdv64", 64, 0, 8192, 320, 1.12), ("dkdv64", 64, 0, 8192, 448, 0.89), ("dkdv64", 64, 0, 1024, 576, 1.08),
+    ("dkdv64", 64, 0, 256, 272, 1.06), ("dkdv64", 64, 0, 1280, 540, 1.04), ("dkdv64", 64, 0, 512, 448, 0.95), ("dkdv64", 64, 0, 512, 1024, 0.96),
+    ("dkdv64", 64, 0, 768, 465, 0.92), ("dkdv64", 64, 0, 1024, 1024, 0.95),
     ("dkdv64", 64, 1, 2048, 192, 0.92), ("dkdv64", 64, 1, 1024, 288, 1.55), ("dkdv64", 64, 1, 3072, 192, 1.12), ("dkdv64", 64, 1, 8192, 256, 1.18),
     ("dkdv64", 64, 1, 8192, 512, 0.89)]
 

@@ -111,3 +111,25 @@ def test_key_tiles_in_turns(oracle, causal, N, Hkv, G, dtype):
         first = a[:, :, :n]
         assert torch.equal(a, first.repeat(1, 1, Hkv // 2, 1)), what
         assert_close(first.float().cpu().numpy(), r, what)
+
+
+# the same at d = 64 without a mask: a last turn of 7/8, totals that are not dealt, units of several XCDs, two and three key tiles
+# per head, two query heads per KV head
+TURNS64 = [(256, 448, 1), (256, 962, 2), (768, 166, 1), (512, 236, 2), (1024, 124, 1)]
+
+
+@pytest.mark.parametrize("N,Hkv,G", TURNS64)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_key_tiles_in_turns_d64(oracle, N, Hkv, G, dtype):
+    import paper_2603_05451_amd as A
+    x = I.make_inputs(I.Workload("turns", 1, 2 * G, 2, N, 64, 64, False, 380 + N + Hkv))
+    q, do = (x[n].to(dtype).repeat(1, 1, Hkv // 2, 1).cuda() for n in ("q", "do"))
+    k, v = (x[n].to(dtype).repeat(1, 1, Hkv // 2, 1).cuda() for n in ("k", "v"))
+    o, lse = A.attn_fwd(q, k, v, 0.125, False)
+    got = A.attn_bwd(q, k, v, o, do, lse, 0.125, False)
+    torch.cuda.synchronize()
+    ref = oracle.attn_bwd(*(I.to_f64(x[n].to(dtype)) for n in ("q", "k", "v", "do")), 0.125, False)
+    for what, a, r, n in zip(("dQ", "dK", "dV"), got, ref, (2 * G, 2, 2)):
+        first = a[:, :, :n]
+        assert torch.equal(a, first.repeat(1, 1, Hkv // 2, 1)), what
+        assert_close(first.float().cpu().numpy(), r, what)
