@@ -31,7 +31,7 @@
  *     ATTN_ETOOLARGE are found before anything is enqueued: no output has been touched.
  *     ATTN_ELAUNCH (the HIP runtime refused a launch or an attribute) can come from any of the
  *     launches of a call that has several (the backward pass: dQ kernel, then dK/dV, at d = 256 as a
- *     dV and a dK kernel; the variable-length calls: a small table kernel first; a variable-length
+ *     dV and a dK kernel; most variable-length calls: a small table kernel first; a variable-length
  *     or strided forward pass whose keys are divided: a merge kernel last, without which o and lse
  *     are untouched): the launches before the failed one stay enqueued and write their outputs (dq,
  *     dv, the workspace); the outputs of the failed and later launches are untouched.
@@ -146,7 +146,8 @@ size_t attn_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d_qk, int d_v)
  *                            mask at least as many keys as queries.
  *   causal != 0: the last query of a sequence is aligned with its last key: key j is visible to
  *   query i iff j <= i + (keys - queries) of that sequence; j <= i for self-attention.
- *   The host never reads the lengths: a small kernel turns them into tables of 128-row tiles,
+ *   The host never reads the lengths: a small kernel (in a forward call of at most 64 sequences with no
+ *   more queries than sequences the attention kernel itself) turns them into tables of 128-row tiles,
  *   sequences with the longest loop per tile first (the longest-processing-time-first order of
  *   Sec. 3.3), and the attention kernels are launched over upper bounds of total_q/128 + B query
  *   tiles per head and total_k/128 + B key tiles per key/value head.
@@ -157,7 +158,7 @@ size_t attn_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d_qk, int d_v)
  *   alone, a call divides them less, and its results differ by the rounding of another summation
  *   order.)  All other conventions (device pointers, stream, alignment, head dims, error codes) are
  *   those of attn_fwd_ex / attn_bwd_ex.
- *   The table kernel checks every sequence's boundaries on the device against total_q and total_k:
+ *   What makes the tables checks every sequence's boundaries on the device against total_q and total_k:
  *   a sequence whose rows do not lie inside the tensors (decreasing boundaries, boundaries past the
  *   totals) is left out, i.e. none of its rows is read or written, and the other sequences are
  *   served.  The remaining conditions (a key for every sequence with queries; keys >= queries under
