@@ -135,7 +135,9 @@ inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
     if (N % 256 != 0 || N < 1024 || b <= 128) return false;
     const bool one_round = b <= 256;
     if (!causal) {          // d = 64: the vector port binds, the gain is smaller (N = 1024 one round 1.01 ... 1.04)
-        if (d_qk == 64) return one_round ? N > 1024 : b > 384 && N >= 8192;
+        // (N = 4096 ... 6144, rounds 15/16 full: b = 480 and 512 0.92 ... 0.95, 960 and 1024 0.92 ... 0.96, 2048 0.95 and 0.96, 4096
+        // 1.00; 7/8 full: 448 0.92, 896 1.03; N = 3072 0.98 ... 1.03, 2048 1.01 ... 1.06, 1024 1.03 ... 1.13)
+        if (d_qk == 64) return one_round ? N > 1024 : b > 384 && (N >= 8192 || (N >= 4096 && b >= (b + 255) / 256 * 240));
         return one_round || N >= 2048;
     }
     if (d_qk == 64)         // (N = 8192, b = 288 ... 384: 0.88, 0.92, 1.03, 0.89; N = 12288 there 1.05 ... 1.10)

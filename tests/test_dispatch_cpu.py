@@ -134,7 +134,8 @@ def test_turns(D):
 MEASURED = [
     ("fwd", 128, 0, 8192, 128, 1.08), ("fwd", 128, 0, 2048, 136, 0.78), ("fwd", 128, 0, 1024, 256, 0.95), ("fwd", 128, 0, 1024, 264, 1.16),
     ("fwd", 128, 0, 2048, 416, 0.85), ("fwd", 64, 0, 1024, 160, 1.04), ("fwd", 64, 0, 2048, 256, 0.94), ("fwd", 64, 0, 8192, 320, 1.24),
-    ("fwd", 64, 0, 8192, 448, 0.92), ("fwd", 64, 0, 4096, 576, 1.19), ("fwd", 128, 1, 1024, 136, 1.04), ("fwd", 128, 1, 2048, 160, 0.94),
+    ("fwd", 64, 0, 8192, 448, 0.92), ("fwd", 64, 0, 4096, 576, 1.19), ("fwd", 64, 0, 4096, 480, 0.92),
+    ("fwd", 64, 0, 6144, 960, 0.92), ("fwd", 64, 0, 7168, 896, 1.03), ("fwd", 64, 0, 3072, 960, 1.02), ("fwd", 128, 1, 1024, 136, 1.04), ("fwd", 128, 1, 2048, 160, 0.94),
     ("fwd", 128, 1, 3072, 192, 1.13), ("fwd", 128, 1, 4096, 256, 0.90), ("fwd", 128, 1, 8192, 256, 1.06), ("fwd", 128, 1, 4096, 448, 1.12),
     ("fwd", 128, 1, 8192, 512, 0.88), ("fwd", 192, 1, 8192, 192, 0.91), ("fwd", 192, 1, 4096, 288, 1.04), ("fwd", 192, 1, 6144, 288, 0.87),
     ("fwd", 64, 1, 4096, 448, 1.15), ("fwd", 64, 1, 8192, 320, 0.92), ("fwd", 64, 1, 8192, 448, 1.14), ("fwd", 64, 1, 12288, 336, 1.10),
