@@ -11,8 +11,8 @@
 
 namespace attn {
 
-// Place of a block in the work list for kernels whose blocks take two 128-row tiles and have nothing to do for every second
-// entry of a sequence.  An XCD takes one section of the list, and in it places 0, 2, 4, ... first, then 1, 3, 5, ...:
+// Place of a block in the work list of a launch over tables whose blocks take two 128-row tiles and have nothing to do for every
+// second entry of a sequence.  An XCD takes one section of the list, and in it places 0, 2, 4, ... first, then 1, 3, 5, ...:
 // dispatched alternately, the empty blocks would all fall to the same shader engines and leave the others twice the work.
 // The order is one of the section, not of the head: with a head's even places before its odd ones, 2 or 4 heads left half of
 // the XCDs with empty blocks alone (d = 64, 16 sequences of 4096 tokens, H = 8/2, no mask, dK/dV: 731 us of a 2791 us backward
@@ -76,6 +76,46 @@ inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
     return o;
 }
 
+// Order and blocks of a launch over query tiles (forward, dQ) or key tiles (dK/dV) of `rows` rows (FwdArgs, BwdArgs).
+// Equal-length batches count every (sequence, head) as a head; the tables of packed ones are sorted already, for every head
+// alike, and list 128-row tiles whatever `rows`.  In a launch of 256-row blocks over equal lengths every block has work: were
+// 128-row tiles its places, an XCD's list would have to keep the empty ones from alternating with the live ones, which
+// under the mask, where places go from head to head of a group, no order of places does (dQ, d = 128, B H = 32 heads in groups of
+// 4, N = 4096: two empty places, two live ones, and so on).
+template <typename Args>
+inline int tiles_of_query_launch(const Args& a, int rows)
+{
+    return a.max_tiles == 0 ? a.N / rows : a.st.nq > 0 ? (a.st.nq + rows - 1) / rows : a.max_tiles;
+}
+template <typename Args>
+inline int tiles_of_key_launch(const Args& a, int rows)
+{
+    return a.max_tiles == 0 ? a.N / rows : a.st.nq > 0 ? (a.st.nk + rows - 1) / rows : a.max_tiles_k;
+}
+template <typename Args>
+inline int query_blocks(const Args& a, int rows) { return tiles_of_query_launch(a, rows) * (a.max_tiles > 0 && a.st.nq == 0 ? 1 : a.B) * a.H; }
+template <typename Args>
+inline int key_blocks(const Args& a, int rows) { return tiles_of_key_launch(a, rows) * (a.max_tiles > 0 && a.st.nq == 0 ? 1 : a.B) * a.Hkv; }
+
+template <typename Args>
+inline TileOrder query_order(const Args& a, int rows)
+{
+    const int tiles = tiles_of_query_launch(a, rows);
+    if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.H, tiles);
+    if (!a.causal) return tile_order(a.B * a.H, tiles);
+    return causal_order(a.B * a.H, tiles, a.H / a.Hkv, (int64_t)(a.max_tiles > 0 ? a.st.nk : a.N) * (a.d_qk + a.d_v) * 2);
+}
+template <typename Args>
+inline TileOrder key_order(const Args& a, int rows)
+{
+    const int tiles = tiles_of_key_launch(a, rows);
+    if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.Hkv, tiles);
+    if (!a.causal) return tile_order(a.B * a.Hkv, tiles);
+    // the query heads of a KV head pass one after the other: two of them are in flight where blocks drift apart
+    const int in_flight = a.H > a.Hkv ? 2 : 1;
+    return causal_order(a.B * a.Hkv, tiles, 1, (int64_t)(a.max_tiles > 0 ? a.st.nq : a.N) * (a.d_qk + a.d_v) * 2 * in_flight);
+}
+
 // Whether the dK/dV kernel of one block per CU gets 256 blocks that take an XCD's places in turns (32 apart, every second
 // turn in reverse) instead of one block per place.  A block then brings in its next tile under the end of the one before
 // (N = 128 ... 1024, 65 536 x 16 rows, d = 128, no mask: 4 ... 10 % of the backward pass, N = 8192 0.5 %; d = 64: dkdv64_one_wave),
@@ -87,7 +127,7 @@ inline bool takes_turns(const TileOrder& o, int tiles, int64_t items, bool causa
     return !causal || (o.dealt && o.log_m == 0 && items % 512 == 0 && tiles <= 16);
 }
 
-// Place of a block; for kernels with nothing to do at every second place, in the order of section_order.
+// Place of a block; for launches over tables with nothing to do at every second entry, in the order of section_order.
 ATTN_ANYWHERE Place block_place(const TileOrder& o, int block)
 {
     return o.dealt ? Place{block & 7, block >> 3} : Place{0, block};
@@ -95,6 +135,12 @@ ATTN_ANYWHERE Place block_place(const TileOrder& o, int block)
 ATTN_ANYWHERE Place block_place_alternate(const TileOrder& o, int block, int total)
 {
     return o.dealt ? Place{block & 7, section_order(block, total) - (block & 7) * (total >> 3)} : Place{0, section_order(block, total)};
+}
+
+// The place of a block of `rows` rows in a launch over equal lengths or over tables of 128-row tiles.
+ATTN_ANYWHERE Place entry_place(const TileOrder& o, int rows, bool equal, int block, int total)
+{
+    return rows == 256 && !equal ? block_place_alternate(o, block, total) : block_place(o, block);
 }
 
 // (head, tile) of a place.  Branches instead of divisions by 1: an integer division is 0.1 us of a block's start.

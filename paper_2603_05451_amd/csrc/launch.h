@@ -55,19 +55,20 @@ __device__ __forceinline__ HeadTile uniform_head_tile(const TileOrder& order, Pl
     return {__builtin_amdgcn_readfirstlane(ht.head), __builtin_amdgcn_readfirstlane(ht.tile)};
 }
 
-// The table entry and the head of a place in the launch's order (query_order, key_order); the same arithmetic as tile_entry
-// where equal lengths need no table.
-template <bool QUERY_SIDE>
+// The table entry and the head of a place in the launch's order (query_order, key_order); where equal lengths need no table,
+// the same arithmetic as tile_entry, for blocks of two tiles that of the first of them.
+template <bool QUERY_SIDE, int ROWS = 128>
 __device__ __forceinline__ void placed_entry(const int4* __restrict__ plan, const TileOrder& order, Place place, int max_tiles, int heads,
                                              const VarlenStrides& st, int& head, int4& seq, int4& til)
 {
     if (st.nq > 0) {
-        const int nt = ((QUERY_SIDE ? st.nq : st.nk) + 127) / 128;
+        const int n = QUERY_SIDE ? st.nq : st.nk, nt = (n + ROWS - 1) / ROWS;
         const HeadTile ht = uniform_head_tile(order, place, nt);
         const int b = ht.head / heads;
         head = ht.head - b * heads;
         seq = make_int4(b * st.nq, st.nq, b * st.nk, st.nk);
-        til = make_int4(nt - 1 - ht.tile, kPlanUsed, b, 0);
+        // (query tiles: the last has the longest loop under the mask; key tiles, which the tables list backwards: the first)
+        til = make_int4(QUERY_SIDE ? (ROWS / 128) * (nt - 1 - ht.tile) : (n + 127) / 128 - 1 - (ROWS / 128) * ht.tile, kPlanUsed, b, 0);
     } else {
         const HeadTile ht = uniform_head_tile(order, place, max_tiles);
         head = ht.head;
@@ -231,26 +232,6 @@ struct LdsOptIn {
         return true;
     }
 };
-
-// Order of a launch over query tiles (forward, dQ) or key tiles (dK/dV) of `rows` rows.  Equal-length batches count every
-// (sequence, head) as a head; the tables of packed ones are sorted already, for every head alike.
-template <typename Args>
-inline TileOrder query_order(const Args& a, int rows)
-{
-    if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.H, a.max_tiles);
-    const int heads = a.B * a.H, tiles = a.max_tiles > 0 ? a.max_tiles / a.B : a.N / rows;
-    if (!a.causal) return tile_order(heads, tiles);
-    return causal_order(heads, tiles, a.H / a.Hkv, (int64_t)(a.max_tiles > 0 ? a.st.nk : a.N) * (a.d_qk + a.d_v) * 2);
-}
-inline TileOrder key_order(const BwdArgs& a, int rows)
-{
-    if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.Hkv, a.max_tiles_k);
-    const int heads = a.B * a.Hkv, tiles = a.max_tiles > 0 ? a.max_tiles_k / a.B : a.N / rows;
-    if (!a.causal) return tile_order(heads, tiles);
-    // the query heads of a KV head pass one after the other: two of them are in flight where blocks drift apart
-    const int in_flight = a.H > a.Hkv ? 2 : 1;
-    return causal_order(heads, tiles, 1, (int64_t)(a.max_tiles > 0 ? a.st.nq : a.N) * (a.d_qk + a.d_v) * 2 * in_flight);
-}
 
 // 0 on success, -2 unsupported head dims, -3 launch failure.
 int launch_fwd(const FwdArgs& a);

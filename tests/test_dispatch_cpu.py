@@ -21,6 +21,18 @@ int t_order(int block, int heads, int tiles, int share, long long bytes, int cau
     const HeadTile t = head_tile(o, half_empty ? block_place_alternate(o, block, total) : block_place(o, block), tiles);
     return t.head * tiles + t.tile;
 }
+// What block `block` of a launch over the query (key) tiles of an equal-length batch does: head * 2^16 + 128-row tile, counted
+// from the longest loop; -1 past the launch.
+struct Args { int B, H, Hkv, N, d_qk, d_v, causal, max_tiles, max_tiles_k; struct { int nq, nk; } st; };
+int t_equal(int block, int keys, int B, int H, int Hkv, int nq, int nk, int d, int causal, int rows)
+{
+    const Args a{B, H, Hkv, 0, d, d, causal, B * ((nq + 127) / 128), B * ((nk + 127) / 128), {nq, nk}};
+    const int total = keys ? key_blocks(a, rows) : query_blocks(a, rows);
+    if (block >= total) return -1;
+    const TileOrder o = keys ? key_order(a, rows) : query_order(a, rows);
+    const HeadTile t = head_tile(o, entry_place(o, rows, true, block, total), keys ? tiles_of_key_launch(a, rows) : tiles_of_query_launch(a, rows));
+    return t.head * 65536 + t.tile * (rows / 128);
+}
 int t_fwd_varlen(int d, int causal, int B, int Tq, int Tk, int H, int Hkv, int uniform)
 {
     const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d, 128, uniform);
@@ -116,6 +128,25 @@ def test_order_of_blocks(D, heads, tiles, half_empty):
                     assert falls == max(1, unit // 8) or tiles == 1
                 if unit and nbytes == 1 << 40:
                     assert falls == unit or tiles == 1
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d", [(2, 16, 16, 4096, 128), (1, 32, 32, 8192, 128), (2, 8, 8, 4096, 128), (2, 16, 16, 4000, 128),
+                                         (8, 16, 16, 1000, 128), (1, 12, 4, 2300, 128), (3, 5, 5, 513, 64), (2, 16, 16, 8192, 64)])
+@pytest.mark.parametrize("causal", [0, 1])
+@pytest.mark.parametrize("keys", [0, 1])
+def test_equal_lengths_in_blocks_of_256_rows(D, B, H, Hkv, N, d, causal, keys):
+    """Equal lengths, kernels that take two 128-row tiles: every pair of tiles once, no block without one (empty blocks that
+    alternate with live ones leave half of the shader engines idle), and under the mask an XCD's blocks from long to short within a
+    group of heads."""
+    tiles, heads = (N + 255) // 256, B * (Hkv if keys else H)
+    at = [D.t_equal(b, keys, B, H, Hkv, N, N, d, causal, 256) for b in range(heads * tiles + 1)]
+    assert at.pop() == -1
+    assert sorted(at) == [h * 65536 + 2 * t for h in range(heads) for t in range(tiles)]
+    if causal and len(at) % 8 == 0:
+        for xcd in range(8):
+            mine = np.array(at[xcd::8]) % 65536 // 2
+            falls = np.flatnonzero(np.diff(mine) < 0) + 1           # a new group starts, with its longest tile
+            assert (mine[falls] == mine[0]).all() and len(falls) + 1 <= max(1, heads // 8)
 
 
 def test_turns(D):
