@@ -39,6 +39,9 @@
  *     chosen by all sizes, B and H among them, and differ in the order of fp32 sums (forward, dQ):
  *     the rows of one sequence agree to rounding, not to the bit, between calls with another number
  *     of sequences or heads beside it.
+ *   - A NaN or an infinity in a row of v reaches o of the queries that see the row and, under the causal mask, may
+ *     reach o of up to 94 queries before them (a masked probability of 0 times it), no others; in the
+ *     backward pass it may reach every gradient of its sequence.
  *   - Re-entrant; no global state.  Calls on different streams may run concurrently
  *     as long as their outputs and workspaces do not overlap.
  */

@@ -85,3 +85,35 @@ def test_overlapping_rows(oracle):
     o, lse = A.attn_fwd_strided(q.repeat(1, H // 2, 1)[None].cuda(), gk, gk, 128 ** -0.5, True)
     torch.cuda.synchronize()
     _check(oracle, q, k.contiguous(), v.contiguous(), o[0], lse[0], 128, True, "overlapping")
+
+
+# (d_qk, B, queries, keys, H, key): divided; self-attention whole; the fixed-length form; a later part that begins past the first queries' diagonal
+NOT_FINITE = [(128, 1, 500, 4161, 64, 4160), (128, 1, 500, 4161, 64, 3900), (192, 1, 385, 6001, 40, 5990), (128, 1, 3600, 3600, 18, 3400),
+              (128, 1, 6144, 6144, 12, 6000), (192, 2, 6144, 6144, 6, 255)]
+
+
+@pytest.mark.parametrize("d,B,nq,nk,H,key", NOT_FINITE)
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_values_that_are_not_finite_stay_near_their_diagonal(oracle, d, B, nq, nk, H, key, value, dtype):
+    """A row of V that is infinite or NaN reaches the queries that see it and, as 0 * inf, at most those whose 32-query block has its
+    64-key tile in its loop: fewer than 95 before them, not the 256 of a block."""
+    import paper_2603_05451_amd as A
+    q, k, v = _inputs(d, nq, nk, "normal", dtype, 600 + d + nq)
+    bad = v.clone()
+    bad[key, :, 5] = value
+    rep = lambda t: t.repeat(1, H // 2, 1)[None].repeat(B, 1, 1, 1).cuda()
+    o, lse = A.attn_fwd_strided(rep(q), rep(k), rep(bad), d ** -0.5, True)
+    torch.cuda.synchronize()
+    shift = nk - nq
+    first = max(0, key - shift)                                     # first query that sees the key
+    near = min((q0 for q0 in range(0, nq, 32) if key // 64 * 64 <= q0 + 31 + shift), default=nq)
+    assert first - near < 95
+    assert torch.isfinite(o[:, :near]).all() and torch.isfinite(lse).all()
+    assert not torch.isfinite(o[:, first:, :, 5]).any()
+    assert torch.isfinite(torch.cat([o[..., :5], o[..., 6:]], 3)).all()
+    ro, rlse = oracle.attn_fwd(*(I.to_f64(t[None]) for t in (q[max(0, near - 300):near], k, v)), d ** -0.5, True,
+                               q_pos=np.arange(max(0, near - 300), near) + shift) if near else (None, None)
+    if near:
+        assert_close(o[:1, max(0, near - 300):near, :2].float().cpu().numpy(), ro, "O before the row")
+        assert np.abs(lse[:1, :2, max(0, near - 300):near].cpu().numpy() - rlse).max() <= LSE_ABS
