@@ -31,20 +31,26 @@ ATTN_ANYWHERE int section_order(int block, int total)
 
 // ---- Order of the blocks of a launch over heads x tiles (a head's tiles listed longest first, or as a table lists them).
 // Blocks are dealt to the 8 XCDs round robin.  An XCD works on heads of its own, one after the other, so that the tiles of a
-// head share its L2.  Where the heads do not divide, 2, 4 or 8 XCDs work on a unit of heads together and take its places in
-// turn: in contiguous shares (the longer tiles of a head here, the shorter there) the first XCD ends last (packed
-// batch of 16 sequences of 64 ... 8192 tokens under the mask, H = 16/4, d = 128, four KV heads on eight XCDs: backward pass
-// 2237 us, 1917 in turn).  Every second turn is taken in reverse: the first XCD does not get the longer tile each time, nor one
+// head share its L2.  Where the heads do not divide and the tiles are not alike, 2, 4 or 8 XCDs work on a unit of heads together
+// and take its places in turn: in contiguous shares (the longer tiles of a head here, the shorter there) the first XCD ends last
+// (packed batch of 16 sequences of 64 ... 8192 tokens under the mask, H = 16/4, d = 128, four KV heads on eight XCDs: backward
+// pass 2237 us, 1917 in turn).  Every second turn is taken in reverse: the first XCD does not get the longer tile each time, nor one
 // of them all places of the parity that is empty in kernels which take two entries per block.
 // Under the causal mask the tiles of a group of heads are taken together, longest first: one head's tiles after
 // the other's end with the longest tiles of the last head beside idle CUs, and pair long with short ones on a
 // CU at random.  (Forward / dQ / dK/dV, us, head by head -> groups of 8: B = 16, H = 16, N = 1024, d = 128: 106 -> 92, 170 -> 158,
 // 211 -> 188; B = 4, H = 8, N = 2048, d = 256, a unit of 4 heads: 132 -> 97, 133 -> 110, 233 -> 183; N = 8192, d = 128, H = 16,
-// B = 2: 476 -> 457, 650 -> 632, 943 -> 927; without the mask all tiles are equal and the order stays.)
+// B = 2: 476 -> 457, 650 -> 632, 943 -> 927.)
+// Where nothing is to be balanced -- equal tiles without the mask, or a launch of at most one block per CU, which ends with its
+// longest tile in any order -- an XCD takes a contiguous share of the places, head by head: in a unit of many heads it reads the
+// rows of all of them (us, units -> shares as before: no mask, 31 heads of N = 1024 forward d = 96 21.5 -> 17.8, d = 128 24.5 ->
+// 21.3, d = 256 45 -> 40, its backward pass 150 -> 131; 15 of 4096, d = 64 87.8 -> 80.0; mask, 13 of 2048, (192, 128) 51.0 -> 48.3,
+// d = 96 backward pass 86.4 -> 80.9; beyond 256 blocks the mask needs the units: 12 of 4096, d = 64 48 against 68).
 struct TileOrder {
     int dealt;          // whether every XCD gets an eighth of the places; otherwise they go by the block's number
     int unit, log_m;    // `unit` heads are worked on by 2^log_m XCDs
     int group;          // heads whose tiles are taken together
+    int share;          // places of an XCD in a row, before those of the next; 0: by units
 };
 struct Place {
     int xcd, at;        // at: in the XCD's list
@@ -59,7 +65,13 @@ inline TileOrder tile_order(int heads, int tiles)
     const bool dealt = (total & 7) == 0;
     int log_m = 0;
     if (dealt) while (((int64_t)heads << log_m & 7) != 0) ++log_m;
-    return {dealt, dealt ? (int)(((int64_t)heads << log_m) >> 3) : heads, log_m, 1};
+    return {dealt, dealt ? (int)(((int64_t)heads << log_m) >> 3) : heads, log_m, 1, 0};
+}
+// The same in contiguous shares.
+inline TileOrder share_order(int heads, int tiles)
+{
+    const TileOrder o = tile_order(heads, tiles);
+    return o.log_m == 0 ? o : TileOrder{1, 0, 0, 1, (int)((int64_t)heads * tiles >> 3)};
 }
 
 // The same under the causal mask.  `share` heads read the same rows, `bytes` of them.  Groups of about 8 heads (4 ... 16 are
@@ -70,6 +82,7 @@ inline TileOrder tile_order(int heads, int tiles)
 inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
 {
     TileOrder o = tile_order(heads, tiles);
+    if (o.log_m > 0 && (int64_t)heads * tiles <= 256) return share_order(heads, tiles);
     const int64_t fit = (16 << 20) / (bytes < 1 ? 1 : bytes), most = (fit < 1 ? 1 : fit) * share;
     const int want = (int)(most < 8 ? most : 8), n = o.unit / want < 1 ? 1 : o.unit / want;
     o.group = (o.unit + n - 1) / n;
@@ -102,7 +115,7 @@ inline TileOrder query_order(const Args& a, int rows)
 {
     const int tiles = tiles_of_query_launch(a, rows);
     if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.H, tiles);
-    if (!a.causal) return tile_order(a.B * a.H, tiles);
+    if (!a.causal) return share_order(a.B * a.H, tiles);
     return causal_order(a.B * a.H, tiles, a.H / a.Hkv, (int64_t)(a.max_tiles > 0 ? a.st.nk : a.N) * (a.d_qk + a.d_v) * 2);
 }
 template <typename Args>
@@ -110,7 +123,7 @@ inline TileOrder key_order(const Args& a, int rows)
 {
     const int tiles = tiles_of_key_launch(a, rows);
     if (a.max_tiles > 0 && a.st.nq == 0) return tile_order(a.Hkv, tiles);
-    if (!a.causal) return tile_order(a.B * a.Hkv, tiles);
+    if (!a.causal) return share_order(a.B * a.Hkv, tiles);
     // the query heads of a KV head pass one after the other: two of them are in flight where blocks drift apart
     const int in_flight = a.H > a.Hkv ? 2 : 1;
     return causal_order(a.B * a.Hkv, tiles, 1, (int64_t)(a.max_tiles > 0 ? a.st.nq : a.N) * (a.d_qk + a.d_v) * 2 * in_flight);
@@ -146,7 +159,8 @@ ATTN_ANYWHERE Place entry_place(const TileOrder& o, int rows, bool equal, int bl
 // (head, tile) of a place.  Branches instead of divisions by 1: an integer division is 0.1 us of a block's start.
 ATTN_ANYWHERE HeadTile head_tile(const TileOrder& o, Place place, int tiles)
 {
-    const int m = 1 << o.log_m, turn = place.xcd & (m - 1), p = place.at * m + ((place.at & 1) ? m - 1 - turn : turn);
+    const int m = 1 << o.log_m, turn = place.xcd & (m - 1);
+    const int p = place.xcd * o.share + place.at * m + ((place.at & 1) ? m - 1 - turn : turn);
     const int base = (place.xcd >> o.log_m) * o.unit;
     if (o.group == 1) {
         const int head = p / tiles;
