@@ -51,6 +51,8 @@ struct TileOrder {
     int unit, log_m;    // `unit` heads are worked on by 2^log_m XCDs
     int group;          // heads whose tiles are taken together
     int share;          // places of an XCD in a row, before those of the next; 0: by units
+    // `own` heads of an XCD's own behind its `first` places of the units, taken together in groups of `own_group`
+    int own, first, own_group;
 };
 struct Place {
     int xcd, at;        // at: in the XCD's list
@@ -65,13 +67,13 @@ inline TileOrder tile_order(int heads, int tiles)
     const bool dealt = (total & 7) == 0;
     int log_m = 0;
     if (dealt) while (((int64_t)heads << log_m & 7) != 0) ++log_m;
-    return {dealt, dealt ? (int)(((int64_t)heads << log_m) >> 3) : heads, log_m, 1, 0};
+    return {dealt, dealt ? (int)(((int64_t)heads << log_m) >> 3) : heads, log_m, 1, 0, 0, 0, 0};
 }
 // The same in contiguous shares.
 inline TileOrder share_order(int heads, int tiles)
 {
     const TileOrder o = tile_order(heads, tiles);
-    return o.log_m == 0 ? o : TileOrder{1, 0, 0, 1, (int)((int64_t)heads * tiles >> 3)};
+    return o.log_m == 0 ? o : TileOrder{1, 0, 0, 1, (int)((int64_t)heads * tiles >> 3), 0, 0, 0};
 }
 
 // The same under the causal mask.  `share` heads read the same rows, `bytes` of them.  Groups of about 8 heads (4 ... 16 are
@@ -79,13 +81,29 @@ inline TileOrder share_order(int heads, int tiles)
 // they drift apart the L2 no longer holds what they share (N = 16384, d = 128, 8 MB per head, B = 4, H = 16: dK/dV 7586, 7508,
 // 7632, 7958 us in groups of 1, 2, 4, 8).  Equal groups: a small last one ends like a single head (12 heads, N = 1024,
 // d = 256, forward: 102 us one by one, 88 as 8 + 4, 80 as 12).
+// From 32 heads on, and from 17 where the unit would be all of them, an XCD has heads enough of its own: only those left over
+// are shared in units, before its own, and it does not read the rows of every head of a large unit (us, units -> this, in brackets
+// contiguous shares: forward, 63 heads of N = 1024, d = 96 31.2 -> 23.5 (26.8), d = 128 37.2 -> 28.2 (32.3); 47 of 2048, d = 128 83 ->
+// 61 (79); 100 of 512, d = 96 18.2 -> 13.9 (16.7); 25 of 2048, d = 192 68 -> 53, its backward pass 172 -> 133; 17 of 4096, d = 128
+// 102 -> 84.  Fewer: 15 of 4096, forward, d = 96 66 -> 79, d = 256 209 -> 155; 20 of 4096, d = 64 61 -> 66, d = 128 93 -> 97; 28 of 2048
+// 0.99 ... 1.03).
 inline TileOrder causal_order(int heads, int tiles, int share, int64_t bytes)
 {
     TileOrder o = tile_order(heads, tiles);
     if (o.log_m > 0 && (int64_t)heads * tiles <= 256) return share_order(heads, tiles);
     const int64_t fit = (16 << 20) / (bytes < 1 ? 1 : bytes), most = (fit < 1 ? 1 : fit) * share;
-    const int want = (int)(most < 8 ? most : 8), n = o.unit / want < 1 ? 1 : o.unit / want;
-    o.group = (o.unit + n - 1) / n;
+    const int want = (int)(most < 8 ? most : 8);
+    auto groups = [&](int unit) { const int n = unit / want < 1 ? 1 : unit / want; return (unit + n - 1) / n; };
+    if (o.log_m > 0 && heads >= (o.log_m == 3 ? 17 : 32)) {
+        const int own = heads / 8;
+        o = tile_order(heads - 8 * own, tiles);
+        o.own = own;
+        o.first = o.unit * tiles >> o.log_m;
+        o.own_group = groups(own);
+        o.group = o.unit;
+        return o;
+    }
+    o.group = groups(o.unit);
     return o;
 }
 
@@ -160,19 +178,25 @@ ATTN_ANYWHERE Place entry_place(const TileOrder& o, int rows, bool equal, int bl
 ATTN_ANYWHERE HeadTile head_tile(const TileOrder& o, Place place, int tiles)
 {
     const int m = 1 << o.log_m, turn = place.xcd & (m - 1);
-    const int p = place.xcd * o.share + place.at * m + ((place.at & 1) ? m - 1 - turn : turn);
-    const int base = (place.xcd >> o.log_m) * o.unit;
-    if (o.group == 1) {
+    int p = place.xcd * o.share + place.at * m + ((place.at & 1) ? m - 1 - turn : turn);
+    int base = (place.xcd >> o.log_m) * o.unit, unit = o.unit, group = o.group;
+    if (o.own > 0 && place.at >= o.first) {
+        p = place.at - o.first;
+        base = (8 >> o.log_m) * o.unit + place.xcd * o.own;
+        unit = o.own;
+        group = o.own_group;
+    }
+    if (group == 1) {
         const int head = p / tiles;
         return {base + head, p - head * tiles};
     }
     int first = 0, r = p;
-    if (o.group < o.unit) {
-        const int whole = o.group * tiles, g = p / whole;
-        first = g * o.group;
+    if (group < unit) {
+        const int whole = group * tiles, g = p / whole;
+        first = g * group;
         r = p - g * whole;
     }
-    const int width = o.unit - first < o.group ? o.unit - first : o.group, tile = r / width;
+    const int width = unit - first < group ? unit - first : group, tile = r / width;
     return {base + first + (r - tile * width), tile};
 }
 

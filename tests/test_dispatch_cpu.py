@@ -103,7 +103,7 @@ def test_places_of_blocks_that_take_two_tiles(D, heads, lens):
         assert used / 2 - 1 <= want <= used / 2 + len(lens) * (1 + heads // 8)
 
 
-@pytest.mark.parametrize("heads", [1, 2, 3, 4, 5, 8, 12, 16, 20, 96, 136, 248])
+@pytest.mark.parametrize("heads", [1, 2, 3, 4, 5, 8, 12, 16, 20, 33, 36, 63, 96, 98, 100, 136, 248])
 @pytest.mark.parametrize("tiles", [1, 2, 3, 8, 16, 31, 64])
 @pytest.mark.parametrize("half_empty", [0, 1])
 def test_order_of_blocks(D, heads, tiles, half_empty):
@@ -163,6 +163,17 @@ def test_shares_of_equal_work(D, B, H, N, causal, rows, keys):
     assert len(set(at)) == total
     for xcd in range(8):
         assert len(set(at[xcd::8] // 65536)) <= (total // 8 - 1) // tiles + 2
+
+
+@pytest.mark.parametrize("heads,tiles", [(63, 8), (45, 8), (100, 4), (202, 4), (47, 16), (33, 32), (255, 8), (17, 32), (25, 16)])
+def test_heads_of_its_own_before_shared_ones(D, heads, tiles):
+    """Under the mask, many heads that do not divide: an XCD reads the rows of its own eighth of the heads, rounded down, and of the few
+    that are left over, and within either its blocks go from long to short."""
+    total = heads * tiles
+    for xcd in range(8):
+        at = np.array([D.t_order(b, heads, tiles, 1, 1, 1, 0) for b in range(xcd, total, 8)])
+        assert len(set(at // tiles)) <= heads // 8 + heads % 8
+        assert (np.diff(at % tiles) < 0).sum() <= 1 + max(1, heads // 8 // 8)
 
 
 def test_turns(D):

@@ -63,9 +63,10 @@ def test_backward(oracle, causal, N, H, d):
 
 
 # heads that do not divide among the 8 XCDs (units of 2, 4 and 8 XCDs, and totals that are not dealt at all), groups of
-# unequal width, one tile per head: the order of the blocks decides which work is done, not what it gives
+# unequal width, one tile per head, heads of an XCD's own behind shared ones: the order of the blocks decides which work is done, not what it gives
 @pytest.mark.parametrize("B,H,Hkv,N,d,dv", [(1, 12, 4, 512, 128, 128), (1, 2, 1, 1024, 64, 64), (1, 1, 1, 384, 128, 128), (3, 5, 5, 384, 96, 96),
-                                            (9, 16, 8, 256, 64, 64), (1, 20, 20, 128, 256, 256), (1, 6, 3, 1024, 192, 128)])
+                                            (9, 16, 8, 256, 64, 64), (1, 20, 20, 128, 256, 256), (1, 6, 3, 1024, 192, 128),
+                                            (1, 33, 11, 1024, 128, 128), (5, 20, 20, 512, 64, 64), (1, 34, 34, 1024, 64, 64)])
 @pytest.mark.parametrize("layout", ["fixed", "views", "packed"])
 def test_orders_of_blocks_under_the_mask(oracle, B, H, Hkv, N, d, dv, layout):
     import paper_2603_05451_amd as A
