@@ -224,3 +224,32 @@ def test_table_of_a_few_sequences(lens, H, Hkv, d):
     assert entries(got) == entries(want)
     keys = [e[3] for e in got if e[5] == 0x5A17AB1E]
     assert keys == sorted(keys, reverse=True)
+
+
+@pytest.mark.parametrize("B,Nk,parts", [(64, 700, 1), (40, 2600, 3)])
+@pytest.mark.parametrize("side", ["k", "q", "both", "decreasing"])
+def test_few_sequences_outside_the_tensors_are_left_out(B, Nk, parts, side):
+    """Boundaries that run past the stated totals, or decrease, in a step whose table the decode kernel makes itself: that sequence
+    is not read or written, the others come out bit for bit as in the sound call."""
+    import paper_2603_05451_amd as A
+    from test_gpu_varlen import read_tables
+    H, Hkv, d = 8, 2, 128
+    g = torch.Generator(device="cuda").manual_seed(830 + B)
+    q, k, v = (torch.randn(n, h, d, generator=g, device="cuda").bfloat16() for n, h in ((B, H), (B * Nk, Hkv), (B * Nk, Hkv)))
+    good = [torch.arange(B + 1, dtype=torch.int32, device="cuda") * n for n in (1, Nk)]
+    ws = torch.zeros(A.attn_varlen_workspace_bytes(B, B, B * Nk, H, Hkv, d, d, True), dtype=torch.uint8, device="cuda")
+    o_ref, lse_ref = A.attn_varlen_fwd(q, k, v, good[0], 0.1, True, cu_seqlens_k=good[1])
+    cq, ck = good[0].clone(), good[1].clone()
+    if side in ("k", "both"):
+        ck[B] += 64
+    if side in ("q", "both"):
+        cq[B] += 3
+    if side == "decreasing":
+        ck[B] = 0
+    o, lse = torch.full_like(o_ref, 7.0), torch.full_like(lse_ref, 7.0)
+    A.attn_varlen_fwd(q, k, v, cq, 0.1, True, o=o, lse=lse, workspace=ws, cu_seqlens_k=ck)
+    torch.cuda.synchronize()
+    assert torch.equal(o[:-1], o_ref[:-1]) and torch.equal(lse[:, :-1], lse_ref[:, :-1])
+    assert (o[-1] == 7.0).all() and (lse[:, -1] == 7.0).all()
+    table = read_tables(ws, B, B, B * Nk)[0]
+    assert sorted(t[6] for t in table if t[5] == 0x5A17AB1E) == list(range(B - 1))

@@ -1,6 +1,6 @@
 """GPU tests of the variable-length form of the forward kernel with 64 queries per wave, whole and with the keys divided:
 ragged ends, blocks with a few rows, sequences without queries, a diagonal that is not aligned with the tiles, scores that
-send it through its second pass, overlapping rows (which it leaves to the 128-row kernel).  Two heads are generated and
+send it through its second pass, overlapping rows (which it leaves to the 128-row kernel), grouped heads in views, values that are not finite.  Two heads are generated and
 repeated, so that the oracle computes two and every repetition has to reproduce their bits."""
 import numpy as np
 import pytest
@@ -17,6 +17,12 @@ EQUAL = [(128, True, 1, 500, 4161, 64), (128, True, 2, 511, 2033, 64), (192, Fal
 # packed: (d_qk, causal, [(queries, keys)], H): whole; divided, where a short sequence has fewer parts; without the mask
 PACKED = [(128, True, [(500, 4000), (1, 3000), (0, 50), (700, 2900), (257, 3777)], 64), (128, True, [(300, 5000), (513, 6500), (30, 130)], 24),
           (192, False, [(1300, 1300), (129, 1200), (64, 2000), (1000, 700)], 32)]
+
+
+# packed, divided, under the mask: blocks whose second part of the keys begins past what their first queries see (none, then all of a wave)
+UNSEEN = [(128, True, [(300, 7000), (256, 406), (513, 9000)], 20), (192, True, [(700, 8001), (257, 400)], 24)]
+# grouped heads: (d_qk, causal, B, queries, keys, H, Hkv): divided, whole, without the mask
+GROUPED = [(128, True, 1, 500, 8100, 32, 8), (192, True, 1, 385, 6001, 40, 10), (128, True, 1, 3600, 3600, 18, 6), (128, False, 2, 1281, 1281, 16, 2)]
 
 
 def _inputs(d, nq, nk, kind, dtype, seed):
@@ -70,6 +76,48 @@ def test_packed(oracle, d, causal, lens, H, kind, dtype):
         if nq:
             _check(oracle, *x[i], o[at:at + nq], lse[:, at:at + nq], d, causal, f"{kind} sequence {i}")
         at += nq
+
+
+@pytest.mark.parametrize("d,causal,lens,H", UNSEEN)
+@pytest.mark.parametrize("kind,dtype", [("normal", torch.bfloat16), ("growing", torch.bfloat16), ("normal", torch.float16)])
+def test_parts_that_some_queries_see_nothing_of(oracle, d, causal, lens, H, kind, dtype):
+    test_packed(oracle, d, causal, lens, H, kind, dtype)
+
+
+@pytest.mark.parametrize("d,causal,B,nq,nk,H,Hkv", GROUPED)
+@pytest.mark.parametrize("layout", ["bhnd", "fused"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_grouped_heads_in_views(oracle, d, causal, B, nq, nk, H, Hkv, layout, dtype):
+    """[B, heads, N, d] storage of Q, K, V and O, and Q beside K and V beside each other in wider buffers with O inside one: the
+    bits of contiguous tensors, and the oracle's values.  Every KV head holds one of two, every query head of a group likewise."""
+    import paper_2603_05451_amd as A
+    q, k, v = _inputs(d, nq, nk, "normal", dtype, 560 + d + nq)
+    q = q.repeat(1, H // 2, 1)[None].repeat(B, 1, 1, 1).cuda()
+    k, v = (t.repeat(1, Hkv // 2, 1)[None].repeat(B, 1, 1, 1).cuda() for t in (k, v))
+    ro, rlse = A.attn_fwd_strided(q, k, v, d ** -0.5, causal)
+    if layout == "bhnd":
+        view = lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)
+        wq, wk, wv = view(q), view(k), view(v)
+        o = torch.full((B, H, nq, 128), 7.0, dtype=dtype, device="cuda").transpose(1, 2)
+    else:
+        wide = lambda t, e: torch.full(t.shape[:2] + (t.shape[2] + 1, e), 7.0, dtype=dtype, device="cuda")
+        bq, bkv, bo = wide(q, d), torch.full((B, nk, 2 * Hkv, 192), 7.0, dtype=dtype, device="cuda"), wide(q, 128)
+        wq, wk, wv, o = bq[:, :, 1:], bkv[:, :, :Hkv, :d], bkv[:, :, Hkv:, :128], bo[:, :, :H]
+        wq.copy_(q); wk.copy_(k); wv.copy_(v)
+    _, lse = A.attn_fwd_strided(wq, wk, wv, d ** -0.5, causal, o=o)
+    torch.cuda.synchronize()
+    assert torch.equal(o, ro) and torch.equal(lse, rlse)
+    if layout == "fused":
+        assert (bo[:, :, H:] == 7.0).all()
+    # query head h meets KV head h / (H / Hkv): the pairs (0, 0) and (G, 1) with G = H / Hkv, and where G is odd (1, 0) ...
+    G = H // Hkv
+    for h in (0, G, H - 1):
+        one = lambda t, i: t[:1, :, i:i + 1].float().cpu().to(dtype)
+        rows = np.unique(np.concatenate([np.arange(0, nq, 53), np.arange(max(0, nq - 40), nq)]))
+        x = (one(q, h)[:, rows], one(k, h // G), one(v, h // G))
+        xo, xl = oracle.attn_fwd(*(I.to_f64(t) for t in x), d ** -0.5, causal, q_pos=rows + (nk - nq))
+        assert_close(o[:1, rows, h:h + 1].float().cpu().numpy(), xo, f"O head {h}")
+        assert np.abs(lse[:1, h:h + 1].cpu().numpy()[:, :, rows] - xl).max() <= LSE_ABS
 
 
 def test_overlapping_rows(oracle):
