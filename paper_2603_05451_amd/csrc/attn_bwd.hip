@@ -119,7 +119,7 @@ int launch_bwd(const BwdArgs& a)
         const bool as_fixed = a.st.nq > 0 && a.st.nq == a.st.nk && a.st.nq % 128 == 0;
         const int64_t half = ((int64_t)a.T + 255) / 256 * a.H, blocks64 = (int64_t)a.max_tiles_k / 2 * a.Hkv;
         const bool dq = rows && (as_fixed ? dq_q64_at(a.st.nq) || dq_t32_at(a.st.nq) || dq256_at(a.st.nq)
-                                          : dq_one_wave_varlen(a.d_qk, a.causal, n, k, half));
+                                          : dq_one_wave_varlen(a.d_qk, a.causal, n, k, half, a.st.nq > 0));
         dq_q64 = dq && (d128 || d64);
         dq_t32 = dq && (d192 || d256);
         dkdv_t32 = rows && dkdv_one_wave_varlen(a.d_qk, a.causal, n, k, a.H / a.Hkv, blocks64);

@@ -204,16 +204,12 @@ ATTN_ANYWHERE HeadTile head_tile(const TileOrder& o, Place place, int tiles)
 // rows, two per CU).  b = blocks of 256 rows in the launch.  Measured over N = 512 ... 16384 and b = 8 ... 1536, as time of
 // the first over time of the second:
 //   b <= 128           half the chip idles: forward, d = 128, N = 8192 1.08 ... 1.19 (1.21 ... 1.25 under the mask)
-//   128 < b <= 256     one round either way, and a large block beats two small ones: 0.75 ... 0.87 without the mask
+//   128 < b <= 256     one round either way, and without the mask a large block beats two small ones: 0.75 ... 0.87
 //   256 < b <= 384     the last round is at most half full, and small blocks spread over it: d = 128 0.98 ... 1.05, d = 64
 //                      1.05 ... 1.30
 //   beyond             full rounds: 0.8 ... 0.95 where the key loop outweighs a lone block's prologue
-// Under the mask a round's length is that of its unluckiest CU.  A CU's two small blocks are 32 places apart in an XCD's
-// list: where 32 is a multiple of a head's tiles (N = 1024, 2048, 4096) those are two tiles of the same length, and the
-// CU with the two longest ends last (b = 160, d = 128, forward, N = 2048 ... 8192: 0.94, 1.10 at 3072, 0.89, 0.97, 1.01).
-// (Ratios under the mask beyond one round are of launches that take groups of heads together, longest tiles first.)
-inline bool equal_pairs(int N) { return 32 % (N / 128) == 0; }
-
+// Under the mask a round's length is that of its unluckiest CU, and with the tiles of a group of heads taken together (causal_order)
+// the small blocks of a CU are a long and a short one: in one round the large blocks, each alone on its CU, end with the longest.
 inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
 {
     if (N % 256 != 0 || N < 1024 || b <= 128) return false;
@@ -224,11 +220,17 @@ inline bool fwd_one_wave(int d_qk, bool causal, int N, long long b)
         if (d_qk == 64) return one_round ? N > 1024 : b > 384 && (N >= 8192 || (N >= 4096 && b >= (b + 255) / 256 * 240));
         return one_round || N >= 2048;
     }
-    if (d_qk == 64)         // (N = 8192, b = 288 ... 384: 0.88, 0.92, 1.03, 0.89; N = 12288 there 1.05 ... 1.10)
-        return !one_round && (N >= 16384 || (b <= 384 && N >= 8192 && N < 12288));
-    // (d = 192: N = 2048, b = 128 ... 256 1.23 ... 1.15, N = 4096 1.06 ... 0.97, N = 8192 1.00 ... 0.91)
-    if (one_round) return d_qk == 192 ? N == 4096 || N >= 8192 : equal_pairs(N) && N >= 2048;
-    return N >= 6144;           // (b = 384 ... 1152: N = 4096 0.91 ... 1.02, N = 6144 0.96 ... 0.99, at 192 0.97; N = 3072 0.95 ... 1.07)
+    // d = 64: one round 1.30 ... 1.42; N = 4096 ... 8192, b = 288 ... 384 1.04 ... 1.16, two full rounds (432 ... 528) 0.92 ... 0.97 from
+    // N = 8192 (1.00 at 4096), 576 ... 768 1.02 ... 1.16; N = 16384 from b = 1024 0.98 ... 0.99
+    if (d_qk == 64) return N >= 8192 && ((b > 416 && b <= 512) || (N >= 16384 && b >= 1024));
+    // d = 128: one round 1.05 ... 1.33.  d = 192, one round: N = 2048 1.08 ... 1.14, N = 3072 1.03 ... 1.10, N = 4096 b <= 192 1.03 ... 1.08,
+    // from b = 208 1.02 and 1.01 with even numbers of heads, 0.89 and 0.82 with odd ones, N = 5120 ... 7168 from 200 0.85 ... 1.03, below
+    // 1.03 ... 1.05, N = 8192 and more 0.75 ... 1.03
+    if (one_round) return d_qk == 192 && N >= (b > 192 ? 4096 : 8192);
+    // d = 128: N = 4096, b = 272 ... 352 1.03 ... 1.08, from 384 0.89 ... 1.05 (0.96 on average), N = 5120 from 400 0.88 ... 0.99 (1.13 where
+    // the blocks are no multiple of 8), N = 6144 0.87 ... 1.05, N = 3072 0.95 ... 1.13.  d = 192: N = 4096 0.86 ... 1.03, N = 5120 ... 6144
+    // 0.82 ... 1.09, N = 3072 0.85 ... 1.02
+    return N >= 6144 || (N >= 4096 && (d_qk == 192 || b >= 384));
 }
 
 // dQ with 64 queries per wave (d_qk = d_v = 128 or 64).
@@ -236,11 +238,12 @@ inline bool dq_one_wave(int d_qk, bool causal, int N, long long b)
 {
     if (N % 256 != 0 || N < 1024 || b <= 128) return false;
     const bool one_round = b <= 256;
-    // (causal, N = 1024 and 2048: b = 288 1.33, 1.23; b = 384 0.96, 0.92; b = 512 ... 2048 0.90 ... 0.98; N = 1280 and 1536
-    // 1.03 ... 0.91)
-    if (d_qk == 128) return one_round || !causal || N >= 3072 || !equal_pairs(N) || b > 320;
-    if (!causal) return one_round || N >= 2048;
-    return one_round ? equal_pairs(N) && N >= 2048 : N >= 8192;            // (N = 1024, b = 264 ... 480: 1.12 ... 1.62)
+    if (!causal) return one_round || N >= 2048 || d_qk == 128;
+    // (mask, share of the whole backward pass: one round d = 128 0.99 ... 1.05, d = 64 1.04 ... 1.11; beyond, d = 128: N = 1024 ... 1792 b = 288 ...
+    // 320 0.99 ... 1.17, from 384 0.96 ... 1.01, N = 2560 and more 0.92 ... 1.00; d = 64: N = 4096 and more b = 288 ... 352 1.00 ... 1.04, from 384
+    // 0.94 ... 0.99, N = 1024 ... 3072 0.97 ... 1.14)
+    if (one_round) return false;
+    return d_qk == 128 ? N >= 2560 || b > 320 : N >= 4096 && b >= 384;
 }
 
 // dK/dV with 64 keys per wave (d = 64); b counts 256-key blocks.
@@ -254,7 +257,7 @@ inline bool dkdv64_one_wave(bool causal, int N, long long b)
     if (N < 1024) return false;
     const bool one_round = b <= 256;
     if (!causal) return one_round || (b > 384 && N >= 2048);               // (N = 8192, b = 288 ... 384: 1.13 ... 1.04, 416: 0.86)
-    return one_round ? equal_pairs(N) : N >= 8192;                         // (N = 1024, b = 264 ... 480: 1.06 ... 1.57)
+    return N >= 4096 && b > 384;        // (mask: one round 1.08 ... 1.17, b = 288 ... 384 0.98 ... 1.07, beyond 0.94 ... 1.02, N = 3072 and less 0.98 ... 1.19)
 }
 
 // d = 256, the pipelined kernels with one wave per SIMD against the general ones (one block of 128 rows per CU both):
@@ -289,16 +292,18 @@ inline bool fwd_one_wave_varlen(int d_qk, bool causal, int64_t B, int64_t Tq, in
 // dQ with one wave per SIMD; half = 256-row blocks of queries x heads.
 //   d = 128  64 queries per wave: half as many blocks as the 4-wave kernel, each with a CU to itself as there; with r rounds
 //            of 256 blocks against s it takes 1.8 r to s.  n = 100 +11 ... +23 %, n = 512 -4 ... -11 %, n = 8192 -9 ... -20 %.
-//            Under the mask a single round of short ragged sequences ends with its longest tile (5 x 800 +13 %).
+//            Under the mask a single round of short ragged sequences ends with its longest tile (5 x 800 +13 %), one of equal
+//            lengths, whose 128-row blocks pair a long with a short tile per CU, at any length (2 x 1500 ... 6000 x 8 ... 16 heads
+//            +5 ... +15 %; beyond one round -1 ... -12 %).
 //   d = 64   the 4-wave kernel has two blocks per CU: n = 1024 +11 ... +26 % (mask), n = 2048 +5, n = 4096 -1, n = 8192 -5 %;
 //            without the mask n = 800 +7, n = 2048 -3, n = 8192 -6 %.
 //   (192, 128) and 256, 32 queries per wave, 128-row blocks as in the general kernel: n = 64 and less +5 ... +15 % (a tile
 //            mostly empty costs the longer prologue), (192, 128) n = 512 without and 1024 with the mask -2 %, 256 from n = 100
 //            or k = 1000 -2 ... -17 %.
-inline bool dq_one_wave_varlen(int d_qk, bool causal, int64_t n, int64_t k, int64_t half)
+inline bool dq_one_wave_varlen(int d_qk, bool causal, int64_t n, int64_t k, int64_t half, bool equal)
 {
     const int64_t r = (half + 255) / 256, s = (2 * half + 255) / 256;
-    if (d_qk == 128) return n >= 512 && 9 * r <= 5 * s && (!causal || half > 256 || n >= 1500);
+    if (d_qk == 128) return n >= 512 && 9 * r <= 5 * s && (!causal || half > 256 || (!equal && n >= 1500));
     if (d_qk == 64) return n >= (causal ? 4096 : 2048) && half >= 512;
     if (d_qk == 192) return n >= (causal ? 1024 : 512);
     return d_qk == 256 && (n > 64 || k > 64);

@@ -57,7 +57,7 @@ int t_shares(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform
 {
     return merge_shares(fwd_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform), uniform, Tq / B, H / Hkv, dv);
 }
-int t_dq_varlen(int d, int causal, long long n, long long k, long long half) { return dq_one_wave_varlen(d, causal, n, k, half); }
+int t_dq_varlen(int d, int causal, long long n, long long k, long long half) { return dq_one_wave_varlen(d, causal, n, k, half, false); }
 int t_dkdv_varlen(int d, int causal, long long n, long long k, int group, long long blocks64)
 { return dkdv_one_wave_varlen(d, causal, n, k, group, blocks64); }
 }
@@ -198,25 +198,29 @@ def test_turns(D):
 
 
 # measured times of the kernels with one wave per SIMD over those of the 4-wave kernels: (pass, d, causal, N, 256-row blocks,
-# ratio), both sides of every line of the rules
+# ratio), both sides of every line of the rules; under the mask with the tiles of groups of heads taken together
 MEASURED = [
     ("fwd", 128, 0, 8192, 128, 1.08), ("fwd", 128, 0, 2048, 136, 0.78), ("fwd", 128, 0, 1024, 256, 0.95), ("fwd", 128, 0, 1024, 264, 1.16),
     ("fwd", 128, 0, 2048, 416, 0.85), ("fwd", 64, 0, 1024, 160, 1.04), ("fwd", 64, 0, 2048, 256, 0.94), ("fwd", 64, 0, 8192, 320, 1.24),
     ("fwd", 64, 0, 8192, 448, 0.92), ("fwd", 64, 0, 4096, 576, 1.19), ("fwd", 64, 0, 4096, 480, 0.92),
-    ("fwd", 64, 0, 6144, 960, 0.92), ("fwd", 64, 0, 7168, 896, 1.03), ("fwd", 64, 0, 3072, 960, 1.02), ("fwd", 128, 1, 1024, 136, 1.04), ("fwd", 128, 1, 2048, 160, 0.94),
-    ("fwd", 128, 1, 3072, 192, 1.13), ("fwd", 128, 1, 4096, 256, 0.90), ("fwd", 128, 1, 8192, 256, 1.06), ("fwd", 128, 1, 4096, 448, 1.12),
-    ("fwd", 128, 1, 8192, 512, 0.88), ("fwd", 192, 1, 8192, 192, 0.91), ("fwd", 192, 1, 4096, 288, 1.04), ("fwd", 192, 1, 6144, 288, 0.87),
-    ("fwd", 64, 1, 4096, 448, 1.15), ("fwd", 64, 1, 8192, 320, 0.92), ("fwd", 64, 1, 8192, 448, 1.14), ("fwd", 64, 1, 12288, 336, 1.10),
-    ("fwd", 64, 1, 16384, 512, 0.96),
-    ("dq", 128, 0, 1024, 128, 1.12), ("dq", 128, 0, 1024, 136, 0.78), ("dq", 128, 1, 1024, 192, 0.84), ("dq", 128, 1, 1024, 288, 1.33),
-    ("dq", 128, 1, 2048, 288, 1.23), ("dq", 128, 1, 1280, 450, 0.92), ("dq", 128, 1, 3072, 288, 0.94), ("dq", 64, 0, 1024, 256, 0.91),
-    ("dq", 64, 0, 1024, 288, 1.20), ("dq", 64, 1, 2048, 160, 0.91), ("dq", 64, 1, 1024, 288, 1.61), ("dq", 64, 1, 4096, 448, 1.07),
-    ("dq", 64, 1, 8192, 256, 1.10), ("dq", 64, 1, 8192, 384, 0.85),
+    ("fwd", 64, 0, 6144, 960, 0.92), ("fwd", 64, 0, 7168, 896, 1.03), ("fwd", 64, 0, 3072, 960, 1.02), ("fwd", 128, 1, 1024, 136, 1.33),
+    ("fwd", 128, 1, 2048, 160, 1.22), ("fwd", 128, 1, 3072, 192, 1.15), ("fwd", 128, 1, 4096, 256, 1.08), ("fwd", 128, 1, 8192, 256, 1.05),
+    ("fwd", 128, 1, 4096, 320, 1.03), ("fwd", 128, 1, 4096, 384, 0.94), ("fwd", 128, 1, 4096, 448, 0.91), ("fwd", 128, 1, 3072, 576, 1.03),
+    ("fwd", 128, 1, 6144, 384, 0.97), ("fwd", 128, 1, 8192, 512, 0.88), ("fwd", 192, 1, 2048, 256, 1.08), ("fwd", 192, 1, 3072, 240, 1.03),
+    ("fwd", 192, 1, 4096, 192, 1.05), ("fwd", 192, 1, 4096, 208, 0.89), ("fwd", 192, 1, 7168, 168, 1.03), ("fwd", 192, 1, 7168, 224, 0.99),
+    ("fwd", 192, 1, 8192, 192, 0.99), ("fwd", 192, 1, 3072, 576, 1.02), ("fwd", 192, 1, 4096, 384, 0.93), ("fwd", 192, 1, 6144, 288, 0.98),
+    ("fwd", 64, 1, 4096, 448, 1.15), ("fwd", 64, 1, 8192, 384, 1.04), ("fwd", 64, 1, 8192, 448, 0.93), ("fwd", 64, 1, 8192, 640, 1.08),
+    ("fwd", 64, 1, 12288, 336, 1.07), ("fwd", 64, 1, 16384, 512, 0.93), ("fwd", 64, 1, 16384, 768, 1.02), ("fwd", 64, 1, 16384, 1024, 0.98),
+    ("dq", 128, 0, 1024, 128, 1.12), ("dq", 128, 0, 1024, 136, 0.78), ("dq", 128, 1, 1024, 192, 1.02), ("dq", 128, 1, 1536, 300, 1.17),
+    ("dq", 128, 1, 1024, 384, 0.98), ("dq", 128, 1, 2048, 256, 1.02), ("dq", 128, 1, 2048, 512, 0.96), ("dq", 128, 1, 8192, 160, 1.02),
+    ("dq", 128, 1, 2560, 300, 0.99), ("dq", 128, 1, 1280, 450, 0.92), ("dq", 128, 1, 3072, 384, 0.96), ("dq", 64, 0, 1024, 256, 0.91),
+    ("dq", 64, 0, 1024, 288, 1.20), ("dq", 64, 1, 2048, 160, 1.09), ("dq", 64, 1, 1024, 288, 1.04), ("dq", 64, 1, 4096, 320, 1.02),
+    ("dq", 64, 1, 4096, 384, 0.97), ("dq", 64, 1, 2560, 700, 1.12), ("dq", 64, 1, 8192, 256, 1.04), ("dq", 64, 1, 8192, 384, 0.98),
     ("dkdv64", 64, 0, 1024, 136, 0.85), ("dkdv64", 64, 0, 8192, 320, 1.12), ("dkdv64", 64, 0, 8192, 448, 0.89), ("dkdv64", 64, 0, 1024, 576, 1.08),
     ("dkdv64", 64, 0, 256, 272, 1.06), ("dkdv64", 64, 0, 1280, 540, 1.04), ("dkdv64", 64, 0, 512, 448, 0.95), ("dkdv64", 64, 0, 512, 1024, 0.96),
     ("dkdv64", 64, 0, 768, 465, 0.92), ("dkdv64", 64, 0, 1024, 1024, 0.95),
-    ("dkdv64", 64, 1, 2048, 192, 0.92), ("dkdv64", 64, 1, 1024, 288, 1.55), ("dkdv64", 64, 1, 3072, 192, 1.12), ("dkdv64", 64, 1, 8192, 256, 1.18),
-    ("dkdv64", 64, 1, 8192, 512, 0.89)]
+    ("dkdv64", 64, 1, 2048, 192, 1.12), ("dkdv64", 64, 1, 1024, 288, 1.04), ("dkdv64", 64, 1, 2560, 700, 1.15), ("dkdv64", 64, 1, 4096, 320, 1.04),
+    ("dkdv64", 64, 1, 4096, 448, 0.97), ("dkdv64", 64, 1, 8192, 256, 1.09), ("dkdv64", 64, 1, 8192, 512, 0.95)]
 
 
 @pytest.mark.parametrize("what,d,causal,N,b,ratio", MEASURED)
@@ -361,11 +365,12 @@ def test_gpu_tests_reach_what_they_are_written_for(D):
         assert D.t_fwd(w.dqk, w.causal, w.N, w.B * w.H * times * w.N // 256), w.name
     for causal, N, d, _, times, *_ in F.GROWING + F.STEPS:
         assert D.t_fwd(d, causal, N, 2 * times * N // 256), (causal, N, d)
-    for causal, N, heads, d, _ in S.FORWARD:
-        assert D.t_fwd(d, causal, N, heads * N // 256), (causal, N, heads, d)
-    for causal, N, heads, d in S.BACKWARD:
-        assert bool(D.t_dq(d, causal, N, heads * N // 256)) == ((d, causal, N) != (64, True, 1024))
-        assert d != 64 or D.t_dkdv64(d, causal, N, heads * N // 256)
+    for causal, N, heads, d, _ in S.FORWARD + S.FORWARD_4_WAVE:
+        assert bool(D.t_fwd(d, causal, N, heads * N // 256)) == ((causal, N, heads, d, d) not in S.FORWARD_4_WAVE), (causal, N, heads, d)
+    for causal, N, heads, d in S.BACKWARD + S.BACKWARD_4_WAVE:
+        want = (causal, N, heads, d) in S.BACKWARD
+        assert bool(D.t_dq(d, causal, N, heads * N // 256)) == want
+        assert d != 64 or bool(D.t_dkdv64(d, causal, N, heads * N // 256)) == want
     for causal, d, N, times in E.DQ_TILES:
         assert D.t_dq(d, causal, N, 4 * times * N // 256), (causal, N, d)
     for w, times in H.ONE_WAVE:

@@ -159,7 +159,7 @@ def test_literal_north_star_entry_points_on_live_tensors():
 
 
 # (causal, d, N, times four heads)
-DQ_TILES = [(True, 128, 4096, 3), (False, 128, 4096, 3), (True, 64, 8192, 3), (False, 64, 2048, 5)]
+DQ_TILES = [(True, 128, 4096, 5), (False, 128, 4096, 3), (True, 64, 8192, 3), (False, 64, 2048, 5)]
 
 
 @pytest.mark.parametrize("causal,d,N,times", DQ_TILES)

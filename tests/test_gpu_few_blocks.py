@@ -17,12 +17,13 @@ def _repeat(t, H):
     return t.repeat(1, 1, H // 2, 1).cuda()
 
 
-# 144, 208, 140, 320, 136, 224 blocks of 256 queries
-FORWARD = [(False, 2048, 18, 128, 128), (True, 2048, 26, 128, 128), (False, 1280, 28, 64, 64), (True, 8192, 10, 64, 64),
+# 144, 384, 140, 448, 136, 224 blocks of 256 queries
+FORWARD = [(False, 2048, 18, 128, 128), (True, 4096, 24, 128, 128), (False, 1280, 28, 64, 64), (True, 8192, 14, 64, 64),
            (False, 1024, 34, 192, 128), (True, 4096, 14, 192, 128)]
+FORWARD_4_WAVE = [(True, 2048, 26, 128, 128), (True, 8192, 10, 64, 64)]         # one round and a little more under the mask
 
 
-@pytest.mark.parametrize("causal,N,H,d,dv", FORWARD)
+@pytest.mark.parametrize("causal,N,H,d,dv", FORWARD + FORWARD_4_WAVE)
 @pytest.mark.parametrize("kind", ["normal", "growing", "climbing"])
 def test_forward(oracle, causal, N, H, d, dv, kind):
     import paper_2603_05451_amd as A
@@ -43,12 +44,12 @@ def test_forward(oracle, causal, N, H, d, dv, kind):
     assert np.abs(lse[:, :2].cpu().numpy()[:, :, rows] - rlse).max() <= LSE_ABS * max(1.0, np.abs(rlse).max() / 64)
 
 
-# 136, 136, 136, 200, 144, 320 blocks of 256 queries or keys; (d = 64, N = 1024 under the mask: dK/dV alone)
-BACKWARD = [(True, 1024, 34, 128), (False, 1024, 34, 128), (False, 1024, 34, 64), (True, 1024, 50, 64), (True, 2048, 18, 64),
-            (True, 8192, 10, 64)]
+# 328, 136, 136, 416, 448 blocks of 256 queries or keys
+BACKWARD = [(True, 1024, 82, 128), (False, 1024, 34, 128), (False, 1024, 34, 64), (True, 4096, 26, 64), (True, 8192, 14, 64)]
+BACKWARD_4_WAVE = [(True, 1024, 34, 128), (True, 1024, 50, 64), (True, 2048, 18, 64), (True, 8192, 10, 64)]
 
 
-@pytest.mark.parametrize("causal,N,H,d", BACKWARD)
+@pytest.mark.parametrize("causal,N,H,d", BACKWARD + BACKWARD_4_WAVE)
 def test_backward(oracle, causal, N, H, d):
     import paper_2603_05451_amd as A
     x = I.make_inputs(I.Workload("few", 1, 2, 2, N, d, d, causal, 320 + d + H))

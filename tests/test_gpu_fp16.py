@@ -24,7 +24,7 @@ CASES = [
 # wave (32 at (192, 128)), dK/dV with 64 keys per wave at d = 64 (the case without groups) and 32 elsewhere
 ONE_WAVE = [
     (I.Workload("h_d128_nc_2048_gqa", 1, 2, 1, 2048, 128, 128, False, 68), 9),
-    (I.Workload("h_d128_c_4096", 1, 1, 1, 4096, 128, 128, True, 69), 9),
+    (I.Workload("h_d128_c_4096", 1, 1, 1, 4096, 128, 128, True, 69), 25),
     (I.Workload("h_d64_nc_2048", 1, 2, 2, 2048, 64, 64, False, 71), 9),
     (I.Workload("h_d64_nc_2048_gqa", 1, 2, 1, 2048, 64, 64, False, 73), 9),
     (I.Workload("h_d192_nc_2048_gqa", 1, 2, 1, 2048, 192, 128, False, 72), 9),
