@@ -149,8 +149,9 @@ size_t attn_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d_qk, int d_v)
  *                            mask at least as many keys as queries.
  *   causal != 0: the last query of a sequence is aligned with its last key: key j is visible to
  *   query i iff j <= i + (keys - queries) of that sequence; j <= i for self-attention.
- *   The host never reads the lengths: a small kernel (in a forward call of at most 64 sequences with no
- *   more queries than sequences the attention kernel itself) turns them into tables of 128-row tiles,
+ *   The host never reads the lengths: a small kernel turns them into tables of 128-row tiles (a decode
+ *   step of at most 64 sequences -- no more queries than sequences, and H > Hkv, d_qk = 192 or more than
+ *   128 keys per query -- does so in its attention kernel),
  *   sequences with the longest loop per tile first (the longest-processing-time-first order of
  *   Sec. 3.3), and the attention kernels are launched over upper bounds of total_q/128 + B query
  *   tiles per head and total_k/128 + B key tiles per key/value head.

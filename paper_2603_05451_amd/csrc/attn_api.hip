@@ -393,8 +393,8 @@ int attn_varlen_bwd(const void* q, const void* k, const void* v, const void* o, 
 // strided entry points: equal-length batches (Nq queries and Nk keys per sequence) in any layout
 // whose head dim is contiguous, run by the variable-length kernels as if on the boundaries
 // cu_seqlens_q = {0, Nq, 2 Nq, ...}, cu_seqlens_k = {0, Nk, 2 Nk, ...}: the kernels compute the tile-table
-// entries of such a batch themselves (tile_entry in launch.h).  The workspace keeps the room that the
-// boundaries and tables used to take, so that its size is the packed call's.
+// entries of such a batch themselves (placed_entry and, for few queries, query_tile_entry in launch.h).  The workspace
+// keeps the room that the boundaries and tables used to take, so that its size is the packed call's.
 
 namespace {
 

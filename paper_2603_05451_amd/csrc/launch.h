@@ -19,7 +19,7 @@ struct VarlenStrides {
     Stride3 q, k, v, o, d_o, dq, dk, dv;
     long long lse_batch, lse_head;      // lse index = t + s * lse_batch + h * lse_head
     // equal-length batches (the strided calls): every sequence has nq queries and nk keys, and a kernel
-    // computes its tile-table entry (tile_entry) instead of reading one; 0: the tables say
+    // computes its tile-table entry (placed_entry) instead of reading one; 0: the tables say
     int nq, nk;
 };
 
@@ -30,15 +30,14 @@ constexpr int kPlanUsed = 0x5A17AB1E;
 // row_share); the other kernels pass over it like over an unused one.
 constexpr int kPlanHelp = 0x5A17AB1F;
 
-// Entry e of a tile table: seq = {first query row, query length, first key row, key length} of the sequence,
+// Entry e of the table of query tiles: seq = {first query row, query length, first key row, key length} of the sequence,
 // til = {tile of 128 rows inside it, kPlanUsed, sequence, helpers}; a sequence's tiles are listed last to first.
 // Equal-length batches need no table: the entry follows from e, which spares the strided calls the two
 // boundary kernels and the plan kernel (three launches in a row, 10 us of a call).
-template <bool QUERY_SIDE>
-__device__ __forceinline__ void tile_entry(const int4* __restrict__ plan, int e, const VarlenStrides& st, int4& seq, int4& til)
+__device__ __forceinline__ void query_tile_entry(const int4* __restrict__ plan, int e, const VarlenStrides& st, int4& seq, int4& til)
 {
     if (st.nq > 0) {
-        const int nt = ((QUERY_SIDE ? st.nq : st.nk) + 127) / 128;
+        const int nt = (st.nq + 127) / 128;
         const int b = e / nt;
         seq = make_int4(b * st.nq, st.nq, b * st.nk, st.nk);
         til = make_int4(nt - 1 - (e - b * nt), kPlanUsed, b, 0);
@@ -56,7 +55,7 @@ __device__ __forceinline__ HeadTile uniform_head_tile(const TileOrder& order, Pl
 }
 
 // The table entry and the head of a place in the launch's order (query_order, key_order); where equal lengths need no table,
-// the same arithmetic as tile_entry, for blocks of two tiles that of the first of them.
+// it follows from the place, for blocks of two tiles that of the first of them.
 template <bool QUERY_SIDE, int ROWS = 128>
 __device__ __forceinline__ void placed_entry(const int4* __restrict__ plan, const TileOrder& order, Place place, int max_tiles, int heads,
                                              const VarlenStrides& st, int& head, int4& seq, int4& til)
@@ -87,7 +86,7 @@ __device__ __forceinline__ bool row_share(const int4* __restrict__ plan, int e, 
                                           int i, int n, int4& seq, int4& til, int& unit, int& step)
 {
     constexpr int one_turn = 1 << 24;
-    tile_entry<true>(plan, e, st, seq, til);
+    query_tile_entry(plan, e, st, seq, til);
     unit = i;
     step = til.w != 0 ? one_turn : n;
     if (til.y == kPlanHelp) {
