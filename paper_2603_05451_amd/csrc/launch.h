@@ -47,29 +47,43 @@ __device__ __forceinline__ void query_tile_entry(const int4* __restrict__ plan, 
     }
 }
 
-// head_tile in scalar registers (the divisions run on the vector ALU).
+// (head, tile) of a place in a launch over equal lengths (the functions of dispatch.h in scalar registers).
+template <bool CAUSAL>
 __device__ __forceinline__ HeadTile uniform_head_tile(const TileOrder& order, Place place, int tiles)
 {
-    const HeadTile ht = head_tile(order, place, tiles);
+    HeadTile ht;
+    if constexpr (CAUSAL) {
+        TileOrder o = order;
+        asm volatile("" : "+s"(o.group), "+s"(o.own_group), "+s"(o.unit), "+s"(o.own));     // loaded at once, not each behind its branch
+        ht = head_tile(o, place, tiles);
+    } else {
+        ht = head_tile_in_shares(order, place, tiles);
+    }
+    return {__builtin_amdgcn_readfirstlane(ht.head), __builtin_amdgcn_readfirstlane(ht.tile)};
+}
+// (head, entry) of a place in a launch over a table.
+__device__ __forceinline__ HeadTile uniform_head_entry(const TileOrder& order, Place place, int entries)
+{
+    const HeadTile ht = head_tile_in_units(order, place, entries);
     return {__builtin_amdgcn_readfirstlane(ht.head), __builtin_amdgcn_readfirstlane(ht.tile)};
 }
 
 // The table entry and the head of a place in the launch's order (query_order, key_order); where equal lengths need no table,
 // it follows from the place, for blocks of two tiles that of the first of them.
-template <bool QUERY_SIDE, int ROWS = 128>
+template <bool QUERY_SIDE, bool CAUSAL, int ROWS = 128>
 __device__ __forceinline__ void placed_entry(const int4* __restrict__ plan, const TileOrder& order, Place place, int max_tiles, int heads,
                                              const VarlenStrides& st, int& head, int4& seq, int4& til)
 {
     if (st.nq > 0) {
         const int n = QUERY_SIDE ? st.nq : st.nk, nt = (n + ROWS - 1) / ROWS;
-        const HeadTile ht = uniform_head_tile(order, place, nt);
+        const HeadTile ht = uniform_head_tile<CAUSAL>(order, place, nt);
         const int b = ht.head / heads;
         head = ht.head - b * heads;
         seq = make_int4(b * st.nq, st.nq, b * st.nk, st.nk);
         // (query tiles: the last has the longest loop under the mask; key tiles, which the tables list backwards: the first)
         til = make_int4(QUERY_SIDE ? (ROWS / 128) * (nt - 1 - ht.tile) : (n + 127) / 128 - 1 - (ROWS / 128) * ht.tile, kPlanUsed, b, 0);
     } else {
-        const HeadTile ht = uniform_head_tile(order, place, max_tiles);
+        const HeadTile ht = uniform_head_entry(order, place, max_tiles);
         head = ht.head;
         seq = plan[2 * ht.tile];
         til = plan[2 * ht.tile + 1];

@@ -33,6 +33,17 @@ int t_equal(int block, int keys, int B, int H, int Hkv, int nq, int nk, int d, i
     const HeadTile t = head_tile(o, entry_place(o, rows, true, block, total), keys ? tiles_of_key_launch(a, rows) : tiles_of_query_launch(a, rows));
     return t.head * 65536 + t.tile * (rows / 128);
 }
+// Whether the short forms of head_tile give what it gives on the orders that they are for.
+int t_same(int heads, int tiles)
+{
+    const TileOrder s = share_order(heads, tiles), u = tile_order(heads, tiles);
+    for (int b = 0; b < heads * tiles; ++b) {
+        const HeadTile x = head_tile(s, block_place(s, b), tiles), y = head_tile_in_shares(s, block_place(s, b), tiles);
+        const HeadTile z = head_tile(u, block_place(u, b), tiles), w = head_tile_in_units(u, block_place(u, b), tiles);
+        if (x.head != y.head || x.tile != y.tile || z.head != w.head || z.tile != w.tile) return 0;
+    }
+    return 1;
+}
 int t_fwd_varlen(int d, int causal, int B, int Tq, int Tk, int H, int Hkv, int uniform)
 {
     const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, d, 128, uniform);
@@ -112,6 +123,7 @@ def test_order_of_blocks(D, heads, tiles, half_empty):
     Half empty: launches over tables, whose order is the same with and without the mask; an XCD's live places fall alike on
     the four positions modulo 4, and no XCD gets many fewer of them."""
     total = heads * tiles
+    assert D.t_same(heads, tiles)
     for causal, share, nbytes in ((0, 1, 1), (1, 1, 1), (1, 1, 5 << 20), (1, 4, 5 << 20), (1, 1, 1 << 40)):
         at = np.array([D.t_order(b, heads, tiles, share, nbytes, causal, half_empty) for b in range(total)])
         assert sorted(at) == list(range(total)), (causal, share, nbytes)
