@@ -30,7 +30,7 @@
  *   - Return value: ATTN_OK, or a negative code.  ATTN_EINVAL, ATTN_EUNSUPPORTED and
  *     ATTN_ETOOLARGE are found before anything is enqueued: no output has been touched.
  *     ATTN_ELAUNCH (the HIP runtime refused a launch or an attribute) can come from any of the
- *     launches of a call that has several (the backward pass: dQ kernel, then dK/dV, at d = 256 as a
+ *     launches of a call that has several (the backward pass beyond a few hundred keys: dQ kernel, then dK/dV, at d = 256 as a
  *     dV and a dK kernel; most variable-length calls: a small table kernel first; a variable-length
  *     or strided forward pass whose keys are divided: a merge kernel last, without which o and lse
  *     are untouched): the launches before the failed one stay enqueued and write their outputs (dq,
@@ -86,7 +86,9 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
  * dK and dV accumulated on chip over all query tiles and all query heads of the group: the loop
  * structure of paper Sec. 3.2.2; at d = 256 a dV and a dK kernel).  The paper accumulates dQ with
  * global atomics inside the dK/dV loop (Sec. 3.2.2-3.2.3); on MI355X those atomics are memory-side
- * and cost more than recomputing S and dP, so dQ has its own pass.  No atomics are used: results are bit-reproducible from run to run (the
+ * and cost more than recomputing S and dP, so dQ has its own pass -- except where one workgroup can hold all keys of a
+ * sequence (up to 512 at d = 64, 256 at 96 and 128, of enough sequences and heads or few queries): one kernel then
+ * makes S and dP once and sums dQ over the keys on chip, and the workspace is not used.  No atomics are used: results are bit-reproducible from run to run (the
  * property paper Sec. 3.2.4 obtains with semaphores). */
 int attn_bwd(const void* q, const void* k, const void* v, const void* o, const void* d_o,
              const float* lse, void* dq, void* dk, void* dv,
@@ -106,7 +108,9 @@ int attn_bwd_ex(const void* q, const void* k, const void* v, const void* o, cons
  * so a call whose mask includes ATTN_BWD_DQ launches no prepare kernel: the dQ kernel runs first
  * and ATTN_BWD_DKDV, of the same or of a later call, reads what it left.  attn_bwd_ex is
  * therefore two kernels (three at d = 256, where ATTN_BWD_DKDV is two); ATTN_BWD_PREPARE has an
- * effect only in a mask without ATTN_BWD_DQ. */
+ * effect only in a mask without ATTN_BWD_DQ.  At sizes whose whole backward pass is one kernel, a call for
+ * one pass runs that kernel and has it write the pass's results (the prepare kernel in front where -D and
+ * the base-2 LSE are to be left in the workspace): the same bits, each pass at the whole pass's time. */
 enum { ATTN_BWD_PREPARE = 1, ATTN_BWD_DKDV = 2, ATTN_BWD_DQ = 4, ATTN_BWD_ALL = 7 };
 int attn_bwd_phases(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                     const float* lse, void* dq, void* dk, void* dv,
@@ -233,7 +237,7 @@ int attn_varlen_bwd_dtype(int dtype, const void* q, const void* k, const void* v
  * causal != 0: the last query is aligned with the last key, key j is visible to query i iff
  * j <= i + Nk - Nq (the convention of the variable-length calls; the paper is silent on
  * Nq != Nk), and Nk >= Nq is required (ATTN_EINVAL otherwise).
- * Runs the variable-length kernels as on the sequence boundaries {0, Nq, 2 Nq, ...} and
+ * Runs the variable-length kernels (the backward pass of few keys: attn_bwd's kernel for those) as on the sequence boundaries {0, Nq, 2 Nq, ...} and
  * {0, Nk, 2 Nk, ...}, whose tiles the kernels number themselves; on contiguous [B, N, H, d] tensors with
  * Nq = Nk = N a multiple of 128 the results are bit-identical to attn_fwd_dtype / attn_bwd_dtype (the
  * forward call then is that call).

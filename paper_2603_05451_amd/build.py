@@ -30,6 +30,7 @@ SOURCES = [*[("attn_bwd_dq_q64.hip", f"attn_bwd_dq_q64_{f16}{varlen}.o", [f"-DAT
            ("attn_decode.hip", "attn_decode.o", VGPR_FORM),
            ("attn_bwd.hip", "attn_bwd.o", []),
            ("attn_bwd.hip", "attn_bwd_vgpr_form.o", ["-DATTN_BWD_VGPR_FORM_PART=1", *VGPR_FORM]),
+           ("attn_bwd_short.hip", "attn_bwd_short.o", []),
            ("attn_varlen.hip", "attn_varlen.o", []),
            ("exp2_emulated.hip", "exp2_emulated.o", [])]
 PROBE_SOURCES = [("probes.hip", "probes.o", [])]

@@ -102,6 +102,18 @@ int launch_bwd(const BwdArgs& a)
         part.phases = phases;
         return a.f16 ? f16k::launch_bwd_dims(part) : launch_bwd_dims(part);
     };
+    // In variable-length mode the copies are bounded by whole rows, so a row has to be as long as its stride at most:
+    // overlapping rows (sliding windows) stay with the general kernels.
+    const bool long_rows = a.st.q.row >= a.d_qk && a.st.k.row >= a.d_qk && a.st.v.row >= a.d_v && a.st.d_o.row >= a.d_v;
+    // Few keys: everything in one kernel, which needs nothing from the workspace.  A call for the dQ pass or the dK/dV pass alone runs it for
+    // that pass's results, and leaves -D and the base-2 LSE in the workspace where the split into passes says so.
+    if ((a.phases & 6) && (a.max_tiles == 0 || (a.st.nq > 0 && long_rows)) &&
+        bwd_short(a.d_qk, a.d_v, a.causal, a.max_tiles > 0 ? a.st.nq : a.N, a.max_tiles > 0 ? a.st.nk : a.N, a.B, a.H, a.Hkv)) {
+        if (a.phases != 7 && (a.phases & 5)) {
+            if (const int rc = generic(1)) return rc;
+        }
+        return launch_bwd_short(a);
+    }
     const bool d128 = a.d_qk == 128 && a.d_v == 128, d64 = a.d_qk == 64 && a.d_v == 64, d192 = a.d_qk == 192 && a.d_v == 128, d256 = a.d_qk == 256;
     // The dQ kernels with one wave per SIMD at a fixed length of N tokens.  (192, 128) and 256: the 64-query
     // kernel's fragments and accumulators do not fit; 32 queries per wave.
@@ -110,19 +122,17 @@ int launch_bwd(const BwdArgs& a)
     auto dq256_at = [&](int N) { return d256 && dq256_one_wave(a.causal, N, (long long)a.B * a.H); };
     bool dq_q64, dq_t32, dkdv_t32;
     if (a.max_tiles > 0) {
-        // Variable-length mode, by the mean numbers of queries and keys.  Their copies are bounded by whole rows, so a row has
-        // to be as long as its stride at most: overlapping rows (sliding windows) stay with the general kernels.
-        const bool rows = a.st.q.row >= a.d_qk && a.st.k.row >= a.d_qk && a.st.v.row >= a.d_v && a.st.d_o.row >= a.d_v;
+        // Variable-length mode, by the mean numbers of queries and keys.
         const int n = a.T / a.B, k = a.Tk / a.B;
         // Equal lengths in whole tiles promise the bits of the fixed-length call, whose dQ kernels differ by the
         // rounding of dP - D: the same choice there.
         const bool as_fixed = a.st.nq > 0 && a.st.nq == a.st.nk && a.st.nq % 128 == 0;
         const int64_t half = ((int64_t)a.T + 255) / 256 * a.H, blocks64 = (int64_t)a.max_tiles_k / 2 * a.Hkv;
-        const bool dq = rows && (as_fixed ? dq_q64_at(a.st.nq) || dq_t32_at(a.st.nq) || dq256_at(a.st.nq)
+        const bool dq = long_rows && (as_fixed ? dq_q64_at(a.st.nq) || dq_t32_at(a.st.nq) || dq256_at(a.st.nq)
                                           : dq_one_wave_varlen(a.d_qk, a.causal, n, k, half, a.st.nq > 0));
         dq_q64 = dq && (d128 || d64);
         dq_t32 = dq && (d192 || d256);
-        dkdv_t32 = rows && dkdv_one_wave_varlen(a.d_qk, a.causal, n, k, a.H / a.Hkv, blocks64);
+        dkdv_t32 = long_rows && dkdv_one_wave_varlen(a.d_qk, a.causal, n, k, a.H / a.Hkv, blocks64);
     } else {
         dq_q64 = dq_q64_at(a.N);
         dq_t32 = dq_t32_at(a.N) || dq256_at(a.N);

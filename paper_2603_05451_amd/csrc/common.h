@@ -42,6 +42,9 @@ __device__ __forceinline__ f32x16 mfma32(f16x8 a, f16x8 b, f32x16 c)      // v_m
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+// Lanes that share one row where -D = -rowsum(dO o O) is summed: a power of two (butterfly reduction) >= DV / 8.
+constexpr int prepare_lanes(int dv) { return dv / 8 <= 8 ? 8 : dv / 8 <= 16 ? 16 : 32; }
+
 // Row of a 32x32 accumulator register r for lane half h.
 __device__ __forceinline__ constexpr int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 

@@ -278,6 +278,37 @@ inline bool dkdv64_one_wave(bool causal, int N, long long b)
 inline bool dq256_one_wave(bool causal, int N, long long heads) { return !(causal && N == 128 && heads >= 128); }
 inline bool dkdv256_one_wave(int N, long long heads) { return !(N == 128 && heads >= 128); }
 
+// ---- Equal lengths, few keys: dQ, dK and dV in one kernel (attn_bwd_short_kernel.inc), a block per (sequence, KV head) that holds all its
+// keys, of four waves and two per CU up to 128 keys (d = 64: 256), of eight and one per CU beyond.  Share of the two kernels' time:
+//   few steps of 32 queries: one launch for two, in every number of blocks: 1 ... 3 steps 0.62 ... 0.88; 4 0.70 ... 0.97 (d = 64, more than
+//            256 keys 1.02); 5 0.74 ... 0.82 at d = 96 and 128 with 8 waves (0.80 and 0.88 with 4), 1.03 at d = 64, 6 0.87 ... 1.18
+//   more:    a block walks alone along queries that the two kernels spread over many, so it takes blocks enough to fill the chip:
+//            d = 64, up to 128 keys, 4 ... 16 steps  128 blocks 0.95 ... 1.29, 224 0.96 ... 1.03, 256 0.82 ... 0.99, 512 0.63 ... 0.66
+//            d = 64, 160 keys  160 blocks 0.76 ... 1.04, 224 0.73 ... 0.83; 200 keys  224 0.85 ... 1.01, 256 0.86 ... 0.95; 256 keys  256 0.91 ... 1.08,
+//            320 0.78 ... 0.82, 512 0.61 ... 0.79
+//            d = 64, up to 512 keys, rounds of 256: ragged 192 blocks 0.81 ... 0.94, 256 0.75 ... 0.90, 320 1.14 ... 1.17, 512 and 1024 0.85 ... 0.92;
+//            whole tiles under the mask 192 0.94 ... 1.04, 256 0.75 ... 0.86, 384 1.14, 448 1.02, 512 ... 1024 0.94 ... 0.98, without it 256 0.90, 512 ... 1024
+//            0.99 ... 1.07 (the dK/dV kernel in turns)
+//            d = 96  up to 128 keys 128 blocks 1.02 ... 1.15, 160 0.89 ... 1.00, 224 0.81 ... 0.90; up to 256 128 0.84 ... 1.15, 160 0.49 ... 0.86, 512 0.59 ... 0.68
+//            d = 128 up to 128 keys 160 blocks 1.00 ... 1.07, 224 0.88 ... 0.96, 512 0.54 ... 0.73; up to 256 128 0.74 ... 1.11, 160 0.45 ... 0.89, 256 0.42 ... 0.76,
+//            512 0.53 ... 0.85
+//            77 keys against 1000 queries  64 blocks 1.5 ... 1.9, 256 0.85 (d = 64) and 1.05 (128), 1024 0.61 and 0.72: waves without keys
+inline int short_keys(int d_qk, int d_v) { return d_qk != d_v ? 0 : d_qk == 64 ? 512 : d_qk <= 128 ? 256 : 0; }
+inline bool bwd_short(int d_qk, int d_v, bool causal, int nq, int nk, int B, int H, int Hkv)
+{
+    if (nk > short_keys(d_qk, d_v)) return false;
+    const int64_t blocks = (int64_t)B * Hkv, steps = (int64_t)(H / Hkv) * ((nq + 31) / 32);
+    if (steps <= (nk > 256 ? 3 : d_qk == 64 || nk <= 128 ? 4 : 5)) return true;
+    if (nk < 96) return blocks >= 1024;
+    if (nk > 256) {
+        const int64_t rounds = (blocks + 255) / 256;
+        const bool whole = nq == nk && nq % 128 == 0;
+        return (!whole || causal || rounds == 1) && blocks >= rounds * (whole ? 240 : 192);
+    }
+    if (nk <= 128) return blocks >= (d_qk == 64 ? 256 : d_qk == 96 ? 192 : 224);
+    return blocks >= (d_qk == 64 ? nk + nk / 5 : 160);
+}
+
 // ---- Variable-length calls, by the mean numbers of queries n and keys k per sequence (the host never sees the lengths).
 // Shares are of the whole backward pass, kernel of the rule against the general one, over equal lengths of 8 ... 8192 and
 // mixed ones, 4096 ... 65 536 tokens, H = 4/4 ... 16/16.

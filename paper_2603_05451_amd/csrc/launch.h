@@ -267,7 +267,10 @@ int launch_bwd_dkdv_t32(const BwdArgs& a);
 // The dQ kernel with one wave per SIMD and 32 queries per wave (head dims (192, 128) and 256; fixed length
 // N % 128 = 0, or variable-length mode as above); it also leaves -D and the base-2 LSE of every row in the workspace.
 int launch_bwd_dq_t32(const BwdArgs& a);
-// The same by element type (bf16 in attn::, fp16 in attn::f16k::) and mode: one translation unit each.
+// dQ, dK and dV in one kernel, one block per (sequence, KV head) (d_qk = d_v = 64 up to 512 keys, 96 or 128 up to 256; equal lengths, in
+// variable-length mode with row strides of at least a row); what it writes: dQ with phases & 4, dK and dV with phases & 2.
+int launch_bwd_short(const BwdArgs& a);
+// The kernels with one wave per SIMD by element type (bf16 in attn::, fp16 in attn::f16k::) and mode: one translation unit each.
 int run_bwd_dq_q64(const BwdArgs& a);
 int run_bwd_dq_t32(const BwdArgs& a);
 int run_bwd_dkdv_t32(const BwdArgs& a);

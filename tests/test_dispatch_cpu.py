@@ -58,6 +58,7 @@ int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, 
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
+int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
 int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
 {
     const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform);
@@ -357,6 +358,29 @@ def test_partly_filled_rounds_are_divided_where_it_pays(D, items, Nk, d, ratio):
     assert decode and (abs(ratio - 1) < 0.035 or nsplit == (3 if ratio < 1 else 1))
 
 
+# (d, causal, queries, keys, KV heads in all, query heads per KV head, one kernel over two): both sides of the lines
+MEASURED_SHORT = [(64, 0, 128, 128, 8, 1, 0.85), (64, 1, 128, 128, 128, 4, 1.22), (64, 1, 128, 128, 512, 4, 0.65), (64, 0, 100, 512, 64, 1, 0.96),
+                  (64, 0, 128, 512, 16, 1, 1.02), (64, 0, 160, 256, 16, 1, 1.03), (64, 0, 200, 200, 96, 1, 1.10), (64, 0, 200, 200, 320, 1, 0.72),
+                  (64, 0, 256, 256, 96, 1, 1.27), (64, 0, 256, 256, 512, 1, 0.79), (64, 1, 384, 384, 384, 1, 1.14), (64, 1, 512, 512, 256, 1, 0.86),
+                  (64, 0, 512, 512, 512, 1, 1.02), (64, 0, 512, 512, 256, 1, 0.90), (64, 0, 4096, 512, 64, 1, 2.47), (64, 0, 4096, 512, 256, 1, 0.85),
+                  (96, 0, 160, 256, 16, 1, 0.80), (96, 1, 100, 100, 128, 4, 1.08), (96, 1, 128, 128, 224, 4, 0.81), (96, 0, 256, 256, 128, 4, 1.15),
+                  (96, 0, 256, 256, 512, 1, 0.65), (128, 0, 128, 128, 8, 1, 0.87), (128, 0, 100, 100, 128, 4, 1.28), (128, 0, 128, 128, 256, 4, 0.85),
+                  (128, 0, 256, 256, 128, 1, 1.11), (128, 0, 256, 256, 256, 1, 0.76), (128, 0, 1000, 77, 256, 1, 1.05), (128, 0, 1000, 77, 1024, 1, 0.72),
+                  (128, 1, 256, 256, 512, 8, 0.58)]
+
+
+@pytest.mark.parametrize("d,causal,nq,nk,blocks,group,ratio", MEASURED_SHORT)
+def test_short_backward_rule_takes_the_faster_route(D, d, causal, nq, nk, blocks, group, ratio):
+    """(Within 4 % either choice will do.)"""
+    assert abs(ratio - 1) < 0.045 or bool(D.t_short(d, causal, nq, nk, 1, blocks * group, blocks)) == (ratio < 1)
+
+
+def test_short_backward_keys_fit_the_block(D):
+    """Never more keys than a block holds, and no other head dims, however many blocks."""
+    for d, most in ((64, 512), (96, 256), (128, 256), (192, 0), (256, 0)):
+        assert not D.t_short(d, 1, 1, most + 1, 1024, 64, 64) and (most == 0 or D.t_short(d, 1, 1, most, 1024, 64, 64))
+
+
 def test_parts_of_a_packed_step(D):
     assert route(D, 1, 1, 32768, 32, 8, 128, 128, 0) == (True, 16)              # a sequence alone: 128 blocks, not 1024
     assert route(D, 48, 48, 48 * 1700, 32, 8, 128, 128, 0) == (True, 3)
@@ -366,6 +390,7 @@ def test_parts_of_a_packed_step(D):
 
 def test_gpu_tests_reach_what_they_are_written_for(D):
     """The case lists of the GPU tests, through the rules: a kernel's tests stop being its tests when a line moves."""
+    import test_gpu_bwd_short as K
     import test_gpu_edge as E
     import test_gpu_few_blocks as S
     import test_gpu_fp16 as H
@@ -373,6 +398,10 @@ def test_gpu_tests_reach_what_they_are_written_for(D):
     import test_gpu_varlen as V
     import test_gpu_varlen_one_wave as W
     from test_gpu_decode import CHUNKS, FEW_KEYS, SHAPES, SLOTS
+    for d, nq, nk, group, Hkv, causal, _ in K.CASES:
+        assert D.t_short(d, causal, nq, nk, 1, Hkv * group, Hkv), (d, nq, nk, group, Hkv)
+    for d, N, B, causal in K.PASSES:
+        assert D.t_short(d, causal, N, N, B, 8, 8), (d, N, B)
     for w, times in F.Q64 + H.ONE_WAVE:
         assert D.t_fwd(w.dqk, w.causal, w.N, w.B * w.H * times * w.N // 256), w.name
     for causal, N, d, _, times, *_ in F.GROWING + F.STEPS:
