@@ -14,6 +14,7 @@ from functools import lru_cache
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn.so")
 _lib = None
+_native = None          # _binding: the well-formed calls, marshalled natively (csrc/binding.cpp); loaded with the library
 
 ATTN_OK, ATTN_EINVAL, ATTN_EUNSUPPORTED, ATTN_ELAUNCH = 0, -1, -2, -3
 
@@ -26,7 +27,7 @@ class AttnError(RuntimeError):
 
 def lib():
     """Load libattn.so (built in-tree by build.py); fail loudly when it is absent."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} not found: run `python -m paper_2603_05451_amd.build` "
@@ -86,8 +87,31 @@ def lib():
         L.attn_strerror.argtypes = [i]
         L.attn_strerror.restype = ctypes.c_char_p
         L.attn_version.restype = i
-        _lib = L
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise ImportError(f"{_HERE}/_binding.so is missing or does not load ({e}): run `python -m paper_2603_05451_amd.build`; "
+                              "there is no fallback path") from e
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        _binding.bind(*(address(f) for f in (L.attn_fwd_dtype, L.attn_bwd_phases, L.attn_bwd_dtype, L.attn_bwd_workspace_bytes, L.attn_varlen_fwd_dtype,
+                                             L.attn_varlen_bwd_dtype, L.attn_varlen_workspace_bytes, L.attn_fwd_strided, L.attn_bwd_strided,
+                                             L.attn_strided_workspace_bytes)),
+                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.nn.Parameter)
+        _lib, _native = L, _binding
     return _lib
+
+
+def _call():
+    if _native is None:
+        lib()
+    return _native
+
+
+def _done(r):
+    """Outputs of a native call, or its error."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def attn_strerror(code: int) -> str:
@@ -103,9 +127,9 @@ def _check(rc: int):
         raise AttnError(rc, attn_strerror(rc))
 
 
-# The marshalling below is most of a small call's time (three kernels of 5 us each against 37 us for forward and
-# backward of 2 heads x 128 tokens when every argument was wrapped in a ctypes object of its own and the stream
-# came from torch.cuda.current_stream()): plain integers, which ctypes converts by argtypes, and the raw stream.
+# Well-formed calls go through _binding (the first lines of each function below: None means that it left the call alone).
+# The Python text after them takes the rest -- tensor subclasses, numbers that are no floats, tables kept in a workspace -- and
+# says what is wrong with a call that is refused.
 def _stream(stream):
     """Raw hipStream_t of `stream`, or of the current device's current stream."""
     if stream is not None:
@@ -158,6 +182,9 @@ def attn_fwd(q, k, v, scale, causal, o=None, lse=None, stream=None):
     """q [B,N,H,d_qk], k [B,N,Hkv,d_qk], v [B,N,Hkv,d_v] bf16 (or all fp16) on the GPU ->
     (o [B,N,H,d_v] of the same type, lse [B,H,N] fp32).  Outputs are allocated with torch unless
     passed in."""
+    r = (_native or _call()).fwd(q, k, v, scale, causal, o, lse, stream)
+    if r is not None:
+        return _done(r)
     import torch
     B, N, H, dqk = q.shape
     Hkv, dv = k.shape[2], v.shape[3]
@@ -201,6 +228,9 @@ def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, worksp
     """Packed variable-length batch: q [Tq,H,d_qk], k [Tk,Hkv,d_qk], v [Tk,Hkv,d_v] bf16 (or all fp16),
     cu_seqlens [B+1] int32 (query rows; also the key rows unless cu_seqlens_k is given), all on the
     GPU -> (o [Tq,H,d_v], lse [H,Tq] fp32)."""
+    r = (_native or _call()).varlen_fwd(q, k, v, cu_seqlens, scale, causal, o, lse, workspace, stream, cu_seqlens_k)
+    if r is not None:
+        return _done(r)
     import torch
     T, H, dqk = q.shape
     Tk, Hkv, dv = k.shape[0], k.shape[1], v.shape[2]
@@ -230,6 +260,9 @@ def attn_varlen_fwd(q, k, v, cu_seqlens, scale, causal, o=None, lse=None, worksp
 def attn_varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, scale, causal, dq=None, dk=None, dv=None, workspace=None,
                     stream=None, cu_seqlens_k=None, B=None):
     """Backward of attn_varlen_fwd: returns (dq [Tq,H,d_qk], dk [Tk,Hkv,d_qk], dv [Tk,Hkv,d_v])."""
+    r = (_native or _call()).varlen_bwd(q, k, v, o, d_o, lse, cu_seqlens, scale, causal, dq, dk, dv, workspace, stream, cu_seqlens_k)
+    if r is not None:
+        return _done(r)
     import torch
     T, H, dqk = q.shape
     Tk, Hkv, dv_ = k.shape[0], k.shape[1], v.shape[2]
@@ -287,6 +320,9 @@ def attn_fwd_strided(q, k, v, scale, causal, o=None, lse=None, workspace=None, s
     last axis contiguous), e.g. x.permute(0, 2, 1, 3) of a [B,H,N,d] tensor; any Nq, Nk >= 1 (under a
     causal mask the last query sees the last key, Nk >= Nq).  o may be a view too (default: a new
     contiguous [B,Nq,H,d_v]); lse [B,H,Nq] fp32 contiguous."""
+    r = (_native or _call()).fwd_strided(q, k, v, scale, causal, o, lse, workspace, stream)
+    if r is not None:
+        return _done(r)
     import torch
     B, N, H, dqk = q.shape
     Nk, Hkv, dv = k.shape[1], k.shape[2], v.shape[3]
@@ -309,6 +345,9 @@ def attn_fwd_strided(q, k, v, scale, causal, o=None, lse=None, workspace=None, s
 def attn_bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq=None, dk=None, dv=None, workspace=None, stream=None):
     """Backward of attn_fwd_strided; every tensor may be a view.  Gradients default to new
     contiguous tensors shaped like q, k and v."""
+    r = (_native or _call()).bwd_strided(q, k, v, o, d_o, lse, scale, causal, dq, dk, dv, workspace, stream)
+    if r is not None:
+        return _done(r)
     import torch
     B, N, H, dqk = q.shape
     Nk, Hkv, dv_ = k.shape[1], k.shape[2], v.shape[3]
@@ -347,6 +386,9 @@ def attn_bwd(q, k, v, o, do, lse, scale, causal, dq=None, dk=None, dv=None, work
              stream=None, phases=ATTN_BWD_ALL):
     """Gradients dq, dk, dv (bf16, layouts of q, k, v) from do, the forward's o and lse.
     phases != ATTN_BWD_ALL maps to attn_bwd_phases (per-kernel timing only)."""
+    r = (_native or _call()).bwd(q, k, v, o, do, lse, scale, causal, dq, dk, dv, workspace, stream, phases)
+    if r is not None:
+        return _done(r)
     import torch
     B, N, H, dqk = q.shape
     Hkv, dvd = k.shape[2], v.shape[3]

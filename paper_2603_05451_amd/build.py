@@ -1,10 +1,13 @@
 """Compile the HIP sources into libattn.so (the attention library) and libattn_probes.so (measurement
-probes, a library of their own) next to this file (hipcc, gfx950 only)."""
+probes, a library of their own) next to this file (hipcc, gfx950 only), and the Python binding's native part,
+_binding.so (host compiler, torch's headers)."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import shutil
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -12,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattn.so")
 PROBES_LIB = os.path.join(HERE, "libattn_probes.so")
+BINDING = os.path.join(HERE, "_binding.so")
 # VGPR_FORM: kernels that run one wave per SIMD may use the accumulation registers (AGPRs) next to
 # the 256 vector registers; by default the compiler then gives every MFMA an AGPR accumulator,
 # and where vector instructions read those accumulators every tile (softmax on the scores, dS from
@@ -47,7 +51,14 @@ def _run(cmd, verbose):
         if keep:
             print("\n".join(keep))
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed building libattn.so: " + " ".join(cmd[-3:]))
+        raise RuntimeError("compiler failed building libattn.so or _binding.so: " + " ".join(cmd[-3:]))
+
+
+def binding_command(out: str) -> list:
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
+    return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-w", *("-I" + d for d in include),
+            os.path.join(CSRC, "binding.cpp"), "-o", out, "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
 
 
 def build_library(verbose: bool = False) -> str:
@@ -57,7 +68,8 @@ def build_library(verbose: bool = False) -> str:
     tmp = tempfile.mkdtemp(prefix="libattn_build_")
     try:
         every = SOURCES + PROBE_SOURCES
-        jobs = [[hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(tmp, obj)]
+        binding = os.path.join(tmp, "_binding.so")
+        jobs = [binding_command(binding)] + [[hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(tmp, obj)]
                 for src, obj, extra in every]
         with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1, 8)) as pool:
             list(pool.map(lambda c: _run(c, verbose), jobs))
@@ -65,6 +77,8 @@ def build_library(verbose: bool = False) -> str:
             objs = [os.path.join(tmp, obj) for _, obj, _ in sources]
             _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib + ".tmp", *objs], verbose)
             os.replace(lib + ".tmp", lib)
+        shutil.copyfile(binding, BINDING + ".tmp")
+        os.replace(BINDING + ".tmp", BINDING)
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
     return LIB

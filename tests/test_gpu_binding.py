@@ -1,0 +1,96 @@
+"""GPU tests of the binding's native part (csrc/binding.cpp) against the Python text of the same functions: same outputs, same objects back, same
+refusals; calls that it leaves to the Python text."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+class _Nobody:
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _both(monkeypatch, call):
+    import paper_2603_05451_amd as A
+    A.lib()
+    native = call(A)
+    with monkeypatch.context() as m:
+        m.setattr(A, "_native", _Nobody())
+        python = call(A)
+    torch.cuda.synchronize()
+    return native, python
+
+
+def _t(*shape, dtype=torch.bfloat16, seed=0):
+    return torch.randn(*shape, generator=torch.Generator("cpu").manual_seed(seed + len(shape))).to(dtype).cuda()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("given", [False, True])
+def test_same_outputs(monkeypatch, dtype, given):
+    B, N, H, Hkv, d = 2, 256, 4, 2, 64
+    q, k, v, do = (_t(B, N, h, d, dtype=dtype, seed=h) for h in (H, Hkv, Hkv, H))
+    qv = _t(B, H, 100, d, dtype=dtype).transpose(1, 2)                          # views; more keys than queries
+    kv = [_t(B, Hkv, 150, d, dtype=dtype, seed=i).transpose(1, 2) for i in (1, 2)]
+    cu = torch.tensor([0, 100, 512], dtype=torch.int32, device="cuda")
+    p = lambda t: t.reshape(B * N, *t.shape[2:])
+    new = lambda *ts: [torch.full_like(t, float("nan")) for t in ts] if given else [None] * len(ts)
+
+    def calls(A):
+        out = []
+        o, lse = (torch.empty_like(q), torch.empty(B, H, N, device="cuda")) if given else (None, None)
+        a = A.attn_fwd(q, k, v, 0.125, True, o, lse)
+        assert not given or (a[0] is o and a[1] is lse)
+        ws = torch.empty(A.attn_bwd_workspace_bytes(B, H, Hkv, N, d, d), dtype=torch.uint8, device="cuda") if given else None
+        g = new(q, k, v)
+        b = A.attn_bwd(q, k, v, a[0], do, a[1], 0.125, True, *g, ws, stream=torch.cuda.current_stream() if given else None)
+        assert not given or all(x is y for x, y in zip(b, g))
+        out += [*a, *b]
+        f = A.attn_varlen_fwd(p(q), p(k), p(v), cu, 0.125, True, cu_seqlens_k=cu if given else None)
+        out += [*f, *A.attn_varlen_bwd(p(q), p(k), p(v), f[0], p(do), f[1], cu, 0.125, True, *(p(x) if given else x for x in new(q, k, v)))]
+        s = A.attn_fwd_strided(qv, *kv, 0.125, True, o=torch.empty_like(qv) if given else None)
+        g = new(qv, *kv)
+        g[1] = None                                                             # one of three missing
+        out += [*s, *A.attn_bwd_strided(qv, *kv, s[0], s[0], s[1], 0.125, True, *g)]
+        return out
+
+    native, python = _both(monkeypatch, calls)
+    assert len(native) == len(python) == 15
+    for x, y in zip(native, python):
+        assert type(x) is torch.Tensor and x.shape == y.shape and x.stride() == y.stride() and x.dtype == y.dtype and not x.requires_grad
+        assert torch.equal(x, y) and torch.isfinite(x.float()).all()
+
+
+def test_same_refusals(monkeypatch):
+    q = _t(1, 128, 2, 64)
+    lse = torch.empty(1, 2, 128, device="cuda")
+    cu = torch.tensor([0, 128], dtype=torch.int32, device="cuda")
+    bad = [lambda A: A.attn_fwd(q, q[:, :, ::2], q, 0.1, False), lambda A: A.attn_fwd(q, q.half(), q, 0.1, False), lambda A: A.attn_fwd(q.cpu(), q, q, 0.1, False),
+           lambda A: A.attn_fwd(q, q, q, -1.0, False), lambda A: A.attn_fwd(q[:, :100].contiguous(), *[q[:, :100].contiguous()] * 2, 0.1, False),
+           lambda A: A.attn_fwd(q, q, q, 0.1, False, lse=lse.half()), lambda A: A.attn_bwd(q, q, q, q, q[:, :64], lse, 0.1, False),
+           lambda A: A.attn_bwd(q, q, q, q, q, lse, 0.1, False, phases=9), lambda A: A.attn_bwd(q, q, q, q, q, lse, 0.1, False, workspace=torch.empty(8, device="cuda")),
+           lambda A: A.attn_varlen_fwd(q[0], q[0], q[0], cu.long(), 0.1, False), lambda A: A.attn_varlen_fwd(q[0], q[0], q[0], cu, 0.1, False, cu_seqlens_k=cu[:1]),
+           lambda A: A.attn_fwd_strided(q, q[..., ::2], q, 0.1, False), lambda A: A.attn_fwd_strided(q, q[:, :64], q[:, :64], 0.1, True),
+           lambda A: A.attn_bwd_strided(q, q, q, q, q, lse, 0.1, False, dq=q[:, :64])]
+    for i, f in enumerate(bad):
+        def said(A):
+            with pytest.raises((ValueError, A.AttnError)) as e:
+                f(A)
+            return type(e.value), str(e.value)
+        native, python = _both(monkeypatch, said)
+        assert native == python, i
+
+
+def test_left_to_the_python_text(monkeypatch):
+    """Numbers that are no floats, parameters and tensor subclasses: the results of the plain call."""
+    import paper_2603_05451_amd as A
+
+    class Mine(torch.Tensor):
+        pass
+
+    q = _t(1, 128, 2, 64)
+    ref = A.attn_fwd(q, q, q, 1.0, True)[0]
+    for a in ((q, q, q, 1, 1), (torch.nn.Parameter(q), q, q, torch.tensor(1.0), True), (q.as_subclass(Mine), q, q, 1.0, True)):
+        o, _ = A.attn_fwd(*a)
+        assert torch.equal(o.as_subclass(torch.Tensor), ref) and not o.requires_grad
