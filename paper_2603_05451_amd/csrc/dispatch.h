@@ -411,9 +411,12 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
             const int64_t even = (1023 + items) / items, alone = (127 + Hkv * nsub) / (Hkv * nsub);
             r.nsplit = clamp(even < alone ? even : alone, (steps + 2) / 3);
         } else if (items < 128) {
-            // 128 blocks reach the memory's rate; parts below four steps cost more than they spread
-            // (B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
-            r.nsplit = clamp((127 + items) / items, steps / 4);
+            // 128 blocks reach the memory's rate.  Parts of two steps and more (d = 64: three, 256: one), from six, for a part costs its
+            // first loads and the merge (us, parts of four steps at least -> these: 4 x 1000 keys, Hkv = 8, d = 128 11.1 -> 9.7, 1 x 1000
+            // 11.0 -> 9.7, 2 x 1316, Hkv = 2, d = 96 11.4 -> 9.4, 2 x 2000, d = 64 10.0 -> 9.5, 2 x 1000, d = 256 16.1 -> 11.6; 4 x 600, Hkv = 16,
+            // d = 64 7.8 whole, 9.2 in two; B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
+            const int64_t least = d_qk == 64 ? 3 : d_qk > 192 ? 1 : 2;
+            r.nsplit = clamp((127 + items) / items, steps >= (d_qk > 192 ? 3 : 6) ? steps / least : 1);
         } else if (items > 256 && items < 1024) {
             // A last round of 256 that leaves CUs idle, in three parts per sequence, where the keys are long enough and
             // the round empty enough to pay for the partial results (three parts against one, 264 ... 320 / 352, 384 /
@@ -427,12 +430,18 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
     } else if (Tk > Tq) {
         // (self-attention is never divided: on whole tiles its bits are those of the fixed-length call where both run the
         // 128-row kernel)
-        // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, but not below 16
-        // tiles of 64 keys, for the partial results travel through memory in fp32 (512 queries of 32 heads
-        // against 8 k keys: 155 us whole, 92 in 2, 86 in 4, 95 in 8; 2048 of 16 heads against themselves, whose
-        // loops are half as long: 42 whole, 49 in 2)
+        // Fewer blocks than the chip holds (two per CU, one at d = 256): divide the key loops, for the partial results travel
+        // through memory in fp32: into parts of at least 4 tiles of 64 keys, from 12, while the blocks have a CU each, of at
+        // least 16 where two share one (us, whole -> parts: 512 queries of 32 heads against 8 k keys 155 -> 92 in 2, 86 in 4, 95 in 8; 59 of 16
+        // against 1687, B = 3, d = 96 25.9 -> 15.7 in 5; 34 of 16 against 1359, B = 2, d = 256 49.7 -> 23.9 in 5; 100 of 32 against 2000
+        // 36.6 -> 20; 128 of 16 against 2000, B = 2 37.7 -> 19.2 in 7; 1000 of 8 against 4000 36.7 in 3, 32.2 in 4, 33.4 in 8; 600 of 8 against
+        // 1200, d = 64 16.8 -> 14.1 in 3; 128 queries of 32 heads against 600 keys 15.7 whole, 16.5 in 2; 500 of 16 against 700 16.9 and 19.4;
+        // two per CU: 200 of 16 against 3000, B = 4 55.6 whole, 41.4 in 2, 44.6 in 4, 100 of 32 against 4000 65, 53 in 3, 47 in 4; 2048 of 16 heads
+        // against themselves, whose loops are half as long: 42 whole, 49 in 2)
         const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
-        r.nsplit = clamp((d_qk > 192 ? 256 : 512) / blocks, (Nk - Nq / 2) / (16 * 64));
+        const int64_t tiles = (Nk - Nq / 2) / 64;
+        const int alone = clamp(256 / blocks, tiles >= 12 ? tiles / 4 : 1), shared = clamp((d_qk > 192 ? 256 : 512) / blocks, tiles / 16);
+        r.nsplit = alone > shared ? alone : shared;
     }
     return r;
 }

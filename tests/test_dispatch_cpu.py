@@ -381,6 +381,21 @@ def test_short_backward_keys_fit_the_block(D):
         assert not D.t_short(d, 1, 1, most + 1, 1024, 64, 64) and (most == 0 or D.t_short(d, 1, 1, most, 1024, 64, 64))
 
 
+# (B, H, Hkv, queries, keys, d, parts): one CU per block, parts of four tiles; two per CU, of sixteen; loops too short to divide
+@pytest.mark.parametrize("B,H,Hkv,Nq,Nk,d,parts", [(3, 16, 2, 59, 1687, 96, 5), (2, 16, 16, 34, 1359, 256, 5), (1, 32, 8, 512, 8192, 128, 4), (1, 8, 8, 1000, 4000, 128, 4),
+                                                   (4, 16, 16, 200, 3000, 128, 2), (4, 32, 8, 100, 4000, 128, 3), (1, 32, 8, 128, 600, 128, 1),
+                                                   (1, 16, 16, 500, 700, 128, 1), (16, 16, 4, 100, 1500, 128, 1), (8, 32, 8, 200, 6000, 128, 1)])
+def test_parts_of_a_chunk(D, B, H, Hkv, Nq, Nk, d, parts):
+    assert route(D, B, B * Nq, B * Nk, H, Hkv, d, d, 1) == (False, parts)
+
+
+# (B, H, Hkv, keys, d, parts)
+@pytest.mark.parametrize("B,H,Hkv,Nk,d,parts", [(4, 8, 8, 1000, 128, 4), (1, 8, 8, 1000, 128, 4), (2, 8, 2, 1316, 96, 5), (2, 8, 8, 2000, 64, 5), (4, 16, 16, 600, 64, 1),
+                                                (2, 8, 8, 1000, 256, 8), (16, 32, 8, 1000, 128, 1), (8, 16, 4, 273, 64, 1), (1, 32, 8, 32768, 128, 16)])
+def test_parts_of_a_decode_step_of_few_blocks(D, B, H, Hkv, Nk, d, parts):
+    assert route(D, B, B, B * Nk, H, Hkv, d, d, 1) == (True, parts)
+
+
 def test_parts_of_a_packed_step(D):
     assert route(D, 1, 1, 32768, 32, 8, 128, 128, 0) == (True, 16)              # a sequence alone: 128 blocks, not 1024
     assert route(D, 48, 48, 48 * 1700, 32, 8, 128, 128, 0) == (True, 3)
