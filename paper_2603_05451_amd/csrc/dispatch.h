@@ -272,6 +272,15 @@ inline bool dkdv64_one_wave(bool causal, int N, long long b)
     return N >= 4096 && b > 384;        // (mask: one round 1.08 ... 1.17, b = 288 ... 384 0.98 ... 1.07, beyond 0.94 ... 1.02, N = 3072 and less 0.98 ... 1.19)
 }
 
+// The general kernels at d = 64, three blocks of 4 waves per CU and not two, where there are more blocks than two per CU hold; loop = mean
+// number of rows that a block walks.  (Share of the whole backward pass.  Variable length, no mask 0.90 ... 1.00, mask 0.86 ... 1.00; fixed length
+// 0.96 ... 1.00 and 0.95 ... 1.00.  Up to 512 blocks 1.00 ... 1.045, and under the mask 528 ... 640 blocks 0.96 ... 1.06: a block alone or beside
+// one other misses what the wider kernel reads ahead.  Dk and dV of 700 keys: 60 queries 1.05 (mask 0.97), 100 ... 128 1.01 and 1.02, 130 0.94.)
+inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop)
+{
+    return d_qk == 64 && loop > 128 && blocks > (causal ? 640 : 512);
+}
+
 // d = 256, the pipelined kernels with one wave per SIMD against the general ones (one block of 128 rows per CU both):
 // 0.65 ... 0.97 but for single-tile sequences in more than half a round (N = 128, 128 ... 1024 blocks: dK/dV 1.02 ...
 // 1.09, dQ 1.01 ... 1.05 under the mask and 0.87 ... 0.95 without).

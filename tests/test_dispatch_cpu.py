@@ -58,6 +58,7 @@ int t_dq(int d, int causal, int N, long long b) { return dq_one_wave(d, causal, 
 int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(causal, N, b); }
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
+int t_lean(int d, int causal, long long blocks, long long loop) { return lean_blocks(d, causal, blocks, loop); }
 int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
 int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
 {
@@ -381,6 +382,14 @@ def test_short_backward_keys_fit_the_block(D):
         assert not D.t_short(d, 1, 1, most + 1, 1024, 64, 64) and (most == 0 or D.t_short(d, 1, 1, most, 1024, 64, 64))
 
 
+# (causal, blocks, rows that a block walks, three blocks per CU over two), d = 64: both sides of the lines
+@pytest.mark.parametrize("causal,blocks,loop,ratio", [(0, 512, 1024, 1.02), (0, 528, 384, 0.92), (0, 576, 1000, 0.93), (0, 640, 2000, 0.95), (1, 528, 384, 1.06), (1, 576, 1000, 1.03),
+                                                      (1, 640, 2000, 1.05), (1, 704, 1000, 0.93), (1, 1088, 1024, 0.90), (0, 6144, 60, 1.05), (0, 6144, 130, 0.94)])
+def test_lean_backward_rule(D, causal, blocks, loop, ratio):
+    assert bool(D.t_lean(64, causal, blocks, loop)) == (ratio < 1)
+    assert not any(D.t_lean(d, causal, blocks, loop) for d in (96, 128, 192, 256))
+
+
 # (B, H, Hkv, queries, keys, d, parts): one CU per block, parts of four tiles; two per CU, of sixteen; loops too short to divide
 @pytest.mark.parametrize("B,H,Hkv,Nq,Nk,d,parts", [(3, 16, 2, 59, 1687, 96, 5), (2, 16, 16, 34, 1359, 256, 5), (1, 32, 8, 512, 8192, 128, 4), (1, 8, 8, 1000, 4000, 128, 4),
                                                    (4, 16, 16, 200, 3000, 128, 2), (4, 32, 8, 100, 4000, 128, 3), (1, 32, 8, 128, 600, 128, 1),
@@ -405,6 +414,7 @@ def test_parts_of_a_packed_step(D):
 
 def test_gpu_tests_reach_what_they_are_written_for(D):
     """The case lists of the GPU tests, through the rules: a kernel's tests stop being its tests when a line moves."""
+    import test_gpu_bwd_lean as L
     import test_gpu_bwd_short as K
     import test_gpu_edge as E
     import test_gpu_few_blocks as S
@@ -417,6 +427,9 @@ def test_gpu_tests_reach_what_they_are_written_for(D):
         assert D.t_short(d, causal, nq, nk, 1, Hkv * group, Hkv), (d, nq, nk, group, Hkv)
     for d, N, B, causal in K.PASSES:
         assert D.t_short(d, causal, N, N, B, 8, 8), (d, N, B)
+    for nq, nk, group, Hkv, causal, _ in L.CASES:
+        assert D.t_lean(64, causal, (nk + 127) // 128 * Hkv, nq * group) and not D.t_short(64, causal, nq, nk, 1, Hkv * group, Hkv), (nq, nk, Hkv)
+        assert not D.t_lean(64, causal, (nk + 127) // 128 * 2, nq * group) and not D.t_short(64, causal, nq, nk, 1, 2 * group, 2), (nq, nk)
     for w, times in F.Q64 + H.ONE_WAVE:
         assert D.t_fwd(w.dqk, w.causal, w.N, w.B * w.H * times * w.N // 256), w.name
     for causal, N, d, _, times, *_ in F.GROWING + F.STEPS:
