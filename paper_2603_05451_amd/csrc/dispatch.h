@@ -449,7 +449,8 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
         // against themselves, whose loops are half as long: 42 whole, 49 in 2)
         const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
         const int64_t tiles = (Nk - Nq / 2) / 64;
-        const int alone = clamp(256 / blocks, tiles >= 12 ? tiles / 4 : 1), shared = clamp((d_qk > 192 ? 256 : 512) / blocks, tiles / 16);
+        // (a packed batch may hold any lengths: parts of 16 tiles of the mean, and the workspace that this needs)
+        const int alone = clamp(256 / blocks, uniform && tiles >= 12 ? tiles / 4 : 1), shared = clamp((d_qk > 192 ? 256 : 512) / blocks, tiles / 16);
         r.nsplit = alone > shared ? alone : shared;
     }
     return r;

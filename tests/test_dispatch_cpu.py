@@ -406,6 +406,8 @@ def test_parts_of_a_decode_step_of_few_blocks(D, B, H, Hkv, Nk, d, parts):
 
 
 def test_parts_of_a_packed_step(D):
+    assert route(D, 3, 1000, 5000, 4, 2, 128, 128, 0) == (False, 1)             # a packed chunk: parts of 16 tiles
+    assert route(D, 3, 1000, 10000, 4, 2, 128, 128, 0) == (False, 3)
     assert route(D, 1, 1, 32768, 32, 8, 128, 128, 0) == (True, 16)              # a sequence alone: 128 blocks, not 1024
     assert route(D, 48, 48, 48 * 1700, 32, 8, 128, 128, 0) == (True, 3)
     assert route(D, 512, 512, 512 * 64, 16, 16, 64, 64, 0)[0] is False          # tiny caches of many heads
