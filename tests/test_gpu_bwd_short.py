@@ -95,3 +95,17 @@ def test_passes_compose(d, N, B, causal):
             A.attn_bwd(q, k, v, o, do, lse, d ** -0.5, causal, *got, ws, phases=p)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, ref)), order
+
+
+@pytest.mark.parametrize("d,N,Hkv,row", [(64, 128, 256, 40), (64, 256, 320, 70), (64, 512, 240, 300), (96, 250, 160, 133), (128, 128, 224, 5), (128, 256, 160, 200)])
+def test_a_query_that_is_no_number(d, N, Hkv, row):
+    """Under the mask it reaches the dV of the keys that it sees and of no other."""
+    import paper_2603_05451_amd as A
+    _, (q, k, v, do) = _inputs(d, N, N, 1, Hkv, "bhnd", torch.bfloat16, 990 + d)
+    o, lse = A.attn_fwd_strided(q, k, v, d ** -0.5, True)
+    clean = A.attn_bwd_strided(q, k, v, o, do, lse, d ** -0.5, True)[2]
+    q[:, row] = float("nan")
+    o, lse = A.attn_fwd_strided(q, k, v, d ** -0.5, True)
+    dv = A.attn_bwd_strided(q, k, v, o, do, lse, d ** -0.5, True)[2]
+    torch.cuda.synchronize()
+    assert torch.isnan(dv[:, :row + 1].float()).all() and torch.equal(dv[:, row + 1:], clean[:, row + 1:])
