@@ -109,3 +109,21 @@ def test_a_query_that_is_no_number(d, N, Hkv, row):
     dv = A.attn_bwd_strided(q, k, v, o, do, lse, d ** -0.5, True)[2]
     torch.cuda.synchronize()
     assert torch.isnan(dv[:, :row + 1].float()).all() and torch.equal(dv[:, row + 1:], clean[:, row + 1:])
+
+
+@pytest.mark.parametrize("d,Nq,Nk,causal", [(64, 33, 40, True), (64, 70, 200, False), (64, 90, 300, True), (64, 50, 512, False), (96, 33, 97, False), (96, 100, 200, True),
+                                            (128, 50, 100, True), (128, 97, 250, False)])
+def test_a_key_that_nobody_sees(d, Nq, Nk, causal):
+    """A row of K whose scores are all -inf has P = 0 everywhere, in the rows past the end of the last query tile, too: dK = dV = 0 there, and
+    the other keys' gradients are those of the same keys with a row of finite scores so low that P = 0."""
+    import paper_2603_05451_amd as A
+    _, (q, k, v, do) = _inputs(d, Nq, Nk, 1, 2, "room", torch.bfloat16, 995 + d)
+    q = q.abs() + 0.5
+    got = []
+    for low in (-1e4, float("-inf")):
+        k[:, 5] = low
+        o, lse = A.attn_fwd_strided(q, k, v, d ** -0.5, causal)
+        got.append(A.attn_bwd_strided(q, k, v, o, do, lse, d ** -0.5, causal)[1:])
+    torch.cuda.synchronize()
+    for what, a, b in zip(("dK", "dV"), *got):
+        assert torch.isfinite(b.float()).all() and (b[:, 5] == 0).all() and torch.equal(a, b), what
