@@ -390,6 +390,7 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
     FwdRoute r{false, 1, 1};
     const int64_t G = H / Hkv, Nq = Tq / B, Nk = Tk / B;
     auto clamp = [](int64_t n, int64_t most) { return (int)(n < 1 || most < 1 ? 1 : n < most ? n : most); };
+    auto root = [](int64_t n) { int64_t x = 0; while ((x + 1) * (x + 1) <= n) ++x; return x; };
     // Decode: a (sequence, KV head) is nsub groups of 32 rows there and G tiles of 128 rows in attn_fwd_kernel,
     // at about the same cost per group as per tile (B = 4, H = 32/8, Nk = 4096, d = 128: Nq = 16 31 us against
     // 44, Nq = 24 34 against 44, Nq = 32 45 against 45; G = 1: Nq = 64 46 against 41).  In a packed batch only
@@ -424,8 +425,16 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
             // first loads and the merge (us, parts of four steps at least -> these: 4 x 1000 keys, Hkv = 8, d = 128 11.1 -> 9.7, 1 x 1000
             // 11.0 -> 9.7, 2 x 1316, Hkv = 2, d = 96 11.4 -> 9.4, 2 x 2000, d = 64 10.0 -> 9.5, 2 x 1000, d = 256 16.1 -> 11.6; 4 x 600, Hkv = 16,
             // d = 64 7.8 whole, 9.2 in two; B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
-            const int64_t least = d_qk == 64 ? 3 : d_qk > 192 ? 1 : 2;
-            r.nsplit = clamp((127 + items) / items, steps >= (d_qk > 192 ? 3 : 6) ? steps / least : 1);
+            // A part's loop shrinks as the merge's grows: the best number grows with the root of the keys (us, one KV head, parts of two steps at
+            // least -> at most these: d = 128 32 k keys 24.2 in 128 -> 16.9 in 32, 21.0 in 16, 8 k 12.4 in 32, 12.0 in 16, 14.2 in 8; d = 64 32 k 19.5 in
+            // 85, 16.2 in 32, 20.0 in 16; (192, 128) 32 k 25.4 in 128, 19.3 in 48, 19.5 in 32; d = 256 32 k 28.7 in 128, 22.6 in 64, 24.9 in 32, 8 k
+            // 17.8 in 64, 15.5 in 32, 16.6 in 16)
+            const int64_t least = d_qk == 64 ? 3 : d_qk > 192 ? 1 : 2, most = root((d_qk > 192 ? 16 : d_qk > 128 ? 6 : 5) * steps);
+            const int64_t parts = steps / least < most ? steps / least : most;
+            r.nsplit = clamp((127 + items) / items, steps >= (d_qk > 192 ? 3 : 6) ? parts : 1);
+            // (two parts of few steps: 64 ... 112 items, 6 and 7 steps d = 96, 128, 192 1.00 ... 1.18 of one part, d = 256 3 ... 7 steps 0.98 ... 1.15;
+            // d = 64, 2 ... 112 items 0.99 ... 1.07; three and more 0.68 ... 1.01, from 8 steps 0.71 ... 0.97)
+            if (r.nsplit == 2 && steps < 8) r.nsplit = 1;
         } else if (items > 256 && items < 1024) {
             // A last round of 256 that leaves CUs idle, in three parts per sequence, where the keys are long enough and
             // the round empty enough to pay for the partial results (three parts against one, 264 ... 320 / 352, 384 /
@@ -448,12 +457,24 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
         // two per CU: 200 of 16 against 3000, B = 4 55.6 whole, 41.4 in 2, 44.6 in 4, 100 of 32 against 4000 65, 53 in 3, 47 in 4; 2048 of 16 heads
         // against themselves, whose loops are half as long: 42 whole, 49 in 2)
         const int64_t blocks = (uniform ? (int64_t)B * ((Nq + 127) / 128) : (int64_t)Tq / 128 + B) * H;
-        const int64_t tiles = (Nk - Nq / 2) / 64;
+        // The parts of blocks that are alone are no more than pay for their merge, as above (us, 31 ... 127 parts of four tiles -> at most these; parts
+        // of 16 tiles: 64 queries of one head, d = 64 32 k keys 27.8 in 127, 20.8 in 48, 22.7 in 31, 8 k 14.2 in 31, 13.3 in 24, 20.5 in 7; d = 128
+        // 32 k 30.4 in 127, 25.4 in 48, 28.8 in 31; d = 256 32 k 39.4 in 127, 34.8 in 64, 49.0 in 31; 300 of 4, d = 64 8 k 17.2 in 21, 16.7 in 16)
+        const int64_t tiles = (Nk - Nq / 2) / 64, most = root((d_qk > 128 ? 9 : 4) * tiles);
         // (a packed batch may hold any lengths: parts of 16 tiles of the mean, and the workspace that this needs)
-        const int alone = clamp(256 / blocks, uniform && tiles >= 12 ? tiles / 4 : 1), shared = clamp((d_qk > 192 ? 256 : 512) / blocks, tiles / 16);
+        const int alone = clamp(256 / blocks, uniform && tiles >= 12 ? tiles / 4 < most ? tiles / 4 : most : 1), shared = clamp((d_qk > 192 ? 256 : 512) / blocks, tiles / 16);
         r.nsplit = alone > shared ? alone : shared;
     }
     return r;
+}
+
+// The parts of a decode step of equal lengths that hold keys, of nsplit: a part is whole steps of 128 keys, so that the last ones may be
+// left without any (2000 keys in 5: 4 parts of 4 steps; d = 64, 2048 keys, one head: 9.4 us with the empty part, 9.0 without).
+inline int parts_with_keys(const FwdRoute& r, bool uniform, int nk, int nsplit)
+{
+    if (!uniform || !r.decode || nsplit <= 1) return nsplit;
+    const int steps = nk / 128 + (nk % 128 != 0), per = (steps - 1) / nsplit + 1;
+    return (steps - 1) / per + 1;
 }
 
 // Blocks of the merge kernel that share the rows of a tile, in turns of 1024 / d_v rows per block.  On the decode route a

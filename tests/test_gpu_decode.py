@@ -58,6 +58,16 @@ def test_few_queries_against_many_keys(oracle, shape):
     _check(oracle, x, o1, lse1, dqk ** -0.5, causal, "whole")
 
 
+# a few heads against long caches, in as many parts as the merge pays for: decode steps with and without empty parts, chunks
+MANY_PARTS = [(1, 1, 1, 1, 32768, 128, 128, True), (1, 2, 1, 1, 20011, 64, 64, True), (1, 1, 1, 2, 9000, 256, 256, True), (1, 1, 1, 64, 32768, 128, 128, True),
+              (1, 2, 1, 100, 9001, 64, 64, False)]
+
+
+@pytest.mark.parametrize("shape", MANY_PARTS, ids=["B%d_H%d_%d_q%d_k%d_d%d_%d_%s" % s for s in MANY_PARTS])
+def test_many_parts(oracle, shape):
+    test_few_queries_against_many_keys(oracle, shape)
+
+
 @pytest.mark.parametrize("H,Hkv,d,lens", [(8, 2, 128, (700, 1, 64, 0, 33, 5000)), (4, 4, 64, (31, 32, 2000)),
                                           (64, 1, 256, (129, 400)), (6, 3, 96, (1500, 96, 5))])
 def test_packed_decode_step(oracle, H, Hkv, d, lens):
