@@ -302,7 +302,27 @@ inline bool dkdv256_one_wave(int N, long long heads) { return !(N == 128 && head
 //            d = 128 up to 128 keys 160 blocks 1.00 ... 1.07, 224 0.88 ... 0.96, 512 0.54 ... 0.73; up to 256 128 0.74 ... 1.11, 160 0.45 ... 0.89, 256 0.42 ... 0.76,
 //            512 0.53 ... 0.85
 //            77 keys against 1000 queries  64 blocks 1.5 ... 1.9, 256 0.85 (d = 64) and 1.05 (128), 1024 0.61 and 0.72: waves without keys
+//   just past a round (512 blocks of four waves, 256 of eight), long walks (steps of 32 ... 128): the last blocks run alone
+//            d = 64, up to 128 keys 520 and 544 blocks 1.04 ... 1.08 (query heads of a group under the mask 0.99 ... 1.01), 576 0.94 ... 1.06; 160 keys 520
+//            0.89 ... 1.00; 192 ... 256 keys 520 1.02 ... 1.14, 544 0.98 ... 1.13, 576 0.94 ... 1.08, 608 0.86 ... 0.99; 1032 0.66 ... 0.81; 256 keys, 16 steps 520
+//            1.02 ... 1.05, 544 0.98 ... 1.04; 192 keys also 256 ...
+//            288 0.97 ... 1.08, up to 128 keys against 4096 queries 264 1.10, 320 0.97
+//            d = 96  up to 128 keys 0.71 ... 0.91; 192 and 256 keys 264 0.96 ... 1.14, 296 0.99 ... 1.10, 320 0.94 ... 1.08, 352 0.84 ... 1.02, 520 0.83 ... 0.93
+//            d = 128 up to 128 keys against 4096 queries 264 1.04 ... 1.06, 320 0.95, 520 ... 608 1.03 ... 1.08, 640 0.96, other 0.75 ... 1.01; 256 keys, or more than four
+//            times as many queries as keys 264 1.00 ... 1.16, 296 1.00 ... 1.12, 320 0.94 ... 1.06, 352 0.87 ... 1.03, 520 0.85 ... 0.98; else 264 0.78 ... 0.98
+//            d = 64, 300 keys, four rounds and more 776 blocks 1.07 ... 1.11 (2048 queries 0.89), 1032 1.00 ... 1.07 (0.78); 450 keys 776 0.98 ... 1.02
 inline int short_keys(int d_qk, int d_v) { return d_qk != d_v ? 0 : d_qk == 64 ? 512 : d_qk <= 128 ? 256 : 0; }
+inline bool short_last_round_alone(int d_qk, int nq, int nk, int64_t blocks, int64_t steps)
+{
+    auto past = [&](int64_t round, int64_t most) { return blocks > round && blocks <= most; };
+    if (steps < 32) return d_qk == 64 && nk > 224 && steps >= 16 && past(512, 544);
+    if (d_qk == 64) {
+        if (nk <= 128) return past(512, 576) || (steps >= 96 && past(256, 288));
+        return nk > 160 && (past(512, 576) || (nk <= 208 && past(255, 288)));
+    }
+    if (nk <= 128) return d_qk == 128 && steps >= 96 && (past(256, 288) || past(512, 608));
+    return past(256, 320) && (nk > (d_qk == 96 ? 160 : 224) || nq >= 4 * nk);
+}
 inline bool bwd_short(int d_qk, int d_v, bool causal, int nq, int nk, int B, int H, int Hkv)
 {
     if (nk > short_keys(d_qk, d_v)) return false;
@@ -312,8 +332,9 @@ inline bool bwd_short(int d_qk, int d_v, bool causal, int nq, int nk, int B, int
     if (nk > 256) {
         const int64_t rounds = (blocks + 255) / 256;
         const bool whole = nq == nk && nq % 128 == 0;
-        return (!whole || causal || rounds == 1) && blocks >= rounds * (whole ? 240 : 192);
+        return (!whole || causal || rounds == 1) && blocks >= rounds * (whole || (nk <= 384 && steps < 32 && rounds > 3) ? 240 : 192);
     }
+    if (short_last_round_alone(d_qk, nq, nk, blocks, steps)) return false;
     if (nk <= 128) return blocks >= (d_qk == 64 ? 256 : d_qk == 96 ? 192 : 224);
     return blocks >= (d_qk == 64 ? nk + nk / 5 : 160);
 }

@@ -377,6 +377,17 @@ def test_short_backward_rule_takes_the_faster_route(D, d, causal, nq, nk, blocks
     assert abs(ratio - 1) < 0.045 or bool(D.t_short(d, causal, nq, nk, 1, blocks * group, blocks)) == (ratio < 1)
 
 
+# just past a full round of blocks, beside the same call with a round that fills: (d, causal, queries, keys, blocks, heads per KV head, ratio)
+@pytest.mark.parametrize("d,causal,nq,nk,blocks,group,ratio", [
+    (64, 1, 256, 256, 520, 8, 1.14), (64, 0, 1024, 256, 544, 1, 1.11), (64, 0, 1024, 256, 512, 1, 0.78), (64, 0, 1024, 256, 768, 1, 0.82), (64, 0, 1024, 128, 520, 1, 1.08),
+    (64, 0, 128, 128, 520, 2, 0.85), (64, 1, 160, 160, 520, 8, 0.89), (64, 1, 192, 192, 264, 8, 1.08), (64, 0, 4096, 100, 264, 1, 1.11), (64, 0, 4096, 256, 1032, 1, 0.78),
+    (96, 1, 256, 256, 264, 8, 1.14), (96, 0, 4096, 256, 320, 1, 1.08), (96, 0, 256, 256, 264, 2, 0.89), (96, 0, 4096, 128, 520, 1, 0.90),
+    (128, 0, 4096, 256, 264, 1, 1.16), (128, 1, 192, 192, 264, 8, 0.90), (128, 0, 4096, 224, 264, 1, 1.13), (128, 0, 4096, 256, 256, 1, 0.67), (128, 0, 4096, 256, 520, 1, 0.98),
+    (128, 0, 4096, 100, 520, 1, 1.08), (128, 1, 100, 100, 520, 8, 0.92), (64, 0, 300, 300, 776, 1, 1.11), (64, 0, 2048, 300, 776, 1, 0.89), (64, 1, 256, 256, 520, 2, 1.05), (64, 0, 300, 300, 512, 1, 0.85), (64, 1, 450, 450, 1032, 1, 0.93)])
+def test_short_backward_rule_leaves_rounds_that_barely_begin(D, d, causal, nq, nk, blocks, group, ratio):
+    test_short_backward_rule_takes_the_faster_route(D, d, causal, nq, nk, blocks, group, ratio)
+
+
 def test_short_backward_keys_fit_the_block(D):
     """Never more keys than a block holds, and no other head dims, however many blocks."""
     for d, most in ((64, 512), (96, 256), (128, 256), (192, 0), (256, 0)):
