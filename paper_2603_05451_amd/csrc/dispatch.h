@@ -280,6 +280,12 @@ inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop)
 {
     return d_qk == 64 && loop > 128 && blocks > (causal ? 640 : 512);
 }
+// dQ: not for a single query tile per sequence (no mask / mask, dK and dV on the wide kernel: 60 queries against 700 keys 1.00 / 1.02, 2000 keys
+// 1.06 / 1.05; 128 against 700 1.01 / 1.01, 2000 1.05 / 1.04; 129 against 700 0.95 / 0.90, 300 against 2000 0.93 / 0.89).
+inline bool lean_dq_blocks(int d_qk, bool causal, long long blocks, long long queries, long long keys)
+{
+    return queries > 128 && lean_blocks(d_qk, causal, blocks, keys);
+}
 
 // d = 256, the pipelined kernels with one wave per SIMD against the general ones (one block of 128 rows per CU both):
 // 0.65 ... 0.97 but for single-tile sequences in more than half a round (N = 128, 128 ... 1024 blocks: dK/dV 1.02 ...

@@ -59,6 +59,7 @@ int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(cau
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
 int t_lean(int d, int causal, long long blocks, long long loop) { return lean_blocks(d, causal, blocks, loop); }
+int t_lean_dq(int d, int causal, long long blocks, long long nq, long long nk) { return lean_dq_blocks(d, causal, blocks, nq, nk); }
 int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
 int t_live(int uniform, int decode, int nk, int nsplit) { return parts_with_keys(FwdRoute{decode != 0, 1, nsplit}, uniform, nk, nsplit); }
 int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
@@ -400,6 +401,13 @@ def test_short_backward_keys_fit_the_block(D):
 def test_lean_backward_rule(D, causal, blocks, loop, ratio):
     assert bool(D.t_lean(64, causal, blocks, loop)) == (ratio < 1)
     assert not any(D.t_lean(d, causal, blocks, loop) for d in (96, 128, 192, 256))
+
+
+# dQ, d = 64: (causal, blocks, queries, keys, three blocks per CU over two)
+@pytest.mark.parametrize("causal,blocks,nq,nk,ratio", [(0, 1024, 60, 2000, 1.06), (1, 1024, 60, 2000, 1.05), (1, 1024, 20, 700, 1.02), (0, 1024, 128, 2000, 1.05), (0, 2048, 129, 700, 0.95),
+                                                       (1, 2048, 129, 700, 0.90), (0, 768, 300, 2000, 0.93)])
+def test_lean_dq_rule(D, causal, blocks, nq, nk, ratio):
+    assert bool(D.t_lean_dq(64, causal, blocks, nq, nk)) == (ratio < 1)
 
 
 # (B, H, Hkv, queries, keys, d, parts): one CU per block, parts of four tiles; two per CU, of sixteen; loops too short to divide
