@@ -280,6 +280,10 @@ inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop)
 {
     return d_qk == 64 && loop > 128 && blocks > (causal ? 640 : 512);
 }
+// Tiles of 128 rows in a packed batch, of which the host knows the totals: half a tile per sequence is past its end.  (The tables have room for
+// T / 128 + B.  Blocks of 64 ... 300 rows x 64 sequences x 4 heads: 436 by this, 432 there, room for 564, on which three blocks per CU
+// took 1.04; 129 ... 1000 x 64 x 2 512, 520, 576, 1.06; 140 ... 500 x 20 x 8 456, 464, 536, 1.06; 200 ... 400 x 24 x 8 536, 520, 632, 0.97.)
+inline long long likely_tiles(bool equal, int max_tiles, int T, int B) { return equal ? max_tiles : (long long)T / 128 + B / 2; }
 // dQ: not for a single query tile per sequence (no mask / mask, dK and dV on the wide kernel: 60 queries against 700 keys 1.00 / 1.02, 2000 keys
 // 1.06 / 1.05; 128 against 700 1.01 / 1.01, 2000 1.05 / 1.04; 129 against 700 0.95 / 0.90, 300 against 2000 0.93 / 0.89).
 inline bool lean_dq_blocks(int d_qk, bool causal, long long blocks, long long queries, long long keys)

@@ -60,6 +60,7 @@ int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, 
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
 int t_lean(int d, int causal, long long blocks, long long loop) { return lean_blocks(d, causal, blocks, loop); }
 int t_lean_dq(int d, int causal, long long blocks, long long nq, long long nk) { return lean_dq_blocks(d, causal, blocks, nq, nk); }
+int t_tiles(int equal, int max_tiles, int T, int B) { return (int)likely_tiles(equal, max_tiles, T, B); }
 int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
 int t_live(int uniform, int decode, int nk, int nsplit) { return parts_with_keys(FwdRoute{decode != 0, 1, nsplit}, uniform, nk, nsplit); }
 int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
@@ -408,6 +409,15 @@ def test_lean_backward_rule(D, causal, blocks, loop, ratio):
                                                        (1, 2048, 129, 700, 0.90), (0, 768, 300, 2000, 0.93)])
 def test_lean_dq_rule(D, causal, blocks, nq, nk, ratio):
     assert bool(D.t_lean_dq(64, causal, blocks, nq, nk)) == (ratio < 1)
+
+
+# packed, d = 64, no mask: (lengths, heads, three blocks per CU on the room of the tables over two)
+@pytest.mark.parametrize("B,T,room,H,lean", [(64, 9856, 141, 4, False), (20, 6016, 67, 8, False), (48, 10752, 132, 4, False), (40, 7800, 101, 8, True), (9, 9000, 79, 8, True),
+                                             (24, 7128, 79, 8, True), (30, 4020, 62, 12, True)])
+def test_lean_rule_counts_tiles_that_are_there(D, B, T, room, H, lean):
+    blocks = D.t_tiles(0, room, T, B) * H
+    assert blocks <= room * H and bool(D.t_lean(64, 0, blocks, T // B)) == lean
+    assert D.t_tiles(1, room, T, B) == room
 
 
 # (B, H, Hkv, queries, keys, d, parts): one CU per block, parts of four tiles; two per CU, of sixteen; loops too short to divide
