@@ -276,8 +276,11 @@ inline bool dkdv64_one_wave(bool causal, int N, long long b)
 // number of rows that a block walks.  (Share of the whole backward pass.  Variable length, no mask 0.90 ... 1.00, mask 0.86 ... 1.00; fixed length
 // 0.96 ... 1.00 and 0.95 ... 1.00.  Up to 512 blocks 1.00 ... 1.045, and under the mask 528 ... 640 blocks 0.96 ... 1.06: a block alone or beside
 // one other misses what the wider kernel reads ahead.  Dk and dV of 700 keys: 60 queries 1.05 (mask 0.97), 100 ... 128 1.01 and 1.02, 130 0.94.)
-inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop)
+// Variable length, equal lengths, no mask, just past three blocks per CU, short loops: 300 rows 792 blocks 1.03, 600 rows 776 ... 1000 1.00 ... 1.02, 1040
+// 0.96; 640 rows 0.97 ... 1.00, 2000 1.00; under the mask 300 ... 2000 rows 0.89 ... 0.97; fixed length 0.97 ... 0.99.
+inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop, bool strided = false)
 {
+    if (strided && !causal && loop <= 600 && blocks > 768 && blocks <= 1024) return false;
     return d_qk == 64 && loop > 128 && blocks > (causal ? 640 : 512);
 }
 // Tiles of 128 rows in a packed batch, of which the host knows the totals: half a tile per sequence is past its end.  (The tables have room for
@@ -286,9 +289,9 @@ inline bool lean_blocks(int d_qk, bool causal, long long blocks, long long loop)
 inline long long likely_tiles(bool equal, int max_tiles, int T, int B) { return equal ? max_tiles : (long long)T / 128 + B / 2; }
 // dQ: not for a single query tile per sequence (no mask / mask, dK and dV on the wide kernel: 60 queries against 700 keys 1.00 / 1.02, 2000 keys
 // 1.06 / 1.05; 128 against 700 1.01 / 1.01, 2000 1.05 / 1.04; 129 against 700 0.95 / 0.90, 300 against 2000 0.93 / 0.89).
-inline bool lean_dq_blocks(int d_qk, bool causal, long long blocks, long long queries, long long keys)
+inline bool lean_dq_blocks(int d_qk, bool causal, long long blocks, long long queries, long long keys, bool strided)
 {
-    return queries > 128 && lean_blocks(d_qk, causal, blocks, keys);
+    return queries > 128 && lean_blocks(d_qk, causal, blocks, keys, strided);
 }
 
 // d = 256, the pipelined kernels with one wave per SIMD against the general ones (one block of 128 rows per CU both):

@@ -59,7 +59,8 @@ int t_dkdv64(int d, int causal, int N, long long b) { return dkdv64_one_wave(cau
 int t_dq256(int causal, int N, long long heads) { return dq256_one_wave(causal, N, heads); }
 int t_dkdv256(int N, long long heads) { return dkdv256_one_wave(N, heads); }
 int t_lean(int d, int causal, long long blocks, long long loop) { return lean_blocks(d, causal, blocks, loop); }
-int t_lean_dq(int d, int causal, long long blocks, long long nq, long long nk) { return lean_dq_blocks(d, causal, blocks, nq, nk); }
+int t_lean_dq(int d, int causal, long long blocks, long long nq, long long nk) { return lean_dq_blocks(d, causal, blocks, nq, nk, false); }
+int t_lean_strided(int causal, long long blocks, long long loop) { return lean_blocks(64, causal, blocks, loop, true); }
 int t_tiles(int equal, int max_tiles, int T, int B) { return (int)likely_tiles(equal, max_tiles, T, B); }
 int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
 int t_live(int uniform, int decode, int nk, int nsplit) { return parts_with_keys(FwdRoute{decode != 0, 1, nsplit}, uniform, nk, nsplit); }
@@ -418,6 +419,11 @@ def test_lean_rule_counts_tiles_that_are_there(D, B, T, room, H, lean):
     blocks = D.t_tiles(0, room, T, B) * H
     assert blocks <= room * H and bool(D.t_lean(64, 0, blocks, T // B)) == lean
     assert D.t_tiles(1, room, T, B) == room
+
+
+@pytest.mark.parametrize("causal,blocks,loop,lean", [(0, 792, 300, False), (0, 800, 600, False), (0, 768, 600, True), (0, 1040, 600, True), (0, 800, 640, True), (1, 800, 600, True)])
+def test_lean_rule_past_three_blocks_per_cu(D, causal, blocks, loop, lean):
+    assert bool(D.t_lean_strided(causal, blocks, loop)) == lean and D.t_lean(64, causal, blocks, loop)
 
 
 # (B, H, Hkv, queries, keys, d, parts): one CU per block, parts of four tiles; two per CU, of sixteen; loops too short to divide
