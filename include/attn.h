@@ -109,8 +109,8 @@ int attn_bwd_ex(const void* q, const void* k, const void* v, const void* o, cons
  * and ATTN_BWD_DKDV, of the same or of a later call, reads what it left.  attn_bwd_ex is
  * therefore two kernels (three at d = 256, where ATTN_BWD_DKDV is two); ATTN_BWD_PREPARE has an
  * effect only in a mask without ATTN_BWD_DQ.  At sizes whose whole backward pass is one kernel, a call for
- * one pass runs that kernel and has it write the pass's results (the prepare kernel in front where -D and
- * the base-2 LSE are to be left in the workspace): the same bits, each pass at the whole pass's time. */
+ * one pass is that kernel without the other pass's products: the same bits, in any order, and the workspace is
+ * written by ATTN_BWD_PREPARE only and read by none. */
 enum { ATTN_BWD_PREPARE = 1, ATTN_BWD_DKDV = 2, ATTN_BWD_DQ = 4, ATTN_BWD_ALL = 7 };
 int attn_bwd_phases(const void* q, const void* k, const void* v, const void* o, const void* d_o,
                     const float* lse, void* dq, void* dk, void* dv,

@@ -106,11 +106,11 @@ int launch_bwd(const BwdArgs& a)
     // In variable-length mode the copies are bounded by whole rows, so a row has to be as long as its stride at most:
     // overlapping rows (sliding windows) stay with the general kernels.
     const bool long_rows = a.st.q.row >= a.d_qk && a.st.k.row >= a.d_qk && a.st.v.row >= a.d_v && a.st.d_o.row >= a.d_v;
-    // Few keys: everything in one kernel, which needs nothing from the workspace.  A call for the dQ pass or the dK/dV pass alone runs it for
-    // that pass's results, and leaves -D and the base-2 LSE in the workspace where the split into passes says so.
+    // Few keys: everything in one kernel, which needs nothing from the workspace and leaves nothing there.  A call for the dQ pass or the dK/dV
+    // pass alone runs it without the other's products; -D and the base-2 LSE go to the workspace where the call asks for them.
     if ((a.phases & 6) && (a.max_tiles == 0 || (a.st.nq > 0 && long_rows)) &&
         bwd_short(a.d_qk, a.d_v, a.causal, a.max_tiles > 0 ? a.st.nq : a.N, a.max_tiles > 0 ? a.st.nk : a.N, a.B, a.H, a.Hkv)) {
-        if (a.phases != 7 && (a.phases & 5)) {
+        if (a.phases == 3) {
             if (const int rc = generic(1)) return rc;
         }
         return launch_bwd_short(a);

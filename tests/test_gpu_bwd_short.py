@@ -97,6 +97,22 @@ def test_passes_compose(d, N, B, causal):
         assert all(torch.equal(a, b) for a, b in zip(got, ref)), order
 
 
+@pytest.mark.parametrize("d,N,B,causal", PASSES)
+def test_one_pass_launches_one_kernel(d, N, B, causal):
+    """The workspace is neither read nor written but by the prepare pass, and a call for one pass writes that pass's results alone."""
+    import paper_2603_05451_amd as A
+    g = torch.Generator(device="cuda").manual_seed(965 + d)
+    q, k, v, do = (torch.randn(B, N, 8, d, generator=g, device="cuda").bfloat16() for _ in range(4))
+    o, lse = A.attn_fwd(q, k, v, d ** -0.5, causal)
+    for phases in range(1, 8):
+        got = [torch.full_like(t, 7.0) for t in (q, k, v)]
+        ws = torch.full((A.attn_bwd_workspace_bytes(B, 8, 8, N, d, d),), 0xA5, dtype=torch.uint8, device="cuda")
+        A.attn_bwd(q, k, v, o, do, lse, d ** -0.5, causal, *got, ws, phases=phases)
+        torch.cuda.synchronize()
+        assert bool((ws == 0xA5).all()) == (phases not in (1, 3)), phases
+        assert [bool((t == 7.0).all()) for t in got] == [not phases & 4, not phases & 2, not phases & 2], phases
+
+
 @pytest.mark.parametrize("d,N,Hkv,row", [(64, 128, 256, 40), (64, 256, 320, 70), (64, 512, 240, 300), (96, 250, 160, 133), (128, 128, 224, 5), (128, 256, 160, 200)])
 def test_a_query_that_is_no_number(d, N, Hkv, row):
     """Under the mask it reaches the dV of the keys that it sees and of no other."""
