@@ -51,36 +51,52 @@ def _run(cmd, verbose):
         if keep:
             print("\n".join(keep))
     if res.returncode != 0:
-        raise RuntimeError("compiler failed building libattn.so or _binding.so: " + " ".join(cmd[-3:]))
+        raise RuntimeError("compiler failed: " + " ".join(cmd[-3:]))
 
 
 def binding_command(out: str) -> list:
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
     include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
-    return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-w", *("-I" + d for d in include),
+    return [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wextra", "-Wconversion",
+            *(x for d in include for x in ("-isystem", d)),
             os.path.join(CSRC, "binding.cpp"), "-o", out, "-L" + os.path.join(torch, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+
+
+def build_binding(verbose: bool = False) -> str:
+    """_binding.so alone.  The libraries above neither need it nor torch."""
+    if importlib.util.find_spec("torch") is None:
+        raise RuntimeError("_binding.so (the Python binding's native part) needs torch, which is not installed; "
+                           "libattn.so is built without it")
+    tmp = BINDING + f".{os.getpid()}.tmp"
+    try:
+        _run(binding_command(tmp), verbose)
+        os.replace(tmp, BINDING)
+    finally:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+    return BINDING
 
 
 def build_library(verbose: bool = False) -> str:
     """One hipcc process per source file (the attention files dominate: every kernel body is
-    instantiated per head dim, mask, mode and element type), then one link step per library."""
+    instantiated per head dim, mask, mode and element type), then one link step per library.  The
+    binding is compiled beside them; what fails there is raised once the libraries are in place."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = tempfile.mkdtemp(prefix="libattn_build_")
     try:
         every = SOURCES + PROBE_SOURCES
-        binding = os.path.join(tmp, "_binding.so")
-        jobs = [binding_command(binding)] + [[hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(tmp, obj)]
+        jobs = [[hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", os.path.join(tmp, obj)]
                 for src, obj, extra in every]
-        with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1, 8)) as pool:
+        with ThreadPoolExecutor(max_workers=min(len(jobs) + 1, os.cpu_count() or 1, 8)) as pool:
+            binding = pool.submit(build_binding, verbose)
             list(pool.map(lambda c: _run(c, verbose), jobs))
-        for lib, sources in ((LIB, SOURCES), (PROBES_LIB, PROBE_SOURCES)):
-            objs = [os.path.join(tmp, obj) for _, obj, _ in sources]
-            _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib + ".tmp", *objs], verbose)
-            os.replace(lib + ".tmp", lib)
-        shutil.copyfile(binding, BINDING + ".tmp")
-        os.replace(BINDING + ".tmp", BINDING)
+            for lib, sources in ((LIB, SOURCES), (PROBES_LIB, PROBE_SOURCES)):
+                objs = [os.path.join(tmp, obj) for _, obj, _ in sources]
+                _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib + ".tmp", *objs], verbose)
+                os.replace(lib + ".tmp", lib)
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
+    binding.result()
     return LIB
 
 

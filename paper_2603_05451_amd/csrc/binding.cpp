@@ -116,6 +116,8 @@ struct Call {
     }
 };
 
+int size(const at::Tensor* t, int dim) { return (int)t->size(dim); }       // (Call::fits)
+
 at::Tensor make(const at::Tensor& like, Sizes shape) { return at::empty(shape, like.options().requires_grad(false)); }
 at::Tensor make_f32(const at::Tensor& like, Sizes shape) { return at::empty(shape, like.options().requires_grad(false).dtype(at::kFloat)); }
 at::Tensor make_bytes(const at::Tensor& like, size_t n)
@@ -159,7 +161,7 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 8) NOT_HERE;
     const at::Tensor *q = c.first(a[0], 4), *k = c.other(a[1], 4), *v = c.other(a[2], 4);
     if (!c.ok) NOT_HERE;
-    const int64_t B = q->size(0), N = q->size(1), H = q->size(2), dqk = q->size(3), Hkv = k->size(2), dv = v->size(3);
+    const int B = size(q, 0), N = size(q, 1), H = size(q, 2), dqk = size(q, 3), Hkv = size(k, 2), dv = size(v, 3);
     const double scale = c.number(a[3]);
     const int causal = c.truth(a[4]);
     at::Tensor o = c.given(a[5]), lse = c.given(a[6]);
@@ -186,7 +188,7 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!c.ok) NOT_HERE;
     const long phases = PyLong_AsLong(a[13]);
     if (PyErr_Occurred()) { PyErr_Clear(); NOT_HERE; }
-    const int64_t B = q->size(0), N = q->size(1), H = q->size(2), dqk = q->size(3), Hkv = k->size(2), dvd = v->size(3);
+    const int B = size(q, 0), N = size(q, 1), H = size(q, 2), dqk = size(q, 3), Hkv = size(k, 2), dvd = size(v, 3);
     const double scale = c.number(a[6]);
     const int causal = c.truth(a[7]);
     at::Tensor dq = c.given(a[8]), dk = c.given(a[9]), dv = c.given(a[10]), ws = c.given(a[11]);
@@ -215,11 +217,11 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
 }
 
 // Boundaries [B + 1] on the device; both given here (tables kept in a workspace: the Python text).
-const int* boundaries(Call& c, PyObject* x, int64_t B)
+const int* boundaries(Call& c, PyObject* x, int B)
 {
     const at::Tensor* t = c.ok ? plain(x) : nullptr;
     if (!t) { c.ok = false; return nullptr; }
-    return (const int*)c.dense(*t, {B + 1}, at::kInt);
+    return (const int*)c.dense(*t, {(int64_t)B + 1}, at::kInt);
 }
 
 // q, k, v, cu_seqlens, scale, causal, o, lse, workspace, stream, cu_seqlens_k
@@ -230,7 +232,7 @@ PyObject* varlen_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 11) NOT_HERE;
     const at::Tensor *q = c.first(a[0], 3), *k = c.other(a[1], 3), *v = c.other(a[2], 3), *cu = c.other(a[3], 1);
     if (!c.ok) NOT_HERE;
-    const int64_t T = q->size(0), H = q->size(1), dqk = q->size(2), Tk = k->size(0), Hkv = k->size(1), dv = v->size(2), B = cu->numel() - 1;
+    const int T = size(q, 0), H = size(q, 1), dqk = size(q, 2), Tk = size(k, 0), Hkv = size(k, 1), dv = size(v, 2), B = size(cu, 0) - 1;
     const double scale = c.number(a[4]);
     const int causal = c.truth(a[5]);
     const int *cq = boundaries(c, a[3], B), *ck = a[10] == Py_None ? cq : boundaries(c, a[10], B);
@@ -260,7 +262,7 @@ PyObject* varlen_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     const at::Tensor *q = c.first(a[0], 3), *k = c.other(a[1], 3), *v = c.other(a[2], 3), *o = c.other(a[3], 3), *g = c.other(a[4], 3), *lse = c.other(a[5], 2),
                      *cu = c.other(a[6], 1);
     if (!c.ok) NOT_HERE;
-    const int64_t T = q->size(0), H = q->size(1), dqk = q->size(2), Tk = k->size(0), Hkv = k->size(1), dvd = v->size(2), B = cu->numel() - 1;
+    const int T = size(q, 0), H = size(q, 1), dqk = size(q, 2), Tk = size(k, 0), Hkv = size(k, 1), dvd = size(v, 2), B = size(cu, 0) - 1;
     const double scale = c.number(a[7]);
     const int causal = c.truth(a[8]);
     const int *cq = boundaries(c, a[6], B), *ck = a[14] == Py_None ? cq : boundaries(c, a[14], B);
@@ -292,7 +294,7 @@ PyObject* fwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 9) NOT_HERE;
     const at::Tensor *q = c.first(a[0], 4), *k = c.other(a[1], 4), *v = c.other(a[2], 4);
     if (!c.ok) NOT_HERE;
-    const int64_t B = q->size(0), N = q->size(1), H = q->size(2), dqk = q->size(3), Nk = k->size(1), Hkv = k->size(2), dv = v->size(3);
+    const int B = size(q, 0), N = size(q, 1), H = size(q, 2), dqk = size(q, 3), Nk = size(k, 1), Hkv = size(k, 2), dv = size(v, 3);
     const double scale = c.number(a[3]);
     const int causal = c.truth(a[4]);
     at::Tensor o = c.given(a[5]), lse = c.given(a[6]), ws = c.given(a[7]);
@@ -322,7 +324,7 @@ PyObject* bwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 13) NOT_HERE;
     const at::Tensor *q = c.first(a[0], 4), *k = c.other(a[1], 4), *v = c.other(a[2], 4), *o = c.other(a[3], 4), *g = c.other(a[4], 4), *lse = c.other(a[5], 3);
     if (!c.ok) NOT_HERE;
-    const int64_t B = q->size(0), N = q->size(1), H = q->size(2), dqk = q->size(3), Nk = k->size(1), Hkv = k->size(2), dvd = v->size(3);
+    const int B = size(q, 0), N = size(q, 1), H = size(q, 2), dqk = size(q, 3), Nk = size(k, 1), Hkv = size(k, 2), dvd = size(v, 3);
     const double scale = c.number(a[6]);
     const int causal = c.truth(a[7]);
     at::Tensor dq = c.given(a[8]), dk = c.given(a[9]), dv = c.given(a[10]), ws = c.given(a[11]);
