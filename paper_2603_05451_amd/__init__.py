@@ -97,7 +97,8 @@ def lib():
                                              L.attn_varlen_bwd_dtype, L.attn_varlen_workspace_bytes, L.attn_fwd_strided, L.attn_bwd_strided,
                                              L.attn_strided_workspace_bytes)),
                       torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.nn.Parameter)
-        _lib, _native = L, _binding
+        _native = _binding
+        _lib = L                # last: another thread that finds it set uses both
     return _lib
 
 

@@ -225,3 +225,27 @@ def test_workspace_sizes_are_asked_anew(L):
         assert f(*args[:at], n, *args[at + 1:]) == f(*args)
         n.n *= 2
         assert f(*args[:at], n, *args[at + 1:]) == f(*args[:at], 2 * args[at], *args[at + 1:]) > f(*args)
+
+
+def test_a_loaded_library_comes_with_its_native_part(L, monkeypatch):
+    """At no point of the first call's loading does another thread find the library loaded and the native module missing."""
+    import sys
+    import paper_2603_05451_amd as A
+    monkeypatch.setattr(A, "_lib", None)
+    monkeypatch.setattr(A, "_native", None)
+    seen = []
+
+    def trace(frame, event, arg):
+        if frame.f_code is not A.lib.__code__:
+            return None
+        frame.f_trace_opcodes = True
+        seen.append(A._lib is not None and A._native is None)
+        return trace
+
+    old = sys.gettrace()
+    sys.settrace(trace)
+    try:
+        A.lib()
+    finally:
+        sys.settrace(old)
+    assert len(seen) > 100 and not any(seen) and A._call() is A._native
