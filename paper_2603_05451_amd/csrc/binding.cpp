@@ -140,16 +140,13 @@ PyObject* outs(int rc, std::initializer_list<std::pair<PyObject*, const at::Tens
     return r;
 }
 
-// The library's call, other Python threads running meanwhile.
-template <typename F, typename... Args>
-int unlocked(F f, Args... args)
-{
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f(args...);
-    Py_END_ALLOW_THREADS
-    return rc;
-}
+// Other Python threads run while this lives: allocations, which may wait for memory, and the library's call, as with torch.empty and ctypes.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 
 #define NOT_HERE Py_RETURN_NONE
 
@@ -171,9 +168,13 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!c.ok) NOT_HERE;
     void* s = c.stream(a[7]);
     if (!c.ok) NOT_HERE;
-    if (!o.defined()) o = make(*q, {B, N, H, dv});
-    if (!lse.defined()) lse = make_f32(*q, {B, H, N});
-    const int rc = unlocked(p_fwd, c.dtype, qp, kp, vp, o.data_ptr(), (float*)lse.data_ptr(), B, H, Hkv, N, dqk, dv, (float)scale, causal, s);
+    int rc;
+    {
+        Unlocked threads;
+        if (!o.defined()) o = make(*q, {B, N, H, dv});
+        if (!lse.defined()) lse = make_f32(*q, {B, H, N});
+        rc = p_fwd(c.dtype, qp, kp, vp, o.data_ptr(), (float*)lse.data_ptr(), B, H, Hkv, N, dqk, dv, (float)scale, causal, s);
+    }
     return outs(rc, {{a[5], &o}, {a[6], &lse}});
     END_HANDLE_TH_ERRORS
 }
@@ -202,16 +203,20 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (need == 0 || (ws.defined() && !ws.is_cuda())) NOT_HERE;
     void* s = c.stream(a[12]);
     if (!c.ok) NOT_HERE;
-    if (!dq.defined()) dq = make(*q, {B, N, H, dqk});
-    if (!dk.defined()) dk = make(*q, {B, N, Hkv, dqk});
-    if (!dv.defined()) dv = make(*q, {B, N, Hkv, dvd});
-    if (!ws.defined()) ws = make_bytes(*q, need);
-    const size_t bytes = (size_t)ws.numel() * ws.element_size();
-    const int rc = c.type == at::kHalf
-        ? unlocked(p_bwd_dtype, c.dtype, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H, Hkv, N, dqk, dvd, (float)scale, causal,
-                      ws.data_ptr(), bytes, s)
-        : unlocked(p_bwd_phases, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H, Hkv, N, dqk, dvd, (float)scale, causal,
-                       ws.data_ptr(), bytes, s, (int)phases);
+    int rc;
+    {
+        Unlocked threads;
+        if (!dq.defined()) dq = make(*q, {B, N, H, dqk});
+        if (!dk.defined()) dk = make(*q, {B, N, Hkv, dqk});
+        if (!dv.defined()) dv = make(*q, {B, N, Hkv, dvd});
+        if (!ws.defined()) ws = make_bytes(*q, need);
+        const size_t bytes = (size_t)ws.numel() * ws.element_size();
+        rc = c.type == at::kHalf
+            ? p_bwd_dtype(c.dtype, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H, Hkv, N, dqk, dvd, (float)scale, causal,
+                          ws.data_ptr(), bytes, s)
+            : p_bwd_phases(qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, H, Hkv, N, dqk, dvd, (float)scale, causal,
+                           ws.data_ptr(), bytes, s, (int)phases);
+    }
     return outs(rc, {{a[8], &dq}, {a[9], &dk}, {a[10], &dv}});
     END_HANDLE_TH_ERRORS
 }
@@ -244,11 +249,15 @@ PyObject* varlen_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     const size_t need = ws.defined() ? 0 : p_varlen_bytes(B, T, Tk, H, Hkv, dqk, dv, 0);
     void* s = c.stream(a[9]);
     if (!c.ok) NOT_HERE;
-    if (!o.defined()) o = make(*q, {T, H, dv});
-    if (!lse.defined()) lse = make_f32(*q, {H, T});
-    if (!ws.defined()) ws = make_bytes(*q, need);
-    const int rc = unlocked(p_varlen_fwd, c.dtype, qp, kp, vp, o.data_ptr(), (float*)lse.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dv, (float)scale, causal,
-                                ws.data_ptr(), (size_t)ws.numel(), s);
+    int rc;
+    {
+        Unlocked threads;
+        if (!o.defined()) o = make(*q, {T, H, dv});
+        if (!lse.defined()) lse = make_f32(*q, {H, T});
+        if (!ws.defined()) ws = make_bytes(*q, need);
+        rc = p_varlen_fwd(c.dtype, qp, kp, vp, o.data_ptr(), (float*)lse.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dv, (float)scale, causal,
+                                    ws.data_ptr(), (size_t)ws.numel(), s);
+    }
     return outs(rc, {{a[6], &o}, {a[7], &lse}});
     END_HANDLE_TH_ERRORS
 }
@@ -276,12 +285,16 @@ PyObject* varlen_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     const size_t need = ws.defined() ? 0 : p_varlen_bytes(B, T, Tk, H, Hkv, dqk, dvd, 1);
     void* s = c.stream(a[13]);
     if (!c.ok) NOT_HERE;
-    if (!dq.defined()) dq = make(*q, {T, H, dqk});
-    if (!dk.defined()) dk = make(*q, {Tk, Hkv, dqk});
-    if (!dv.defined()) dv = make(*q, {Tk, Hkv, dvd});
-    if (!ws.defined()) ws = make_bytes(*q, need);
-    const int rc = unlocked(p_varlen_bwd, c.dtype, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dvd,
-                                (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    int rc;
+    {
+        Unlocked threads;
+        if (!dq.defined()) dq = make(*q, {T, H, dqk});
+        if (!dk.defined()) dk = make(*q, {Tk, Hkv, dqk});
+        if (!dv.defined()) dv = make(*q, {Tk, Hkv, dvd});
+        if (!ws.defined()) ws = make_bytes(*q, need);
+        rc = p_varlen_bwd(c.dtype, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dvd,
+                                    (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    }
     return outs(rc, {{a[9], &dq}, {a[10], &dk}, {a[11], &dv}});
     END_HANDLE_TH_ERRORS
 }
@@ -306,12 +319,16 @@ PyObject* fwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
     const size_t need = ws.defined() ? 0 : p_strided_bytes(B, H, Hkv, N, Nk, dqk, dv, 0);
     void* s = c.stream(a[8]);
     if (!c.ok) NOT_HERE;
-    if (!o.defined()) { o = make(*q, {B, N, H, dv}); c.view(o, {B, N, H, dv}); }
-    if (!lse.defined()) lse = make_f32(*q, {B, H, N});
-    if (!ws.defined()) ws = make_bytes(*q, need);
-    const attn_strides_t* st = c.strides;
-    const int rc = unlocked(p_fwd_strided, c.dtype, qp, st, kp, st + 1, vp, st + 2, o.data_ptr(), st + 3, (float*)lse.data_ptr(), B, H, Hkv, N, Nk, dqk, dv, (float)scale,
-                                 causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    int rc;
+    {
+        Unlocked threads;
+        if (!o.defined()) { o = make(*q, {B, N, H, dv}); c.view(o, {B, N, H, dv}); }
+        if (!lse.defined()) lse = make_f32(*q, {B, H, N});
+        if (!ws.defined()) ws = make_bytes(*q, need);
+        const attn_strides_t* st = c.strides;
+        rc = p_fwd_strided(c.dtype, qp, st, kp, st + 1, vp, st + 2, o.data_ptr(), st + 3, (float*)lse.data_ptr(), B, H, Hkv, N, Nk, dqk, dv, (float)scale,
+                                     causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    }
     return outs(rc, {{a[5], &o}, {a[6], &lse}});
     END_HANDLE_TH_ERRORS
 }
@@ -340,17 +357,21 @@ PyObject* bwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
     const size_t need = ws.defined() ? 0 : p_strided_bytes(B, H, Hkv, N, Nk, dqk, dvd, 1);
     void* s = c.stream(a[12]);
     if (!c.ok) NOT_HERE;
-    if (!dq.defined()) dq = make(*q, {B, N, H, dqk});
-    if (!dk.defined()) dk = make(*q, {B, Nk, Hkv, dqk});
-    if (!dv.defined()) dv = make(*q, {B, Nk, Hkv, dvd});
-    if (!ws.defined()) ws = make_bytes(*q, need);
-    c.nstrides = inputs;
-    c.view(dq, {B, N, H, dqk});
-    c.view(dk, {B, Nk, Hkv, dqk});
-    c.view(dv, {B, Nk, Hkv, dvd});
-    const attn_strides_t* st = c.strides;
-    const int rc = unlocked(p_bwd_strided, c.dtype, qp, st, kp, st + 1, vp, st + 2, op, st + 3, gp, st + 4, (float*)lp, dq.data_ptr(), st + 5, dk.data_ptr(), st + 6,
-                                 dv.data_ptr(), st + 7, B, H, Hkv, N, Nk, dqk, dvd, (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    int rc;
+    {
+        Unlocked threads;
+        if (!dq.defined()) dq = make(*q, {B, N, H, dqk});
+        if (!dk.defined()) dk = make(*q, {B, Nk, Hkv, dqk});
+        if (!dv.defined()) dv = make(*q, {B, Nk, Hkv, dvd});
+        if (!ws.defined()) ws = make_bytes(*q, need);
+        c.nstrides = inputs;
+        c.view(dq, {B, N, H, dqk});
+        c.view(dk, {B, Nk, Hkv, dqk});
+        c.view(dv, {B, Nk, Hkv, dvd});
+        const attn_strides_t* st = c.strides;
+        rc = p_bwd_strided(c.dtype, qp, st, kp, st + 1, vp, st + 2, op, st + 3, gp, st + 4, (float*)lp, dq.data_ptr(), st + 5, dk.data_ptr(), st + 6,
+                                     dv.data_ptr(), st + 7, B, H, Hkv, N, Nk, dqk, dvd, (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+    }
     return outs(rc, {{a[8], &dq}, {a[9], &dk}, {a[10], &dv}});
     END_HANDLE_TH_ERRORS
 }
