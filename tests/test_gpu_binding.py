@@ -11,15 +11,36 @@ class _Nobody:
         return lambda *a: None
 
 
-def _both(monkeypatch, call):
+class _Watched:
+    """The native module, every call's result noted under its name: the outputs, an error code, or None where it left the call alone."""
+    def __init__(self, module):
+        self.module, self.results = module, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.module, name)(*a)
+            self.results.append((name, r))
+            return r
+        return call
+
+
+def _watched(monkeypatch, call):
     import paper_2603_05451_amd as A
     A.lib()
-    native = call(A)
+    with monkeypatch.context() as m:
+        watch = _Watched(A._native)
+        m.setattr(A, "_native", watch)
+        return call(A), watch.results
+
+
+def _both(monkeypatch, call):
+    import paper_2603_05451_amd as A
+    native, results = _watched(monkeypatch, call)
     with monkeypatch.context() as m:
         m.setattr(A, "_native", _Nobody())
         python = call(A)
     torch.cuda.synchronize()
-    return native, python
+    return native, python, results
 
 
 def _t(*shape, dtype=torch.bfloat16, seed=0):
@@ -55,7 +76,8 @@ def test_same_outputs(monkeypatch, dtype, given):
         out += [*s, *A.attn_bwd_strided(qv, *kv, s[0], s[0], s[1], 0.125, True, *g)]
         return out
 
-    native, python = _both(monkeypatch, calls)
+    native, python, results = _both(monkeypatch, calls)
+    assert [n for n, r in results] == ["fwd", "bwd", "varlen_fwd", "varlen_bwd", "fwd_strided", "bwd_strided"] and all(type(r) is tuple for n, r in results)
     assert len(native) == len(python) == 15
     for x, y in zip(native, python):
         assert type(x) is torch.Tensor and x.shape == y.shape and x.stride() == y.stride() and x.dtype == y.dtype and not x.requires_grad
@@ -66,20 +88,33 @@ def test_same_refusals(monkeypatch):
     q = _t(1, 128, 2, 64)
     lse = torch.empty(1, 2, 128, device="cuda")
     cu = torch.tensor([0, 128], dtype=torch.int32, device="cuda")
+    p = q[0]
     bad = [lambda A: A.attn_fwd(q, q[:, :, ::2], q, 0.1, False), lambda A: A.attn_fwd(q, q.half(), q, 0.1, False), lambda A: A.attn_fwd(q.cpu(), q, q, 0.1, False),
            lambda A: A.attn_fwd(q, q, q, -1.0, False), lambda A: A.attn_fwd(q[:, :100].contiguous(), *[q[:, :100].contiguous()] * 2, 0.1, False),
            lambda A: A.attn_fwd(q, q, q, 0.1, False, lse=lse.half()), lambda A: A.attn_bwd(q, q, q, q, q[:, :64], lse, 0.1, False),
            lambda A: A.attn_bwd(q, q, q, q, q, lse, 0.1, False, phases=9), lambda A: A.attn_bwd(q, q, q, q, q, lse, 0.1, False, workspace=torch.empty(8, device="cuda")),
            lambda A: A.attn_varlen_fwd(q[0], q[0], q[0], cu.long(), 0.1, False), lambda A: A.attn_varlen_fwd(q[0], q[0], q[0], cu, 0.1, False, cu_seqlens_k=cu[:1]),
            lambda A: A.attn_fwd_strided(q, q[..., ::2], q, 0.1, False), lambda A: A.attn_fwd_strided(q, q[:, :64], q[:, :64], 0.1, True),
-           lambda A: A.attn_bwd_strided(q, q, q, q, q, lse, 0.1, False, dq=q[:, :64])]
+           lambda A: A.attn_bwd_strided(q, q, q, q, q, lse, 0.1, False, dq=q[:, :64]),
+           lambda A: A.attn_bwd(q, q, q, q[..., :32], q, lse, 0.1, False), lambda A: A.attn_bwd(q, q, q, q.float(), q, lse, 0.1, False),
+           lambda A: A.attn_bwd(q, q, q, q, q, lse, 0.1, False, dk=q.half()), lambda A: A.attn_bwd(*[q.half()] * 5, lse, 0.1, False, phases=4),
+           lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0, :1], cu, 0.1, False), lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0].double(), cu, 0.1, False),
+           lambda A: A.attn_varlen_bwd(p, p, p, p[:64], p, lse[0], cu, 0.1, False), lambda A: A.attn_varlen_bwd(p, p, p, p, p.half(), lse[0], cu, 0.1, False),
+           lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0], cu[:1], 0.1, False), lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0], cu, 0.1, False, dv=p[:, :1]),
+           lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0], cu, 0.1, False, cu_seqlens_k=cu.cpu()),
+           lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0], cu, 0.1, False, workspace=torch.empty(8, dtype=torch.uint8, device="cuda")),
+           lambda A: A.attn_varlen_bwd(p, p, p, p, p, lse[0], None, 0.1, False), lambda A: A.attn_bwd_strided(q, q, q, q, q, lse[:, :1], 0.1, False),
+           lambda A: A.attn_bwd_strided(q, q, q, q, q, lse.half(), 0.1, False), lambda A: A.attn_bwd_strided(q, q, q, q[:, :64], q, lse, 0.1, False),
+           lambda A: A.attn_bwd_strided(q, q, q, q.cpu(), q, lse, 0.1, False), lambda A: A.attn_bwd_strided(q, q, q, q, q, lse, 0.0, False)]
     for i, f in enumerate(bad):
         def said(A):
             with pytest.raises((ValueError, A.AttnError)) as e:
                 f(A)
             return type(e.value), str(e.value)
-        native, python = _both(monkeypatch, said)
-        assert native == python, i
+        native, python, results = _both(monkeypatch, said)
+        assert native == python and len(results) == 1, i
+        r = results[0][1]                                   # left alone, or the error of a call whose tensors are sound
+        assert r is None or (type(r) is int and r < 0 and native[0].__name__ == "AttnError"), i
 
 
 def test_left_to_the_python_text(monkeypatch):
@@ -91,6 +126,8 @@ def test_left_to_the_python_text(monkeypatch):
 
     q = _t(1, 128, 2, 64)
     ref = A.attn_fwd(q, q, q, 1.0, True)[0]
-    for a in ((q, q, q, 1, 1), (torch.nn.Parameter(q), q, q, torch.tensor(1.0), True), (q.as_subclass(Mine), q, q, 1.0, True)):
-        o, _ = A.attn_fwd(*a)
+    for a, here in (((q, q, q, 1, 1), False), ((torch.nn.Parameter(q), q, q, torch.tensor(1.0), True), False), ((q.as_subclass(Mine), q, q, 1.0, True), False),
+                    ((torch.nn.Parameter(q), q, q, 1.0, True), True)):
+        (o, _), results = _watched(monkeypatch, lambda A: A.attn_fwd(*a))
         assert torch.equal(o.as_subclass(torch.Tensor), ref) and not o.requires_grad
+        assert [(n, r is not None) for n, r in results] == [("fwd", here)]
