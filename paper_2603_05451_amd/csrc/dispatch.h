@@ -308,21 +308,19 @@ inline bool dkdv256_one_wave(int N, long long heads) { return !(N == 128 && head
 //            d = 64, up to 128 keys, 4 ... 16 steps  128 blocks 0.95 ... 1.29, 224 0.96 ... 1.03, 256 0.82 ... 0.99, 512 0.63 ... 0.66
 //            d = 64, 160 keys  160 blocks 0.76 ... 1.04, 224 0.73 ... 0.83; 200 keys  224 0.85 ... 1.01, 256 0.86 ... 0.95; 256 keys  256 0.91 ... 1.08,
 //            320 0.78 ... 0.82, 512 0.61 ... 0.79
-//            d = 64, up to 512 keys, rounds of 256: ragged 192 blocks 0.81 ... 0.94, 256 0.75 ... 0.90, 320 1.14 ... 1.17, 512 and 1024 0.85 ... 0.92;
-//            whole tiles under the mask 192 0.94 ... 1.04, 256 0.75 ... 0.86, 384 1.14, 448 1.02, 512 ... 1024 0.94 ... 0.98, without it 256 0.90, 512 ... 1024
-//            0.99 ... 1.07 (the dK/dV kernel in turns)
+//            d = 64, up to 512 keys, rounds of 256: ragged 192 blocks 0.81 ... 0.94, 256 0.75 ... 0.90, 320 1.14 ... 1.17, 512 and 1024 0.85 ... 0.92
 //            d = 96  up to 128 keys 128 blocks 1.02 ... 1.15, 160 0.89 ... 1.00, 224 0.81 ... 0.90; up to 256 128 0.84 ... 1.15, 160 0.49 ... 0.86, 512 0.59 ... 0.68
-//            d = 128 up to 128 keys 160 blocks 1.00 ... 1.07, 224 0.88 ... 0.96, 512 0.54 ... 0.73; up to 256 128 0.74 ... 1.11, 160 0.45 ... 0.89, 256 0.42 ... 0.76,
+//            d = 128 up to 128 keys 160 blocks 0.94 ... 1.28, 192 0.80 ... 1.19, 224 0.70 ... 1.09, 256 0.68 ... 1.06, 512 0.45 ... 0.59; up to 256 128 0.74 ... 1.11, 160 0.45 ... 0.89, 256 0.42 ... 0.76,
 //            512 0.53 ... 0.85
-//            77 keys against 1000 queries  64 blocks 1.5 ... 1.9, 256 0.85 (d = 64) and 1.05 (128), 1024 0.61 and 0.72: waves without keys
+//            77 keys against 1000 queries  64 blocks 1.5 ... 1.9, 256 0.85 (d = 64) and 0.90 (128), 1024 0.61 and 0.52: waves without keys
 //   just past a round (512 blocks of four waves, 256 of eight), long walks (steps of 32 ... 128): the last blocks run alone
 //            d = 64, up to 128 keys 520 and 544 blocks 1.04 ... 1.08 (query heads of a group under the mask 0.99 ... 1.01), 576 0.94 ... 1.06; 160 keys 520
 //            0.89 ... 1.00; 192 ... 256 keys 520 1.02 ... 1.14, 544 0.98 ... 1.13, 576 0.94 ... 1.08, 608 0.86 ... 0.99; 1032 0.66 ... 0.81; 256 keys, 16 steps 520
 //            1.02 ... 1.05, 544 0.98 ... 1.04; 192 keys also 256 ...
 //            288 0.97 ... 1.08, up to 128 keys against 4096 queries 264 1.10, 320 0.97
 //            d = 96  up to 128 keys 0.71 ... 0.91; 192 and 256 keys 264 0.96 ... 1.14, 296 0.99 ... 1.10, 320 0.94 ... 1.08, 352 0.84 ... 1.02, 520 0.83 ... 0.93
-//            d = 128 up to 128 keys against 4096 queries 264 1.04 ... 1.06, 320 0.95, 520 ... 608 1.03 ... 1.08, 640 0.96, other 0.75 ... 1.01; 256 keys, or more than four
-//            times as many queries as keys 264 1.00 ... 1.16, 296 1.00 ... 1.12, 320 0.94 ... 1.06, 352 0.87 ... 1.03, 520 0.85 ... 0.98; else 264 0.78 ... 0.98
+//            d = 128 up to 128 keys 0.69 ... 0.90; 256 keys, or more than four times as many queries as keys 264 1.00 ... 1.16, 296 1.00 ... 1.12, 320
+//            0.94 ... 1.06, 352 0.87 ... 1.03, 520 0.85 ... 0.98; else 264 0.78 ... 0.98
 //            d = 64, 300 keys, four rounds and more 776 blocks 1.07 ... 1.11 (2048 queries 0.89), 1032 1.00 ... 1.07 (0.78); 450 keys 776 0.98 ... 1.02
 inline int short_keys(int d_qk, int d_v) { return d_qk != d_v ? 0 : d_qk == 64 ? 512 : d_qk <= 128 ? 256 : 0; }
 inline bool short_last_round_alone(int d_qk, int nq, int nk, int64_t blocks, int64_t steps)
@@ -333,20 +331,52 @@ inline bool short_last_round_alone(int d_qk, int nq, int nk, int64_t blocks, int
         if (nk <= 128) return past(512, 576) || (steps >= 96 && past(256, 288));
         return nk > 160 && (past(512, 576) || (nk <= 208 && past(255, 288)));
     }
-    if (nk <= 128) return d_qk == 128 && steps >= 96 && (past(256, 288) || past(512, 608));
-    return past(256, 320) && (nk > (d_qk == 96 ? 160 : 224) || nq >= 4 * nk);
+    return nk > 128 && past(256, 320) && (nk > (d_qk == 96 ? 160 : 224) || nq >= 4 * nk);
+}
+// Whole tiles (equal numbers of queries and keys, a multiple of 128): the line of the fixed-length call, whose kernels are faster than the
+// variable-length ones, for both, since contiguous tensors get the same bits from both.  The one kernel takes whole rounds, the two as long as
+// they have blocks (share of the fixed-length call's two kernels; G query heads per KV head):
+//   d = 64, 128 tokens, rounds of 512  mask   G = 2 ... 4 256 0.96 ... 1.01, 512 0.71 ... 0.75, 544 0.87 ... 1.01; G = 8 and 16 320 0.99 and 1.11, 384 0.92 and 1.02,
+//                                             512 0.84, 544 1.12 and 1.23, 704 1.01 and 1.05, 768 0.93 and 0.97, 1056 1.00 and 1.02
+//                                      none   G = 2 256 1.04, 288 0.92, 544 1.02; G = 4 288 1.02, 320 0.98, 512 0.82, 544 1.13, 768 1.06, 832 0.97, 1152 1.07, 1280 0.98;
+//                                             G = 8 and 16 384 1.01 and 1.14, 480 0.95 and 1.05, 544 1.28 and 1.36, 896 0.98 and 1.03, 960 0.95 and 0.98, 1408 0.96 and 0.99
+//           256 tokens                 mask   G = 2 320 0.96, 544 1.10, 640 1.02, 704 0.96; G = 4 ... 16 320 1.10 ... 1.22, 384 0.92 ... 0.98, 544 1.25, 704 0.97 ... 1.02, 1056 1.04
+//                                      none   G = 1 320 0.94, 512 0.79, 540 1.04, 600 1.00; G = 2 ... 16 384 1.01 ... 1.28, 480 0.93 ... 1.05, 544 1.16 ... 1.42, 896 1.00 ... 1.08, 960 1.00
+//           384 and 512, of 256        mask   240 0.83 ... 1.02, 264 1.37 ... 1.70, 480 0.96 ... 1.03, 768 0.90 ... 1.00; none  240 and 256 G = 1, 2 0.88 ... 1.01, G = 4 1.02 ... 1.07,
+//                                             512 1.01 ... 1.11, 768 1.04 ... 1.09
+//   d = 96, 128 tokens   G = 2 192 0.90; G = 4 192 0.99 ... 1.03, 208 0.93; G = 8 and 16 208 1.01 ... 1.06, 224 0.97 ... 1.02, 264 0.84 ... 1.03, 528 0.91 ... 0.98
+//   d = 128              mask or G = 2, 4 224 0.88 ... 0.98; none, G = 8 and 16 224 ... 256 1.07 ... 1.21, 264 0.96 ... 0.99, G = 16 528 1.14, 576 1.08, 640 0.96
+//   256 tokens           d = 96 and 128 G = 2, 4 160 0.80 ... 1.03, G = 8, 16 160 0.92 ... 1.15, 176 0.88 ... 1.03; 264 1.00 ... 1.39, 320 0.98 ... 1.24, 352 mask 0.94 ... 1.08, none d = 96
+//                        0.94 ... 1.07, d = 128 1.08 ... 1.20, 400 0.87 ... 1.00; d = 128 none 528 1.05 ... 1.12, 576 1.01 ... 1.08, 640 0.97 ... 1.00, other 528 0.91 ... 1.04
+inline bool bwd_short_whole(int d, bool causal, int n, int64_t blocks, int64_t steps)
+{
+    auto past = [&](int64_t round, int64_t most) { return blocks > round && blocks <= most; };
+    if (n > 256) {
+        const int64_t rounds = (blocks + 255) / 256;
+        return blocks >= rounds * 240 && (causal || (rounds == 1 && steps <= 32));
+    }
+    if (d == 64) {
+        const int64_t rounds = (blocks + 511) / 512;
+        int percent;                                           // of full rounds
+        if (n == 128) percent = causal ? (steps <= 16 ? 50 : 72) : steps <= 8 ? 52 : steps > 16 ? 90 : rounds == 1 ? 60 : 80;
+        else percent = steps <= 8 ? 56 : causal ? (steps <= 16 ? 62 : 70) : 90;
+        return 100 * blocks >= percent * 512 * rounds;
+    }
+    if (n == 128) {
+        if (d == 96) return blocks >= (steps > 16 ? 224 : steps > 8 ? 208 : 192);
+        return blocks >= (causal || steps < 32 ? 224 : 257) && !(!causal && steps >= 64 && past(512, 592));
+    }
+    const int64_t alone = causal ? 336 : d == 128 ? 384 : steps >= 64 ? 368 : 336;
+    return blocks >= (steps >= 48 ? 176 : 160) && !(steps >= 16 && past(256, alone)) && !(d == 128 && !causal && steps >= 16 && past(512, 592));
 }
 inline bool bwd_short(int d_qk, int d_v, bool causal, int nq, int nk, int B, int H, int Hkv)
 {
     if (nk > short_keys(d_qk, d_v)) return false;
     const int64_t blocks = (int64_t)B * Hkv, steps = (int64_t)(H / Hkv) * ((nq + 31) / 32);
     if (steps <= (nk > 256 ? 3 : d_qk == 64 || nk <= 128 ? 4 : 5)) return true;
+    if (nq == nk && nq % 128 == 0) return bwd_short_whole(d_qk, causal, nq, blocks, steps);
     if (nk < 96) return blocks >= 1024;
-    if (nk > 256) {
-        const int64_t rounds = (blocks + 255) / 256;
-        const bool whole = nq == nk && nq % 128 == 0;
-        return (!whole || causal || rounds == 1) && blocks >= rounds * (whole || (nk <= 384 && steps < 32 && rounds > 3) ? 240 : 192);
-    }
+    if (nk > 256) return blocks >= (blocks + 255) / 256 * (nk <= 384 && steps < 32 && blocks > 768 ? 240 : 192);
     if (short_last_round_alone(d_qk, nq, nk, blocks, steps)) return false;
     if (nk <= 128) return blocks >= (d_qk == 64 ? 256 : d_qk == 96 ? 192 : 224);
     return blocks >= (d_qk == 64 ? nk + nk / 5 : 160);

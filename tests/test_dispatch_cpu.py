@@ -383,12 +383,25 @@ def test_short_backward_rule_takes_the_faster_route(D, d, causal, nq, nk, blocks
 # just past a full round of blocks, beside the same call with a round that fills: (d, causal, queries, keys, blocks, heads per KV head, ratio)
 @pytest.mark.parametrize("d,causal,nq,nk,blocks,group,ratio", [
     (64, 1, 256, 256, 520, 8, 1.14), (64, 0, 1024, 256, 544, 1, 1.11), (64, 0, 1024, 256, 512, 1, 0.78), (64, 0, 1024, 256, 768, 1, 0.82), (64, 0, 1024, 128, 520, 1, 1.08),
-    (64, 0, 128, 128, 520, 2, 0.85), (64, 1, 160, 160, 520, 8, 0.89), (64, 1, 192, 192, 264, 8, 1.08), (64, 0, 4096, 100, 264, 1, 1.11), (64, 0, 4096, 256, 1032, 1, 0.78),
-    (96, 1, 256, 256, 264, 8, 1.14), (96, 0, 4096, 256, 320, 1, 1.08), (96, 0, 256, 256, 264, 2, 0.89), (96, 0, 4096, 128, 520, 1, 0.90),
+    (64, 0, 100, 100, 520, 2, 0.87), (64, 1, 160, 160, 520, 8, 0.89), (64, 1, 192, 192, 264, 8, 1.08), (64, 0, 4096, 100, 264, 1, 1.11), (64, 0, 4096, 256, 1032, 1, 0.78),
+    (96, 1, 256, 256, 264, 8, 1.14), (96, 0, 4096, 256, 320, 1, 1.08), (96, 0, 192, 192, 264, 2, 0.79), (96, 0, 4096, 128, 520, 1, 0.90),
     (128, 0, 4096, 256, 264, 1, 1.16), (128, 1, 192, 192, 264, 8, 0.90), (128, 0, 4096, 224, 264, 1, 1.13), (128, 0, 4096, 256, 256, 1, 0.67), (128, 0, 4096, 256, 520, 1, 0.98),
-    (128, 0, 4096, 100, 520, 1, 1.08), (128, 1, 100, 100, 520, 8, 0.92), (64, 0, 300, 300, 776, 1, 1.11), (64, 0, 2048, 300, 776, 1, 0.89), (64, 1, 256, 256, 520, 2, 1.05), (64, 0, 300, 300, 512, 1, 0.85), (64, 1, 450, 450, 1032, 1, 0.93)])
+    (128, 0, 4096, 100, 520, 1, 0.90), (128, 1, 100, 100, 520, 8, 0.80), (128, 0, 4096, 128, 264, 1, 0.82), (64, 0, 300, 300, 776, 1, 1.11), (64, 0, 2048, 300, 776, 1, 0.89), (64, 1, 256, 256, 520, 2, 1.05), (64, 0, 300, 300, 512, 1, 0.85), (64, 1, 450, 450, 1032, 1, 0.93)])
 def test_short_backward_rule_leaves_rounds_that_barely_begin(D, d, causal, nq, nk, blocks, group, ratio):
     test_short_backward_rule_takes_the_faster_route(D, d, causal, nq, nk, blocks, group, ratio)
+
+
+# whole tiles, by the fixed-length call: (d, causal, tokens, blocks, heads per KV head, ratio)
+@pytest.mark.parametrize("d,causal,n,blocks,group,ratio", [
+    (64, 0, 128, 256, 8, 1.24), (64, 0, 128, 512, 8, 0.94), (64, 0, 128, 544, 4, 1.13), (64, 0, 128, 640, 16, 1.24), (64, 0, 128, 960, 8, 0.95), (64, 0, 128, 320, 4, 0.98),
+    (64, 0, 128, 832, 4, 0.97), (64, 1, 128, 640, 4, 0.94), (64, 1, 128, 256, 16, 1.20), (64, 1, 128, 448, 16, 0.90), (64, 1, 128, 544, 8, 1.12), (64, 1, 128, 768, 8, 0.93),
+    (64, 0, 256, 544, 2, 1.16), (64, 0, 256, 640, 8, 1.27), (64, 0, 256, 512, 1, 0.79), (64, 0, 256, 1536, 8, 0.92), (64, 1, 256, 320, 8, 1.18), (64, 1, 256, 320, 2, 0.96),
+    (64, 1, 256, 768, 4, 0.93), (64, 1, 256, 576, 16, 1.22), (64, 0, 512, 256, 4, 1.06), (64, 0, 512, 256, 1, 0.93), (64, 1, 512, 264, 1, 1.48), (64, 1, 384, 512, 2, 0.97),
+    (96, 0, 128, 192, 8, 1.12), (96, 0, 128, 240, 8, 0.96), (96, 1, 256, 264, 2, 1.17), (96, 1, 256, 160, 8, 1.09), (96, 0, 256, 192, 8, 0.85), (128, 0, 128, 256, 16, 1.19),
+    (128, 0, 128, 264, 16, 0.96), (128, 0, 128, 528, 16, 1.14), (128, 1, 128, 528, 16, 0.94), (128, 0, 256, 352, 8, 1.20), (128, 1, 256, 352, 2, 0.94), (128, 0, 256, 544, 4, 1.09),
+    (128, 1, 256, 192, 8, 0.91), (128, 0, 256, 640, 2, 0.99)])
+def test_short_backward_rule_of_whole_tiles(D, d, causal, n, blocks, group, ratio):
+    assert bool(D.t_short(d, causal, n, n, 1, blocks * group, blocks)) == (ratio < 1)
 
 
 def test_short_backward_keys_fit_the_block(D):
