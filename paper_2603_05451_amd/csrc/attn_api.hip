@@ -271,7 +271,7 @@ int varlen_fwd_run(int dtype, const void* q, const void* k, const void* v, void*
     a.nsub = r.nsub;
     a.nsplit = r.nsplit;
     while (a.nsplit > 1 && w.part_off + partial_bytes(a.nsplit, Tq, H, d_v) > ws_bytes) --a.nsplit;
-    a.nsplit = attn::parts_with_keys(r, uniform, st.nk, a.nsplit);
+    a.nsplit = attn::parts_with_keys(r, uniform, d_qk, st.nk, a.nsplit);
     if (a.nsplit > 1) {
         a.part_o = reinterpret_cast<float*>(ws + w.part_off);
         a.part_ml = a.part_o + (size_t)a.nsplit * Tq * H * d_v;

@@ -493,8 +493,9 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
             // least -> at most these: d = 128 32 k keys 24.2 in 128 -> 16.9 in 32, 21.0 in 16, 8 k 12.4 in 32, 12.0 in 16, 14.2 in 8; d = 64 32 k 19.5 in
             // 85, 16.2 in 32, 20.0 in 16; (192, 128) 32 k 25.4 in 128, 19.3 in 48, 19.5 in 32; d = 256 32 k 28.7 in 128, 22.6 in 64, 24.9 in 32, 8 k
             // 17.8 in 64, 15.5 in 32, 16.6 in 16)
-            const int64_t least = d_qk == 64 ? 3 : d_qk > 192 ? 1 : 2, most = root((d_qk > 192 ? 16 : d_qk > 128 ? 6 : 5) * steps);
-            const int64_t parts = steps / least < most ? steps / least : most;
+            const int64_t least = d_qk == 64 ? 3 : d_qk > 192 ? 1 : 2, grows = root((d_qk > 192 ? 16 : d_qk == 192 ? 8 : d_qk == 64 ? 5 : 6) * steps);
+            const int64_t most = d_qk > 192 && grows < 32 ? 32 : grows;
+            const int64_t parts = steps / least <= most ? steps / least : (steps - 1) / ((steps - 1) / most + 1) + 1;      // (whole steps: none empty)
             r.nsplit = clamp((127 + items) / items, steps >= (d_qk > 192 ? 3 : 6) ? parts : 1);
             // (two parts of few steps: 64 ... 112 items, 6 and 7 steps d = 96, 128, 192 1.00 ... 1.18 of one part, d = 256 3 ... 7 steps 0.98 ... 1.15;
             // d = 64, 2 ... 112 items 0.99 ... 1.07; three and more 0.68 ... 1.01, from 8 steps 0.71 ... 0.97)
@@ -532,11 +533,13 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
     return r;
 }
 
-// The parts of a decode step of equal lengths that hold keys, of nsplit: a part is whole steps of 128 keys, so that the last ones may be
-// left without any (2000 keys in 5: 4 parts of 4 steps; d = 64, 2048 keys, one head: 9.4 us with the empty part, 9.0 without).
-inline int parts_with_keys(const FwdRoute& r, bool uniform, int nk, int nsplit)
+// The parts that a decode step of equal lengths launches, of nsplit: a part is whole steps of 128 keys, so that the last ones may be left without
+// any (2000 keys in 5: 4 parts of 4 steps).  At d = 64 these are not launched (2048 keys, one head 9.4 us with the empty part, 9.0 without; 3513 keys x 5
+// in 9 1.07 of 7).  At larger head dims they cost less than how another number falls on the chip's eight dies (9242 keys, Hkv = 8, 15 parts
+// against 16 with one empty: d = 96 14.0 and 12.9, d = 128 14.3 and 15.6; 6500 keys, d = 96, 13 of 16 12.4 and 11.8).
+inline int parts_with_keys(const FwdRoute& r, bool uniform, int d_qk, int nk, int nsplit)
 {
-    if (!uniform || !r.decode || nsplit <= 1) return nsplit;
+    if (!uniform || !r.decode || d_qk != 64 || nsplit <= 1) return nsplit;
     const int steps = nk / 128 + (nk % 128 != 0), per = (steps - 1) / nsplit + 1;
     return (steps - 1) / per + 1;
 }

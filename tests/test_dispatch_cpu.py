@@ -63,7 +63,7 @@ int t_lean_dq(int d, int causal, long long blocks, long long nq, long long nk) {
 int t_lean_strided(int causal, long long blocks, long long loop) { return lean_blocks(64, causal, blocks, loop, true); }
 int t_tiles(int equal, int max_tiles, int T, int B) { return (int)likely_tiles(equal, max_tiles, T, B); }
 int t_short(int d, int causal, int nq, int nk, int B, int H, int Hkv) { return bwd_short(d, d, causal, nq, nk, B, H, Hkv); }
-int t_live(int uniform, int decode, int nk, int nsplit) { return parts_with_keys(FwdRoute{decode != 0, 1, nsplit}, uniform, nk, nsplit); }
+int t_live(int uniform, int decode, int d, int nk, int nsplit) { return parts_with_keys(FwdRoute{decode != 0, 1, nsplit}, uniform, d, nk, nsplit); }
 int t_route(int B, int Tq, int Tk, int H, int Hkv, int dqk, int dv, int uniform, int* nsplit)
 {
     const FwdRoute r = fwd_route(B, Tq, Tk, H, Hkv, dqk, dv, uniform);
@@ -455,8 +455,8 @@ def test_parts_of_a_decode_step_of_few_blocks(D, B, H, Hkv, Nk, d, parts):
 
 
 # (B, H, Hkv, queries, keys, d, parts): few heads against long caches, where the merge counts
-@pytest.mark.parametrize("B,H,Hkv,Nq,Nk,d,parts", [(1, 1, 1, 1, 32768, 128, 35), (1, 8, 1, 1, 32768, 64, 35), (1, 1, 1, 1, 32768, 256, 64), (2, 8, 2, 1, 8192, 128, 17),
-                                                   (1, 4, 4, 1, 8192, 64, 17), (1, 1, 1, 1, 2048, 128, 8), (1, 1, 1, 1, 2048, 256, 16), (6, 16, 16, 1, 826, 128, 1), (10, 2, 2, 1, 792, 64, 1), (2, 16, 16, 1, 826, 128, 3), (2, 32, 32, 1, 500, 256, 1), (1, 32, 8, 1, 32768, 128, 16),
+@pytest.mark.parametrize("B,H,Hkv,Nq,Nk,d,parts", [(1, 1, 1, 1, 32768, 128, 37), (1, 8, 1, 1, 32768, 64, 32), (1, 1, 1, 1, 32768, 256, 64), (2, 8, 2, 1, 8192, 128, 16), (1, 1, 1, 1, 2300, 256, 18), (1, 8, 8, 1, 3051, 128, 12),
+                                                   (1, 4, 4, 1, 8192, 64, 16), (1, 1, 1, 1, 2048, 128, 8), (1, 1, 1, 1, 2048, 256, 16), (6, 16, 16, 1, 826, 128, 1), (10, 2, 2, 1, 792, 64, 1), (2, 16, 16, 1, 826, 128, 3), (2, 32, 32, 1, 500, 256, 1), (1, 32, 8, 1, 32768, 128, 16),
                                                    (1, 1, 1, 64, 32768, 128, 45), (2, 2, 1, 100, 16384, 128, 31), (1, 4, 4, 100, 32768, 96, 45), (1, 1, 1, 64, 32768, 256, 67),
                                                    (1, 4, 4, 300, 8192, 64, 21), (1, 1, 1, 64, 2048, 128, 7)])
 def test_parts_of_few_heads_against_long_caches(D, B, H, Hkv, Nq, Nk, d, parts):
@@ -464,12 +464,14 @@ def test_parts_of_few_heads_against_long_caches(D, B, H, Hkv, Nq, Nk, d, parts):
 
 
 def test_parts_of_a_decode_step_hold_keys(D):
-    """As many parts as the kernel's division into whole steps of four 32-key tiles leaves with keys; packed batches and chunks as they are."""
+    """d = 64: as many parts as the kernel's division into whole steps of four 32-key tiles leaves with keys; other head dims, packed batches and
+    chunks as they are."""
     for nk in list(range(1, 1200)) + [2000, 2047, 2049, 8191, 32768, 2 ** 31 - 1]:
         for n in (1, 2, 3, 4, 5, 8, 16, 32, 127):
             tiles = (nk + 31) // 32
             per = ((tiles + n - 1) // n + 3) & ~3
-            assert D.t_live(1, 1, nk, n) == -(-tiles // per) and D.t_live(0, 1, nk, n) == n and D.t_live(1, 0, nk, n) == n
+            assert D.t_live(1, 1, 64, nk, n) == -(-tiles // per) and D.t_live(1, 1, 128, nk, n) == n
+            assert D.t_live(0, 1, 64, nk, n) == n and D.t_live(1, 0, 64, nk, n) == n
 
 
 def test_parts_of_a_packed_step(D):
