@@ -30,8 +30,9 @@
  *   - Return value: ATTN_OK, or a negative code.  ATTN_EINVAL, ATTN_EUNSUPPORTED and
  *     ATTN_ETOOLARGE are found before anything is enqueued: no output has been touched.
  *     ATTN_ELAUNCH (the HIP runtime refused a launch or an attribute) can come from any of the
- *     launches of a call that has several (the backward pass beyond a few hundred keys: dQ kernel, then dK/dV, at d = 256 as a
- *     dV and a dK kernel; most variable-length calls: a small table kernel first; a variable-length
+ *     launches of a call that has several (the backward pass, except where it is the one kernel described at attn_bwd: dQ kernel,
+ *     then dK/dV, at d = 256 as a dV and a dK kernel; a call for its dK/dV pass that asks for ATTN_BWD_PREPARE: the
+ *     prepare kernel in front; most variable-length calls: a small table kernel first; a variable-length
  *     or strided forward pass whose keys are divided: a merge kernel last, without which o and lse
  *     are untouched): the launches before the failed one stay enqueued and write their outputs (dq,
  *     dv, the workspace); the outputs of the failed and later launches are untouched.

@@ -487,7 +487,7 @@ inline FwdRoute fwd_route(int B, int Tq, int Tk, int H, int Hkv, int d_qk, int d
         } else if (items < 128) {
             // 128 blocks reach the memory's rate.  Parts of two steps and more (d = 64: three, 256: one), from six, for a part costs its
             // first loads and the merge (us, parts of four steps at least -> these: 4 x 1000 keys, Hkv = 8, d = 128 11.1 -> 9.7, 1 x 1000
-            // 11.0 -> 9.7, 2 x 1316, Hkv = 2, d = 96 11.4 -> 9.4, 2 x 2000, d = 64 10.0 -> 9.5, 2 x 1000, d = 256 16.1 -> 11.6; 4 x 600, Hkv = 16,
+            // 11.0 -> 9.7, 2 x 1316, Hkv = 2, d = 96 11.4 -> 9.4, 2 x 1100, d = 64 11.6 -> 10.5, 2 x 1000, d = 256 16.1 -> 11.6; 4 x 600, Hkv = 16,
             // d = 64 7.8 whole, 9.2 in two; B = 1, Hkv = 8, 32 k keys: 203 us in one part, 61 in 4, 40 in 8, 35 in 16, 40 in 32)
             // A part's loop shrinks as the merge's grows: the best number grows with the root of the keys (us, one KV head, parts of two steps at
             // least -> at most these: d = 128 32 k keys 24.2 in 128 -> 16.9 in 32, 21.0 in 16, 8 k 12.4 in 32, 12.0 in 16, 14.2 in 8; d = 64 32 k 19.5 in
