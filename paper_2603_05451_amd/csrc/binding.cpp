@@ -256,7 +256,7 @@ PyObject* varlen_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
         if (!lse.defined()) lse = make_f32(*q, {H, T});
         if (!ws.defined()) ws = make_bytes(*q, need);
         rc = p_varlen_fwd(c.dtype, qp, kp, vp, o.data_ptr(), (float*)lse.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dv, (float)scale, causal,
-                                    ws.data_ptr(), (size_t)ws.numel(), s);
+                          ws.data_ptr(), (size_t)ws.numel(), s);
     }
     return outs(rc, {{a[6], &o}, {a[7], &lse}});
     END_HANDLE_TH_ERRORS
@@ -293,7 +293,7 @@ PyObject* varlen_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
         if (!dv.defined()) dv = make(*q, {Tk, Hkv, dvd});
         if (!ws.defined()) ws = make_bytes(*q, need);
         rc = p_varlen_bwd(c.dtype, qp, kp, vp, op, gp, (float*)lp, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), cq, ck, B, T, Tk, H, Hkv, dqk, dvd,
-                                    (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+                          (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
     }
     return outs(rc, {{a[9], &dq}, {a[10], &dk}, {a[11], &dv}});
     END_HANDLE_TH_ERRORS
@@ -327,7 +327,7 @@ PyObject* fwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
         if (!ws.defined()) ws = make_bytes(*q, need);
         const attn_strides_t* st = c.strides;
         rc = p_fwd_strided(c.dtype, qp, st, kp, st + 1, vp, st + 2, o.data_ptr(), st + 3, (float*)lse.data_ptr(), B, H, Hkv, N, Nk, dqk, dv, (float)scale,
-                                     causal, ws.data_ptr(), (size_t)ws.numel(), s);
+                           causal, ws.data_ptr(), (size_t)ws.numel(), s);
     }
     return outs(rc, {{a[5], &o}, {a[6], &lse}});
     END_HANDLE_TH_ERRORS
@@ -370,7 +370,7 @@ PyObject* bwd_strided(PyObject*, PyObject* const* a, Py_ssize_t n)
         c.view(dv, {B, Nk, Hkv, dvd});
         const attn_strides_t* st = c.strides;
         rc = p_bwd_strided(c.dtype, qp, st, kp, st + 1, vp, st + 2, op, st + 3, gp, st + 4, (float*)lp, dq.data_ptr(), st + 5, dk.data_ptr(), st + 6,
-                                     dv.data_ptr(), st + 7, B, H, Hkv, N, Nk, dqk, dvd, (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
+                           dv.data_ptr(), st + 7, B, H, Hkv, N, Nk, dqk, dvd, (float)scale, causal, ws.data_ptr(), (size_t)ws.numel(), s);
     }
     return outs(rc, {{a[8], &dq}, {a[9], &dk}, {a[10], &dv}});
     END_HANDLE_TH_ERRORS
